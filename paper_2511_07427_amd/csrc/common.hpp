@@ -16,7 +16,7 @@ constexpr int kMaxClusters = 131072;            // per unit (the selection packs
 constexpr int kMaxInitClusters = 8192;          // clusters built at prefill
 constexpr int kSelectLds = 16384;               // clusters whose scores and sizes the selection keeps in LDS; beyond,
                                                 // it reads them from memory in every pass
-constexpr int kMaxPrefill = 16384;              // k-means sorts one unit's labels in LDS
+constexpr int kMaxPrefill = 16384;              // k-means checks one unit's initial positions in an LDS bitmap
 constexpr int kFusedClusters = 4096;            // clusters per unit the single-kernel retrieval can hold in LDS
 constexpr int kMaxSplitMembers = 4096;          // largest cluster the split kernel handles
 constexpr int kMaxKvSplits = 64;
@@ -95,11 +95,14 @@ struct View {
   double* dist;
   int* koff;         // [U][Mcap+1] start of every cluster in `order`
   // k-means distance filter on the matrix cores
+  int Mpad;          // centres per unit rounded up to the assignment's chunk of 64
   uint16_t* kmA;     // [U][kmA_stride] centroids split into 16-bit terms, in A-operand order (see kmeans.hip)
   size_t kmA_stride; // 16-bit elements per unit
-  float* hn;         // [U][Mpad32] -|r_j|^2 / 2 (-inf for padding rows)
-  float* rmax;       // [U] max_j |r_j|
-  int* nflagged;     // [U] points whose filter gap is below the rounding bound (listed in `order`)
+  float* hn;         // [U][Mpad] -|r_j|^2 / 2 (-3e38 for padding rows)
+  float* rmax;       // [U] largest |r_j| of the build so far
+  float* rhomax;     // [U] largest |r_j - sum of its 16-bit terms| of the build so far
+  int* n_changed;    // [U][2] points that changed their cluster in an iteration, odd and even ones apart
+  int* nflagged;     // [U] import / placement: the unit was accepted
   int* has_empty;    // [U] some cluster got no point in the last assignment
   int* xrange;       // [U][2] smallest and largest binary exponent among the unit's non-zero prefill keys
 };

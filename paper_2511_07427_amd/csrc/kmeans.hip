@@ -4,21 +4,141 @@
 // kept here as the HBM layout).
 //
 // Every label is the float64 nearest centre (ties to the lowest index): a matrix-core filter in
-// float32 settles the clear cases, every point within its error bound is re-assigned by an exact
-// float64 scan.  Centre sums are float64 sums over the members.
+// float32 settles the clear cases, every point within its error bound is decided in float64.
+// Centre sums are float64 sums over the members.
+//
+// One iteration of a 16-bit type is two launches that matter: the assignment, which reads every key once, and the
+// update, which reads the keys of the points that changed their cluster.  256 units x 4096 float16 keys x 256 centres:
+// assignment 115 us, update 35 us, where nine launches that formed every sum anew, checked near-ties in a kernel of their
+// own and split the centres into two 16-bit terms took 320 us; the whole build 4.07 -> 2.57 ms (128 x 8192 x 512: 5.17 ->
+// 3.40 ms; 8 x 16384 x 2048 bfloat16: 3.62 -> 2.52 ms).
 #include "common.hpp"
 
 namespace dynakv {
 
 namespace {
 
-// One workgroup per unit, first kernel of a build: clears the unit's error word, then flags initial positions
-// that are out of range or given twice (the build still runs, with such a position clamped).
+typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+typedef __bf16 b8v __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+// Terms that a centre is split into for the filter (see kmeans_assign_kernel): what one float16 leaves of a coordinate
+// leaves 2 to 6 % of the points undecided by the filter, of one bfloat16 a third of them.
+template <int DT>
+constexpr int kTerms = DT == DYNAKV_F16 ? 1 : 2;
+template <int DT>
+constexpr int kChunkTiles = 2 / kTerms<DT>;          // tiles of 32 centres per LDS buffer of the assignment: 16 KB
+
+// ---- scratch of a build -------------------------------------------------------------------------------------------
+// The page pool holds nothing until the layout at the end of a build, so each unit's part of it serves as scratch:
+// float64 centre sums [M0][128], the centres as plain rows [M0][128] (float32; the comparison of two centres reads whole
+// rows, which the lane-interleaved table has in 32 places), the list of points that changed their cluster [N0], member
+// counts [2][M0].  (M0 (1024 + 512 + 8) + 8 N0 bytes against at least (M0 + N0 / 16) pages of 8 KB.)
+struct Changed {
+  int pos;
+  unsigned move;                                     // old cluster | new cluster << 16
+};
+static_assert(kMaxInitClusters <= 65536, "two cluster ids per word");
+__device__ inline double* km_sums(const View& v, int u) { return (double*)page_ptr(v, u, 0); }
+__device__ inline float* km_rows(const View& v, int u) { return (float*)(km_sums(v, u) + (size_t)v.M0 * kHeadDim); }
+__device__ inline Changed* km_changed(const View& v, int u) { return (Changed*)(km_rows(v, u) + (size_t)v.M0 * kHeadDim); }
+__device__ inline int* km_counts(const View& v, int u, int N0, int which) {
+  return (int*)(km_changed(v, u) + N0) + which * v.M0;
+}
+
+// A-operand order of one 32-cluster tile: [term][k-step of 16][lane][8], lane = (k%16)/8*32 + row.
+__device__ inline size_t kmA_index(int nterms, int j, int term, int d) {
+  return ((((size_t)(j >> 5) * nterms + term) * 8 + (d >> 4)) * 64 + (((d & 15) >> 3) << 5) + (j & 31)) * 8 + (d & 7);
+}
+
+// Sum over the 16 lanes of a row; every lane of the row gets it (float64 butterfly on DPP row operations).
+template <int CTRL>
+__device__ __forceinline__ double row_step(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, false);
+  return x + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_sum_f64(double x) {
+  x = row_step<kDppXor1>(x);
+  x = row_step<kDppXor2>(x);
+  x = row_step<kDppHalfMirror>(x);
+  return row_step<kDppMirror>(x);
+}
+
+// Norms that bound the filter's error, folded over the clusters that a thread has written.
+struct CentreNorms {
+  float r, rho;                                      // |r_j|, |r_j - its 16-bit terms|
+};
+// Sixteen lanes write centre j (lane c of them coordinates 8c .. 8c+7): the float32 table and, for 16-bit types, the
+// filter's terms in A-operand order with -|r_j|^2 / 2.
+template <int DT>
+__device__ inline void write_centre(const View& v, int u, int j, int c, const float (&r)[8], CentreNorms& cn) {
+  float* R = unit_R(v, u);
+  *(f4*)(R + r_index(j, c * 8)) = f4{r[0], r[1], r[2], r[3]};
+  *(f4*)(R + r_index(j, c * 8 + 4)) = f4{r[4], r[5], r[6], r[7]};
+  if constexpr (DT != DYNAKV_F32) {
+    float* row = km_rows(v, u) + (size_t)j * kHeadDim + c * 8;
+    *(f4*)row = f4{r[0], r[1], r[2], r[3]};
+    *(f4*)(row + 4) = f4{r[4], r[5], r[6], r[7]};
+    constexpr int NT = kTerms<DT>;
+    uint16_t bits[NT][8];
+    double nn = 0.0, rr = 0.0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      nn = fma((double)r[e], (double)r[e], nn);
+      float rem = r[e];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        float part;
+        if constexpr (DT == DYNAKV_BF16) { const __bf16 b = (__bf16)rem; part = (float)b; bits[t][e] = __builtin_bit_cast(uint16_t, b); }
+        else { const _Float16 hh = (_Float16)rem; part = (float)hh; bits[t][e] = __builtin_bit_cast(uint16_t, hh); }
+        rem -= part;                                 // exact: part agrees with rem to half of its digits
+      }
+      rr = fma((double)rem, (double)rem, rr);
+    }
+    uint16_t* A = v.kmA + (size_t)u * v.kmA_stride;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      uint4 w;
+      w.x = bits[t][0] | ((uint32_t)bits[t][1] << 16); w.y = bits[t][2] | ((uint32_t)bits[t][3] << 16);
+      w.z = bits[t][4] | ((uint32_t)bits[t][5] << 16); w.w = bits[t][6] | ((uint32_t)bits[t][7] << 16);
+      *(uint4*)(A + kmA_index(NT, j, t, c * 8)) = w;
+    }
+    nn = row_sum_f64(nn);
+    rr = row_sum_f64(rr);
+    if (c == 0) v.hn[(size_t)u * v.Mpad + j] = (float)(-0.5 * nn);
+    cn.r = fmaxf(cn.r, (float)sqrt(nn) * 1.000001f);
+    cn.rho = fmaxf(cn.rho, (float)sqrt(rr) * 1.000001f);
+  }
+}
+// The workgroup's maxima into the unit's (which only ever grow during a build: a bound of an earlier centre stays a
+// bound).  Non-negative floats order like their bits.  sm: 2 ints of LDS per wavefront.
+__device__ inline void fold_norms(const View& v, int u, CentreNorms cn, int* sm) {
+  const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int r = wave_max(__float_as_int(cn.r)), q = wave_max(__float_as_int(cn.rho));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) { sm[2 * w] = r; sm[2 * w + 1] = q; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int mr = sm[0], mq = sm[1];
+    for (int k = 1; k < nw; ++k) { mr = max(mr, sm[2 * k]); mq = max(mq, sm[2 * k + 1]); }
+    atomicMax((int*)&v.rmax[u], mr);
+    atomicMax((int*)&v.rhomax[u], mq);
+  }
+}
+
+// ---- start --------------------------------------------------------------------------------------------------------
+// One workgroup per unit, first kernel of a build: clears the unit's error word and the k-means' own counters, then flags
+// initial positions that are out of range or given twice (the build still runs, with such a position clamped).
 __global__ __launch_bounds__(256) void kmeans_check_init_kernel(View v, int N0, const int* init_idx) {
   __shared__ unsigned seen[kMaxPrefill / 32];
   const int u = blockIdx.x, tid = threadIdx.x;
   for (int i = tid; i < kMaxPrefill / 32; i += 256) seen[i] = 0u;
-  if (tid == 0) v.err[u] = 0;
+  if (tid == 0) {
+    v.err[u] = 0; v.has_empty[u] = 0; v.rmax[u] = 0.f; v.rhomax[u] = 0.f;
+    v.n_changed[2 * u] = 0; v.n_changed[2 * u + 1] = 0;
+    v.xrange[2 * u] = 0x7FFFFFFF; v.xrange[2 * u + 1] = -0x7FFFFFFF;
+  }
   __syncthreads();
   bool bad = false;
   for (int j = tid; j < v.M0; j += 256) {
@@ -29,117 +149,63 @@ __global__ __launch_bounds__(256) void kmeans_check_init_kernel(View v, int N0, 
   if (bad) atomicOr(&v.err[u], DYNAKV_ERR_INIT);
 }
 
-// R[u][j] = key at position init_idx[u][j]
-__global__ __launch_bounds__(128) void kmeans_init_kernel(View v, const void* X, int N0, const int* init_idx) {
-  const int u = blockIdx.y, j = blockIdx.x, d = threadIdx.x;
-  int p = init_idx[(size_t)u * v.M0 + j];
-  p = min(max(p, 0), N0 - 1);
-  unit_R(v, u)[r_index(j, d)] = load_elem(X, ((size_t)u * N0 + p) * kHeadDim + d, v.dtype);
-  if (j == 0 && d == 0) { v.xrange[2 * u] = 0x7FFFFFFF; v.xrange[2 * u + 1] = -0x7FFFFFFF; }
+// Centre j = key at position init_idx[u][j]; the rows that pad the filter's table to whole chunks lose every comparison.
+// grid (ceil(M0 / 16) or ceil(Mpad / 16), U), sixteen lanes per centre.
+template <int DT>
+__global__ __launch_bounds__(256) void kmeans_start_kernel(View v, const void* X, int N0, const int* init_idx) {
+  __shared__ int sm[8];
+  const int u = blockIdx.y, j = blockIdx.x * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15;
+  CentreNorms cn{0.f, 0.f};
+  if (j < v.M0) {
+    const int p = min(max(init_idx[(size_t)u * v.M0 + j], 0), N0 - 1);
+    float r[8];
+    load8(X, ((size_t)u * N0 + p) * kHeadDim + c * 8, DT, r);
+    write_centre<DT>(v, u, j, c, r, cn);
+  } else if (DT != DYNAKV_F32 && j < v.Mpad) {
+    uint16_t* A = v.kmA + (size_t)u * v.kmA_stride;
+    for (int t = 0; t < kTerms<DT>; ++t) *(uint4*)(A + kmA_index(kTerms<DT>, j, t, c * 8)) = uint4{0, 0, 0, 0};
+    if (c == 0) v.hn[(size_t)u * v.Mpad + j] = -3.0e38f;             // (finite: the filter writes into its low bits)
+  }
+  if constexpr (DT != DYNAKV_F32) fold_norms(v, u, cn, sm);
 }
 
 // ---- order-free centre sums -----------------------------------------------------------------------------
-// The centre of a cluster is the float64 sum of its members in ascending position, divided by the count.  Every
+// The centre of a cluster is the float64 sum of its members, divided by the count.  Every
 // key of a 16-bit type is an integer multiple of 2^q, q = (smallest exponent in the unit) - (mantissa bits), and
 // smaller than 2^(emax+1); if (emax + 1 + ceil(log2 N0)) - q <= 53, every partial sum of any subset in any order
-// is exactly representable, so the sum does not depend on the order at all and the members need not be sorted
-// first: a counting sort that leaves them in arbitrary order is enough.  Units whose keys span too wide a range
-// (and float32 keys, and more than 2048 centres) keep the sorted path.
-constexpr int kAtomicCentres = 2048;
-__global__ __launch_bounds__(256) void kmeans_range_kernel(View v, const void* X, int N0) {
-  const int u = blockIdx.y;
-  if (v.dtype == DYNAKV_F32) return;
-  const uint4* x = (const uint4*)((const uint16_t*)X + (size_t)u * N0 * kHeadDim);
-  const int n16 = N0 * kHeadDim / 8;
-  const int ebits = v.dtype == DYNAKV_F16 ? 5 : 8, mbits = v.dtype == DYNAKV_F16 ? 10 : 7;
-  const int bias = v.dtype == DYNAKV_F16 ? 15 : 127, emask = (1 << ebits) - 1;
-  int lo = 0x7FFFFFFF, hi = -0x7FFFFFFF;
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n16; i += gridDim.x * 256) {
-    const uint4 w = x[i];
-    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t h = (ww[e >> 1] >> ((e & 1) * 16)) & 0x7FFFu;
-      if (h == 0) continue;
-      const int eb = (int)(h >> mbits) & emask;
-      // subnormals share the grid of the smallest normal exponent; infinities and NaNs make the range unusable
-      const int ex = eb == emask ? 0x3FFFFFFF : (eb == 0 ? 1 : eb) - bias;
-      lo = min(lo, ex); hi = max(hi, ex);
-    }
-  }
-  for (int o = 32; o > 0; o >>= 1) { lo = min(lo, __shfl_xor(lo, o)); hi = max(hi, __shfl_xor(hi, o)); }
-  if ((threadIdx.x & 63) == 0 && hi >= lo) { atomicMin(&v.xrange[2 * u], lo); atomicMax(&v.xrange[2 * u + 1], hi); }
-}
-// Whether unit u qualifies (see above); q receives the grid exponent.
-__device__ inline bool sums_order_free(const View& v, int u, int N0, int* q) {
-  if (v.dtype == DYNAKV_F32 || v.M0 > kAtomicCentres) return false;
+// is exactly representable.  The sum then does not depend on the order at all and can follow the points that join and
+// leave a cluster: an update reads the changed points' keys only, and its result is the sum formed anew, bit for bit.
+// (float16 with at most 8192 keys always qualifies: exponents -14 .. 15 on a grid of 2^-24.)  Units whose keys span
+// too wide a range, and float32 keys, have their sums formed anew in ascending position in every iteration.
+__host__ __device__ inline bool sums_order_free_by_type(int dtype, int N0) { return dtype == DYNAKV_F16 && N0 <= 8192; }
+__device__ inline bool sums_order_free(const View& v, int u, int N0) {
+  if (v.dtype == DYNAKV_F32) return false;
+  if (sums_order_free_by_type(v.dtype, N0)) return true;
   const int lo = v.xrange[2 * u], hi = v.xrange[2 * u + 1];
   const int mbits = v.dtype == DYNAKV_F16 ? 10 : 7;
-  if (hi < lo) { *q = 0; return true; }               // all keys zero
+  if (hi < lo) return true;                           // all keys zero
   int L = 0;
   while ((1 << L) < N0) ++L;
-  *q = lo - mbits;
   return hi < 0x3FFFFFFF && (hi + 1 + L) - (lo - mbits) <= 53;
 }
 
-// Members of every cluster of the last assignment, in no particular order, for the units whose sums are
-// order-free: a counting sort by label (sizes, their prefix, then one LDS counter per cluster hands out the
-// places).  One workgroup per unit.  Also the cluster sizes and whether any cluster is empty.
-__global__ __launch_bounds__(1024) void kmeans_bucket_kernel(View v, int N0) {
-  __shared__ int cnt[kAtomicCentres], off[kAtomicCentres];
-  __shared__ int sm[64];
-  const int u = blockIdx.x, tid = threadIdx.x;
-  int q;
-  if (!sums_order_free(v, u, N0, &q)) return;
-  for (int j = tid; j < kAtomicCentres; j += 1024) cnt[j] = 0;
-  __syncthreads();
-  const int* lab = v.labels + (size_t)u * v.Ncap;
-  for (int i = tid; i < N0; i += 1024) atomicAdd(&cnt[lab[i]], 1);
-  __syncthreads();
-  int c2[2], tot = 0, empty = 0;
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int j = tid * 2 + k;
-    c2[k] = j < v.M0 ? cnt[j] : 0;
-    tot += c2[k];
-    empty |= j < v.M0 && c2[k] == 0;
-  }
-  int total;
-  int run = block_excl_scan(tot, sm, total);
-  int* koff = v.koff + (size_t)u * (v.Mcap + 1);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int j = tid * 2 + k;
-    if (j < v.M0) { off[j] = run; koff[j] = run; v.cn[(size_t)u * v.Mcap + j] = c2[k]; cnt[j] = 0; }
-    run += c2[k];
-  }
-  if (tid == 0) { koff[v.M0] = N0; v.has_empty[u] = 0; }
-  __syncthreads();
-  if (empty) v.has_empty[u] = 1;
-  int* order = v.order + (size_t)u * v.Ncap;
-  for (int i = tid; i < N0; i += 1024) {
-    const int j = lab[i];
-    order[off[j] + atomicAdd(&cnt[j], 1)] = i;
-  }
-}
-
-// One thread per point: nearest centre in exact float64, centres staged through LDS in tiles.
+// ---- assignment, float32 keys -------------------------------------------------------------------------------------
+// Four lanes per point, 32 coordinates each, nearest centre in exact float64, centres staged through LDS in tiles.  (One
+// lane per point left a small prompt on a handful of wavefronts: 2048 keys x 32 centres 55 us, now 17 us.)
 constexpr int kTileC = 32;
 __global__ __launch_bounds__(256) void kmeans_assign_f64_kernel(View v, const void* X, int N0) {
-  __shared__ float rs[kTileC][kHeadDim];
-  const int u = blockIdx.y;
-  const int i = blockIdx.x * 256 + threadIdx.x;
+  constexpr int kRow = kHeadDim + 16;                 // quarters 36 floats apart: the four lanes of a point hit different banks
+  __shared__ __align__(16) float rs[kTileC][kRow];
+  const int u = blockIdx.y, q = threadIdx.x & 3;
+  const int i = blockIdx.x * 64 + (threadIdx.x >> 2);
   const bool live = i < N0;
-  float x[kHeadDim];
-  {
-    const size_t base = ((size_t)u * N0 + (live ? i : 0)) * kHeadDim;
+  float x[32];
 #pragma unroll
-    for (int d8 = 0; d8 < kHeadDim / 8; ++d8) {
-      float t[8];
-      load8(X, base + d8 * 8, v.dtype, t);
+  for (int k = 0; k < 4; ++k) {
+    float t[8];
+    load8(X, ((size_t)u * N0 + (live ? i : 0)) * kHeadDim + q * 32 + k * 8, DYNAKV_F32, t);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) x[d8 * 8 + e] = t[e];
-    }
+    for (int e = 0; e < 8; ++e) x[k * 8 + e] = t[e];
   }
   double best = __builtin_inf();
   int arg = 0;
@@ -147,247 +213,170 @@ __global__ __launch_bounds__(256) void kmeans_assign_f64_kernel(View v, const vo
   for (int j0 = 0; j0 < v.M0; j0 += kTileC) {
     const int nt = min(kTileC, v.M0 - j0);
     __syncthreads();
-    for (int t = threadIdx.x; t < nt * kHeadDim; t += 256) rs[t / kHeadDim][t % kHeadDim] = R[r_index(j0 + t / kHeadDim, t % kHeadDim)];
+    for (int t = threadIdx.x; t < kTileC * 32; t += 256) {           // 16 bytes per thread, contiguous over the clusters
+      const int d4 = t / kTileC, jj = t % kTileC;
+      if (jj < nt) *(f4*)&rs[jj][d4 * 4 + (d4 >> 3) * 4] = *(const f4*)(R + r_index(j0 + jj, d4 * 4));
+    }
     __syncthreads();
     for (int jj = 0; jj < nt; ++jj) {
-      double blk[16];
+      double blk[4];
 #pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        double a = 0.0;
+      for (int k = 0; k < 4; ++k) {
+        const f4 a = *(const f4*)&rs[jj][q * 36 + k * 8], b = *(const f4*)&rs[jj][q * 36 + k * 8 + 4];
+        double s = 0.0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const double t = (double)x[k * 8 + e] - (double)rs[jj][k * 8 + e];
-          a = fma(t, t, a);
+          const double t = (double)x[k * 8 + e] - (double)(e < 4 ? a[e] : b[e - 4]);
+          s = fma(t, t, s);
         }
-        blk[k] = a;
+        blk[k] = s;
       }
-      double acc = 0.0;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) acc += blk[k];
+      const double acc = blocked16_quad(blk);
       if (acc < best) { best = acc; arg = j0 + jj; }
     }
   }
-  if (live) {
-    v.labels[(size_t)u * v.Ncap + i] = arg;
-    v.dist[(size_t)u * v.Ncap + i] = best;
-  }
+  if (live && q == 0) v.labels[(size_t)u * v.Ncap + i] = arg;
 }
 
-// One workgroup per unit: bitonic sort of (label, position) keys in LDS -> members of every cluster in
-// ascending position, and the start of every cluster in that order.
-__global__ __launch_bounds__(1024) void kmeans_sort_kernel(View v, int N0, int Npad, int pos_bits, int always) {
-  __shared__ uint32_t key[kMaxPrefill];
-  const int u = blockIdx.x, tid = threadIdx.x;
-  int qx;
-  if (!always && sums_order_free(v, u, N0, &qx)) return;       // the order is only needed for the layout
-  const int* lab = v.labels + (size_t)u * v.Ncap;
-  for (int i = tid; i < Npad; i += 1024) key[i] = i < N0 ? ((uint32_t)lab[i] << pos_bits) | (uint32_t)i : 0xFFFFFFFFu;
-  __syncthreads();
-  for (int k = 2; k <= Npad; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = tid; i < Npad; i += 1024) {
-        const int ixj = i ^ j;
-        if (ixj > i) {
-          const uint32_t a = key[i], b = key[ixj];
-          const bool up = (i & k) == 0;
-          if ((a > b) == up) { key[i] = b; key[ixj] = a; }
-        }
-      }
-      __syncthreads();
-    }
-  int* order = v.order + (size_t)u * v.Ncap;
-  int* koff = v.koff + (size_t)u * (v.Mcap + 1);
-  const uint32_t pmask = (1u << pos_bits) - 1;
-  if (tid == 0) v.has_empty[u] = 0;
-  __syncthreads();
-  for (int q = tid; q < N0; q += 1024) {
-    const uint32_t kq = key[q];
-    order[q] = (int)(kq & pmask);
-    const int lq = (int)(kq >> pos_bits);
-    const int lp = q ? (int)(key[q - 1] >> pos_bits) : -1;
-    for (int l = lp + 1; l <= lq; ++l) koff[l] = q;          // also covers empty clusters in between
-    if (lq - lp > 1) v.has_empty[u] = 1;
-    if (q == N0 - 1) {
-      for (int l = lq + 1; l <= v.M0; ++l) koff[l] = N0;
-      if (lq + 1 < v.M0) v.has_empty[u] = 1;
-    }
-  }
+// c + the squares of a pair of 16-bit values, in float32.
+typedef _Float16 h2v __attribute__((ext_vector_type(2)));
+typedef __bf16 b2v __attribute__((ext_vector_type(2)));
+template <bool BF>
+__device__ __forceinline__ float dot2(uint32_t w, float c) {
+  if constexpr (BF) return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2v, w), __builtin_bit_cast(b2v, w), c, false);
+  else return __builtin_amdgcn_fdot2(__builtin_bit_cast(h2v, w), __builtin_bit_cast(h2v, w), c, false);
 }
 
-// Sixteen lanes per cluster, eight coordinates per lane (one 16-byte load per member of a 16-bit type): centre
-// = mean of the members, added one by one in the order of `order` (ascending position after the sort: Eq. 4
-// in the fixed order; any order for the units whose sums are order-free).  The 16 lanes fetch the next 16
-// member positions with one load while the current 16 rows, all in flight at once, are added.
-// grid (ceil(M0/16), U), 256 threads.
-template <int DT>
-__global__ __launch_bounds__(256) void kmeans_update_kernel(View v, const void* X, int N0) {
-  constexpr int RB = DT == DYNAKV_F32 ? 8 : 16;        // rows in flight per lane
-  const int u = blockIdx.y, j = blockIdx.x * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15;
-  if (j >= v.M0) return;
-  const int* koff = v.koff + (size_t)u * (v.Mcap + 1);
-  const int* order = v.order + (size_t)u * v.Ncap;
-  const int b = koff[j], e = koff[j + 1];
-  if (c == 0) v.cn[(size_t)u * v.Mcap + j] = e - b;
-  if (e == b) return;
-  double s[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) s[k] = 0.0;
-  int mine = b + c < e ? order[b + c] : 0;              // lane c holds member c of the current 16
-  for (int q0 = b; q0 < e; q0 += 16) {
-    const int next = q0 + 16 + c < e ? order[q0 + 16 + c] : 0;
-#pragma unroll
-    for (int h = 0; h < 16; h += RB) {
-      if (q0 + h >= e) break;
-      float x[RB][8];
-#pragma unroll
-      for (int k = 0; k < RB; ++k) {
-        const int pos = __shfl(mine, h + k, 16);
-        load8(X, ((size_t)u * N0 + pos) * kHeadDim + c * 8, DT, x[k]);
-      }
-#pragma unroll
-      for (int k = 0; k < RB; ++k)
-        if (q0 + h + k < e) {
-#pragma unroll
-          for (int d = 0; d < 8; ++d) s[d] += (double)x[k][d];
-        }
-    }
-    mine = next;
-  }
-  float* R = unit_R(v, u);
-#pragma unroll
-  for (int d = 0; d < 8; ++d) R[r_index(j, c * 8 + d)] = (float)(s[d] / (double)(e - b));
-}
-
-// One workgroup per unit: every empty cluster, in ascending id, takes the not-yet-taken point that is
-// farthest from its own centre (ties to the lowest position).
-__global__ __launch_bounds__(256) void kmeans_reseed_kernel(View v, const void* X, int N0) {
-  __shared__ double sv[256];
-  __shared__ int si[256];
-  __shared__ int any_empty;
-  const int u = blockIdx.x, tid = threadIdx.x;
-  double* dist = v.dist + (size_t)u * v.Ncap;
-  if (!v.has_empty[u]) return;
-  (void)any_empty;
-  for (int j = 0; j < v.M0; ++j) {
-    if (v.cn[(size_t)u * v.Mcap + j] != 0) continue;   // uniform across the block
-    double bv = -1.0;
-    int bi = -1;
-    for (int i = tid; i < N0; i += 256) {
-      const double t = dist[i];
-      if (t > bv) { bv = t; bi = i; }       // ascending i per thread: the first maximum stays
-    }
-    sv[tid] = bv; si[tid] = bi;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if (tid < o) {
-        const double ov = sv[tid + o];
-        const int oi = si[tid + o];
-        if (oi >= 0 && (ov > sv[tid] || (ov == sv[tid] && (si[tid] < 0 || oi < si[tid])))) { sv[tid] = ov; si[tid] = oi; }
-      }
-      __syncthreads();
-    }
-    const int far = si[0];
-    __syncthreads();
-    if (far < 0) break;                      // every point already taken
-    if (tid < kHeadDim)
-      unit_R(v, u)[r_index(j, tid)] = load_elem(X, ((size_t)u * N0 + far) * kHeadDim + tid, v.dtype);
-    if (tid == 0) dist[far] = -2.0;          // taken
-    __syncthreads();
-  }
+// BYTES (4 or 16) from each lane's global address to LDS at base + lane * BYTES, with no detour through registers.  As an
+// instruction of its own because the compiler, which cannot tell the two LDS buffers of a pipeline apart, would wait for
+// the load before the next read of either; the caller waits (vmcnt) and synchronises before it reads the data.
+template <int BYTES>
+__device__ __forceinline__ void load_to_lds(const void* src, void* base) {
+  const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)base);
+  if constexpr (BYTES == 16)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(at), "v"(src) : "memory", "m0");
 }
 
 // ---- assignment through the matrix cores --------------------------------------------------------------
-// Filter + exact re-check.  z_ij = <x_i, r_j> - |r_j|^2/2 orders the centres like the squared distance.  The
-// filter evaluates it with MFMA on 16-bit operands: x is exact in its storage type, r_j is split into two
-// (f16) or three (bf16) 16-bit terms whose sum carries float32 accuracy, accumulation is float32.  The error
-// of a filtered z is below eps_i = gamma * |x_i| * max_j |r_j|; a point whose best and second-best filtered
-// values are more than 2 eps_i apart has the same nearest centre in exact arithmetic, every other point is
-// listed and gets the exact float64 scan (kmeans_exact_kernel), so labels equal the float64 definition.
-typedef _Float16 h8v __attribute__((ext_vector_type(8)));
-typedef __bf16 b8v __attribute__((ext_vector_type(8)));
-typedef float f16v __attribute__((ext_vector_type(16)));
-// Bound on the relative error of a filtered inner product, |error| <= gamma |x| |r|: the products of two 16-bit
-// values are exact in float32; their accumulation (128 per term: 256 for f16's two terms, 384 for bf16's three)
-// errs by at most n * 2^-24 of the sum of their magnitudes (2^-16 and 2^-15.4); what the terms leave of r is below
-// 2^-22 |r|.  The constants below are twice the sum of those.
-constexpr float kFilterGammaF16 = 1.0f / 32768.0f, kFilterGammaBF16 = 1.0f / 16384.0f;
-
-// A-operand order of one 32-cluster tile: [term][k-step of 16][lane][8], lane = (k%16)/8*32 + row.
-__device__ inline size_t kmA_index(int nterms, int j, int term, int d) {
-  return ((((size_t)(j >> 5) * nterms + term) * 8 + (d >> 4)) * 64 + (((d & 15) >> 3) << 5) + (j & 31)) * 8 + (d & 7);
-}
-
-// Thread per centre (lane = centre, so the table reads are contiguous): splits r_j into 16-bit terms in
-// A-operand order, stores -|r_j|^2/2 and folds |r_j| into the unit's maximum.  grid (ceil(Mpad/256), U).
-__global__ void kmeans_reset_kernel(View v) {
-  const int u = blockIdx.x * 256 + threadIdx.x;
-  if (u < v.U) { v.rmax[u] = 0.f; v.nflagged[u] = 0; }
-}
-template <bool BF>
-__global__ __launch_bounds__(256) void kmeans_prep_kernel(View v) {
-  constexpr int NT = BF ? 3 : 2;
-  const int u = blockIdx.y, j = blockIdx.x * 256 + threadIdx.x;
-  const int mpad = (v.M0 + 31) / 32 * 32;
-  if (j >= mpad) return;
-  const float* R = unit_R(v, u);
-  uint16_t* A = v.kmA + (size_t)u * v.kmA_stride;
-  double nn = 0.0;
-  for (int d8 = 0; d8 < kHeadDim / 8; ++d8) {
-    float r[8];
-    if (j < v.M0) {
-      const f4 a = *(const f4*)(R + r_index(j, d8 * 8)), b = *(const f4*)(R + r_index(j, d8 * 8 + 4));
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { r[e] = a[e]; r[4 + e] = b[e]; }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) r[e] = 0.f;
-    }
-    uint16_t bits[NT][8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      nn += (double)r[e] * (double)r[e];
-      float rem = r[e];
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        float part;
-        if constexpr (BF) { const __bf16 b = (__bf16)rem; part = (float)b; bits[t][e] = __builtin_bit_cast(uint16_t, b); }
-        else { const _Float16 hh = (_Float16)rem; part = (float)hh; bits[t][e] = __builtin_bit_cast(uint16_t, hh); }
-        rem -= part;
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      uint4 w;
-      w.x = bits[t][0] | ((uint32_t)bits[t][1] << 16); w.y = bits[t][2] | ((uint32_t)bits[t][3] << 16);
-      w.z = bits[t][4] | ((uint32_t)bits[t][5] << 16); w.w = bits[t][6] | ((uint32_t)bits[t][7] << 16);
-      *(uint4*)(A + kmA_index(NT, j, t, d8 * 8)) = w;
-    }
-  }
-  v.hn[(size_t)u * mpad + j] = j < v.M0 ? (float)(-0.5 * nn) : -__builtin_inff();
-  if (j < v.M0) atomicMax((int*)&v.rmax[u], __float_as_int((float)sqrt(nn) * 1.000001f));   // non-negative floats order like ints
-}
-
-// grid (ceil(N0/256), U); 4 wavefronts x 64 points.  Z^T = R~ X^T in 32x32 tiles: lane (p, h) ends up with the
-// filtered values of point p for the centres 8*(i/4) + 4*h + i%4 of every tile, so the running best / second
-// best need no cross-lane work until the very end.
-template <bool BF>
-__global__ __launch_bounds__(256, 3) void kmeans_assign_mfma_kernel(View v, const void* X, int N0) {
-  constexpr int NT = BF ? 3 : 2;
-  __shared__ uint4 sA[2][NT * 8 * 64];     // two tiles: the next one is fetched while this one is consumed
-  __shared__ float shn[2][32];
-  const int u = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// z_ij = <x_i, r_j> - |r_j|^2/2 orders the centres like the squared distance.  The filter evaluates it with MFMA on
+// 16-bit operands: x is exact in its storage type, r_j is replaced by the sum of its 16-bit terms (one for float16, two
+// for bfloat16), accumulation is float32.  |error of z| <= eps_i:
+//   |x_i| max_j |r_j - terms|               what the terms leave of a centre (its exact norm is known)
+//   NT 2^-16 (|x_i| B + B^2 / 2)            accumulation of NT x 128 exact products onto -|r_j|^2/2, doubled
+//   2^bits 2^-23 |z|                        the running best three carry the centre's number in their low mantissa bits
+// B bounds the norm of every centre that can be the nearest: such a centre is no farther from x_i than the best one found,
+// whose distance follows from its z (and B <= max |r|).
+// A point whose best and second-best values are more than 2 eps_i apart has the same nearest centre in exact arithmetic.
+// If only the second lies within that distance, the two centres are compared in float64 by 16 lanes; if the third does too
+// (about one point in a thousand), the workgroup goes through all centres in float64.  Labels therefore equal the
+// float64 definition (ties to the lowest index).
+//
+// Shape: 64 points per wavefront as two B operands held in registers; Z^T = R~ X^T in 32x32 tiles, so lane (p, h) ends up
+// with 16 values of point p per tile and the running best three need no cross-lane work until the end.  Four vector
+// instructions per value (number into the low bits, two medians, one maximum) against 8 NT matrix instructions per 32
+// values: with one term the two pipes are about level (measured 49 % and 31 % busy), which is why the second term of
+// float16 was worth dropping for a few per cent of the points to be re-checked.  Centres go through two LDS buffers of 16 KB, the next one filled by direct
+// global-to-LDS loads while this one is consumed, one barrier per buffer; four wavefronts share them (eight were slower: one phase
+// of latency more in step).  All workgroups of a unit have the same number modulo 8, i.e. share an L2.
+// The first iteration (first) labels every point; later ones list the points whose label changed.
+constexpr int kAssignWaves = 4;
+template <int DT>
+__global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(View v, const void* X, int N0, int gx, int first, int slot,
+                                                                  int code_bits) {
+  constexpr bool BF = DT == DYNAKV_BF16;
+  constexpr int NT = kTerms<DT>, NW = kAssignWaves;
+  constexpr int kTileBytes = NT * 8 * 1024;                // one 32-centre tile of terms
+  constexpr int kTiles = kChunkTiles<DT>, kChunkC = 32 * kTiles, kChunkBytes = kTiles * kTileBytes;
+  __shared__ __align__(16) unsigned char sA[2][kChunkBytes];
+  __shared__ __align__(16) float shn[2][kChunkC];
+  constexpr int kScan = 8;                                 // points with many candidates, taken this many at a time
+  __shared__ short s_list[NW * 64];
+  __shared__ double s_d[kScan][NW];
+  __shared__ int s_j[kScan][NW], s_n3;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // workgroup L: unit 8 (L / 8 / gx) + L % 8, points (L / 8) % gx
+  const int u = (blockIdx.x >> 3) / gx * 8 + (blockIdx.x & 7), xb = (blockIdx.x >> 3) % gx;
+  if (u >= v.U) return;
   const int p = lane & 31, h = lane >> 5;
-  const int ntiles = (v.M0 + 31) / 32;
-  const int pbase = blockIdx.x * 256 + wave * 64;
+  const int nchunk = v.Mpad / kChunkC;
+  const int pbase = (xb * NW + wave) * 64;
+  const char* gA = (const char*)(v.kmA + (size_t)u * v.kmA_stride);
+  const float* hn = v.hn + (size_t)u * v.Mpad;
+  auto fetch = [&](int chunk, int buf) __attribute__((always_inline)) {
+    constexpr int kPer = kChunkBytes / 1024 / NW;          // 1 KB pieces per wavefront
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int piece = wave * kPer + k;
+      load_to_lds<16>(gA + (size_t)chunk * kChunkBytes + piece * 1024 + lane * 16, sA[buf] + piece * 1024);
+    }
+    if (wave == NW - 1 && lane < kChunkC) load_to_lds<4>(hn + chunk * kChunkC + lane, shn[buf]);
+  };
+  fetch(0, 0);
+  if (tid == 0) s_n3 = 0;
+  if (xb == 0 && tid == 0) v.n_changed[2 * u + (slot ^ 1)] = 0;        // the list of the coming iteration
   uint4 bx[2][8];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int pt = pbase + t * 32 + p;
-    const uint16_t* xr = (const uint16_t*)X + ((size_t)u * N0 + (pt < N0 ? pt : 0)) * kHeadDim + h * 8;
+    const uint16_t* xr = (const uint16_t*)X + ((size_t)u * N0 + (pt < N0 ? pt : N0 - 1)) * kHeadDim + h * 8;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) bx[t][ks] = pt < N0 ? *(const uint4*)(xr + ks * 16) : uint4{0, 0, 0, 0};
+    for (int ks = 0; ks < 8; ++ks) bx[t][ks] = *(const uint4*)(xr + ks * 16);
   }
-  float xnorm[2];                               // |x| of this lane's point, from the operand registers
+  const float kLow = -3.2e38f;
+  float best[2] = {kLow, kLow}, second[2] = {kLow, kLow}, third[2] = {kLow, kLow};
+  unsigned keep = ~((1u << code_bits) - 1u);
+  asm("" : "+v"(keep));                                    // in a vector register: mask and number go in with one instruction
+  int old = 0;
+  if (!first) old = v.labels[(size_t)u * v.Ncap + min(pbase + lane, N0 - 1)];
+  __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0), in a form that the compiler counts with: no waits for
+                                                           // the operands inside the loop
+  __syncthreads();
+  for (int ch = 0; ch < nchunk; ++ch) {
+    const int cur = ch & 1;
+    if (ch + 1 < nchunk) fetch(ch + 1, cur ^ 1);
+#pragma unroll
+    for (int tt = 0; tt < kTiles; ++tt) {
+      f16v acc[2];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f4 n4 = *(const f4*)&shn[cur][tt * 32 + 8 * g + 4 * h];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { acc[0][4 * g + e] = n4[e]; acc[1][4 * g + e] = n4[e]; }
+      }
+#pragma unroll
+      for (int term = 0; term < NT; ++term)
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          const uint4 a = *(const uint4*)(sA[cur] + tt * kTileBytes + (term * 8 + ks) * 1024 + lane * 16);
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            if constexpr (BF)
+              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(b8v, a), __builtin_bit_cast(b8v, bx[t][ks]), acc[t], 0, 0, 0);
+            else
+              acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8v, a), __builtin_bit_cast(h8v, bx[t][ks]), acc[t], 0, 0, 0);
+          }
+        }
+      const int code0 = (ch * kTiles + tt) * 16;                // this lane's values are numbered in the order it sees them
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        int code = code0 + i;
+        asm("" : "+s"(code));
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const float val = __uint_as_float((__float_as_uint(acc[t][i]) & keep) | (unsigned)code);
+          third[t] = __builtin_amdgcn_fmed3f(second[t], third[t], val);      // best >= second >= third
+          second[t] = __builtin_amdgcn_fmed3f(best[t], second[t], val);
+          // (as an instruction of its own: the compiler would canonicalise val first)
+          asm("v_max_f32_e32 %0, %1, %2" : "=v"(best[t]) : "v"(best[t]), "v"(val));
+        }
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wavefront's part of the next buffer is in place
+    __syncthreads();
+  }
+  float xnorm[2];                                          // |x| of this lane's two points
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     float nn = 0.f;
@@ -395,142 +384,469 @@ __global__ __launch_bounds__(256, 3) void kmeans_assign_mfma_kernel(View v, cons
     for (int ks = 0; ks < 8; ++ks) {
       const uint32_t ww[4] = {bx[t][ks].x, bx[t][ks].y, bx[t][ks].z, bx[t][ks].w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint16_t hh = (uint16_t)(ww[e >> 1] >> ((e & 1) * 16));
-        const float x = BF ? bf16_to_float(hh) : f16_to_float(hh);
-        nn += x * x;
-      }
+      for (int e = 0; e < 4; ++e) nn = dot2<BF>(ww[e], nn);
     }
     nn += __shfl_xor(nn, 32);
     xnorm[t] = __builtin_sqrtf(nn) * 1.0001f;
   }
-  float best[2] = {-__builtin_inff(), -__builtin_inff()}, second[2] = {-__builtin_inff(), -__builtin_inff()};
-  int bidx[2] = {0, 0};
-  const uint4* gA = (const uint4*)(v.kmA + (size_t)u * v.kmA_stride);
-  const float* hn = v.hn + (size_t)u * ntiles * 32;
-  // Tiles travel global -> registers -> LDS one iteration ahead of their use (plain scalars, so that they stay
-  // in registers); the empty asm statement keeps the compiler from sinking the loads down to the LDS stores.
-  uint4 st0, st1, st2, st3, st4 = {0, 0, 0, 0}, st5 = {0, 0, 0, 0};
-  float sh = 0.f;
-#define KM_FETCH(tile)                                                        \
-  {                                                                           \
-    const uint4* g_ = gA + (size_t)(tile) * NT * 512 + tid;                   \
-    st0 = g_[0]; st1 = g_[256]; st2 = g_[512]; st3 = g_[768];                 \
-    if constexpr (NT == 3) { st4 = g_[1024]; st5 = g_[1280]; }                \
-    if (tid < 32) sh = hn[(tile) * 32 + tid];                                 \
-    asm volatile("" ::: "memory");                                            \
-  }
-#define KM_COMMIT(buf)                                                        \
-  {                                                                           \
-    uint4* d_ = sA[buf] + tid;                                                \
-    d_[0] = st0; d_[256] = st1; d_[512] = st2; d_[768] = st3;                 \
-    if constexpr (NT == 3) { d_[1024] = st4; d_[1280] = st5; }                \
-    if (tid < 32) shn[buf][tid] = sh;                                         \
-  }
-  KM_FETCH(0);
-  KM_COMMIT(0);
-  __syncthreads();
-  for (int tile = 0; tile < ntiles; ++tile) {
-    const int cur = tile & 1;
-    if (tile + 1 < ntiles) KM_FETCH(tile + 1);
-    f16v acc[2];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) { acc[0][i] = shn[cur][8 * (i >> 2) + 4 * h + (i & 3)]; acc[1][i] = acc[0][i]; }
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-      for (int term = 0; term < NT; ++term) {
-        const uint4 a = sA[cur][(term * 8 + ks) * 64 + lane];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          if constexpr (BF)
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(b8v, a), __builtin_bit_cast(b8v, bx[t][ks]), acc[t], 0, 0, 0);
-          else
-            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8v, a), __builtin_bit_cast(h8v, bx[t][ks]), acc[t], 0, 0, 0);
-        }
-      }
+  if (first && !sums_order_free_by_type(DT, N0)) {         // the exponents of the unit's coordinates, once
+    unsigned lo16 = 0xFFFFu, hi16 = 0u;                    // smallest (zeros left out, minus one) and largest magnitude bits
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const float val = acc[t][i];
-        second[t] = __builtin_amdgcn_fmed3f(best[t], second[t], val);      // second <= best: the median is the runner-up
-        if (val > best[t]) bidx[t] = tile * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-        best[t] = fmaxf(best[t], val);
+      for (int ks = 0; ks < 8; ++ks) {
+        const uint32_t ww[4] = {bx[t][ks].x, bx[t][ks].y, bx[t][ks].z, bx[t][ks].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const unsigned mag = (ww[e >> 1] >> ((e & 1) * 16)) & 0x7FFFu;
+          hi16 = max(hi16, mag);
+          lo16 = min(lo16, (mag - 1u) & 0xFFFFu);
+        }
       }
-    if (tile + 1 < ntiles) KM_COMMIT(cur ^ 1);
-    __syncthreads();
+    const int hiw = wave_max((int)hi16), low = wave_min((int)lo16);
+    if (lane == 0 && hiw > 0) {
+      constexpr int mbits = BF ? 7 : 10, bias = BF ? 127 : 15, emask = BF ? 255 : 31;
+      const int eh = hiw >> mbits, el = (low + 1) >> mbits;
+      // subnormals share the grid of the smallest normal exponent; infinities and NaNs make the range unusable
+      atomicMax(&v.xrange[2 * u + 1], eh == emask ? 0x3FFFFFFF : max(eh, 1) - bias);
+      atomicMin(&v.xrange[2 * u], max(el, 1) - bias);
+    }
   }
-#undef KM_FETCH
-#undef KM_COMMIT
-  const float rmax = v.rmax[u];
+  // the two halves of every point's centres; afterwards lane l speaks for point pbase + l
+  float pb = kLow, ps = kLow, pt3 = kLow, pn = 0.f;
+  int ib = 0, is = 0;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    const float ob = __shfl_xor(best[t], 32), os = __shfl_xor(second[t], 32);
-    const int oi = __shfl_xor(bidx[t], 32);
-    const float nb = fmaxf(best[t], ob), ns = fmaxf(fmaxf(second[t], os), fminf(best[t], ob));
-    const int idx = (ob > best[t] || (ob == best[t] && oi < bidx[t])) ? oi : bidx[t];
-    const int pt = pbase + t * 32 + p;
-    if (h == 0 && pt < N0) {
-      v.labels[(size_t)u * v.Ncap + pt] = idx;
-      const float eps = (BF ? kFilterGammaBF16 : kFilterGammaF16) * xnorm[t] * rmax + 2.4e-7f * rmax * rmax;
-      if (!(nb - ns > 2.f * eps)) v.order[(size_t)u * v.Ncap + atomicAdd(&v.nflagged[u], 1)] = pt;
+    auto number = [&](float x, int hh) {
+      const unsigned code = __float_as_uint(x) & ~keep;
+      return (int)((code >> 4) * 32 + 8 * ((code & 15) >> 2) + 4 * hh + (code & 3));
+    };
+    const float ob = __shfl_xor(best[t], 32), os = __shfl_xor(second[t], 32), o3 = __shfl_xor(third[t], 32);
+    const bool mine = best[t] > ob || (best[t] == ob && h == 0);
+    const float u1 = mine ? ob : best[t];                              // the loser of the two bests
+    const bool s_mine = second[t] > os || (second[t] == os && h == 0);
+    const float u2 = s_mine ? second[t] : os;
+    const int n1 = mine ? number(ob, h ^ 1) : number(best[t], h), n2 = s_mine ? number(second[t], h) : number(os, h ^ 1);
+    if (t == h) {
+      pb = mine ? best[t] : ob;
+      ib = mine ? number(best[t], h) : number(ob, h ^ 1);
+      ps = fmaxf(u1, u2);
+      is = u1 >= u2 ? n1 : n2;
+      pt3 = fmaxf(fminf(u1, u2), fmaxf(third[t], o3));
+      pn = xnorm[t];
     }
   }
-}
-
-// Exact nearest centre (float64, left to right, ties to the lowest id) of every listed point: one workgroup
-// per point, thread = centre, so the centroid table is read 1 KB per wavefront at a time.  grid (B, U).
-__global__ __launch_bounds__(256) void kmeans_exact_kernel(View v, const void* X, int N0) {
-  __shared__ double xd[kHeadDim];
-  __shared__ double sv[256];
-  __shared__ int si[256];
-  const int u = blockIdx.y, tid = threadIdx.x;
-  const int nf = v.nflagged[u];
-  const float* R = unit_R(v, u);
-  for (int f = blockIdx.x; f < nf; f += gridDim.x) {
-    const int pt = v.order[(size_t)u * v.Ncap + f];
-    __syncthreads();
-    if (tid < kHeadDim) xd[tid] = (double)load_elem(X, ((size_t)u * N0 + pt) * kHeadDim + tid, v.dtype);
-    __syncthreads();
-    double best = __builtin_inf();
-    int arg = -1;
-    for (int j = tid; j < v.M0; j += 256) {
-      f4 row[8];
-      load_centroid_head(R, j, row);
-      double dist[1];
-      centroid_sums<1>(R, j, row, dist, [&](int d, float rv, double (&a)[1]) __attribute__((always_inline)) {
-        const double t = xd[d] - (double)rv;
-        a[0] = fma(t, t, a[0]);
-      });
-      const double acc = dist[0];
-      if (acc < best || arg < 0) { best = acc; arg = j; }
+  const int pt = pbase + lane;
+  const bool valid = pt < N0;
+  const float rmax = v.rmax[u], rho = v.rhomax[u];
+  const float slack = (float)NT / 16384.0f * (pn * rmax + rmax * rmax) + 4.f * pn * rho;
+  const float B = fminf(rmax, pn + __builtin_sqrtf(fmaxf(pn * pn - 2.f * pb, 0.f) + slack));
+  const float eps = pn * rho * 1.0001f + (float)NT / 65536.0f * (pn * B + 0.5f * B * B) * 1.01f +
+                    (float)(1 << code_bits) * 1.2e-7f * fabsf(pb);
+  const bool near2 = valid && !(pb - ps > 2.f * eps);
+  const bool near3 = near2 && !(pb - pt3 > 2.f * eps);
+  int label = min(ib, v.M0 - 1);                           // (the padding rows can only win over values that are not finite)
+  is = min(is, v.M0 - 1);
+  const float* rows = km_rows(v, u);
+  int at3 = -1;
+  if (near3) { at3 = atomicAdd(&s_n3, 1); s_list[at3] = (short)(wave * 64 + lane); }
+  unsigned long long m2 = __ballot(near2 && !near3), swap = 0ull;
+  while (m2) {                                             // four points at a time, sixteen lanes each, 8 coordinates per lane
+    int owner[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      owner[g] = m2 ? (int)__builtin_ctzll(m2) : g ? owner[g - 1] : 0;
+      m2 &= m2 - 1;
     }
-    block_arg_reduce<false>(best, arg, sv, si);
-    if (tid == 0) v.labels[(size_t)u * v.Ncap + pt] = si[0];
-  }
-}
-
-// Only when some cluster came out empty: the distance of every point to the centre it was assigned to (the
-// centres of this assignment, i.e. before the update), which the re-seeding step ranks.
-__global__ __launch_bounds__(256) void kmeans_dist_kernel(View v, const void* X, int N0) {
-  const int u = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
-  if (!v.has_empty[u] || i >= N0) return;
-  const int j = v.labels[(size_t)u * v.Ncap + i];
-  const float* R = unit_R(v, u);
-  const size_t base = ((size_t)u * N0 + i) * kHeadDim;
-  v.dist[(size_t)u * v.Ncap + i] = blocked16([&](int k) __attribute__((always_inline)) {
+    const int g = lane >> 4, c = lane & 15;
+    const int o = g == 0 ? owner[0] : g == 1 ? owner[1] : g == 2 ? owner[2] : owner[3];
+    const int ja = __shfl(label, o), jb = __shfl(is, o);
     float x[8];
-    load8(X, base + k * 8, v.dtype, x);
-    const f4 ra = *(const f4*)(R + r_index(j, k * 8)), rb = *(const f4*)(R + r_index(j, k * 8 + 4));
-    double acc = 0.0;
+    load8(X, ((size_t)u * N0 + min(pbase + o, N0 - 1)) * kHeadDim + c * 8, DT, x);
+    const f4* ra = (const f4*)(rows + (size_t)ja * kHeadDim + c * 8);
+    const f4* rb = (const f4*)(rows + (size_t)jb * kHeadDim + c * 8);
+    const f4 a0 = ra[0], a1 = ra[1], b0 = rb[0], b1 = rb[1];
+    double da = 0.0, db = 0.0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const double t = (double)x[e] - (double)(e < 4 ? ra[e] : rb[e - 4]);
-      acc = fma(t, t, acc);
+      const double ta = (double)x[e] - (double)(e < 4 ? a0[e] : a1[e - 4]), tb = (double)x[e] - (double)(e < 4 ? b0[e] : b1[e - 4]);
+      da = fma(ta, ta, da); db = fma(tb, tb, db);
     }
-    return acc;
-  });
+    da = row_sum_f64(da); db = row_sum_f64(db);
+    const unsigned long long take = __ballot(c == 0 && (db < da || (db == da && jb < ja)));
+#pragma unroll
+    for (int gg = 0; gg < 4; ++gg)
+      if ((take >> (16 * gg)) & 1ull) swap |= 1ull << owner[gg];
+  }
+  if ((swap >> lane) & 1ull) label = is;
+  // points with three or more candidates: the whole workgroup goes through the centres, lane = centre
+  __syncthreads();
+  const int n3 = s_n3;
+  for (int q0 = 0; q0 < n3; q0 += kScan) {                 // workgroup-uniform
+    const float* R = unit_R(v, u);
+    for (int q = q0; q < min(n3, q0 + kScan); ++q) {
+      const size_t row = ((size_t)u * N0 + xb * NW * 64 + s_list[q]) * kHeadDim;
+      double bd = __builtin_inf();
+      int bj = 0x7FFFFFFF;
+      for (int j = wave * 64 + lane; j < v.M0; j += NW * 64) {
+        double acc = 0.0;
+#pragma unroll 8
+        for (int d8 = 0; d8 < 16; ++d8) {
+          float x[8];
+          load8(X, row + d8 * 8, DT, x);
+          const f4 a = *(const f4*)(R + r_index(j, d8 * 8)), b = *(const f4*)(R + r_index(j, d8 * 8 + 4));
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const double t = (double)x[e] - (double)(e < 4 ? a[e] : b[e - 4]);
+            acc = fma(t, t, acc);
+          }
+        }
+        if (acc < bd) { bd = acc; bj = j; }
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const double od = __shfl_xor(bd, o);
+        const int oj = __shfl_xor(bj, o);
+        if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
+      }
+      if (lane == 0) { s_d[q - q0][wave] = bd; s_j[q - q0][wave] = bj; }
+    }
+    __syncthreads();
+    if (at3 >= q0 && at3 < q0 + kScan) {
+      double bd = s_d[at3 - q0][0];
+      int bj = s_j[at3 - q0][0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) {
+        const double od = s_d[at3 - q0][w];
+        const int oj = s_j[at3 - q0][w];
+        if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
+      }
+      if (bj < v.M0) label = bj;                           // (no centre at a finite distance: the filter's choice stays)
+    }
+    __syncthreads();
+  }
+  int* lab = v.labels + (size_t)u * v.Ncap;
+  if (first) {
+    if (valid) lab[pt] = label;
+    return;
+  }
+  const bool moved = valid && old != label;
+  const unsigned long long mv = __ballot(moved);
+  if (mv == 0) return;
+  int base = 0;
+  if (lane == 0) base = atomicAdd(&v.n_changed[2 * u + slot], __popcll(mv));
+  base = __builtin_amdgcn_readfirstlane(base);
+  if (moved) {
+    lab[pt] = label;
+    km_changed(v, u)[base + __popcll(mv & ((1ull << lane) - 1ull))] = Changed{pt, (unsigned)old | ((unsigned)label << 16)};
+  }
+}
+
+// ---- members of every cluster -------------------------------------------------------------------------------------
+// Stable counting sort of one unit's labels by a workgroup of 1024: members of every cluster in ascending position
+// (v.order) and the start of every cluster (v.koff).  Each of the first nw wavefronts counts a contiguous range of
+// positions, one prefix sum over (cluster, wavefront) turns the counts into places, and each wavefront hands them out in
+// order, 64 positions at a time: the lanes with equal labels find each other by one ballot per bit of the label.
+// cnt: kSortCounters ints of LDS; sm: 64.  (A bitonic sort of (label, position) in LDS took 53 us for 4096 keys and
+// 212 us for 16384; this takes 8 and 25 us.)
+constexpr int kSortCounters = 32768;
+static_assert(kMaxInitClusters * 4 <= kSortCounters, "at least four wavefronts hold counters");
+__device__ inline void sort_members(const View& v, int u, int N0, int* cnt, int* sm) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, M0 = v.M0;
+  int nw = 16;
+  while (nw * M0 > kSortCounters) nw >>= 1;
+  const int* lab = v.labels + (size_t)u * v.Ncap;
+  int* order = v.order + (size_t)u * v.Ncap;
+  int* koff = v.koff + (size_t)u * (v.Mcap + 1);
+  for (int i = tid; i < nw * M0; i += 1024) cnt[i] = 0;
+  __syncthreads();
+  const int per = ((N0 + nw - 1) / nw + 63) & ~63, b = min(N0, wave * per), e = wave < nw ? min(N0, b + per) : b;
+  for (int i = b + lane; i < e; i += 64) atomicAdd(&cnt[wave * M0 + lab[i]], 1);
+  __syncthreads();
+  const int R = (M0 + 1023) / 1024;                   // consecutive clusters per thread
+  int tot = 0, empty = 0;
+  for (int k = 0; k < R; ++k) {
+    const int j = tid * R + k;
+    if (j >= M0) break;
+    int n = 0;
+    for (int w = 0; w < nw; ++w) n += cnt[w * M0 + j];
+    tot += n; empty |= n == 0;
+  }
+  int total;
+  int run = block_excl_scan(tot, sm, total);
+  for (int k = 0; k < R; ++k) {
+    const int j = tid * R + k;
+    if (j >= M0) break;
+    koff[j] = run;
+    for (int w = 0; w < nw; ++w) { const int n = cnt[w * M0 + j]; cnt[w * M0 + j] = run; run += n; }
+  }
+  if (tid == 0) { koff[M0] = N0; v.has_empty[u] = 0; }
+  __syncthreads();
+  if (empty) v.has_empty[u] = 1;
+  int bits = 0;
+  while ((1 << bits) < M0) ++bits;
+  for (int i0 = b; i0 < e; i0 += 64) {                 // (no barrier inside: ranges differ from wavefront to wavefront)
+    const int i = i0 + lane;
+    const bool in = i < e;
+    const int l = in ? lab[i] : 0;
+    unsigned long long same = __ballot(in);
+    for (int k = 0; k < bits; ++k) {
+      const unsigned long long bal = __ballot((l >> k) & 1);
+      same &= ((l >> k) & 1) ? bal : ~bal;
+    }
+    if (in) {
+      const int rank = __popcll(same & ((1ull << lane) - 1ull)), at = cnt[wave * M0 + l];
+      order[at + rank] = i;
+      asm volatile("" ::: "memory");
+      if (rank == __popcll(same) - 1) cnt[wave * M0 + l] = at + rank + 1;       // (lock step: every lane has read the counter)
+    }
+    asm volatile("" ::: "memory");
+  }
+  __syncthreads();
+}
+__global__ __launch_bounds__(1024) void kmeans_sort_kernel(View v, int N0) {
+  __shared__ int cnt[kSortCounters];
+  __shared__ int sm[64];
+  sort_members(v, blockIdx.x, N0, cnt, sm);
+}
+
+// ---- update ---------------------------------------------------------------------------------------------
+// Sixteen lanes, eight coordinates each, form the sum of cluster j's members in the order of v.order (ascending
+// position: Eq. 4 in a fixed order) and write centre, sums and count.  The lanes fetch the next 16 member positions with
+// one load while the current 16 rows, all in flight at once, are added.  A cluster without members keeps its centre.
+// RB: rows in flight per lane.
+template <int DT, int RB = 16>
+__device__ inline void update_cluster(const View& v, const void* X, int N0, int u, int j, int c, int* counts, CentreNorms& cn) {
+  const int* koff = v.koff + (size_t)u * (v.Mcap + 1);
+  const int* order = v.order + (size_t)u * v.Ncap;
+  const int b = koff[j], e = koff[j + 1];
+  if (DT != DYNAKV_F32 && c == 0) counts[j] = e - b;
+  double s[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) s[k] = 0.0;
+  if (e > b) {
+    int mine = b + c < e ? order[b + c] : 0;            // lane c holds member c of the current 16
+    for (int q0 = b; q0 < e; q0 += 16) {
+      const int next = q0 + 16 + c < e ? order[q0 + 16 + c] : 0;
+#pragma unroll
+      for (int h = 0; h < 16; h += RB) {
+        float x[RB][8];
+#pragma unroll
+        for (int k = 0; k < RB; ++k) {
+          const int pos = __shfl(mine, h + k, 16);
+          load8(X, ((size_t)u * N0 + pos) * kHeadDim + c * 8, DT, x[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < RB; ++k)
+          if (q0 + h + k < e) {
+#pragma unroll
+            for (int d = 0; d < 8; ++d) s[d] += (double)x[k][d];
+          }
+      }
+      mine = next;
+    }
+    float r[8];
+#pragma unroll
+    for (int d = 0; d < 8; ++d) r[d] = (float)(s[d] / (double)(e - b));
+    write_centre<DT>(v, u, j, c, r, cn);
+  }
+  if constexpr (DT != DYNAKV_F32) {
+    double* S = km_sums(v, u) + (size_t)j * kHeadDim + c * 8;
+#pragma unroll
+    for (int d = 0; d < 8; d += 2) *(double2*)(S + d) = double2{s[d], s[d + 1]};
+  }
+}
+// All sums formed anew from the sorted members.  A unit with empty clusters is left to kmeans_slow_kernel (it needs the old
+// centres), except in the last iteration, where they stay empty.  grid (ceil(M0/16), U).
+template <int DT>
+__global__ __launch_bounds__(256) void kmeans_update_kernel(View v, const void* X, int N0, int which, int last) {
+  __shared__ int sm[8];
+  const int u = blockIdx.y, j = blockIdx.x * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15;
+  if (v.has_empty[u] && !last) return;                  // workgroup-uniform
+  CentreNorms cn{0.f, 0.f};
+  if (j < v.M0) update_cluster<DT>(v, X, N0, u, j, c, km_counts(v, u, N0, which), cn);
+  if constexpr (DT != DYNAKV_F32) fold_norms(v, u, cn, sm);
+}
+
+// The sums follow the points that changed their cluster (16-bit types whose sums are order-free).  A workgroup takes 16
+// clusters: it reads the unit's list of changes once, counts every cluster's members (counts are kept twice, the old ones
+// are still being read by other workgroups) and queues the changes of its own clusters in LDS; sixteen lanes per cluster then
+// add and subtract the rows.  If some cluster of the unit has run empty, nothing is touched and kmeans_slow_kernel takes
+// the unit.  Bound by the dependent round trips list - rows - sums; the list is short after the first iterations.
+constexpr int kQueue = 96;
+template <int DT>
+__global__ __launch_bounds__(256) void kmeans_changed_kernel(View v, const void* X, int N0, int slot, int which, int last) {
+  extern __shared__ int delta[];                        // [M0]
+  __shared__ int queue[16][kQueue], nq[16];
+  __shared__ int any_empty, sm[8];
+  const int u = blockIdx.y, tid = threadIdx.x, j0 = blockIdx.x * 16;
+  if (!sums_order_free(v, u, N0)) return;               // workgroup-uniform
+  const int n = v.n_changed[2 * u + slot];
+  const Changed* chg = km_changed(v, u);
+  const int* was = km_counts(v, u, N0, which ^ 1);
+  int* now = km_counts(v, u, N0, which);
+  for (int i = tid; i < v.M0; i += 256) delta[i] = 0;
+  if (tid < 16) nq[tid] = 0;
+  if (tid == 0) any_empty = 0;
+  __syncthreads();
+  for (int i = tid; i < n; i += 256) {
+    const Changed ch = chg[i];
+    const int from = (int)(ch.move & 0xFFFFu), to = (int)(ch.move >> 16);
+    atomicAdd(&delta[from], -1);
+    atomicAdd(&delta[to], 1);
+    if ((unsigned)(from - j0) < 16u) {
+      const int at = atomicAdd(&nq[from - j0], 1);
+      if (at < kQueue) queue[from - j0][at] = ch.pos << 1 | 1;
+    }
+    if ((unsigned)(to - j0) < 16u) {
+      const int at = atomicAdd(&nq[to - j0], 1);
+      if (at < kQueue) queue[to - j0][at] = ch.pos << 1;
+    }
+  }
+  __syncthreads();
+  if (!last) {
+    for (int i = tid; i < v.M0; i += 256)
+      if (was[i] + delta[i] == 0) any_empty = 1;
+    __syncthreads();
+    if (any_empty) {                                    // the same in every workgroup of the unit
+      if (blockIdx.x == 0 && tid == 0) v.has_empty[u] = 1;
+      return;
+    }
+  }
+  const int k = tid >> 4, j = j0 + k, c = tid & 15;
+  CentreNorms cn{0.f, 0.f};
+  if (j < v.M0) {
+    const int m = was[j] + delta[j], q = nq[k];
+    if (c == 0) now[j] = m;
+    if (q > 0) {
+      double* S = km_sums(v, u) + (size_t)j * kHeadDim + c * 8;
+      double s[8];
+#pragma unroll
+      for (int d = 0; d < 8; d += 2) { const double2 w = *(const double2*)(S + d); s[d] = w.x; s[d + 1] = w.y; }
+      auto apply = [&](const float (&x)[8], bool out) __attribute__((always_inline)) {
+#pragma unroll
+        for (int d = 0; d < 8; ++d) s[d] += out ? -(double)x[d] : (double)x[d];
+      };
+      if (q <= kQueue) {
+        for (int i0 = 0; i0 < q; i0 += 8) {             // eight rows in flight
+          float x[8][8];
+          int e[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            e[i] = queue[k][min(i0 + i, q - 1)];
+            load8(X, ((size_t)u * N0 + (e[i] >> 1)) * kHeadDim + c * 8, DT, x[i]);
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (i0 + i < q) apply(x[i], e[i] & 1);
+        }
+      } else {                                          // more changes than the queue holds: straight from the list
+        for (int i = 0; i < n; ++i) {
+          const Changed ch = chg[i];
+          const bool out = (int)(ch.move & 0xFFFFu) == j;
+          if (!out && (int)(ch.move >> 16) != j) continue;
+          float x[8];
+          load8(X, ((size_t)u * N0 + ch.pos) * kHeadDim + c * 8, DT, x);
+          apply(x, out);
+        }
+      }
+#pragma unroll
+      for (int d = 0; d < 8; d += 2) *(double2*)(S + d) = double2{s[d], s[d + 1]};
+      if (m > 0) {
+        float r[8];
+#pragma unroll
+        for (int d = 0; d < 8; ++d) r[d] = (float)(s[d] / (double)m);
+        write_centre<DT>(v, u, j, c, r, cn);
+      }
+    }
+  }
+  fold_norms(v, u, cn, sm);
+}
+
+// What the parallel kernels leave, one workgroup of 1024 per unit; most launches find nothing to do.
+//   units with an empty cluster: every empty cluster, in ascending id, takes the not-yet-taken point that is farthest from
+//     its own (old) centre, ties to the lowest position; the others get their sums formed anew
+//   units whose sums are not order-free, in every iteration after the first: all sums formed anew
+template <int DT>
+__global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X, int N0, int which, int first, int last) {
+  __shared__ int cnt[kSortCounters];
+  __shared__ int sm[64];
+  __shared__ double sv[16];
+  __shared__ int si[16];
+  const int u = blockIdx.x, tid = threadIdx.x, c = tid & 15;
+  const bool sorted = first || DT == DYNAKV_F32;         // this iteration's kmeans_sort_kernel has run
+  if (!(v.has_empty[u] && !last) && !(!sorted && !sums_order_free(v, u, N0))) return;       // workgroup-uniform
+  if (!sorted) sort_members(v, u, N0, cnt, sm);
+  const bool reseed = v.has_empty[u] && !last;
+  const int* lab = v.labels + (size_t)u * v.Ncap;
+  const int* koff = v.koff + (size_t)u * (v.Mcap + 1);
+  double* dist = v.dist + (size_t)u * v.Ncap;
+  if (reseed) {                                         // distances to the centres of this assignment, before the update
+    const float* R = unit_R(v, u);
+    constexpr int kPts = DT == DYNAKV_F32 ? 4 : 8;       // points in flight per 16 lanes
+    for (int i0 = tid >> 4; i0 < N0; i0 += 64 * kPts) {
+      float x[kPts][8];
+      f4 ra[kPts], rb[kPts];
+#pragma unroll
+      for (int k = 0; k < kPts; ++k) {
+        const int i = min(i0 + 64 * k, N0 - 1), j = lab[i];
+        load8(X, ((size_t)u * N0 + i) * kHeadDim + c * 8, DT, x[k]);
+        if constexpr (DT == DYNAKV_F32) { ra[k] = *(const f4*)(R + r_index(j, c * 8)); rb[k] = *(const f4*)(R + r_index(j, c * 8 + 4)); }
+        else { const f4* r = (const f4*)(km_rows(v, u) + (size_t)j * kHeadDim + c * 8); ra[k] = r[0]; rb[k] = r[1]; }
+      }
+#pragma unroll
+      for (int k = 0; k < kPts; ++k) {
+        double acc = 0.0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const double t = (double)x[k][e] - (double)(e < 4 ? ra[k][e] : rb[k][e - 4]);
+          acc = fma(t, t, acc);
+        }
+        acc = row_sum_f64(acc);
+        if (c == 0 && i0 + 64 * k < N0) dist[i0 + 64 * k] = acc;
+      }
+    }
+    __syncthreads();
+  }
+  CentreNorms cn{0.f, 0.f};
+  int* counts = km_counts(v, u, N0, which);
+  for (int j = tid >> 4; j < v.M0; j += 64) update_cluster<DT, DT == DYNAKV_F32 ? 8 : 16>(v, X, N0, u, j, c, counts, cn);
+  __syncthreads();
+  if (reseed) {
+    const int lane = tid & 63, w = tid >> 6;
+    for (int j = 0; j < v.M0; ++j) {
+      if (koff[j + 1] != koff[j]) continue;              // uniform across the block
+      double bv = -1.0;
+      int bi = -1;
+      for (int i = tid; i < N0; i += 1024) {
+        const double t = dist[i];
+        if (t > bv) { bv = t; bi = i; }                 // ascending i per thread: the first maximum stays
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const double ov = __shfl_xor(bv, o);
+        const int oi = __shfl_xor(bi, o);
+        if (oi >= 0 && (bi < 0 || ov > bv || (ov == bv && oi < bi))) { bv = ov; bi = oi; }
+      }
+      if (lane == 0) { sv[w] = bv; si[w] = bi; }
+      __syncthreads();
+      bv = sv[0]; bi = si[0];
+      for (int k = 1; k < 16; ++k)
+        if (si[k] >= 0 && (bi < 0 || sv[k] > bv || (sv[k] == bv && si[k] < bi))) { bv = sv[k]; bi = si[k]; }
+      if (bi < 0) break;                                // every point already taken
+      if (tid < 16) {
+        float r[8];
+        load8(X, ((size_t)u * N0 + bi) * kHeadDim + c * 8, DT, r);
+        write_centre<DT>(v, u, j, c, r, cn);
+      }
+      __syncthreads();                                  // every thread has read sv / si and this round's distances
+      if (tid == 0) dist[bi] = -2.0;                    // taken
+      __syncthreads();
+    }
+  }
+  if constexpr (DT != DYNAKV_F32) fold_norms(v, u, cn, sm);
+  __syncthreads();
+  if (tid == 0) v.has_empty[u] = 0;
 }
 
 // dist[i] = squared distance of point i to the (updated) centre of its own cluster.  Sixteen lanes per point, one
@@ -666,42 +982,40 @@ __global__ __launch_bounds__(256) void layout_copy_kernel(View v, const void* K,
 
 }  // namespace
 
+template <int DT>
+static void launch_kmeans(const View& v, const void* K, int N0, const int* init_idx, int iters, hipStream_t st) {
+  const dim3 gcl((v.M0 + 15) / 16, v.U);
+  kmeans_check_init_kernel<<<v.U, 256, 0, st>>>(v, N0, init_idx);
+  kmeans_start_kernel<DT><<<dim3(((DT == DYNAKV_F32 ? v.M0 : v.Mpad) + 15) / 16, v.U), 256, 0, st>>>(v, K, N0, init_idx);
+  for (int it = 0; it < iters; ++it) {
+    const int first = it == 0, last = it + 1 == iters, slot = it & 1, which = it & 1;
+    if constexpr (DT == DYNAKV_F32) {
+      kmeans_assign_f64_kernel<<<dim3((N0 + 63) / 64, v.U), 256, 0, st>>>(v, K, N0);
+    } else {
+      int code_bits = 4;                                // a lane sees half of the centres: 16 per tile of 32
+      while ((1 << code_bits) < v.Mpad / 2) ++code_bits;
+      const int gx = (N0 + 64 * kAssignWaves - 1) / (64 * kAssignWaves);
+      kmeans_assign_kernel<DT><<<gx * ((v.U + 7) / 8 * 8), 64 * kAssignWaves, 0, st>>>(v, K, N0, gx, first, slot, code_bits);
+    }
+    if (first || DT == DYNAKV_F32) {
+      kmeans_sort_kernel<<<v.U, 1024, 0, st>>>(v, N0);
+      kmeans_update_kernel<DT><<<gcl, 256, 0, st>>>(v, K, N0, which, last);
+    } else if constexpr (DT != DYNAKV_F32) {
+      kmeans_changed_kernel<DT><<<gcl, 256, v.M0 * sizeof(int), st>>>(v, K, N0, slot, which, last);
+    }
+    const bool sorted = first || DT == DYNAKV_F32;
+    if (!last || (!sorted && !sums_order_free_by_type(DT, N0)))
+      kmeans_slow_kernel<DT><<<v.U, 1024, 0, st>>>(v, K, N0, which, first, last);
+  }
+  if (DT != DYNAKV_F32 && iters > 1) kmeans_sort_kernel<<<v.U, 1024, 0, st>>>(v, N0);
+}
+
 hipError_t launch_build_index(const View& v, const void* K, const void* V, int N0, const int* init_idx, int iters,
                               void* ws, size_t ws_bytes, hipStream_t st) {
   (void)ws; (void)ws_bytes;
-  kmeans_check_init_kernel<<<v.U, 256, 0, st>>>(v, N0, init_idx);
-  kmeans_init_kernel<<<dim3(v.M0, v.U), 128, 0, st>>>(v, K, N0, init_idx);
-  kmeans_range_kernel<<<dim3(16, v.U), 256, 0, st>>>(v, K, N0);
-  int Npad = 2, pos_bits = 1;
-  while (Npad < N0) { Npad <<= 1; ++pos_bits; }
-  const dim3 gpts((N0 + 255) / 256, v.U);
-  const bool mfma = v.dtype != DYNAKV_F32;     // float32 keys keep the plain float64 scan
-  const bool atomic_path = mfma && v.M0 <= kAtomicCentres;   // per unit, the kernels decide by the keys' range
-  const dim3 gprep(((v.M0 + 31) / 32 * 32 + 255) / 256, v.U);
-  for (int it = 0; it < iters; ++it) {
-    if (mfma) {
-      if (v.dtype == DYNAKV_F16) {
-        kmeans_reset_kernel<<<(v.U + 255) / 256, 256, 0, st>>>(v);
-        kmeans_prep_kernel<false><<<gprep, 256, 0, st>>>(v);
-        kmeans_assign_mfma_kernel<false><<<gpts, 256, 0, st>>>(v, K, N0);
-      } else {
-        kmeans_reset_kernel<<<(v.U + 255) / 256, 256, 0, st>>>(v);
-        kmeans_prep_kernel<true><<<gprep, 256, 0, st>>>(v);
-        kmeans_assign_mfma_kernel<true><<<gpts, 256, 0, st>>>(v, K, N0);
-      }
-      kmeans_exact_kernel<<<dim3(64, v.U), 256, 0, st>>>(v, K, N0);
-    } else {
-      kmeans_assign_f64_kernel<<<gpts, 256, 0, st>>>(v, K, N0);
-    }
-    kmeans_sort_kernel<<<v.U, 1024, 0, st>>>(v, N0, Npad, pos_bits, it + 1 == iters);
-    if (atomic_path && it + 1 < iters) kmeans_bucket_kernel<<<v.U, 1024, 0, st>>>(v, N0);
-    if (it + 1 < iters) kmeans_dist_kernel<<<gpts, 256, 0, st>>>(v, K, N0);
-    const dim3 gupd((v.M0 + 15) / 16, v.U);
-    if (v.dtype == DYNAKV_F32) kmeans_update_kernel<DYNAKV_F32><<<gupd, 256, 0, st>>>(v, K, N0);
-    else if (v.dtype == DYNAKV_F16) kmeans_update_kernel<DYNAKV_F16><<<gupd, 256, 0, st>>>(v, K, N0);
-    else kmeans_update_kernel<DYNAKV_BF16><<<gupd, 256, 0, st>>>(v, K, N0);
-    if (it + 1 < iters) kmeans_reseed_kernel<<<v.U, 256, 0, st>>>(v, K, N0);
-  }
+  if (v.dtype == DYNAKV_F32) launch_kmeans<DYNAKV_F32>(v, K, N0, init_idx, iters, st);
+  else if (v.dtype == DYNAKV_F16) launch_kmeans<DYNAKV_F16>(v, K, N0, init_idx, iters, st);
+  else launch_kmeans<DYNAKV_BF16>(v, K, N0, init_idx, iters, st);
   point_dist_kernel<<<dim3((N0 + 15) / 16, v.U), 256, 0, st>>>(v, K, N0);
   finalize_kernel<<<v.U, 1024, 0, st>>>(v, N0);
   layout_copy_kernel<<<dim3((N0 + 15) / 16, v.U), 256, 0, st>>>(v, K, V, N0);

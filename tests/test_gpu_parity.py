@@ -591,6 +591,19 @@ def test_prefill_with_coinciding_centres(dtype):
     assert tally["tie_kmeans"] == 0
 
 
+@pytest.mark.parametrize("dtype,N0,M0", [
+    ("f16", 257, 1), ("f16", 300, 31), ("bf16", 321, 33), ("f16", 4100, 64), ("bf16", 1025, 65), ("f32", 130, 33),
+    ("f16", 3000, 2),          # hundreds of keys move from one cluster to the other at once
+    ("f16", 9000, 2100),       # more than 8192 float16 keys: whether sums may follow the moves depends on their range
+    ("bf16", 8300, 8192)])     # the most centres: counts of the sort for four wavefronts only
+def test_prefill_partition_at_the_edges_of_tiles_and_chunks(dtype, N0, M0):
+    """Labels, centres and statistics of the k-means where the last tile of 32 centres, chunk of 64 points or run of 16
+    clusters is partly filled; memberships exactly as the oracle's."""
+    s = WorkloadSpec("edges", dtype, 2, 2, N0, 4, M0, 256, 6, 0.05, var_alpha=0.0, size_factor=0.0, seed=N0 + M0)
+    ix, o, tally = _build_pair(s, generate(s), 2, kmeans_iters=3 if M0 > 2000 else 5)
+    assert tally["tie_kmeans"] == 0
+
+
 def test_rebuild_resets_the_index_and_runs_are_deterministic():
     s = CONFIGS["tiny"].scaled(prefill=777, n_clusters_init=19)
     w = generate(s, steps=8)
