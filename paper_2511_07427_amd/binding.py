@@ -265,7 +265,9 @@ class Index:
         to_cpu is False.  A set error word does not raise: the returned status is kept in `self.export_status`
         (ECAPACITY in that case) and the words are in the "error" field."""
         spec = self._state_spec()
-        bufs = {k: torch.zeros(spec[k][0], dtype=spec[k][1], device=self.device) for k in fields}
+        # the library writes these from end to end; the others only as far as there are tokens
+        partly = ("members", "gathered", "keys", "values")
+        bufs = {k: (torch.zeros if k in partly else torch.empty)(spec[k][0], dtype=spec[k][1], device=self.device) for k in fields}
         st = _State(**{k: (bufs[k].data_ptr() if k in bufs else None) for k in _STATE_FIELDS})
         rc = self._lib.dynakv_export_state(self._h, C.byref(st), _stream())
         self.export_status = rc

@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdynakv.so")
 OBJ = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "kmeans.hip", "retrieve.hip", "maintain.hip"]
+SOURCES = ["api.hip", "kmeans.hip", "retrieve.hip", "maintain.hip", "state.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
 

@@ -3,7 +3,6 @@
 //                   whole-step call left), UpdateVar, threshold test, AddEntry + UpdateStats or buffer + flag;
 //                   in a whole-step call the due splits follow in the same launch
 //   split_kernel  - delayed splits of flagged clusters in the active set, then the forced split
-//   export_kernel - snapshot of the index for tests
 // One workgroup per unit; each unit's record is touched by that workgroup only.  All decisions are
 // taken on float64 values summed in the fixed order of common.hpp, ties to the lowest index.
 #include "split.hpp"
@@ -363,313 +362,6 @@ __global__ __launch_bounds__(kSplitThreads) void split_kernel(View v) {
   split_unit<DT>(v, blockIdx.x, raw, wk, false);
 }
 
-// ------------------------------------------------------------------------------------------- export
-// One workgroup per unit.  Clusters are dealt in runs of `ch` consecutive ids per thread, so that the member
-// lists come out cluster after cluster whatever the capacity.
-__global__ __launch_bounds__(1024) void export_kernel(View v, dynakv_state_t o) {
-  __shared__ int sm[64];
-  const int u = blockIdx.x, tid = threadIdx.x;
-  const int M = v.M[u], N = v.N[u];
-  const size_t cbase = (size_t)u * v.Mcap;
-  if (tid == 0) {
-    if (o.n_clusters) o.n_clusters[u] = M;
-    if (o.n_tokens) o.n_tokens[u] = N;
-    if (o.error) o.error[u] = v.err[u];
-    if (o.tau) o.tau[u] = v.tau[u];
-    if (o.n_selected) o.n_selected[u] = v.n_sel[u];
-    if (o.n_gathered) o.n_gathered[u] = v.t_sel[u];
-    if (o.last_assign) o.last_assign[u] = v.last_assign[u];
-    if (o.counters) {
-      for (int k = 0; k < kCounters; ++k) o.counters[(size_t)u * kCounters + k] = v.counters[(size_t)u * kCounters + k];
-      o.counters[(size_t)u * kCounters + 3] = v.bump[u] - v.free_top[u];
-    }
-  }
-  for (int j = tid; j < v.Mcap; j += 1024) {
-    const bool in = j < M;
-    if (o.size) o.size[cbase + j] = in ? v.cn[cbase + j] : 0;
-    if (o.buffered) o.buffered[cbase + j] = in ? v.cb[cbase + j] : 0;
-    if (o.flag) o.flag[cbase + j] = in ? v.cflag[cbase + j] : 0;
-    if (o.m2) o.m2[cbase + j] = in ? v.cM2[cbase + j] : 0.0;
-    if (o.scores) o.scores[cbase + j] = in ? v.score[cbase + j] : 0.f;
-    if (o.selected) o.selected[cbase + j] = j < v.n_sel[u] ? v.sel_ids[cbase + j] : -1;
-    if (o.first_page) o.first_page[cbase + j] = in && v.cn[cbase + j] + v.cb[cbase + j] > 0 ? v.cpg[(cbase + j) * kInlinePages] : -1;
-  }
-  if (o.centroids) {
-    const float* R = unit_R(v, u);
-    for (size_t t = tid; t < (size_t)v.Mcap * kHeadDim; t += 1024) {
-      const int j = (int)(t >> 7), d = (int)(t & 127);
-      o.centroids[cbase * kHeadDim + t] = j < M ? R[r_index(j, d)] : 0.f;
-    }
-  }
-  // member lists
-  const int ch = (v.Mcap + 1023) / 1024;
-  int tot = 0;
-  for (int k = 0; k < ch; ++k) {
-    const int j = tid * ch + k;
-    if (j < M) tot += v.cn[cbase + j] + v.cb[cbase + j];
-  }
-  int total;
-  int run = block_excl_scan(tot, sm, total);
-  for (int k = 0; k < ch; ++k) {
-    const int j = tid * ch + k;
-    if (j >= v.Mcap) break;
-    if (o.offsets) o.offsets[(size_t)u * (v.Mcap + 1) + j] = j < M ? run : total;
-    if (j < M) { v.tok_off[cbase + j] = run; run += v.cn[cbase + j] + v.cb[cbase + j]; }
-  }
-  if (tid == 0 && o.offsets) o.offsets[(size_t)u * (v.Mcap + 1) + v.Mcap] = total;
-  __syncthreads();
-  const int es = elem_size(v.dtype);
-  if (o.members || o.keys || o.values)
-    for (int j = tid; j < M; j += 1024) {
-      int w = v.tok_off[cbase + j], left = v.cn[cbase + j] + v.cb[cbase + j], page = -1;
-      for (int k = 0; left > 0; ++k) {
-        page = cluster_page(v, u, cbase + j, k, page);
-        if (page < 0) break;
-        const int nv = min(left, kPageTokens);
-        const char* pg = page_ptr(v, u, page);
-        for (int sl = 0; sl < nv; ++sl) {
-          const int pos = v.ppos[((size_t)u * v.Pcap + page) * kPageTokens + sl];
-          if (o.members) o.members[(size_t)u * v.Ncap + w + sl] = pos;
-          const size_t row = ((size_t)u * v.Ncap + pos) * kHeadDim * es;
-          if (o.keys) {
-            const uint4* src = (const uint4*)(pg + (size_t)k_index(v.dtype, sl, 0) * es);
-            uint4* dst = (uint4*)((char*)o.keys + row);
-            for (int c = 0; c < kHeadDim * es / 16; ++c) dst[c] = src[c];
-          }
-          if (o.values) {
-            const uint4* src = (const uint4*)(pg + (size_t)v_index(v.dtype, sl, 0) * es);
-            uint4* dst = (uint4*)((char*)o.values + row);
-            for (int c = 0; c < kHeadDim * es / 16; ++c) dst[c] = src[c];
-          }
-        }
-        w += nv; left -= nv;
-      }
-    }
-  if (o.gathered) {
-    const int nl = v.n_list[u];
-    for (int w = tid; w < nl; w += 1024) {
-      const int e = v.plist[(size_t)u * v.Lcap + w], t0 = v.plist_off[(size_t)u * v.Lcap + w];
-      const int page = e >> 4, first = ((e >> 2) & 3) * 4, nv = (e & 3) + 1;
-      for (int sl = 0; sl < nv; ++sl)
-        o.gathered[(size_t)u * v.Ncap + t0 + sl] = v.ppos[((size_t)u * v.Pcap + page) * kPageTokens + first + sl];
-    }
-  }
-}
-
-// ------------------------------------------------------------------------------------------- import
-// First kernel of an import, one workgroup per unit: checks the snapshot's sizes, then writes every record of
-// the unit (clusters, page chains, flagged list, active set, counters) and, for the copy kernel that follows,
-// the cluster and the place of every token (labels / order / koff / pg_off, the scratch arrays of the prefill).
-// v.nflagged[u] tells the copy kernel whether the unit was accepted.
-__global__ __launch_bounds__(1024) void import_meta_kernel(View v, dynakv_state_t s) {
-  __shared__ int sm[64];
-  __shared__ int s_bad, s_nflag;
-  const int u = blockIdx.x, tid = threadIdx.x;
-  const size_t cbase = (size_t)u * v.Mcap;
-  const int M = s.n_clusters[u], N = s.n_tokens[u];
-  const int* off = s.offsets + (size_t)u * (v.Mcap + 1);
-  const bool sane = M >= 1 && M <= v.Mcap && N >= 0 && N <= v.Ncap;
-  if (tid == 0) { s_bad = 0; s_nflag = 0; }
-  __syncthreads();
-  const int ch = sane ? (M + 1023) / 1024 : 0;
-  int tot = 0;
-  if (sane) {
-    if (tid == 0 && (off[0] != 0 || off[M] != N)) s_bad = 1;
-    for (int k = 0; k < ch; ++k) {
-      const int j = tid * ch + k;
-      if (j >= M) break;
-      const int n = s.size[cbase + j], b = s.buffered[cbase + j], m = off[j + 1] - off[j];
-      if (n < 0 || b < 0 || m != n + b || (b != 0 && s.flag[cbase + j] == 0)) s_bad = 1;
-      tot += (max(m, 0) + kPageTokens - 1) / kPageTokens;
-    }
-  }
-  int total;
-  int base = block_excl_scan(tot, sm, total);           // also the barrier behind s_bad
-  if (!sane || s_bad || total > v.Pcap) {
-    if (tid == 0) { atomicOr(&v.err[u], DYNAKV_ERR_IMPORT); v.nflagged[u] = 0; }
-    return;
-  }
-  const int* mem = s.members + (size_t)u * v.Ncap;
-  int* labels = v.labels + (size_t)u * v.Ncap;
-  int* order = v.order + (size_t)u * v.Ncap;
-  int* koff = v.koff + (size_t)u * (v.Mcap + 1);
-  for (int k = 0; k < ch; ++k) {
-    const int j = tid * ch + k;
-    if (j >= M) break;
-    const int m = off[j + 1] - off[j], np = (m + kPageTokens - 1) / kPageTokens;
-    v.cn[cbase + j] = s.size[cbase + j]; v.cb[cbase + j] = s.buffered[cbase + j]; v.csz[cbase + j] = m;
-    const int fl = s.flag[cbase + j] != 0;
-    v.cflag[cbase + j] = fl; v.cM2[cbase + j] = s.m2[cbase + j];
-    v.pg_off[cbase + j] = base; koff[j] = off[j];
-    for (int p = 0; p < kInlinePages; ++p) v.cpg[(cbase + j) * kInlinePages + p] = p < np ? base + p : -1;
-    v.ctail[cbase + j] = np ? base + np - 1 : -1;
-    for (int p = 0; p < np; ++p) v.pnext[(size_t)u * v.Pcap + base + p] = p + 1 < np ? base + p + 1 : -1;
-    if (fl) v.flist[cbase + atomicAdd(&s_nflag, 1)] = j;
-    for (int q = off[j]; q < off[j + 1]; ++q) {
-      const int pos = min(max(mem[q], 0), v.Ncap - 1);
-      order[q] = pos; labels[pos] = j;
-    }
-    base += np;
-  }
-  for (int j = tid; j < v.Mcap; j += 1024) {
-    v.in_req[cbase + j] = 0; v.score[cbase + j] = 0.f;
-    if (j >= M) {
-      v.cn[cbase + j] = 0; v.cb[cbase + j] = 0; v.csz[cbase + j] = 0; v.cflag[cbase + j] = 0; v.cM2[cbase + j] = 0.0;
-      v.ctail[cbase + j] = -1;
-      for (int p = 0; p < kInlinePages; ++p) v.cpg[(cbase + j) * kInlinePages + p] = -1;
-    }
-  }
-  for (size_t t = tid; t < (size_t)M * kHeadDim; t += 1024)
-    store_centroid(v, u, (int)(t >> 7), (int)(t & 127), s.centroids[cbase * kHeadDim + t]);
-  __syncthreads();
-  int nsel = 0;
-  if (s.selected) {
-    nsel = min(max(s.n_selected[u], 0), M);
-    for (int i = tid; i < nsel; i += 1024) {
-      const int id = min(max(s.selected[cbase + i], 0), M - 1);
-      v.sel_ids[cbase + i] = id; v.in_req[cbase + id] = 1;
-    }
-  }
-  if (tid == 0) {
-    koff[M] = N;
-    v.M[u] = M; v.N[u] = N; v.tau[u] = s.tau[u]; v.err[u] = 0; v.nflag[u] = s_nflag; v.n_sel[u] = nsel; v.t_sel[u] = 0;
-    v.n_list[u] = 0; v.ticket[u] = 0; v.bump[u] = total; v.free_top[u] = 0; v.last_assign[u] = -1; v.lcount[u] = 0; v.rmax2[u] = 0;
-    for (int k = 0; k < kCounters; ++k) v.counters[(size_t)u * kCounters + k] = 0;
-    v.nflagged[u] = 1;
-  }
-}
-
-// 16 consecutive places of the storage order per workgroup, 16 threads per entry: keys and values move from
-// the snapshot (by position) into their cluster's pages as whole 16-byte chunks.
-// `stride`: tokens per unit in K and V.
-__global__ __launch_bounds__(256) void import_copy_kernel(View v, const void* K, const void* V, int stride) {
-  const int u = blockIdx.y, q = blockIdx.x * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15;
-  if (!v.nflagged[u] || q >= v.N[u]) return;
-  const int pos = v.order[(size_t)u * v.Ncap + q];
-  const int j = v.labels[(size_t)u * v.Ncap + pos];
-  const int rank = q - v.koff[(size_t)u * (v.Mcap + 1) + j];
-  const int page = v.pg_off[(size_t)u * v.Mcap + j] + rank / kPageTokens, slot = rank % kPageTokens;
-  char* pg = page_ptr(v, u, page);
-  const size_t src = ((size_t)u * stride + pos) * kHeadDim + c * 8;
-  if (v.dtype == DYNAKV_F32) {
-    const f4* ks = (const f4*)((const float*)K + src);
-    const f4* vs = (const f4*)((const float*)V + src);
-    *(f4*)((float*)pg + k_index32(slot, c * 8)) = ks[0];
-    *(f4*)((float*)pg + k_index32(slot, c * 8 + 4)) = ks[1];
-    *(f4*)((float*)pg + v_index32(slot, c * 8)) = vs[0];
-    *(f4*)((float*)pg + v_index32(slot, c * 8 + 4)) = vs[1];
-  } else {
-    *(uint4*)((uint16_t*)pg + k_index16(slot, c * 8)) = *(const uint4*)((const uint16_t*)K + src);
-    *(uint4*)((uint16_t*)pg + v_index16(slot, c * 8)) = *(const uint4*)((const uint16_t*)V + src);
-  }
-  if (c == 0) v.ppos[((size_t)u * v.Pcap + page) * kPageTokens + slot] = pos;
-}
-
-// ------------------------------------------------------------------------------------------- placement
-// Correlation-aware placement (Section 5.1, Eq. 8).  F = P while counting: [U][M0][M0] float32 counts (exact).
-__global__ __launch_bounds__(256) void cor_zero_kernel(float* F, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) F[i] = 0.f;
-}
-// After one reference retrieval: every ordered pair of different selected clusters is counted once.  One
-// workgroup per unit; a pair belongs to one thread, and the launches of different queries follow each other.
-__global__ __launch_bounds__(256) void cor_count_kernel(View v, float* F) {
-  const int u = blockIdx.x, n = v.n_sel[u], M0 = v.M0;
-  const int* ids = v.sel_ids + (size_t)u * v.Mcap;
-  float* f = F + (size_t)u * M0 * M0;
-  for (long long t = threadIdx.x; t < (long long)n * n; t += 256) {
-    const int a = ids[t / n], b = ids[t % n];
-    if (a != b && a < M0 && b < M0) f[(size_t)a * M0 + b] += 1.f;
-  }
-}
-// One workgroup of 1024 threads per unit: the greedy chain on the counts, Eq. 8's normalisation, and the page
-// table of the unit in chain order (pg_off / cpg / ctail / pnext), for the copy kernel that follows.
-__global__ __launch_bounds__(1024) void cor_finish_kernel(View v, float* F, int* order_out, int n_tokens) {
-  __shared__ float rowsum[kMaxInitClusters];
-  __shared__ unsigned char placed[kMaxInitClusters];
-  __shared__ float rv[16];
-  __shared__ int ri[16];
-  __shared__ double rt[16];
-  __shared__ int s_last;
-  const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, M0 = v.M0;
-  const size_t cb = (size_t)u * v.Mcap;
-  float* f = F + (size_t)u * M0 * M0;
-  int* chain = v.tok_off + cb;
-  const bool fresh = v.M[u] == M0 && v.N[u] == n_tokens && v.nflag[u] == 0 && v.free_top[u] == 0;
-  if (!fresh) {                                            // workgroup-uniform
-    if (tid == 0) { atomicOr(&v.err[u], DYNAKV_ERR_PLACE); v.nflagged[u] = 0; }
-    return;
-  }
-  double tot = 0.0;
-  for (int i = tid; i < M0; i += 1024) {
-    float rs = 0.f;
-    for (int j = 0; j < M0; ++j) rs += f[(size_t)i * M0 + j];          // whole numbers below 2^24: exact
-    rowsum[i] = rs; placed[i] = 0;
-    tot += (double)rs;
-  }
-  for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o);
-  if (lane == 0) rt[w] = tot;
-  __syncthreads();
-  double total = 0.0;
-  for (int k = 0; k < 16; ++k) total += rt[k];
-  // arg-max over (value, id) pairs of the workgroup, lowest id among equals; id < 0: none
-  auto argmax = [&](float val, int id) {
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(val, o);
-      const int oi = __shfl_xor(id, o);
-      if (oi >= 0 && (id < 0 || ov > val || (ov == val && oi < id))) { val = ov; id = oi; }
-    }
-    __syncthreads();
-    if (lane == 0) { rv[w] = val; ri[w] = id; }
-    __syncthreads();
-    if (tid == 0) {
-      float bv = rv[0]; int bi = ri[0];
-      for (int k = 1; k < 16; ++k)
-        if (ri[k] >= 0 && (bi < 0 || rv[k] > bv || (rv[k] == bv && ri[k] < bi))) { bv = rv[k]; bi = ri[k]; }
-      s_last = bi;
-    }
-    __syncthreads();
-    return s_last;
-  };
-  int last;
-  {
-    float bv = -1.f; int bi = -1;
-    for (int i = tid; i < M0; i += 1024)
-      if (rowsum[i] > bv) { bv = rowsum[i]; bi = i; }                  // ascending i per thread: the first maximum stays
-    last = argmax(bv, bi);
-  }
-  for (int k = 0; k < M0; ++k) {
-    if (tid == 0) { chain[k] = last; placed[last] = 1; }
-    __syncthreads();
-    if (k + 1 == M0) break;
-    float bv = -1.f; int bi = -1;
-    for (int j = tid; j < M0; j += 1024)
-      if (!placed[j] && f[(size_t)last * M0 + j] > bv) { bv = f[(size_t)last * M0 + j]; bi = j; }
-    last = argmax(bv, bi);
-  }
-  // Eq. 8
-  const float inv = total > 0.0 ? (float)(1.0 / total) : 0.f;
-  for (size_t t = tid; t < (size_t)M0 * M0; t += 1024) f[t] = total > 0.0 ? (float)((double)f[t] / total) : 0.f;
-  (void)inv;
-  if (order_out)
-    for (int k = tid; k < M0; k += 1024) order_out[(size_t)u * M0 + k] = chain[k];
-  // pages in chain order
-  if (tid == 0) {
-    int base = 0;
-    for (int k = 0; k < M0; ++k) {
-      const int j = chain[k];
-      v.pg_off[cb + j] = base;
-      base += (v.cn[cb + j] + kPageTokens - 1) / kPageTokens;
-    }
-    v.nflagged[u] = 1;
-  }
-  __syncthreads();
-  for (int j = tid; j < M0; j += 1024) {
-    const int np = (v.cn[cb + j] + kPageTokens - 1) / kPageTokens, base = v.pg_off[cb + j];
-    for (int p = 0; p < kInlinePages; ++p) v.cpg[(cb + j) * kInlinePages + p] = p < np ? base + p : -1;
-    v.ctail[cb + j] = np ? base + np - 1 : -1;
-    for (int p = 0; p < np; ++p) v.pnext[(size_t)u * v.Pcap + base + p] = p + 1 < np ? base + p + 1 : -1;
-  }
-}
 }  // namespace
 
 // prescanned: the score kernel of the same step has already looked at the new key (launch_score_select with kin).
@@ -726,28 +418,4 @@ hipError_t launch_split(const View& v, hipStream_t st) {
   else split_kernel<DYNAKV_BF16><<<v.U, kSplitThreads, 0, st>>>(v);
   return hipGetLastError();
 }
-hipError_t launch_export(const View& v, const dynakv_state_t& dst, hipStream_t st) {
-  export_kernel<<<v.U, 1024, 0, st>>>(v, dst);
-  return hipGetLastError();
-}
-hipError_t launch_place(const View& v, const void* K, const void* V, int n_tokens, const void* Qref, int n_ref, int budget,
-                        float* P, int* order, hipStream_t st) {
-  const size_t n = (size_t)v.U * v.M0 * v.M0;
-  cor_zero_kernel<<<1024, 256, 0, st>>>(P, n);
-  const size_t qbytes = (size_t)v.U * v.G * kHeadDim * elem_size(v.dtype);
-  for (int r = 0; r < n_ref; ++r) {
-    const hipError_t e = launch_score_select(v, (const char*)Qref + (size_t)r * qbytes, budget, nullptr, st);
-    if (e != hipSuccess) return e;
-    cor_count_kernel<<<v.U, 256, 0, st>>>(v, P);
-  }
-  cor_finish_kernel<<<v.U, 1024, 0, st>>>(v, P, order, n_tokens);
-  import_copy_kernel<<<dim3((n_tokens + 15) / 16, v.U), 256, 0, st>>>(v, K, V, n_tokens);
-  return hipGetLastError();
-}
-hipError_t launch_import(const View& v, const dynakv_state_t& src, hipStream_t st) {
-  import_meta_kernel<<<v.U, 1024, 0, st>>>(v, src);
-  import_copy_kernel<<<dim3((v.Ncap + 15) / 16, v.U), 256, 0, st>>>(v, src.keys, src.values, v.Ncap);
-  return hipGetLastError();
-}
-
 }  // namespace dynakv

@@ -648,6 +648,31 @@ def test_timing_aid_brackets_an_even_sample_of_the_launches():
 
 # --------------------------------------------------------------------------- exported and imported state
 
+@pytest.mark.parametrize("dtype,N0,M0,Mcap", [("f16", 1501, 3, 67), ("f32", 700, 65, 65), ("bf16", 333, 333, 9000)])
+def test_snapshot_round_trip(dtype, N0, M0, Mcap):
+    """Export, import into a second index and export again: clusters of many pages (chains past the inline page table),
+    capacities that are no multiple of a table tile, more clusters than one round of the prefix sum takes."""
+    s = WorkloadSpec("snap", dtype, 3, 2, N0, 4, M0, 256, 6, 0.05, var_alpha=1.5, size_factor=0.0, seed=99 + N0)
+    w = generate(s)
+    a, _ = make_pair(s, 3, max_clusters=Mcap, kmeans_iters=2)
+    b, _ = make_pair(s, 3, max_clusters=Mcap, kmeans_iters=2)
+    a.dynakv_build_index(to_dev(w["K0"], dtype), to_dev(w["V0"], dtype), torch.from_numpy(w["init_idx"]).to(DEV))
+    a.dynakv_retrieve_attend(to_dev(w["Q"][0], dtype), 256, torch.empty(3, 2, 128, device=DEV), None)
+    x = a.dynakv_export_state(binding.IMPORT_FIELDS, to_cpu=False)
+    b.dynakv_import_state(x)
+    y = b.dynakv_export_state(binding.IMPORT_FIELDS + ("error",), to_cpu=False)
+    assert int(y["error"].abs().sum()) == 0
+    for k in x:
+        if k == "selected":                      # past the active set the snapshot says -1, an import leaves what was there
+            continue
+        assert torch.equal(x[k], y[k]), k
+    K = to_dev(w["K0"], dtype)
+    for u in range(3):
+        m = x["members"][u, :N0].long()
+        assert torch.equal(torch.sort(m).values, torch.arange(N0, device=DEV))
+        assert torch.equal(x["keys"][u, :N0], K[u])
+
+
 @pytest.mark.parametrize("name,launch", [("llama3_8b", 0), ("tiny", 0), ("qwen25_7b", launch_shape(2, 0, LAUNCH_SEPARATE))])
 def test_imported_state_continues_like_the_exporting_index(name, launch):
     """dynakv_export_state -> dynakv_import_state into a second index: both then take the same steps and must
