@@ -363,6 +363,31 @@ def test_selection_with_equal_scores_and_large_active_sets(launch):
     say("selection paths", hex(launch), "last active set:", st["n_selected"].tolist(), dict(tally))
 
 
+@pytest.mark.parametrize("dtype,M0,kw", [("f16", 7100, {}), ("bf16", 7400, {}), ("f16", 900, dict(search_copy=1)), ("f32", 1025, {})])
+def test_selection_from_contenders(dtype, M0, kw):
+    """Capacity for more clusters than the selection keeps in LDS: it runs on the clusters that the coarse histogram lets
+    through.  Equal scores within (7100) and beyond (7400) what that list holds, a first cluster over budget, cuts
+    anywhere, and everything selected."""
+    s = WorkloadSpec("contenders", dtype, 2, 4, M0 + 300, 4, M0, 10 ** 6, 8, 0.05, var_alpha=0.0, size_factor=0.0, seed=41)
+    w = generate(s)
+    ix, o, tally = _build_pair(s, w, 2, kmeans_iters=1, max_clusters=16400, **kw)
+    out = torch.empty(2, 4, 128, device=DEV)
+    lse = torch.empty(2, 4, device=DEV)
+    zero = np.zeros_like(w["Q"][0])
+    cases = [("all equal", zero, B) for B in (0, 1, 7, 2500)] + [("cut", w["Q"][1 + B % 3], B) for B in (1, 2, 65, 1000, 3900)]
+    if M0 + 300 < 4096:
+        cases.append(("all", w["Q"][1], 10 ** 6))       # (a selection of more than 4096 clusters sets the error word)
+    for what, Q, B in cases:
+        ix.dynakv_retrieve_attend(to_dev(Q, dtype), B, out, lse)
+        oo, ol = o.retrieve_attend(Q, B)
+        dirty = compare_retrieval(ix, o, tally, "%s budget %d" % (what, B), Q=Q, budget=B)
+        assert not dirty or what == "cut"               # exact ties go by id on both sides: never a disagreement
+        keep = [u for u in range(2) if u not in dirty]
+        check_attention(out.cpu().numpy()[keep], lse.cpu().numpy()[keep], oo[keep], ol[keep], "%s budget %d" % (what, B))
+    assert ix.dynakv_export_state(["error"])["error"].tolist() == [0, 0]
+    say("selection from contenders", dtype, M0, dict(tally))
+
+
 def test_group_sum_custom_scale_all_resident_and_huge_logits():
     s = WorkloadSpec("opts", "f16", 3, 3, 700, 64, 24, 200, 6, 0.1, var_alpha=1.2, size_factor=0.0, buffer_max=0, seed=99)
     r = run_trajectory(s, range(3), 64, group_reduce=1, softmax_scale=0.05, kmeans_iters=5, full_every=8)
