@@ -17,12 +17,13 @@ struct AppendSmem {
 };
 
 // What one thread fetches for an append: thread d < 128 coordinate d of the centroid, threads 128..136 one field
-// each of the cluster's record or of the unit's allocator state.  All of it in one round trip to memory.
+// each of the cluster's record or of the unit's allocator state.  All of it in one round trip to memory (two where the height
+// of the free-page stack is not known to the caller: top < 0).
 struct AppendFetch {
   double x;
   int i, k;
 };
-__device__ inline AppendFetch append_fetch(const View& v, int u, int j) {
+__device__ inline AppendFetch append_fetch(const View& v, int u, int j, int top = -1) {
   const int tid = threadIdx.x;
   const size_t cbase = (size_t)u * v.Mcap;
   AppendFetch f{0.0, 0, 0};
@@ -37,7 +38,7 @@ __device__ inline AppendFetch append_fetch(const View& v, int u, int j) {
     case 6: f.i = v.nflag[u]; break;
     case 7: f.i = v.bump[u]; break;
     case 8: {
-      f.i = v.free_top[u];
+      f.i = top >= 0 ? top : v.free_top[u];
       f.k = f.i > 0 ? v.freelist[(size_t)u * v.Pcap + f.i - 1] : -1;
       break;
     }
@@ -49,9 +50,10 @@ __device__ inline AppendFetch append_fetch(const View& v, int u, int j) {
 // Cluster j (of M) receives token N of unit u.  Called by all NT >= 256 threads of the unit's workgroup with
 // what append_fetch returned to each of them (the caller may have issued it long before).  The sum of UpdateVar
 // is formed from 16 block sums computed side by side, and one thread then takes the decisions.
-template <int NT>
+// HELD: thread d < 128 holds the bits of the key's coordinate d, thread 128 + d those of the value's (kin, vin are not read).
+template <int NT, bool HELD = false>
 __device__ inline void append_commit(const View& v, int u, int j, int M, int N, const void* kin, const void* vin,
-                                     AppendSmem& a, const AppendFetch& f) {
+                                     AppendSmem& a, const AppendFetch& f, uint32_t held = 0) {
   const int tid = threadIdx.x;
   const size_t cbase = (size_t)u * v.Mcap;
   const double r = f.x;
@@ -149,7 +151,10 @@ __device__ inline void append_commit(const View& v, int u, int j, int M, int N, 
   if (!a.ok) return;
   if (a.commit && tid < kHeadDim) store_centroid(v, u, j, tid, (float)a.r1[tid]);
   char* pg = page_ptr(v, u, a.page);
-  if (tid < kHeadDim) copy_elem(pg, k_index(v.dtype, a.slot, tid), kin, (size_t)u * kHeadDim + tid, v.dtype);
+  if constexpr (HELD) {
+    if (tid < 2 * kHeadDim)
+      store_bits(pg, tid < kHeadDim ? k_index(v.dtype, a.slot, tid) : v_index(v.dtype, a.slot, tid - kHeadDim), held, v.dtype);
+  } else if (tid < kHeadDim) copy_elem(pg, k_index(v.dtype, a.slot, tid), kin, (size_t)u * kHeadDim + tid, v.dtype);
   else if (tid < 2 * kHeadDim)
     copy_elem(pg, v_index(v.dtype, a.slot, tid - kHeadDim), vin, (size_t)u * kHeadDim + tid - kHeadDim, v.dtype);
 }

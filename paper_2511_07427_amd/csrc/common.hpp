@@ -270,6 +270,19 @@ __device__ inline void copy_elem(void* dst, size_t j, const void* src, size_t i,
   else ((uint16_t*)dst)[j] = ((const uint16_t*)src)[i];
 }
 
+// An element's bits, to be held in a register and stored later, and its value.
+__device__ inline uint32_t load_bits(const void* base, size_t i, int dtype) {
+  return dtype == DYNAKV_F32 ? ((const uint32_t*)base)[i] : (uint32_t)((const uint16_t*)base)[i];
+}
+__device__ inline void store_bits(void* dst, size_t j, uint32_t bits, int dtype) {
+  if (dtype == DYNAKV_F32) ((uint32_t*)dst)[j] = bits;
+  else ((uint16_t*)dst)[j] = (uint16_t)bits;
+}
+__device__ inline float bits_value(uint32_t bits, int dtype) {
+  if (dtype == DYNAKV_F32) return __uint_as_float(bits);
+  return dtype == DYNAKV_F16 ? f16_to_float((uint16_t)bits) : bf16_to_float((uint16_t)bits);
+}
+
 // Eight consecutive elements starting at element i (i a multiple of 8), as floats: two 16-byte loads for
 // float32, one for the 16-bit types.
 __device__ inline void load8(const void* base, size_t i, int dtype, float (&x)[8]) {
