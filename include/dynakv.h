@@ -156,11 +156,13 @@ dynakv_status_t dynakv_extend_index(dynakv_index_t* index, const void* K, const 
  * which tend to be retrieved together sit next to each other in the page pool.  Nothing else changes: partition,
  * statistics and retrieval results are the same as before (the active set is left as the last reference query
  * selected it).
- *   K, V        device, the arrays that were given to dynakv_build_index, [U][n_tokens][head_dim]
+ *   K, V        device, the arrays that were given to dynakv_build_index (after dynakv_import_state of a snapshot
+ *               taken right after a build: its keys and values by position), [U][n_tokens][head_dim]
  *   Qref        device, [n_ref][U][G][head_dim] in cfg.dtype: the reference queries (the initial input)
  *   P           device, float32 [U][M0][M0]: receives Eq. 8's probabilities (used as the counting matrix meanwhile)
  *   order       device, int32 [U][M0] or null: receives the chain
- * A unit that has changed since it was built (appends, splits) is left alone and gets DYNAKV_ERR_PLACE. */
+ * A unit that has changed since it was built (appends, splits), or whose imported members lie beyond n_tokens, is
+ * left alone and gets DYNAKV_ERR_PLACE. */
 dynakv_status_t dynakv_place_by_coretrieval(dynakv_index_t* index, const void* K, const void* V, int32_t n_tokens,
                                             const void* Qref, int32_t n_ref, int32_t token_budget, float* P,
                                             int32_t* order, void* stream);

@@ -275,13 +275,57 @@ __global__ __launch_bounds__(256) void import_pages_kernel(View v, dynakv_state_
 }
 
 // ------------------------------------------------------------------------------------------- placement
-// 16 consecutive places of the prefill's storage order per workgroup, 16 threads per entry: keys and values move by
+// First kernel of a placement, one workgroup per unit: whether the unit is as a build or an import left it
+// (v.nflagged[u], for the kernels that follow), and the storage order of its entries, read from the index's own pages
+// because the arrays of the k-means hold nothing after an import: start of every cluster (koff), and for every place its
+// position (order) and cluster (labels).  A position beyond the caller's K and V refuses the unit.
+__global__ __launch_bounds__(1024) void place_members_kernel(View v, int n_tokens) {
+  __shared__ int sm[64];
+  __shared__ int s_bad;
+  const int u = blockIdx.x, tid = threadIdx.x, c = tid & 15;
+  const size_t cbase = (size_t)u * v.Mcap;
+  int* koff = v.koff + (size_t)u * (v.Mcap + 1);
+  if (v.M[u] != v.M0 || v.N[u] != n_tokens || v.nflag[u] != 0 || v.free_top[u] != 0) {     // workgroup-uniform
+    if (tid == 0) v.nflagged[u] = 0;
+    return;
+  }
+  if (tid == 0) s_bad = 0;
+  int before = 0;
+  for (int j0 = 0; j0 < v.M0; j0 += 1024) {
+    int total;
+    const int run = before + block_excl_scan(j0 + tid < v.M0 ? v.csz[cbase + j0 + tid] : 0, sm, total);
+    if (j0 + tid < v.M0) koff[j0 + tid] = run;
+    before += total;
+  }
+  if (tid == 0) koff[v.M0] = before;
+  __syncthreads();
+  for (int j = tid >> 4; j < v.M0 && before == n_tokens; j += 64) {
+    int w = koff[j], left = v.csz[cbase + j], page = -1;
+    for (int k = 0; left > 0; ++k) {
+      page = cluster_page(v, u, cbase + j, k, page);
+      if (page < 0) break;
+      const int nv = min(left, kPageTokens);
+      if (c < nv) {
+        const int pos = v.ppos[((size_t)u * v.Pcap + page) * kPageTokens + c];
+        if (pos < 0 || pos >= n_tokens) s_bad = 1;
+        v.order[(size_t)u * v.Ncap + w + c] = pos;
+        v.labels[(size_t)u * v.Ncap + w + c] = j;
+      }
+      w += nv; left -= nv;
+    }
+    if (left > 0) s_bad = 1;
+  }
+  __syncthreads();
+  if (tid == 0) v.nflagged[u] = before == n_tokens && !s_bad;
+}
+
+// 16 consecutive places of the storage order per workgroup, 16 threads per entry: keys and values move by
 // position into their cluster's (new) pages as whole 16-byte chunks.  `stride`: tokens per unit in K and V.
 __global__ __launch_bounds__(256) void place_copy_kernel(View v, const void* K, const void* V, int stride) {
   const int u = blockIdx.y, q = blockIdx.x * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15;
   if (!v.nflagged[u] || q >= v.N[u]) return;
   const int pos = v.order[(size_t)u * v.Ncap + q];
-  const int j = v.labels[(size_t)u * v.Ncap + pos];
+  const int j = v.labels[(size_t)u * v.Ncap + q];
   const int rank = q - v.koff[(size_t)u * (v.Mcap + 1) + j];
   const int page = v.pg_off[(size_t)u * v.Mcap + j] + rank / kPageTokens, slot = rank % kPageTokens;
   char* pg = page_ptr(v, u, page);
@@ -317,7 +361,7 @@ __global__ __launch_bounds__(256) void cor_count_kernel(View v, float* F) {
 }
 // One workgroup of 1024 threads per unit: the greedy chain on the counts, Eq. 8's normalisation, and the page
 // table of the unit in chain order (pg_off / cpg / ctail / pnext), for the copy kernel that follows.
-__global__ __launch_bounds__(1024) void cor_finish_kernel(View v, float* F, int* order_out, int n_tokens) {
+__global__ __launch_bounds__(1024) void cor_finish_kernel(View v, float* F, int* order_out) {
   __shared__ float rowsum[kMaxInitClusters];
   __shared__ unsigned char placed[kMaxInitClusters];
   __shared__ float rv[16];
@@ -328,9 +372,8 @@ __global__ __launch_bounds__(1024) void cor_finish_kernel(View v, float* F, int*
   const size_t cb = (size_t)u * v.Mcap;
   float* f = F + (size_t)u * M0 * M0;
   int* chain = v.tok_off + cb;
-  const bool fresh = v.M[u] == M0 && v.N[u] == n_tokens && v.nflag[u] == 0 && v.free_top[u] == 0;
-  if (!fresh) {                                            // workgroup-uniform
-    if (tid == 0) { atomicOr(&v.err[u], DYNAKV_ERR_PLACE); v.nflagged[u] = 0; }
+  if (!v.nflagged[u]) {                                    // workgroup-uniform
+    if (tid == 0) atomicOr(&v.err[u], DYNAKV_ERR_PLACE);
     return;
   }
   double tot = 0.0;
@@ -394,7 +437,6 @@ __global__ __launch_bounds__(1024) void cor_finish_kernel(View v, float* F, int*
       v.pg_off[cb + j] = base;
       base += (v.cn[cb + j] + kPageTokens - 1) / kPageTokens;
     }
-    v.nflagged[u] = 1;
   }
   __syncthreads();
   for (int j = tid; j < M0; j += 1024) {
@@ -421,7 +463,8 @@ hipError_t launch_place(const View& v, const void* K, const void* V, int n_token
     if (e != hipSuccess) return e;
     cor_count_kernel<<<v.U, 256, 0, st>>>(v, P);
   }
-  cor_finish_kernel<<<v.U, 1024, 0, st>>>(v, P, order, n_tokens);
+  place_members_kernel<<<v.U, 1024, 0, st>>>(v, n_tokens);
+  cor_finish_kernel<<<v.U, 1024, 0, st>>>(v, P, order);
   place_copy_kernel<<<dim3((n_tokens + 15) / 16, v.U), 256, 0, st>>>(v, K, V, n_tokens);
   return hipGetLastError();
 }

@@ -523,6 +523,47 @@ def test_coretrieval_placement(dtype, launch):
     assert st["error"].tolist() == [binding.ERR_PLACE] * U
 
 
+@pytest.mark.parametrize("dtype,built_before", [("f16", False), ("bf16", True), ("f32", False)])
+def test_coretrieval_placement_after_an_import(dtype, built_before):
+    """A snapshot taken right after the build counts as a built index: placing the importing index (new, or built
+    earlier on another prompt of the same size) gives what placing the exporting one gives.  A unit whose snapshot names
+    a position beyond the keys at hand is refused."""
+    N0, M0, Mcap, U = 1100, 70, 300, 3
+    s = WorkloadSpec("place", dtype, U, 4, N0, 8, M0, 300, 6, 0.05, var_alpha=1.5, size_factor=0.0, seed=17)
+    w, other = generate(s), generate(s.scaled(seed=18))
+    a, _ = make_pair(s, U, max_tokens=N0 + 40, max_clusters=Mcap, kmeans_iters=3)
+    b, _ = make_pair(s, U, max_tokens=N0 + 40, max_clusters=Mcap, kmeans_iters=3)
+    K, V = to_dev(w["K0"], dtype), to_dev(w["V0"], dtype)
+    a.dynakv_build_index(K, V, torch.from_numpy(w["init_idx"]).to(DEV))
+    snap = a.dynakv_export_state(binding.IMPORT_FIELDS, to_cpu=False)
+    if built_before:
+        b.dynakv_build_index(to_dev(other["K0"], dtype), to_dev(other["V0"], dtype), torch.from_numpy(other["init_idx"]).to(DEV))
+    b.dynakv_import_state(snap)
+    Qref = to_dev(w["Q"], dtype)
+    got = []
+    for ix in (a, b):
+        P, order = ix.dynakv_place_by_coretrieval(K, V, Qref, 300)
+        out, lse = torch.empty(U, 4, 128, device=DEV), torch.empty(U, 4, device=DEV)
+        ix.dynakv_retrieve_attend(Qref[0], 300, out, lse)
+        st = ix.dynakv_export_state(("error", "size", "offsets", "members", "keys", "values", "first_page", "n_gathered", "gathered"))
+        got.append((P.cpu(), order.cpu(), out.cpu(), lse.cpu(), st))
+    (Pa, oa, xa, la, sa), (Pb, ob, xb, lb, sb) = got
+    assert torch.equal(Pa, Pb) and torch.equal(oa, ob)
+    for k in sa:
+        assert torch.equal(sa[k], sb[k]), k
+    assert not sa["error"].any() and torch.equal(sa["keys"][:, :N0], K.cpu()) and torch.equal(sa["values"][:, :N0], V.cpu())
+    # the same entries in the same order; only which wavefront takes a tile differs: float32 sums of up to 300 terms
+    assert torch.allclose(xa, xb, rtol=3e-5, atol=3e-6) and torch.allclose(la, lb, rtol=3e-5)
+    snap["members"][1, 5] = N0 + 7
+    b.dynakv_import_state(snap)
+    before = b.dynakv_export_state(("members", "first_page"))
+    b.dynakv_place_by_coretrieval(K, V, Qref, 300)
+    after = b.dynakv_export_state(("members", "first_page", "error"))
+    assert after["error"].tolist() == [0, binding.ERR_PLACE, 0]
+    assert torch.equal(before["members"], after["members"]) and torch.equal(before["first_page"][1], after["first_page"][1])
+    assert torch.equal(after["first_page"][0], sa["first_page"][0])
+
+
 @pytest.mark.parametrize("dtype,W,k", [("f16", 32, 4), ("bf16", 128, 32), ("f32", 20, 3)])
 def test_local_update_mode(dtype, W, k):
     """The local-update baseline: new entries are clusters of their own until a window is full, its own k-means then
