@@ -265,7 +265,9 @@ dynakv_status_t dynakv_export_state(dynakv_index_t* index, const dynakv_state_t*
  * buffered, flag, m2, offsets, members, keys, values; optional: n_selected with selected (else the active set is
  * empty).  The other fields are ignored.  Pages are laid out afresh, cluster by cluster; error words and counters
  * start at zero.  A unit whose sizes are inconsistent (cluster or token count beyond capacity, offsets that do
- * not match size + buffered) keeps its previous state and gets DYNAKV_ERR_IMPORT.  Counts as building the index. */
+ * not match size + buffered) keeps its previous state and gets DYNAKV_ERR_IMPORT; if the handle has no state yet
+ * (nothing built or imported before), that unit is empty afterwards: no clusters, no tokens, retrievals from it give
+ * zeros and appends are refused.  Counts as building the index. */
 dynakv_status_t dynakv_import_state(dynakv_index_t* index, const dynakv_state_t* src, void* stream);
 
 /* Timing aid: when enabled, the dominant kernel of dynakv_retrieve_attend / dynakv_decode_step (gather +

@@ -359,7 +359,7 @@ dynakv_status_t dynakv_import_state(dynakv_index_t* ix, const dynakv_state_t* sr
       !src->m2 || !src->offsets || !src->members || !src->keys || !src->values)
     return DYNAKV_EINVAL;
   if ((src->n_selected == nullptr) != (src->selected == nullptr)) return DYNAKV_EINVAL;
-  if (launch_import(ix->view, *src, (hipStream_t)stream) != hipSuccess) return DYNAKV_EHIP;
+  if (launch_import(ix->view, *src, !ix->built, (hipStream_t)stream) != hipSuccess) return DYNAKV_EHIP;
   ix->built = true;
   ix->local_count = 0;
   return DYNAKV_OK;

@@ -39,7 +39,7 @@ struct View {
   float var_alpha, size_factor, scale_f;
   double scale_d;
   // per unit
-  int* M;            // [U] clusters in use
+  int* M;            // [U] clusters in use (at least M0; 0 only in a unit that the index's first import has refused)
   int* N;            // [U] tokens stored
   int* err;          // [U] sticky DYNAKV_ERR_* bits
   double* tau;       // [U] split threshold on the variance
@@ -456,7 +456,8 @@ hipError_t launch_split(const View& v, hipStream_t st);
 hipError_t launch_local_recluster(const View& v, int iters, hipStream_t st);
 hipError_t launch_extend(const View& v, const void* K, const void* V, int n, hipStream_t st);
 hipError_t launch_export(const View& v, const dynakv_state_t& dst, hipStream_t st);
-hipError_t launch_import(const View& v, const dynakv_state_t& src, hipStream_t st);
+// first: the index holds no state yet (a refused unit then becomes an empty one).
+hipError_t launch_import(const View& v, const dynakv_state_t& src, bool first, hipStream_t st);
 hipError_t launch_place(const View& v, const void* K, const void* V, int n_tokens, const void* Qref, int n_ref, int budget,
                         float* P, int* order, hipStream_t st);
 

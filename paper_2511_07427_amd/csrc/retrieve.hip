@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void score_mfma_kernel(View v, const void* Q, 
       for (int s = 0; s < 4; ++s)
         dst[t][s] = (size_t)(g * 4 + t + 1) * kTileElems <= v.Rstride ? tiles[((size_t)(g * 4 + t) * 4 + s) * 64 + lane] : uint4{0, 0, 0, 0};
   };
-  // the first M0 clusters exist in every state (M never drops below M0): their rows are requested before M is known
+  // the first M0 clusters exist in every state but an empty unit's: their rows are requested before M is known
   const bool early = (g0 + 1) * 64 <= v.M0;
   if (early) fetch(b, g0);
   const int M = v.M[u];
@@ -872,7 +872,7 @@ __global__ __launch_bounds__(1024) void select_kernel(View v, const void* Q, int
       int sz8[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const size_t i = (size_t)u * v.Mcap + min(i0 + k * 1024, M - 1);
+        const size_t i = (size_t)u * v.Mcap + max(min(i0 + k * 1024, M - 1), 0);
         sc8[k] = v.score[i]; sz8[k] = v.csz[i];
       }
 #pragma unroll
@@ -1348,7 +1348,7 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   ScoreRows<1> A;
   load_score_rows<1>(A, G, Q, APPEND ? kin : nullptr, u, lane);
   const int N = APPEND ? v.N[u] : 0;
-  const bool room = APPEND && N < v.Ncap;              // otherwise the append is refused, as by the append kernel
+  const bool room = APPEND && N < v.Ncap && M > 0;     // otherwise the append is refused, as by the append kernel
   if (APPEND && tid < kHeadDim) ap.kd[tid] = (double)load_elem(kin, (size_t)u * kHeadDim + tid, v.dtype);
   int Mpad = 2;
   while (Mpad < M) Mpad <<= 1;

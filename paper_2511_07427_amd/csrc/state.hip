@@ -128,10 +128,18 @@ __global__ __launch_bounds__(256) void export_clusters_kernel(View v, dynakv_sta
 }
 
 // ------------------------------------------------------------------------------------------- import
+// One thread: unit u's scalars as they are before its first retrieval, with nothing flagged or selected and no page recycled.
+__device__ inline void reset_unit(const View& v, int u, int M, int N, double tau, int pages) {
+  v.M[u] = M; v.N[u] = N; v.tau[u] = tau; v.err[u] = 0; v.nflag[u] = 0; v.n_sel[u] = 0; v.t_sel[u] = 0; v.n_list[u] = 0;
+  v.ticket[u] = 0; v.bump[u] = pages; v.free_top[u] = 0; v.last_assign[u] = -1; v.lcount[u] = 0; v.rmax2[u] = 0;
+  for (int k = 0; k < kCounters; ++k) v.counters[(size_t)u * kCounters + k] = 0;
+}
+
 // First kernel of an import, one workgroup per unit: checks the snapshot's sizes, deals out the pages cluster by cluster
 // (v.pg_off), and writes the unit's scalars, flagged list and active set.
-// v.nflagged[u] tells the kernels that follow whether the unit was accepted.
-__global__ __launch_bounds__(1024) void import_unit_kernel(View v, dynakv_state_t s) {
+// v.nflagged[u] tells the kernels that follow whether the unit was accepted.  first: the index has never been built, so a
+// refused unit has no previous state to keep: it becomes an empty one.
+__global__ __launch_bounds__(1024) void import_unit_kernel(View v, dynakv_state_t s, int first) {
   __shared__ int sm[64];
   __shared__ int s_bad, s_nflag;
   const int u = blockIdx.x, tid = threadIdx.x;
@@ -169,7 +177,10 @@ __global__ __launch_bounds__(1024) void import_unit_kernel(View v, dynakv_state_
   }
   __syncthreads();
   if (!sane || s_bad || pages > v.Pcap) {
-    if (tid == 0) { atomicOr(&v.err[u], DYNAKV_ERR_IMPORT); v.nflagged[u] = 0; }
+    if (tid == 0) {
+      if (first) reset_unit(v, u, 0, 0, 0.0, 0);
+      v.err[u] |= DYNAKV_ERR_IMPORT; v.nflagged[u] = 0;
+    }
     return;
   }
   for (int j = tid; j < v.Mcap; j += 1024) {
@@ -186,10 +197,8 @@ __global__ __launch_bounds__(1024) void import_unit_kernel(View v, dynakv_state_
     }
   }
   if (tid == 0) {
-    v.M[u] = M; v.N[u] = N; v.tau[u] = s.tau[u]; v.err[u] = 0; v.nflag[u] = s_nflag; v.n_sel[u] = nsel; v.t_sel[u] = 0;
-    v.n_list[u] = 0; v.ticket[u] = 0; v.bump[u] = (int)pages; v.free_top[u] = 0; v.last_assign[u] = -1; v.lcount[u] = 0; v.rmax2[u] = 0;
-    for (int k = 0; k < kCounters; ++k) v.counters[(size_t)u * kCounters + k] = 0;
-    v.nflagged[u] = 1;
+    reset_unit(v, u, M, N, s.tau[u], (int)pages);
+    v.nflag[u] = s_nflag; v.n_sel[u] = nsel; v.nflagged[u] = 1;
   }
 }
 
@@ -468,8 +477,8 @@ hipError_t launch_place(const View& v, const void* K, const void* V, int n_token
   place_copy_kernel<<<dim3((n_tokens + 15) / 16, v.U), 256, 0, st>>>(v, K, V, n_tokens);
   return hipGetLastError();
 }
-hipError_t launch_import(const View& v, const dynakv_state_t& src, hipStream_t st) {
-  import_unit_kernel<<<v.U, 1024, 0, st>>>(v, src);
+hipError_t launch_import(const View& v, const dynakv_state_t& src, bool first, hipStream_t st) {
+  import_unit_kernel<<<v.U, 1024, 0, st>>>(v, src, first);
   import_clusters_kernel<<<dim3((v.Mcap + kStateTile - 1) / kStateTile, v.U), 256, 0, st>>>(v, src);
   const dim3 pages((v.Pcap + 15) / 16, v.U);
   if (v.dtype == DYNAKV_F32) import_pages_kernel<4><<<pages, 256, 0, st>>>(v, src);

@@ -739,6 +739,51 @@ def test_snapshot_round_trip(dtype, N0, M0, Mcap):
         assert torch.equal(x["keys"][u, :N0], K[u])
 
 
+@pytest.mark.parametrize("dtype,launch,Mcap,kw", [
+    ("f16", 0, 200, {}), ("bf16", launch_shape(2, 0, LAUNCH_SEPARATE), 200, {}), ("f32", 0, 200, {}),
+    ("f16", 0, 17000, {}), ("f16", 0, 200, dict(search_copy=1)), ("bf16", LAUNCH_SPLIT_KERNEL, 200, {})])
+def test_units_refused_by_the_first_import_are_empty(dtype, launch, Mcap, kw):
+    """On a handle without a state an import that refuses a unit leaves it empty, whatever the workspace held: every
+    later call is defined on it (exports of nothing, zeros, refused appends) and its neighbours are as if alone."""
+    N0, M0, U = 500, 20, 3
+    s = WorkloadSpec("refuse", dtype, U, 2, N0, 6, M0, 100, 6, 0.05, var_alpha=1.5, size_factor=0.0, seed=23)
+    w = generate(s)
+    a, b = (make_pair(s, U, max_clusters=Mcap, kmeans_iters=2, launch=launch, **kw)[0] for _ in range(2))
+    K, V = to_dev(w["K0"], dtype), to_dev(w["V0"], dtype)
+    a.dynakv_build_index(K, V, torch.from_numpy(w["init_idx"]).to(DEV))
+    snap = a.dynakv_export_state(binding.IMPORT_FIELDS, to_cpu=False)
+    snap["n_clusters"][0], snap["n_tokens"][2] = Mcap + 1, -1
+    b.workspace.fill_(0x5A)
+    b.dynakv_import_state(snap)
+    st = b.dynakv_export_state(binding.IMPORT_FIELDS + ("error", "counters", "last_assign", "n_gathered", "first_page"))
+    assert st["error"].tolist() == [binding.ERR_IMPORT, 0, binding.ERR_IMPORT]
+    for u in (0, 2):
+        for k in ("n_clusters", "n_tokens", "n_selected", "n_gathered", "tau", "size", "offsets", "members", "centroids", "counters"):
+            assert not st[k][u].any(), k
+    Q, kn, vn = (to_dev(w[k], dtype) for k in ("Q", "Knew", "Vnew"))
+    outs = []
+    for ix in (a, b):
+        out, lse = torch.full((6, U, 2, 128), 7.0, device=DEV), torch.full((6, U, 2), 7.0, device=DEV)
+        for t in range(4):
+            ix.dynakv_decode_step(Q[t], 100, out[t], lse[t], kn[t], vn[t])
+        ix.dynakv_retrieve_attend(Q[4], 100, out[4], lse[4])
+        ix.dynakv_append(kn[4], vn[4])
+        ix.dynakv_split()
+        ix.dynakv_extend_index(kn[5][:, None].contiguous(), vn[5][:, None].contiguous())
+        ix.dynakv_retrieve_attend(Q[5], 100, out[5], lse[5])
+        outs.append((out.cpu(), lse.cpu()))
+    (oa, la), (ob, lb) = outs
+    assert torch.allclose(oa[:, 1], ob[:, 1], rtol=3e-5, atol=3e-6) and torch.allclose(la[:, 1], lb[:, 1], rtol=3e-5)
+    assert not ob[:, [0, 2]].any() and bool((lb[:, [0, 2]] == -float("inf")).all())
+    sa, sb = (ix.dynakv_export_state(("error", "n_clusters", "n_tokens", "size", "members", "offsets")) for ix in (a, b))
+    assert sb["error"].tolist() == [binding.ERR_IMPORT | binding.ERR_TOKENS, 0, binding.ERR_IMPORT | binding.ERR_TOKENS]
+    assert sb["n_tokens"].tolist() == [0, N0 + 6, 0]
+    for k in ("n_clusters", "size", "members", "offsets"):
+        assert torch.equal(sa[k][1], sb[k][1]) and not sb[k][[0, 2]].any(), k
+    b.dynakv_place_by_coretrieval(K, V, Q[:2].contiguous(), 100)     # nothing to place in any of them
+    assert all(e & binding.ERR_PLACE for e in b.dynakv_export_state(["error"])["error"].tolist())
+
+
 @pytest.mark.parametrize("name,launch", [("llama3_8b", 0), ("tiny", 0), ("qwen25_7b", launch_shape(2, 0, LAUNCH_SEPARATE))])
 def test_imported_state_continues_like_the_exporting_index(name, launch):
     """dynakv_export_state -> dynakv_import_state into a second index: both then take the same steps and must
