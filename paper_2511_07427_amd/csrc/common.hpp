@@ -25,6 +25,7 @@ constexpr int kLocalWindowMax = 128, kLocalClustersMax = 32;   // local update: 
 constexpr int kInlinePages = 8;                 // pages of a cluster found without walking its chain                // workgroups that share one unit's gathered pages
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // in a caller's float array, which need not be aligned further
 
 // Device-side view of one index.  All arrays live in the caller's workspace.
 struct View {

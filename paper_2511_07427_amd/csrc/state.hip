@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void export_clusters_kernel(View v, dynakv_sta
     const float* R = unit_R(v, u);
     for_each_table_piece([&](int c, int d) __attribute__((always_inline)) {
       const int j = j0 + c;
-      if (j < v.Mcap) *(f4*)(o.centroids + (cbase + j) * kHeadDim + d) = j < M ? *(const f4*)(R + r_index(j, d)) : f4{0, 0, 0, 0};
+      if (j < v.Mcap) *(f4u*)(o.centroids + (cbase + j) * kHeadDim + d) = j < M ? *(const f4*)(R + r_index(j, d)) : f4{0, 0, 0, 0};
     });
   }
   if (o.gathered) {
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256) void import_clusters_kernel(View v, dynakv_sta
     for_each_table_piece([&](int c, int d) __attribute__((always_inline)) {
       const int j = j0 + c;
       if (j >= M) return;
-      const f4 x = *(const f4*)(s.centroids + (cbase + j) * kHeadDim + d);
+      const f4 x = *(const f4u*)(s.centroids + (cbase + j) * kHeadDim + d);
       *(f4*)(R + r_index(j, d)) = x;
       if (v.dtype != DYNAKV_F32) {
         const uint2 q = {round_bits16(x[0], v.dtype) | ((uint32_t)round_bits16(x[1], v.dtype) << 16),

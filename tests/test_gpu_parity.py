@@ -4,6 +4,7 @@ Sizes are chosen so the oracle finishes in seconds while every kernel still sees
 tails and (where the workload drifts) real splits.  Each of the five benchmark configurations appears
 with its own storage type, group size, cluster count and budget, on a few of its units.
 """
+import ctypes
 import json
 import os
 import sys
@@ -737,6 +738,24 @@ def test_snapshot_round_trip(dtype, N0, M0, Mcap):
         m = x["members"][u, :N0].long()
         assert torch.equal(torch.sort(m).values, torch.arange(N0, device=DEV))
         assert torch.equal(x["keys"][u, :N0], K[u])
+
+
+def test_snapshot_arrays_need_their_element_alignment_only():
+    """Centroids of a snapshot at an address that is a multiple of four bytes and no more, out and in."""
+    s = WorkloadSpec("align", "f16", 2, 2, 300, 4, 21, 100, 6, 0.05, var_alpha=1.5, size_factor=0.0, seed=31)
+    w = generate(s)
+    a, b = (make_pair(s, 2, max_clusters=90, kmeans_iters=2)[0] for _ in range(2))
+    a.dynakv_build_index(to_dev(w["K0"], "f16"), to_dev(w["V0"], "f16"), torch.from_numpy(w["init_idx"]).to(DEV))
+    x = a.dynakv_export_state(binding.IMPORT_FIELDS, to_cpu=False)
+    flat = torch.full((2 * 90 * 128 + 2,), 5.0, device=DEV)
+    odd = flat[1:-1].view(2, 90, 128)
+    assert odd.data_ptr() % 16 == 4
+    st = binding._State(**{k: (odd.data_ptr() if k == "centroids" else None) for k in binding._STATE_FIELDS})
+    assert a._lib.dynakv_export_state(a._h, ctypes.byref(st), torch.cuda.current_stream().cuda_stream) == binding.OK
+    assert torch.equal(odd, x["centroids"]) and flat[0] == 5.0 and flat[-1] == 5.0
+    b.dynakv_import_state(dict(x, centroids=odd))
+    y = b.dynakv_export_state(binding.IMPORT_FIELDS, to_cpu=False)
+    assert torch.equal(y["centroids"], x["centroids"]) and torch.equal(y["members"], x["members"])
 
 
 @pytest.mark.parametrize("dtype,launch,Mcap,kw", [
