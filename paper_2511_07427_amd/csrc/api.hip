@@ -139,13 +139,11 @@ size_t carve(const dynakv_config_t& c, char* base, View* out) {
   v.part = (float*)take(U * v.S * v.G * (kHeadDim + 2) * 4);
   v.labels = (int*)take(UN * 4); v.order = (int*)take(UN * 4); v.dist = (double*)take(UN * 8);
   v.koff = (int*)take(U * (v.Mcap + 1) * 4);
-  const size_t mpad = (size_t)((v.M0 + 63) / 64) * 64;
-  v.Mpad = (int)mpad;
+  const size_t mpad = km_pad(v.M0);
   v.kmA_stride = mpad * kHeadDim * 2;                    // up to two 16-bit terms per coordinate
   v.kmA = (uint16_t*)take(U * v.kmA_stride * 2);
-  v.hn = (float*)take(U * mpad * 4); v.rmax = (float*)take(U * 4);
-  v.rhomax = (float*)take(U * 4); v.n_changed = (int*)take(U * 8);
-  v.nflagged = (int*)take(U * 4); v.has_empty = (int*)take(U * 4); v.xrange = (int*)take(U * 8);
+  v.hn = (float*)take(U * mpad * 4); v.rmax = (float*)take(U * 8);
+  v.nflagged = (int*)take(U * 4); v.has_empty = (int*)take(U * 4); v.xrange = (int*)take(U * 16);
   if (out) *out = v;
   return off;
 }

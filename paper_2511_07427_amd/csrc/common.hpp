@@ -96,17 +96,21 @@ struct View {
   double* dist;
   int* koff;         // [U][Mcap+1] start of every cluster in `order`
   // k-means distance filter on the matrix cores
-  int Mpad;          // centres per unit rounded up to the assignment's chunk of 64
   uint16_t* kmA;     // [U][kmA_stride] centroids split into 16-bit terms, in A-operand order (see kmeans.hip)
   size_t kmA_stride; // 16-bit elements per unit
-  float* hn;         // [U][Mpad] -|r_j|^2 / 2 (-3e38 for padding rows)
-  float* rmax;       // [U] largest |r_j| of the build so far
-  float* rhomax;     // [U] largest |r_j - sum of its 16-bit terms| of the build so far
-  int* n_changed;    // [U][2] points that changed their cluster in an iteration, odd and even ones apart
+  float* hn;         // [U][km_pad(M0)] -|r_j|^2 / 2 (-3e38 for padding rows)
+  float* rmax;       // [U][2] largest |r_j| and largest |r_j - sum of its 16-bit terms| of the build so far
   int* nflagged;     // [U] import / placement: the unit was accepted
   int* has_empty;    // [U] some cluster got no point in the last assignment
-  int* xrange;       // [U][2] smallest and largest binary exponent among the unit's non-zero prefill keys
+  int* xrange;       // [U][4] smallest and largest binary exponent among the unit's non-zero prefill keys; points that
+                     // changed their cluster in an iteration, even and odd ones apart
 };
+// The kernels take the whole struct as an argument, and each of its 64-byte lines that a launch touches is a trip to host
+// memory: the k-means' small counters share arrays, and what follows from other fields is computed (three fields more cost
+// a retrieval from one small unit, three dependent launches, 0.5 of 32 us).
+static_assert(sizeof(View) <= 568, "View: see above");
+// Centres per unit rounded up to the assignment's chunk of 64.
+__host__ __device__ inline int km_pad(int M0) { return (M0 + 63) & ~63; }
 
 __host__ __device__ inline int elem_size(int dtype) { return dtype == DYNAKV_F32 ? 4 : 2; }
 

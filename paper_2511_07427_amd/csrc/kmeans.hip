@@ -46,6 +46,9 @@ __device__ inline int* km_counts(const View& v, int u, int N0, int which) {
   return (int*)(km_changed(v, u) + N0) + which * v.M0;
 }
 
+// Points that changed their cluster in the iterations of parity `slot`.
+__device__ inline int& km_changed_count(const View& v, int u, int slot) { return v.xrange[4 * u + 2 + slot]; }
+
 // A-operand order of one 32-cluster tile: [term][k-step of 16][lane][8], lane = (k%16)/8*32 + row.
 __device__ inline size_t kmA_index(int nterms, int j, int term, int d) {
   return ((((size_t)(j >> 5) * nterms + term) * 8 + (d >> 4)) * 64 + (((d & 15) >> 3) << 5) + (j & 31)) * 8 + (d & 7);
@@ -106,7 +109,7 @@ __device__ inline void write_centre(const View& v, int u, int j, int c, const fl
     }
     nn = row_sum_f64(nn);
     rr = row_sum_f64(rr);
-    if (c == 0) v.hn[(size_t)u * v.Mpad + j] = (float)(-0.5 * nn);
+    if (c == 0) v.hn[(size_t)u * km_pad(v.M0) + j] = (float)(-0.5 * nn);
     cn.r = fmaxf(cn.r, (float)sqrt(nn) * 1.000001f);
     cn.rho = fmaxf(cn.rho, (float)sqrt(rr) * 1.000001f);
   }
@@ -122,8 +125,8 @@ __device__ inline void fold_norms(const View& v, int u, CentreNorms cn, int* sm)
   if (threadIdx.x == 0) {
     int mr = sm[0], mq = sm[1];
     for (int k = 1; k < nw; ++k) { mr = max(mr, sm[2 * k]); mq = max(mq, sm[2 * k + 1]); }
-    atomicMax((int*)&v.rmax[u], mr);
-    atomicMax((int*)&v.rhomax[u], mq);
+    atomicMax((int*)&v.rmax[2 * u], mr);
+    atomicMax((int*)&v.rmax[2 * u + 1], mq);
   }
 }
 
@@ -135,9 +138,8 @@ __global__ __launch_bounds__(256) void kmeans_check_init_kernel(View v, int N0, 
   const int u = blockIdx.x, tid = threadIdx.x;
   for (int i = tid; i < kMaxPrefill / 32; i += 256) seen[i] = 0u;
   if (tid == 0) {
-    v.err[u] = 0; v.has_empty[u] = 0; v.rmax[u] = 0.f; v.rhomax[u] = 0.f;
-    v.n_changed[2 * u] = 0; v.n_changed[2 * u + 1] = 0;
-    v.xrange[2 * u] = 0x7FFFFFFF; v.xrange[2 * u + 1] = -0x7FFFFFFF;
+    v.err[u] = 0; v.has_empty[u] = 0; v.rmax[2 * u] = 0.f; v.rmax[2 * u + 1] = 0.f;
+    v.xrange[4 * u] = 0x7FFFFFFF; v.xrange[4 * u + 1] = -0x7FFFFFFF; v.xrange[4 * u + 2] = 0; v.xrange[4 * u + 3] = 0;
   }
   __syncthreads();
   bool bad = false;
@@ -150,7 +152,7 @@ __global__ __launch_bounds__(256) void kmeans_check_init_kernel(View v, int N0, 
 }
 
 // Centre j = key at position init_idx[u][j]; the rows that pad the filter's table to whole chunks lose every comparison.
-// grid (ceil(M0 / 16) or ceil(Mpad / 16), U), sixteen lanes per centre.
+// grid (ceil(M0 / 16) or ceil(km_pad(M0) / 16), U), sixteen lanes per centre.
 template <int DT>
 __global__ __launch_bounds__(256) void kmeans_start_kernel(View v, const void* X, int N0, const int* init_idx) {
   __shared__ int sm[8];
@@ -161,10 +163,10 @@ __global__ __launch_bounds__(256) void kmeans_start_kernel(View v, const void* X
     float r[8];
     load8(X, ((size_t)u * N0 + p) * kHeadDim + c * 8, DT, r);
     write_centre<DT>(v, u, j, c, r, cn);
-  } else if (DT != DYNAKV_F32 && j < v.Mpad) {
+  } else if (DT != DYNAKV_F32 && j < km_pad(v.M0)) {
     uint16_t* A = v.kmA + (size_t)u * v.kmA_stride;
     for (int t = 0; t < kTerms<DT>; ++t) *(uint4*)(A + kmA_index(kTerms<DT>, j, t, c * 8)) = uint4{0, 0, 0, 0};
-    if (c == 0) v.hn[(size_t)u * v.Mpad + j] = -3.0e38f;             // (finite: the filter writes into its low bits)
+    if (c == 0) v.hn[(size_t)u * km_pad(v.M0) + j] = -3.0e38f;             // (finite: the filter writes into its low bits)
   }
   if constexpr (DT != DYNAKV_F32) fold_norms(v, u, cn, sm);
 }
@@ -181,7 +183,7 @@ __host__ __device__ inline bool sums_order_free_by_type(int dtype, int N0) { ret
 __device__ inline bool sums_order_free(const View& v, int u, int N0) {
   if (v.dtype == DYNAKV_F32) return false;
   if (sums_order_free_by_type(v.dtype, N0)) return true;
-  const int lo = v.xrange[2 * u], hi = v.xrange[2 * u + 1];
+  const int lo = v.xrange[4 * u], hi = v.xrange[4 * u + 1];
   const int mbits = v.dtype == DYNAKV_F16 ? 10 : 7;
   if (hi < lo) return true;                           // all keys zero
   int L = 0;
@@ -300,10 +302,10 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
   const int u = (blockIdx.x >> 3) / gx * 8 + (blockIdx.x & 7), xb = (blockIdx.x >> 3) % gx;
   if (u >= v.U) return;
   const int p = lane & 31, h = lane >> 5;
-  const int nchunk = v.Mpad / kChunkC;
+  const int nchunk = km_pad(v.M0) / kChunkC;
   const int pbase = (xb * NW + wave) * 64;
   const char* gA = (const char*)(v.kmA + (size_t)u * v.kmA_stride);
-  const float* hn = v.hn + (size_t)u * v.Mpad;
+  const float* hn = v.hn + (size_t)u * km_pad(v.M0);
   auto fetch = [&](int chunk, int buf) __attribute__((always_inline)) {
     constexpr int kPer = kChunkBytes / 1024 / NW;          // 1 KB pieces per wavefront
 #pragma unroll
@@ -315,7 +317,7 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
   };
   fetch(0, 0);
   if (tid == 0) s_n3 = 0;
-  if (xb == 0 && tid == 0) v.n_changed[2 * u + (slot ^ 1)] = 0;        // the list of the coming iteration
+  if (xb == 0 && tid == 0) km_changed_count(v, u, slot ^ 1) = 0;        // the list of the coming iteration
   uint4 bx[2][8];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
@@ -408,8 +410,8 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
       constexpr int mbits = BF ? 7 : 10, bias = BF ? 127 : 15, emask = BF ? 255 : 31;
       const int eh = hiw >> mbits, el = (low + 1) >> mbits;
       // subnormals share the grid of the smallest normal exponent; infinities and NaNs make the range unusable
-      atomicMax(&v.xrange[2 * u + 1], eh == emask ? 0x3FFFFFFF : max(eh, 1) - bias);
-      atomicMin(&v.xrange[2 * u], max(el, 1) - bias);
+      atomicMax(&v.xrange[4 * u + 1], eh == emask ? 0x3FFFFFFF : max(eh, 1) - bias);
+      atomicMin(&v.xrange[4 * u], max(el, 1) - bias);
     }
   }
   // the two halves of every point's centres; afterwards lane l speaks for point pbase + l
@@ -438,7 +440,7 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
   }
   const int pt = pbase + lane;
   const bool valid = pt < N0;
-  const float rmax = v.rmax[u], rho = v.rhomax[u];
+  const float rmax = v.rmax[2 * u], rho = v.rmax[2 * u + 1];
   const float slack = (float)NT / 16384.0f * (pn * rmax + rmax * rmax) + 4.f * pn * rho;
   const float B = fminf(rmax, pn + __builtin_sqrtf(fmaxf(pn * pn - 2.f * pb, 0.f) + slack));
   const float eps = pn * rho * 1.0001f + (float)NT / 65536.0f * (pn * B + 0.5f * B * B) * 1.01f +
@@ -534,7 +536,7 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
   const unsigned long long mv = __ballot(moved);
   if (mv == 0) return;
   int base = 0;
-  if (lane == 0) base = atomicAdd(&v.n_changed[2 * u + slot], __popcll(mv));
+  if (lane == 0) base = atomicAdd(&km_changed_count(v, u, slot), __popcll(mv));
   base = __builtin_amdgcn_readfirstlane(base);
   if (moved) {
     lab[pt] = label;
@@ -681,7 +683,7 @@ __global__ __launch_bounds__(256) void kmeans_changed_kernel(View v, const void*
   __shared__ int any_empty, sm[8];
   const int u = blockIdx.y, tid = threadIdx.x, j0 = blockIdx.x * 16;
   if (!sums_order_free(v, u, N0)) return;               // workgroup-uniform
-  const int n = v.n_changed[2 * u + slot];
+  const int n = km_changed_count(v, u, slot);
   const Changed* chg = km_changed(v, u);
   const int* was = km_counts(v, u, N0, which ^ 1);
   int* now = km_counts(v, u, N0, which);
@@ -986,14 +988,14 @@ template <int DT>
 static void launch_kmeans(const View& v, const void* K, int N0, const int* init_idx, int iters, hipStream_t st) {
   const dim3 gcl((v.M0 + 15) / 16, v.U);
   kmeans_check_init_kernel<<<v.U, 256, 0, st>>>(v, N0, init_idx);
-  kmeans_start_kernel<DT><<<dim3(((DT == DYNAKV_F32 ? v.M0 : v.Mpad) + 15) / 16, v.U), 256, 0, st>>>(v, K, N0, init_idx);
+  kmeans_start_kernel<DT><<<dim3(((DT == DYNAKV_F32 ? v.M0 : km_pad(v.M0)) + 15) / 16, v.U), 256, 0, st>>>(v, K, N0, init_idx);
   for (int it = 0; it < iters; ++it) {
     const int first = it == 0, last = it + 1 == iters, slot = it & 1, which = it & 1;
     if constexpr (DT == DYNAKV_F32) {
       kmeans_assign_f64_kernel<<<dim3((N0 + 63) / 64, v.U), 256, 0, st>>>(v, K, N0);
     } else {
       int code_bits = 4;                                // a lane sees half of the centres: 16 per tile of 32
-      while ((1 << code_bits) < v.Mpad / 2) ++code_bits;
+      while ((1 << code_bits) < km_pad(v.M0) / 2) ++code_bits;
       const int gx = (N0 + 64 * kAssignWaves - 1) / (64 * kAssignWaves);
       kmeans_assign_kernel<DT><<<gx * ((v.U + 7) / 8 * 8), 64 * kAssignWaves, 0, st>>>(v, K, N0, gx, first, slot, code_bits);
     }

@@ -867,19 +867,20 @@ __global__ __launch_bounds__(1024) void select_kernel(View v, const void* Q, int
   if constexpr (!BIG) {
     int Mpad = 2;
     while (Mpad < M) Mpad <<= 1;
-    for (int i0 = tid; i0 < Mpad; i0 += 8 * 1024) {      // eight of each in flight
+    // eight of each in flight, and none past the last cluster: a table of a few dozen clusters is one load of each
+    for (int i0 = tid; i0 < Mpad; i0 += 8 * 1024) {
       float sc8[8];
       int sz8[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const size_t i = (size_t)u * v.Mcap + max(min(i0 + k * 1024, M - 1), 0);
-        sc8[k] = v.score[i]; sz8[k] = v.csz[i];
+        const int i = i0 + k * 1024;
+        if (i < M) { sc8[k] = v.score[(size_t)u * v.Mcap + i]; sz8[k] = v.csz[(size_t)u * v.Mcap + i]; }
       }
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         const int i = i0 + k * 1024;
-        if (i < Mpad) skey_[i] = i < M ? orderable(sc8[k]) : 0u;
-        if (i < M) ssz_[i] = sz8[k];
+        if (i < M) { skey_[i] = orderable(sc8[k]); ssz_[i] = sz8[k]; }
+        else if (i < Mpad) skey_[i] = 0u;
       }
     }
     for (int i = tid; i < kSelectLds / 32; i += 1024) selbits_[i] = 0u;
