@@ -68,6 +68,7 @@ __device__ __forceinline__ double row_sum_f64(double x) {
   return row_step<kDppMirror>(x);
 }
 
+constexpr float kNoCentre = -3.0e38f;                  // in place of -|r_j|^2 / 2 (finite: the filter writes into its low bits)
 // Norms that bound the filter's error, folded over the clusters that a thread has written.
 struct CentreNorms {
   float r, rho;                                      // |r_j|, |r_j - its 16-bit terms|
@@ -99,19 +100,23 @@ __device__ inline void write_centre(const View& v, int u, int j, int c, const fl
       }
       rr = fma((double)rem, (double)rem, rr);
     }
+    nn = row_sum_f64(nn);
+    rr = row_sum_f64(rr);
+    // a centre that is not finite is nearest to no point: it enters the filter as a padding row does
+    const bool finite = nn < __builtin_inf();
     uint16_t* A = v.kmA + (size_t)u * v.kmA_stride;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       uint4 w;
       w.x = bits[t][0] | ((uint32_t)bits[t][1] << 16); w.y = bits[t][2] | ((uint32_t)bits[t][3] << 16);
       w.z = bits[t][4] | ((uint32_t)bits[t][5] << 16); w.w = bits[t][6] | ((uint32_t)bits[t][7] << 16);
-      *(uint4*)(A + kmA_index(NT, j, t, c * 8)) = w;
+      *(uint4*)(A + kmA_index(NT, j, t, c * 8)) = finite ? w : uint4{0, 0, 0, 0};
     }
-    nn = row_sum_f64(nn);
-    rr = row_sum_f64(rr);
-    if (c == 0) v.hn[(size_t)u * km_pad(v.M0) + j] = (float)(-0.5 * nn);
-    cn.r = fmaxf(cn.r, (float)sqrt(nn) * 1.000001f);
-    cn.rho = fmaxf(cn.rho, (float)sqrt(rr) * 1.000001f);
+    if (c == 0) v.hn[(size_t)u * km_pad(v.M0) + j] = finite ? (float)(-0.5 * nn) : kNoCentre;
+    if (finite) {
+      cn.r = fmaxf(cn.r, (float)sqrt(nn) * 1.000001f);
+      cn.rho = fmaxf(cn.rho, (float)sqrt(rr) * 1.000001f);
+    }
   }
 }
 // The workgroup's maxima into the unit's (which only ever grow during a build: a bound of an earlier centre stays a
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(256) void kmeans_start_kernel(View v, const void* X
   } else if (DT != DYNAKV_F32 && j < km_pad(v.M0)) {
     uint16_t* A = v.kmA + (size_t)u * v.kmA_stride;
     for (int t = 0; t < kTerms<DT>; ++t) *(uint4*)(A + kmA_index(kTerms<DT>, j, t, c * 8)) = uint4{0, 0, 0, 0};
-    if (c == 0) v.hn[(size_t)u * km_pad(v.M0) + j] = -3.0e38f;             // (finite: the filter writes into its low bits)
+    if (c == 0) v.hn[(size_t)u * km_pad(v.M0) + j] = kNoCentre;
   }
   if constexpr (DT != DYNAKV_F32) fold_norms(v, u, cn, sm);
 }
@@ -177,7 +182,9 @@ __global__ __launch_bounds__(256) void kmeans_start_kernel(View v, const void* X
 // smaller than 2^(emax+1); if (emax + 1 + ceil(log2 N0)) - q <= 53, every partial sum of any subset in any order
 // is exactly representable.  The sum then does not depend on the order at all and can follow the points that join and
 // leave a cluster: an update reads the changed points' keys only, and its result is the sum formed anew, bit for bit.
-// (float16 with at most 8192 keys always qualifies: exponents -14 .. 15 on a grid of 2^-24.)  Units whose keys span
+// (float16 with at most 8192 keys always qualifies: exponents -14 .. 15 on a grid of 2^-24.  A key that is not finite needs no
+// exception there: it is at no finite distance from any centre, so every assignment leaves it in cluster 0, whose sums in
+// the coordinates concerned are infinite or NaN whichever way they are formed.)  Units whose keys span
 // too wide a range, and float32 keys, have their sums formed anew in ascending position in every iteration.
 __host__ __device__ inline bool sums_order_free_by_type(int dtype, int N0) { return dtype == DYNAKV_F16 && N0 <= 8192; }
 __device__ inline bool sums_order_free(const View& v, int u, int N0) {
@@ -447,7 +454,7 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
                     (float)(1 << code_bits) * 1.2e-7f * fabsf(pb);
   const bool near2 = valid && !(pb - ps > 2.f * eps);
   const bool near3 = near2 && !(pb - pt3 > 2.f * eps);
-  int label = min(ib, v.M0 - 1);                           // (the padding rows can only win over values that are not finite)
+  int label = min(ib, v.M0 - 1);                           // (padding rows win where no value is finite; such a point is near3)
   is = min(is, v.M0 - 1);
   const float* rows = km_rows(v, u);
   int at3 = -1;
@@ -523,7 +530,7 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
         const int oj = s_j[at3 - q0][w];
         if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
       }
-      if (bj < v.M0) label = bj;                           // (no centre at a finite distance: the filter's choice stays)
+      label = bj < v.M0 ? bj : 0;                          // (a key that is not finite is at no finite distance from any)
     }
     __syncthreads();
   }

@@ -671,6 +671,30 @@ def test_prefill_partition_at_the_edges_of_tiles_and_chunks(dtype, N0, M0):
     assert tally["tie_kmeans"] == 0
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("bad", [(np.inf,), (-np.inf, np.inf), (np.nan, np.inf)])
+def test_prefill_with_keys_that_are_not_finite(dtype, bad):
+    """Such a key is at no finite distance from any centre: the lowest id takes it, its centre is then nearest to
+    no other key, and the partition of all others is the oracle's."""
+    U, N0, M0 = 2, 700, 12
+    s = WorkloadSpec("inf", dtype, U, 2, N0, 4, M0, 256, 6, 0.05, var_alpha=1.5, size_factor=0.0, seed=77)
+    w = generate(s)
+    for i, x in enumerate(bad):
+        w["K0"][:, 300 + 170 * i, 5 + 40 * i] = x
+    ix, o = make_pair(s, U, kmeans_iters=5)
+    ix.dynakv_build_index(to_dev(w["K0"], dtype), to_dev(w["V0"], dtype), torch.from_numpy(w["init_idx"]).to(DEV))
+    o.build_index(w["K0"], w["V0"], w["init_idx"])
+    st = ix.dynakv_export_state(["size", "offsets", "members", "centroids", "error"])
+    assert not st["error"].any()
+    for u in range(U):
+        off, mem = o.members(u)
+        np.testing.assert_array_equal(st["offsets"][u, :M0 + 1].numpy(), off)
+        np.testing.assert_array_equal(st["members"][u, :N0].numpy(), mem)
+        c = o.clusters(u)["centroids"]
+        np.testing.assert_allclose(st["centroids"][u, :M0].numpy(), c, rtol=1e-6, atol=1e-6)
+        assert not np.isfinite(c[0]).all() and np.isfinite(c[1:]).all()
+
+
 def test_rebuild_resets_the_index_and_runs_are_deterministic():
     s = CONFIGS["tiny"].scaled(prefill=777, n_clusters_init=19)
     w = generate(s, steps=8)
