@@ -275,6 +275,8 @@ __device__ __forceinline__ void load_to_lds(const void* src, void* base) {
 //   |x_i| max_j |r_j - terms|               what the terms leave of a centre (its exact norm is known)
 //   NT 2^-16 (|x_i| B + B^2 / 2)            accumulation of NT x 128 exact products onto -|r_j|^2/2, doubled
 //   2^bits 2^-23 |z|                        the running best three carry the centre's number in their low mantissa bits
+//   1e-35                                   all of these where float32 has no digits left: products, squares of |x|^2 and
+//                                           z itself below 2^-126 (up to 128 of them), the number in a z of zero
 // B bounds the norm of every centre that can be the nearest: such a centre is no farther from x_i than the best one found,
 // whose distance follows from its z (and B <= max |r|).
 // A point whose best and second-best values are more than 2 eps_i apart has the same nearest centre in exact arithmetic.
@@ -396,7 +398,7 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
       for (int e = 0; e < 4; ++e) nn = dot2<BF>(ww[e], nn);
     }
     nn += __shfl_xor(nn, 32);
-    xnorm[t] = __builtin_sqrtf(nn) * 1.0001f;
+    xnorm[t] = __builtin_sqrtf(nn + 2e-36f) * 1.0001f;     // (128 squares below 2^-126 may be missing)
   }
   if (first && !sums_order_free_by_type(DT, N0)) {         // the exponents of the unit's coordinates, once
     unsigned lo16 = 0xFFFFu, hi16 = 0u;                    // smallest (zeros left out, minus one) and largest magnitude bits
@@ -451,7 +453,7 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
   const float slack = (float)NT / 16384.0f * (pn * rmax + rmax * rmax) + 4.f * pn * rho;
   const float B = fminf(rmax, pn + __builtin_sqrtf(fmaxf(pn * pn - 2.f * pb, 0.f) + slack));
   const float eps = pn * rho * 1.0001f + (float)NT / 65536.0f * (pn * B + 0.5f * B * B) * 1.01f +
-                    (float)(1 << code_bits) * 1.2e-7f * fabsf(pb);
+                    (float)(1 << code_bits) * 1.2e-7f * fabsf(pb) + 1e-35f;
   const bool near2 = valid && !(pb - ps > 2.f * eps);
   const bool near3 = near2 && !(pb - pt3 > 2.f * eps);
   int label = min(ib, v.M0 - 1);                           // (padding rows win where no value is finite; such a point is near3)

@@ -671,6 +671,30 @@ def test_prefill_partition_at_the_edges_of_tiles_and_chunks(dtype, N0, M0):
     assert tally["tie_kmeans"] == 0
 
 
+@pytest.mark.parametrize("dtype,scale", [("f16", 0.0), ("bf16", 0.0), ("f32", 0.0), ("f16", 2.0 ** -24), ("bf16", 1e-20), ("bf16", 1e-38)])
+@pytest.mark.parametrize("M0", [2, 3, 40])
+def test_prefill_with_keys_of_zero_and_at_the_end_of_the_range(dtype, scale, M0):
+    """Equal distances of zero go to the lowest id, and distances that float32 cannot tell from zero are told apart in
+    float64.  Where the keys are zero, the second unit also holds entries of ordinary size."""
+    N0 = 200
+    s = WorkloadSpec("zero", dtype, 2, 2, N0, 4, M0, 64, 4, 0.05, var_alpha=1.5, size_factor=0.0, seed=9)
+    w = generate(s)
+    rng = np.random.default_rng(3)
+    q = lambda a: torch.from_numpy(a.astype(np.float32)).to(binding.TORCH_DTYPES[dtype]).float().numpy()  # noqa: E731
+    w["K0"][0] = q(rng.integers(-2, 3, (N0, 128)) * np.float32(scale))
+    w["K0"][1, :N0 if scale else 120] = q(rng.standard_normal((N0 if scale else 120, 128)) * np.float32(scale))
+    w["init_idx"][:] = np.arange(M0)
+    ix, o = make_pair(s, 2, kmeans_iters=3)
+    ix.dynakv_build_index(to_dev(w["K0"], dtype), to_dev(w["V0"], dtype), torch.from_numpy(w["init_idx"]).to(DEV))
+    o.build_index(w["K0"], w["V0"], w["init_idx"])
+    st = ix.dynakv_export_state(["offsets", "members", "error"])
+    assert not st["error"].any()
+    for u in range(2):
+        off, mem = o.members(u)
+        np.testing.assert_array_equal(st["offsets"][u, :M0 + 1].numpy(), off)
+        np.testing.assert_array_equal(st["members"][u, :N0].numpy(), mem)
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 @pytest.mark.parametrize("bad", [(np.inf,), (-np.inf, np.inf), (np.nan, np.inf)])
 def test_prefill_with_keys_that_are_not_finite(dtype, bad):
