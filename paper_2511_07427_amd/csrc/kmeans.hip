@@ -54,7 +54,8 @@ __device__ inline size_t kmA_index(int nterms, int j, int term, int d) {
   return ((((size_t)(j >> 5) * nterms + term) * 8 + (d >> 4)) * 64 + (((d & 15) >> 3) << 5) + (j & 31)) * 8 + (d & 7);
 }
 
-// Sum over the 16 lanes of a row; every lane of the row gets it (float64 butterfly on DPP row operations).
+// Sum over the 16 lanes of a row in any order (for bounds); every lane of the row gets it (float64 butterfly on DPP row
+// operations).
 template <int CTRL>
 __device__ __forceinline__ double row_step(double x) {
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
@@ -66,6 +67,19 @@ __device__ __forceinline__ double row_sum_f64(double x) {
   x = row_step<kDppXor2>(x);
   x = row_step<kDppHalfMirror>(x);
   return row_step<kDppMirror>(x);
+}
+
+// Sum over the 16 lanes of a row, left to right as common.hpp fixes it for sums over the coordinates (lane c holding the sum of
+// block c); lane 15 of the row has it.
+__device__ __forceinline__ double row_blocked16(double x) {
+  double t = x;
+#pragma unroll
+  for (int k = 1; k < 16; ++k) {                      // lanes 0 .. k hold their prefixes
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(t), 0x111, 0xF, 0xF, false);     // row_shr:1
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(t), 0x111, 0xF, 0xF, false);
+    t = __hiloint2double(hi, lo) + x;
+  }
+  return t;
 }
 
 constexpr float kNoCentre = -3.0e38f;                  // in place of -|r_j|^2 / 2 (finite: the filter writes into its low bits)
@@ -282,7 +296,7 @@ __device__ __forceinline__ void load_to_lds(const void* src, void* base) {
 // A point whose best and second-best values are more than 2 eps_i apart has the same nearest centre in exact arithmetic.
 // If only the second lies within that distance, the two centres are compared in float64 by 16 lanes; if the third does too
 // (about one point in a thousand), the workgroup goes through all centres in float64.  Labels therefore equal the
-// float64 definition (ties to the lowest index).
+// float64 definition (sums in the one order of common.hpp whichever way a point is decided; ties to the lowest index).
 //
 // Shape: 64 points per wavefront as two B operands held in registers; Z^T = R~ X^T in 32x32 tiles, so lane (p, h) ends up
 // with 16 values of point p per tile and the running best three need no cross-lane work until the end.  Four vector
@@ -483,8 +497,8 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
       const double ta = (double)x[e] - (double)(e < 4 ? a0[e] : a1[e - 4]), tb = (double)x[e] - (double)(e < 4 ? b0[e] : b1[e - 4]);
       da = fma(ta, ta, da); db = fma(tb, tb, db);
     }
-    da = row_sum_f64(da); db = row_sum_f64(db);
-    const unsigned long long take = __ballot(c == 0 && (db < da || (db == da && jb < ja)));
+    da = row_blocked16(da); db = row_blocked16(db);
+    const unsigned long long take = __ballot(c == 15 && (db < da || (db == da && jb < ja))) >> 15;
 #pragma unroll
     for (int gg = 0; gg < 4; ++gg)
       if ((take >> (16 * gg)) & 1ull) swap |= 1ull << owner[gg];
@@ -506,11 +520,13 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
           float x[8];
           load8(X, row + d8 * 8, DT, x);
           const f4 a = *(const f4*)(R + r_index(j, d8 * 8)), b = *(const f4*)(R + r_index(j, d8 * 8 + 4));
+          double blk = 0.0;
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const double t = (double)x[e] - (double)(e < 4 ? a[e] : b[e - 4]);
-            acc = fma(t, t, acc);
+            blk = fma(t, t, blk);
           }
+          acc += blk;
         }
         if (acc < bd) { bd = acc; bj = j; }
       }
@@ -813,8 +829,8 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
           const double t = (double)x[k][e] - (double)(e < 4 ? ra[k][e] : rb[k][e - 4]);
           acc = fma(t, t, acc);
         }
-        acc = row_sum_f64(acc);
-        if (c == 0 && i0 + 64 * k < N0) dist[i0 + 64 * k] = acc;
+        acc = row_blocked16(acc);
+        if (c == 15 && i0 + 64 * k < N0) dist[i0 + 64 * k] = acc;
       }
     }
     __syncthreads();

@@ -8,6 +8,7 @@ import ctypes
 import json
 import os
 import sys
+from fractions import Fraction
 
 import numpy as np
 import pytest
@@ -717,6 +718,55 @@ def test_prefill_with_keys_that_are_not_finite(dtype, bad):
         c = o.clusters(u)["centroids"]
         np.testing.assert_allclose(st["centroids"][u, :M0].numpy(), c, rtol=1e-6, atol=1e-6)
         assert not np.isfinite(c[0]).all() and np.isfinite(c[1:]).all()
+
+
+def _blocked_sqdist(x, r):
+    """The library's float64 squared distance: blocks of 8 coordinates by fused multiply-adds, block sums left to right."""
+    total = 0.0
+    for k in range(16):
+        blk = 0.0
+        for e in range(8):
+            t = float(x[8 * k + e]) - float(r[8 * k + e])
+            blk = float(Fraction(t) * Fraction(t) + Fraction(blk))
+        total += blk
+    return total
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("M0", [2, 3, 7])
+def test_prefill_decides_equal_distances_by_one_order_of_summation(dtype, M0):
+    """Centres that are block rotations of each other are equally far from a key whose blocks are all alike, up to the
+    rounding of the sum: with two of them (pair comparison) and with more (all centres) that decides as in one fixed
+    order.  The reseeding's farthest key likewise: two equal centres, candidates that are rotations of each other."""
+    rng = np.random.default_rng(5 + M0)
+    q = lambda a: torch.from_numpy(a.astype(np.float32)).to(binding.TORCH_DTYPES[dtype]).float().numpy()  # noqa: E731
+    # magnitudes over a range whose squares do not fit 53 bits together
+    a = q(rng.standard_normal((16, 8)) * np.exp2(rng.integers(-14, 4, (16, 8))))
+    same = q(np.tile(rng.standard_normal((90, 1, 8)) * np.exp2(rng.integers(-14, 3, (90, 1, 8))), (1, 16, 1)))
+    rot = np.stack([np.roll(a, 2 * j + 1, axis=0) for j in range(M0)])
+    K = np.concatenate([rot, same]).reshape(1, -1, 128).astype(np.float32)
+    U = 1
+
+    def labels(K, init, iters):
+        ix = binding.Index(binding.Config(U, 2, dtype, len(init), 4 * len(init), K.shape[1], iters), DEV)
+        Kd = to_dev(K, dtype)
+        ix.dynakv_build_index(Kd, Kd, torch.tensor([init], dtype=torch.int32, device=DEV))
+        st = ix.dynakv_export_state(["offsets", "members"])
+        lab = np.zeros(K.shape[1], int)
+        for j in range(len(init)):
+            lab[st["members"][0, st["offsets"][0, j]:st["offsets"][0, j + 1]].numpy()] = j
+        return lab
+
+    got = labels(K, list(range(M0)), 1)
+    want = [int(np.argmin([_blocked_sqdist(x, r) for r in K[0, :M0]])) for x in K[0]]
+    np.testing.assert_array_equal(got, want)
+    assert len(set(want[M0:])) > 1                       # the rounding does decide
+    if M0 == 7:
+        K2 = np.concatenate([np.zeros((2, 16, 8), np.float32)] + [np.roll(a, j, axis=0)[None] for j in range(16)]).reshape(1, -1, 128)
+        d = [_blocked_sqdist(x, K2[0, 0]) for x in K2[0]]
+        assert len(set(d[2:])) > 1
+        got = labels(K2, [0, 1], 2)
+        assert np.flatnonzero(got).tolist() == [int(np.argmax(d))]
 
 
 def test_rebuild_resets_the_index_and_runs_are_deterministic():
