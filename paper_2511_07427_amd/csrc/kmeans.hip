@@ -307,6 +307,79 @@ __device__ __forceinline__ void load_to_lds(const void* src, void* base) {
 // of latency more in step).  All workgroups of a unit have the same number modulo 8, i.e. share an L2.
 // The first iteration (first) labels every point; later ones list the points whose label changed.
 constexpr int kAssignWaves = 4;
+
+// Nearest of all centres in float64 for NP points (xd: their coordinates in LDS; n of them count) by one wavefront of the
+// `share` that split the centres among them: lane = centre, NC centres per lane at once.  Every coordinate of a centre is
+// loaded once for NP points and every coordinate of a point read once for NC centres; the float64 pipe is what is left.
+// (One point at a time by the whole workgroup read the centres anew for each: where most points have three candidates,
+// e.g. 256 x 4096 float16 keys about a common offset of 16 times their spread x 256 centres, a build took 44.5 ms.)
+constexpr int kScanPoints = 4, kScanCentres = 2;
+// Wavefronts that share the centres of a batch of points; the others take further batches.
+__device__ __forceinline__ int scan_share(int M0, int nc) { return M0 <= 64 * nc ? 1 : M0 <= 128 * nc ? 2 : kAssignWaves; }
+template <int NP, int NC>
+__device__ __forceinline__ void scan_centres(const View& v, int u, const double* xd, int n, int mine, int share,
+                                             double (*out_d)[kAssignWaves], int (*out_j)[kAssignWaves]) {
+  const int lane = threadIdx.x & 63;
+  const float* R = unit_R(v, u);
+  double bd[NP];
+  int bj[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) { bd[p] = __builtin_inf(); bj[p] = 0x7FFFFFFF; }
+  for (int j0 = mine * NC * 64; j0 < v.M0; j0 += share * NC * 64) {
+    double acc[NC][NP];
+#pragma unroll
+    for (int k = 0; k < NC; ++k)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) acc[k][p] = 0.0;
+    for (int d8 = 0; d8 < 16; ++d8) {
+      f4 r[NC][2];
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        const int j = min(j0 + k * 64 + lane, v.M0 - 1);
+        r[k][0] = *(const f4*)(R + r_index(j, d8 * 8)); r[k][1] = *(const f4*)(R + r_index(j, d8 * 8 + 4));
+      }
+      double blk[NC][NP];
+#pragma unroll
+      for (int k = 0; k < NC; ++k)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) blk[k][p] = 0.0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          const double x = xd[p * kHeadDim + d8 * 8 + e];
+#pragma unroll
+          for (int k = 0; k < NC; ++k) {
+            const double t = x - (double)r[k][e >> 2][e & 3];
+            blk[k][p] = fma(t, t, blk[k][p]);
+          }
+          if (p + 1 == NP && (e & 1)) asm volatile("" ::: "memory");      // points' coordinates stay two deep in registers
+        }
+#pragma unroll
+      for (int k = 0; k < NC; ++k)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) acc[k][p] += blk[k][p];
+    }
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      const int j = j0 + k * 64 + lane;
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+        if (j < v.M0 && acc[k][p] < bd[p]) { bd[p] = acc[k][p]; bj[p] = j; }      // ascending j per lane: the first minimum stays
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const double od = __shfl_xor(bd[p], o);
+      const int oj = __shfl_xor(bj[p], o);
+      if (od < bd[p] || (od == bd[p] && oj < bj[p])) { bd[p] = od; bj[p] = oj; }
+    }
+    if (lane == 0 && p < n) { out_d[p][mine] = bd[p]; out_j[p][mine] = bj[p]; }
+  }
+}
+
 template <int DT>
 __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(View v, const void* X, int N0, int gx, int first, int slot,
                                                                   int code_bits) {
@@ -316,10 +389,10 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
   constexpr int kTiles = kChunkTiles<DT>, kChunkC = 32 * kTiles, kChunkBytes = kTiles * kTileBytes;
   __shared__ __align__(16) unsigned char sA[2][kChunkBytes];
   __shared__ __align__(16) float shn[2][kChunkC];
-  constexpr int kScan = 8;                                 // points with many candidates, taken this many at a time
   __shared__ short s_list[NW * 64];
-  __shared__ double s_d[kScan][NW];
-  __shared__ int s_j[kScan][NW], s_n3;
+  __shared__ double s_d[kScanPoints * NW][kAssignWaves];
+  __shared__ int s_j[kScanPoints * NW][kAssignWaves], s_n3;
+  static_assert(sizeof(sA) >= sizeof(double) * kScanPoints * NW * kHeadDim, "points of a scan, in float64");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // workgroup L: unit 8 (L / 8 / gx) + L % 8, points (L / 8) % gx
   const int u = (blockIdx.x >> 3) / gx * 8 + (blockIdx.x & 7), xb = (blockIdx.x >> 3) % gx;
@@ -504,46 +577,33 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
       if ((take >> (16 * gg)) & 1ull) swap |= 1ull << owner[gg];
   }
   if ((swap >> lane) & 1ull) label = is;
-  // points with three or more candidates: the whole workgroup goes through the centres, lane = centre
+  // points with three or more candidates: all centres in float64, lane = centre.  One point alone: its centres are dealt
+  // to all wavefronts.  Several: four at a time per wavefront, against two centres per lane.
   __syncthreads();
   const int n3 = s_n3;
-  for (int q0 = 0; q0 < n3; q0 += kScan) {                 // workgroup-uniform
-    const float* R = unit_R(v, u);
-    for (int q = q0; q < min(n3, q0 + kScan); ++q) {
-      const size_t row = ((size_t)u * N0 + xb * NW * 64 + s_list[q]) * kHeadDim;
-      double bd = __builtin_inf();
-      int bj = 0x7FFFFFFF;
-      for (int j = wave * 64 + lane; j < v.M0; j += NW * 64) {
-        double acc = 0.0;
-#pragma unroll 8
-        for (int d8 = 0; d8 < 16; ++d8) {
-          float x[8];
-          load8(X, row + d8 * 8, DT, x);
-          const f4 a = *(const f4*)(R + r_index(j, d8 * 8)), b = *(const f4*)(R + r_index(j, d8 * 8 + 4));
-          double blk = 0.0;
+  for (int q0 = 0; q0 < n3;) {                             // workgroup-uniform
+    const bool alone = n3 - q0 == 1;
+    const int share = scan_share(v.M0, alone ? 1 : kScanCentres), mine = wave % share, group = wave / share;
+    const int nq = alone ? 1 : min(n3 - q0, kScanPoints * (NW / share));
+    double* xd = (double*)sA;                              // the buffers of the filter are dead
+    for (int t = tid; t < nq * 16; t += NW * 64) {
+      float x[8];
+      load8(X, ((size_t)u * N0 + xb * NW * 64 + s_list[q0 + (t >> 4)]) * kHeadDim + (t & 15) * 8, DT, x);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const double t = (double)x[e] - (double)(e < 4 ? a[e] : b[e - 4]);
-            blk = fma(t, t, blk);
-          }
-          acc += blk;
-        }
-        if (acc < bd) { bd = acc; bj = j; }
-      }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const double od = __shfl_xor(bd, o);
-        const int oj = __shfl_xor(bj, o);
-        if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
-      }
-      if (lane == 0) { s_d[q - q0][wave] = bd; s_j[q - q0][wave] = bj; }
+      for (int e = 0; e < 8; e += 2) *(double2*)(xd + t * 8 + e) = double2{(double)x[e], (double)x[e + 1]};
     }
     __syncthreads();
-    if (at3 >= q0 && at3 < q0 + kScan) {
+    const int p0 = group * kScanPoints;
+    if (alone) {
+      if (group == 0) scan_centres<1, 1>(v, u, xd, 1, mine, share, s_d, s_j);
+    } else if (p0 < nq) {
+      scan_centres<kScanPoints, kScanCentres>(v, u, xd + p0 * kHeadDim, min(kScanPoints, nq - p0), mine, share, s_d + p0, s_j + p0);
+    }
+    __syncthreads();
+    if (at3 >= q0 && at3 < q0 + nq) {
       double bd = s_d[at3 - q0][0];
       int bj = s_j[at3 - q0][0];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) {
+      for (int w = 1; w < share; ++w) {
         const double od = s_d[at3 - q0][w];
         const int oj = s_j[at3 - q0][w];
         if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
@@ -551,6 +611,7 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
       label = bj < v.M0 ? bj : 0;                          // (a key that is not finite is at no finite distance from any)
     }
     __syncthreads();
+    q0 += nq;
   }
   int* lab = v.labels + (size_t)u * v.Ncap;
   if (first) {
