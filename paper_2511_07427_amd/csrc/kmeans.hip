@@ -31,15 +31,27 @@ constexpr int kChunkTiles = 2 / kTerms<DT>;          // tiles of 32 centres per 
 
 // ---- scratch of a build -------------------------------------------------------------------------------------------
 // The page pool holds nothing until the layout at the end of a build, so each unit's part of it serves as scratch:
-// float64 centre sums [M0][128], the centres as plain rows [M0][128] (float32; the comparison of two centres reads whole
+// the offset that the filter takes off the centres (see Offset), float64 centre sums [M0][128], the centres as plain rows [M0][128] (float32; the comparison of two centres reads whole
 // rows, which the lane-interleaved table has in 32 places), the list of points that changed their cluster [N0], member
-// counts [2][M0].  (M0 (1024 + 512 + 8) + 8 N0 bytes against at least (M0 + N0 / 16) pages of 8 KB.)
+// counts [2][M0].  (1024 + M0 (1024 + 512 + 8) + 8 N0 bytes against at least (M0 + N0 / 16) pages of 8 KB.)
 struct Changed {
   int pos;
   unsigned move;                                     // old cluster | new cluster << 16
 };
 static_assert(kMaxInitClusters <= 65536, "two cluster ids per word");
-__device__ inline double* km_sums(const View& v, int u) { return (double*)page_ptr(v, u, 0); }
+// What the keys of a unit have in common: a vector c of the keys' type, zero if nothing stands out.  <x, r_j> - |r_j|^2 / 2 and
+// <x, r_j - c> - <c, r_j - c> - |r_j - c|^2 / 2 differ by a number that is the same for every centre, but the second leaves a
+// 16-bit term of a centre only its distance from c to round.  (256 units x 4096 float16 keys x 256 centres, 16 N(0, 1) added
+// per channel: build 20.1 -> 4.0 ms; 64 N(0, 1): 30.2 -> 17.7 ms; without: 2.2 ms either way.  Two terms without the offset,
+// as there once were, took 10.4, 55.9 and 3.8 ms.)
+struct Offset {
+  uint16_t bits[kHeadDim];
+  float c[kHeadDim];
+  float norm;                                        // |c| or a little more; 0: c is zero
+};
+static_assert(sizeof(Offset) <= 1024, "room in front of the sums");
+__device__ inline Offset* km_offset(const View& v, int u) { return (Offset*)page_ptr(v, u, 0); }
+__device__ inline double* km_sums(const View& v, int u) { return (double*)(page_ptr(v, u, 0) + 1024); }
 __device__ inline float* km_rows(const View& v, int u) { return (float*)(km_sums(v, u) + (size_t)v.M0 * kHeadDim); }
 __device__ inline Changed* km_changed(const View& v, int u) { return (Changed*)(km_rows(v, u) + (size_t)v.M0 * kHeadDim); }
 __device__ inline int* km_counts(const View& v, int u, int N0, int which) {
@@ -85,12 +97,22 @@ __device__ __forceinline__ double row_blocked16(double x) {
 constexpr float kNoCentre = -3.0e38f;                  // in place of -|r_j|^2 / 2 (finite: the filter writes into its low bits)
 // Norms that bound the filter's error, folded over the clusters that a thread has written.
 struct CentreNorms {
-  float r, rho;                                      // |r_j|, |r_j - its 16-bit terms|
+  float r, rho;                                      // |d_j| = |r_j - offset|, |d_j - its 16-bit terms|
 };
-// Sixteen lanes write centre j (lane c of them coordinates 8c .. 8c+7): the float32 table and, for 16-bit types, the
-// filter's terms in A-operand order with -|r_j|^2 / 2.
+// Coordinates 8c .. 8c+7 of the unit's offset, requested at the start of a kernel for the centres that it writes at its end.
+struct OffsetPart {
+  f4 lo, hi;
+};
 template <int DT>
-__device__ inline void write_centre(const View& v, int u, int j, int c, const float (&r)[8], CentreNorms& cn) {
+__device__ inline OffsetPart load_offset(const View& v, int u, int c) {
+  OffsetPart o{{0, 0, 0, 0}, {0, 0, 0, 0}};
+  if constexpr (DT != DYNAKV_F32) { const f4* p = (const f4*)(km_offset(v, u)->c + c * 8); o.lo = p[0]; o.hi = p[1]; }
+  return o;
+}
+// Sixteen lanes write centre j (lane c of them coordinates 8c .. 8c+7): the float32 table and, for 16-bit types, the
+// filter's terms of d = r_j - offset in A-operand order with -<offset, d> - |d|^2 / 2.
+template <int DT>
+__device__ inline void write_centre(const View& v, int u, int j, int c, const float (&r)[8], const OffsetPart& off, CentreNorms& cn) {
   float* R = unit_R(v, u);
   *(f4*)(R + r_index(j, c * 8)) = f4{r[0], r[1], r[2], r[3]};
   *(f4*)(R + r_index(j, c * 8 + 4)) = f4{r[4], r[5], r[6], r[7]};
@@ -100,22 +122,25 @@ __device__ inline void write_centre(const View& v, int u, int j, int c, const fl
     *(f4*)(row + 4) = f4{r[4], r[5], r[6], r[7]};
     constexpr int NT = kTerms<DT>;
     uint16_t bits[NT][8];
-    double nn = 0.0, rr = 0.0;
+    double nn = 0.0, rr = 0.0, cc = 0.0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      nn = fma((double)r[e], (double)r[e], nn);
-      float rem = r[e];
+      const double ce = (double)(e < 4 ? off.lo[e] : off.hi[e - 4]);
+      double rem = (double)r[e] - ce;
+      nn = fma(rem, rem, nn);
+      cc = fma(ce, rem, cc);
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        float part;
-        if constexpr (DT == DYNAKV_BF16) { const __bf16 b = (__bf16)rem; part = (float)b; bits[t][e] = __builtin_bit_cast(uint16_t, b); }
-        else { const _Float16 hh = (_Float16)rem; part = (float)hh; bits[t][e] = __builtin_bit_cast(uint16_t, hh); }
-        rem -= part;                                 // exact: part agrees with rem to half of its digits
+        double part;
+        if constexpr (DT == DYNAKV_BF16) { const __bf16 b = (__bf16)(float)rem; part = (double)(float)b; bits[t][e] = __builtin_bit_cast(uint16_t, b); }
+        else { const _Float16 hh = (_Float16)(float)rem; part = (double)(float)hh; bits[t][e] = __builtin_bit_cast(uint16_t, hh); }
+        rem -= part;
       }
-      rr = fma((double)rem, (double)rem, rr);
+      rr = fma(rem, rem, rr);
     }
     nn = row_sum_f64(nn);
     rr = row_sum_f64(rr);
+    cc = row_sum_f64(cc);
     // a centre that is not finite is nearest to no point: it enters the filter as a padding row does
     const bool finite = nn < __builtin_inf();
     uint16_t* A = v.kmA + (size_t)u * v.kmA_stride;
@@ -126,7 +151,7 @@ __device__ inline void write_centre(const View& v, int u, int j, int c, const fl
       w.z = bits[t][4] | ((uint32_t)bits[t][5] << 16); w.w = bits[t][6] | ((uint32_t)bits[t][7] << 16);
       *(uint4*)(A + kmA_index(NT, j, t, c * 8)) = finite ? w : uint4{0, 0, 0, 0};
     }
-    if (c == 0) v.hn[(size_t)u * km_pad(v.M0) + j] = finite ? (float)(-0.5 * nn) : kNoCentre;
+    if (c == 0) v.hn[(size_t)u * km_pad(v.M0) + j] = finite ? (float)(-0.5 * nn - cc) : kNoCentre;
     if (finite) {
       cn.r = fmaxf(cn.r, (float)sqrt(nn) * 1.000001f);
       cn.rho = fmaxf(cn.rho, (float)sqrt(rr) * 1.000001f);
@@ -151,8 +176,10 @@ __device__ inline void fold_norms(const View& v, int u, CentreNorms cn, int* sm)
 
 // ---- start --------------------------------------------------------------------------------------------------------
 // One workgroup per unit, first kernel of a build: clears the unit's error word and the k-means' own counters, then flags
-// initial positions that are out of range or given twice (the build still runs, with such a position clamped).
-__global__ __launch_bounds__(256) void kmeans_check_init_kernel(View v, int N0, const int* init_idx) {
+// initial positions that are out of range or given twice (the build still runs, with such a position clamped).  For 16-bit
+// types also the unit's offset: the mean of (up to 64 of) the initial centres, if it outweighs their spread about it.
+template <int DT>
+__global__ __launch_bounds__(256) void kmeans_check_init_kernel(View v, const void* X, int N0, const int* init_idx) {
   __shared__ unsigned seen[kMaxPrefill / 32];
   const int u = blockIdx.x, tid = threadIdx.x;
   for (int i = tid; i < kMaxPrefill / 32; i += 256) seen[i] = 0u;
@@ -168,6 +195,50 @@ __global__ __launch_bounds__(256) void kmeans_check_init_kernel(View v, int N0, 
     else if (atomicOr(&seen[p >> 5], 1u << (p & 31)) & (1u << (p & 31))) bad = true;
   }
   if (bad) atomicOr(&v.err[u], DYNAKV_ERR_INIT);
+  if constexpr (DT != DYNAKV_F32) {
+    __shared__ float part[16][kHeadDim];
+    __shared__ float s_sq[4], s_m2[2];
+    const int n = min(v.M0, 64), c = tid & 15;
+    float s[8] = {}, sq = 0.f;
+    for (int k = tid >> 4; k < n; k += 16) {
+      float x[8];
+      const int p = min(max(init_idx[(size_t)u * v.M0 + k], 0), N0 - 1);
+      load8(X, ((size_t)u * N0 + p) * kHeadDim + c * 8, DT, x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { s[e] += x[e]; sq = fmaf(x[e], x[e], sq); }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) part[tid >> 4][c * 8 + e] = s[e];
+    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+    if ((tid & 63) == 0) s_sq[tid >> 6] = sq;
+    __syncthreads();
+    float m = 0.f, m2 = 0.f;
+    if (tid < kHeadDim) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) m += part[k][tid];
+      m /= (float)n;
+      m2 = m * m;
+      for (int o = 32; o > 0; o >>= 1) m2 += __shfl_xor(m2, o);
+      if ((tid & 63) == 0) s_m2[tid >> 6] = m2;
+    }
+    __syncthreads();
+    m2 = s_m2[0] + s_m2[1];
+    const float mean_sq = (s_sq[0] + s_sq[1] + s_sq[2] + s_sq[3]) / (float)n;
+    const bool use = mean_sq < __builtin_inff() && m2 > 0.5f * mean_sq;       // (false for a NaN)
+    Offset* o = km_offset(v, u);
+    __syncthreads();                                     // every thread has read s_m2
+    if (tid < kHeadDim) {
+      const uint16_t b = use ? round_bits16(m, DT) : 0;
+      const float x = DT == DYNAKV_F16 ? f16_to_float(b) : bf16_to_float(b);
+      o->bits[tid] = b;
+      o->c[tid] = x;
+      float c2 = x * x;
+      for (int w = 32; w > 0; w >>= 1) c2 += __shfl_xor(c2, w);
+      if ((tid & 63) == 0) s_m2[tid >> 6] = c2;
+    }
+    __syncthreads();
+    if (tid == 0) o->norm = __builtin_sqrtf(s_m2[0] + s_m2[1]) * 1.0001f;
+  }
 }
 
 // Centre j = key at position init_idx[u][j]; the rows that pad the filter's table to whole chunks lose every comparison.
@@ -181,7 +252,7 @@ __global__ __launch_bounds__(256) void kmeans_start_kernel(View v, const void* X
     const int p = min(max(init_idx[(size_t)u * v.M0 + j], 0), N0 - 1);
     float r[8];
     load8(X, ((size_t)u * N0 + p) * kHeadDim + c * 8, DT, r);
-    write_centre<DT>(v, u, j, c, r, cn);
+    write_centre<DT>(v, u, j, c, r, load_offset<DT>(v, u, c), cn);
   } else if (DT != DYNAKV_F32 && j < km_pad(v.M0)) {
     uint16_t* A = v.kmA + (size_t)u * v.kmA_stride;
     for (int t = 0; t < kTerms<DT>; ++t) *(uint4*)(A + kmA_index(kTerms<DT>, j, t, c * 8)) = uint4{0, 0, 0, 0};
@@ -261,13 +332,13 @@ __global__ __launch_bounds__(256) void kmeans_assign_f64_kernel(View v, const vo
   if (live && q == 0) v.labels[(size_t)u * v.Ncap + i] = arg;
 }
 
-// c + the squares of a pair of 16-bit values, in float32.
+// c + the inner product of two pairs of 16-bit values, in float32.
 typedef _Float16 h2v __attribute__((ext_vector_type(2)));
 typedef __bf16 b2v __attribute__((ext_vector_type(2)));
 template <bool BF>
-__device__ __forceinline__ float dot2(uint32_t w, float c) {
-  if constexpr (BF) return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2v, w), __builtin_bit_cast(b2v, w), c, false);
-  else return __builtin_amdgcn_fdot2(__builtin_bit_cast(h2v, w), __builtin_bit_cast(h2v, w), c, false);
+__device__ __forceinline__ float dot2(uint32_t w, uint32_t y, float c) {
+  if constexpr (BF) return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2v, w), __builtin_bit_cast(b2v, y), c, false);
+  else return __builtin_amdgcn_fdot2(__builtin_bit_cast(h2v, w), __builtin_bit_cast(h2v, y), c, false);
 }
 
 // BYTES (4 or 16) from each lane's global address to LDS at base + lane * BYTES, with no detour through registers.  As an
@@ -283,16 +354,17 @@ __device__ __forceinline__ void load_to_lds(const void* src, void* base) {
 }
 
 // ---- assignment through the matrix cores --------------------------------------------------------------
-// z_ij = <x_i, r_j> - |r_j|^2/2 orders the centres like the squared distance.  The filter evaluates it with MFMA on
-// 16-bit operands: x is exact in its storage type, r_j is replaced by the sum of its 16-bit terms (one for float16, two
-// for bfloat16), accumulation is float32.  |error of z| <= eps_i:
-//   |x_i| max_j |r_j - terms|               what the terms leave of a centre (its exact norm is known)
-//   NT 2^-16 (|x_i| B + B^2 / 2)            accumulation of NT x 128 exact products onto -|r_j|^2/2, doubled
+// z_ij = <x_i, d_j> - <c, d_j> - |d_j|^2/2 with d_j = r_j - c, c the unit's offset (see Offset; mostly zero), orders the centres
+// like the squared distance.  The filter evaluates it with MFMA on 16-bit operands: x is exact in its storage type, d_j is
+// replaced by the sum of its 16-bit terms (one for float16, two for bfloat16), accumulation is float32.
+// |error of z| <= eps_i:
+//   |x_i| max_j |d_j - terms|               what the terms leave of a centre (its exact norm is known)
+//   NT 2^-16 ((|x_i| + |c|) B + B^2 / 2)    accumulation of NT x 128 exact products onto -<c, d_j> - |d_j|^2/2, doubled
 //   2^bits 2^-23 |z|                        the running best three carry the centre's number in their low mantissa bits
 //   1e-35                                   all of these where float32 has no digits left: products, squares of |x|^2 and
 //                                           z itself below 2^-126 (up to 128 of them), the number in a z of zero
-// B bounds the norm of every centre that can be the nearest: such a centre is no farther from x_i than the best one found,
-// whose distance follows from its z (and B <= max |r|).
+// B bounds |d_j| of every centre that can be the nearest: such a centre is no farther from x_i than the best one found,
+// whose distance follows from its z and |x_i - c| (and B <= max |d|).
 // A point whose best and second-best values are more than 2 eps_i apart has the same nearest centre in exact arithmetic.
 // If only the second lies within that distance, the two centres are compared in float64 by 16 lanes; if the third does too
 // (about one point in a thousand), the workgroup goes through all centres in float64.  Labels therefore equal the
@@ -311,8 +383,8 @@ constexpr int kAssignWaves = 4;
 // Nearest of all centres in float64 for NP points (xd: their coordinates in LDS; n of them count) by one wavefront of the
 // `share` that split the centres among them: lane = centre, NC centres per lane at once.  Every coordinate of a centre is
 // loaded once for NP points and every coordinate of a point read once for NC centres; the float64 pipe is what is left.
-// (One point at a time by the whole workgroup read the centres anew for each: where most points have three candidates,
-// e.g. 256 x 4096 float16 keys about a common offset of 16 times their spread x 256 centres, a build took 44.5 ms.)
+// (One point at a time by the whole workgroup read the centres anew for each: 64 units x 4096 float16 keys of 64 different
+// values x 256 centres, where every point has several equal candidates, 25.4 ms, now 16.)
 constexpr int kScanPoints = 4, kScanCentres = 2;
 // Wavefronts that share the centres of a batch of points; the others take further batches.
 __device__ __forceinline__ int scan_share(int M0, int nc) { return M0 <= 64 * nc ? 1 : M0 <= 128 * nc ? 2 : kAssignWaves; }
@@ -482,10 +554,24 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
     for (int ks = 0; ks < 8; ++ks) {
       const uint32_t ww[4] = {bx[t][ks].x, bx[t][ks].y, bx[t][ks].z, bx[t][ks].w};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) nn = dot2<BF>(ww[e], nn);
+      for (int e = 0; e < 4; ++e) nn = dot2<BF>(ww[e], ww[e], nn);
     }
     nn += __shfl_xor(nn, 32);
     xnorm[t] = __builtin_sqrtf(nn + 2e-36f) * 1.0001f;     // (128 squares below 2^-126 may be missing)
+  }
+  const float cnorm = km_offset(v, u)->norm;
+  float xc[2] = {0.f, 0.f};                                // <x, offset> of the two points
+  if (cnorm > 0.f) {                                       // workgroup-uniform
+    const uint16_t* cb = km_offset(v, u)->bits + h * 8;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const uint4 w = *(const uint4*)(cb + ks * 16);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        xc[t] = dot2<BF>(bx[t][ks].w, w.w, dot2<BF>(bx[t][ks].z, w.z, dot2<BF>(bx[t][ks].y, w.y, dot2<BF>(bx[t][ks].x, w.x, xc[t]))));
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) xc[t] += __shfl_xor(xc[t], 32);
   }
   if (first && !sums_order_free_by_type(DT, N0)) {         // the exponents of the unit's coordinates, once
     unsigned lo16 = 0xFFFFu, hi16 = 0u;                    // smallest (zeros left out, minus one) and largest magnitude bits
@@ -511,7 +597,7 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
     }
   }
   // the two halves of every point's centres; afterwards lane l speaks for point pbase + l
-  float pb = kLow, ps = kLow, pt3 = kLow, pn = 0.f;
+  float pb = kLow, ps = kLow, pt3 = kLow, pn = 0.f, pc = 0.f;
   int ib = 0, is = 0;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
@@ -532,15 +618,18 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
       is = u1 >= u2 ? n1 : n2;
       pt3 = fmaxf(fminf(u1, u2), fmaxf(third[t], o3));
       pn = xnorm[t];
+      pc = xc[t];
     }
   }
   const int pt = pbase + lane;
   const bool valid = pt < N0;
   const float rmax = v.rmax[2 * u], rho = v.rmax[2 * u + 1];
-  const float slack = (float)NT / 16384.0f * (pn * rmax + rmax * rmax) + 4.f * pn * rho;
-  const float B = fminf(rmax, pn + __builtin_sqrtf(fmaxf(pn * pn - 2.f * pb, 0.f) + slack));
-  const float eps = pn * rho * 1.0001f + (float)NT / 65536.0f * (pn * B + 0.5f * B * B) * 1.01f +
-                    (float)(1 << code_bits) * 1.2e-7f * fabsf(pb) + 1e-35f;
+  const float code_err = (float)(1 << code_bits) * 1.2e-7f * fabsf(pb);
+  // |x - offset|^2, not below: the norms are rounded up, the product errs by 128 * 2^-24 of theirs at most
+  const float y2 = fmaxf(pn * pn - 2.f * pc + cnorm * cnorm, 0.f) + 1e-4f * pn * cnorm;
+  const float slack = (float)NT / 16384.0f * ((pn + cnorm) * rmax + rmax * rmax) + 4.f * pn * rho + 4.f * code_err;
+  const float B = fminf(rmax, __builtin_sqrtf(y2) + __builtin_sqrtf(fmaxf(y2 - 2.f * pb, 0.f) + slack));
+  const float eps = pn * rho * 1.0001f + (float)NT / 65536.0f * ((pn + cnorm) * B + 0.5f * B * B) * 1.01f + code_err + 1e-35f;
   const bool near2 = valid && !(pb - ps > 2.f * eps);
   const bool near3 = near2 && !(pb - pt3 > 2.f * eps);
   int label = min(ib, v.M0 - 1);                           // (padding rows win where no value is finite; such a point is near3)
@@ -704,7 +793,8 @@ __global__ __launch_bounds__(1024) void kmeans_sort_kernel(View v, int N0) {
 // one load while the current 16 rows, all in flight at once, are added.  A cluster without members keeps its centre.
 // RB: rows in flight per lane.
 template <int DT, int RB = 16>
-__device__ inline void update_cluster(const View& v, const void* X, int N0, int u, int j, int c, int* counts, CentreNorms& cn) {
+__device__ inline void update_cluster(const View& v, const void* X, int N0, int u, int j, int c, int* counts, const OffsetPart& off,
+                                      CentreNorms& cn) {
   const int* koff = v.koff + (size_t)u * (v.Mcap + 1);
   const int* order = v.order + (size_t)u * v.Ncap;
   const int b = koff[j], e = koff[j + 1];
@@ -736,7 +826,7 @@ __device__ inline void update_cluster(const View& v, const void* X, int N0, int 
     float r[8];
 #pragma unroll
     for (int d = 0; d < 8; ++d) r[d] = (float)(s[d] / (double)(e - b));
-    write_centre<DT>(v, u, j, c, r, cn);
+    write_centre<DT>(v, u, j, c, r, off, cn);
   }
   if constexpr (DT != DYNAKV_F32) {
     double* S = km_sums(v, u) + (size_t)j * kHeadDim + c * 8;
@@ -752,7 +842,7 @@ __global__ __launch_bounds__(256) void kmeans_update_kernel(View v, const void* 
   const int u = blockIdx.y, j = blockIdx.x * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15;
   if (v.has_empty[u] && !last) return;                  // workgroup-uniform
   CentreNorms cn{0.f, 0.f};
-  if (j < v.M0) update_cluster<DT>(v, X, N0, u, j, c, km_counts(v, u, N0, which), cn);
+  if (j < v.M0) update_cluster<DT>(v, X, N0, u, j, c, km_counts(v, u, N0, which), load_offset<DT>(v, u, c), cn);
   if constexpr (DT != DYNAKV_F32) fold_norms(v, u, cn, sm);
 }
 
@@ -773,6 +863,8 @@ __global__ __launch_bounds__(256) void kmeans_changed_kernel(View v, const void*
   const Changed* chg = km_changed(v, u);
   const int* was = km_counts(v, u, N0, which ^ 1);
   int* now = km_counts(v, u, N0, which);
+  const int c = tid & 15;
+  const OffsetPart off = load_offset<DT>(v, u, c);
   for (int i = tid; i < v.M0; i += 256) delta[i] = 0;
   if (tid < 16) nq[tid] = 0;
   if (tid == 0) any_empty = 0;
@@ -801,7 +893,7 @@ __global__ __launch_bounds__(256) void kmeans_changed_kernel(View v, const void*
       return;
     }
   }
-  const int k = tid >> 4, j = j0 + k, c = tid & 15;
+  const int k = tid >> 4, j = j0 + k;
   CentreNorms cn{0.f, 0.f};
   if (j < v.M0) {
     const int m = was[j] + delta[j], q = nq[k];
@@ -844,7 +936,7 @@ __global__ __launch_bounds__(256) void kmeans_changed_kernel(View v, const void*
         float r[8];
 #pragma unroll
         for (int d = 0; d < 8; ++d) r[d] = (float)(s[d] / (double)m);
-        write_centre<DT>(v, u, j, c, r, cn);
+        write_centre<DT>(v, u, j, c, r, off, cn);
       }
     }
   }
@@ -897,8 +989,9 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
     __syncthreads();
   }
   CentreNorms cn{0.f, 0.f};
+  const OffsetPart off = load_offset<DT>(v, u, c);
   int* counts = km_counts(v, u, N0, which);
-  for (int j = tid >> 4; j < v.M0; j += 64) update_cluster<DT, DT == DYNAKV_F32 ? 8 : 16>(v, X, N0, u, j, c, counts, cn);
+  for (int j = tid >> 4; j < v.M0; j += 64) update_cluster<DT, DT == DYNAKV_F32 ? 8 : 16>(v, X, N0, u, j, c, counts, off, cn);
   __syncthreads();
   if (reseed) {
     const int lane = tid & 63, w = tid >> 6;
@@ -925,7 +1018,7 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
       if (tid < 16) {
         float r[8];
         load8(X, ((size_t)u * N0 + bi) * kHeadDim + c * 8, DT, r);
-        write_centre<DT>(v, u, j, c, r, cn);
+        write_centre<DT>(v, u, j, c, r, off, cn);
       }
       __syncthreads();                                  // every thread has read sv / si and this round's distances
       if (tid == 0) dist[bi] = -2.0;                    // taken
@@ -1073,7 +1166,7 @@ __global__ __launch_bounds__(256) void layout_copy_kernel(View v, const void* K,
 template <int DT>
 static void launch_kmeans(const View& v, const void* K, int N0, const int* init_idx, int iters, hipStream_t st) {
   const dim3 gcl((v.M0 + 15) / 16, v.U);
-  kmeans_check_init_kernel<<<v.U, 256, 0, st>>>(v, N0, init_idx);
+  kmeans_check_init_kernel<DT><<<v.U, 256, 0, st>>>(v, K, N0, init_idx);
   kmeans_start_kernel<DT><<<dim3(((DT == DYNAKV_F32 ? v.M0 : km_pad(v.M0)) + 15) / 16, v.U), 256, 0, st>>>(v, K, N0, init_idx);
   for (int it = 0; it < iters; ++it) {
     const int first = it == 0, last = it + 1 == iters, slot = it & 1, which = it & 1;

@@ -720,14 +720,18 @@ def test_prefill_with_keys_that_are_not_finite(dtype, bad):
         assert not np.isfinite(c[0]).all() and np.isfinite(c[1:]).all()
 
 
-@pytest.mark.parametrize("dtype,M0,N0", [("f16", 60, 700), ("f16", 150, 1000), ("bf16", 129, 513), ("f16", 300, 1000), ("bf16", 700, 1500)])
-def test_prefill_where_most_keys_have_many_candidates(dtype, M0, N0):
-    """Keys about a common offset far beyond their spread, which the 16-bit filter cannot tell apart: nearly every
-    key is decided among all centres in float64, with one, two or four wavefronts to a batch of keys."""
+@pytest.mark.parametrize("dtype,M0,N0,offset", [
+    ("f16", 60, 700, 2), ("f16", 150, 1000, 200), ("bf16", 129, 513, 30), ("f16", 300, 1000, 15), ("bf16", 700, 1500, 200), ("f16", 5, 400, 8000)])
+def test_prefill_where_most_keys_have_many_candidates(dtype, M0, N0, offset):
+    """Keys about a common offset far beyond their spread, which the 16-bit filter hardly tells apart, and keys of a few
+    values each, where every key has several equal centres: such keys are decided among all centres in float64, with one,
+    two or four wavefronts to a batch of them."""
     s = WorkloadSpec("offset", dtype, 2, 2, N0, 4, M0, 64, 4, 0.05, var_alpha=1.5, size_factor=0.0, n_outliers=0, seed=M0)
     w = generate(s)
-    off = 200.0 * np.random.default_rng(1).standard_normal((2, 1, 128)).astype(np.float32)
-    w["K0"] = torch.from_numpy(w["K0"] + off).to(binding.TORCH_DTYPES[dtype]).float().numpy()
+    rng = np.random.default_rng(1)
+    w["K0"][0] += offset * rng.standard_normal((1, 128)).astype(np.float32)
+    w["K0"][1] = w["K0"][1, :M0 // 4][rng.integers(0, M0 // 4, N0)]
+    w["K0"] = torch.from_numpy(w["K0"]).to(binding.TORCH_DTYPES[dtype]).float().numpy()
     ix, o = make_pair(s, 2, kmeans_iters=4)
     ix.dynakv_build_index(to_dev(w["K0"], dtype), to_dev(w["V0"], dtype), torch.from_numpy(w["init_idx"]).to(DEV))
     o.build_index(w["K0"], w["V0"], w["init_idx"])
