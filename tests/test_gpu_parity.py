@@ -662,6 +662,7 @@ def test_prefill_with_coinciding_centres(dtype):
 @pytest.mark.parametrize("dtype,N0,M0", [
     ("f16", 257, 1), ("f16", 300, 31), ("bf16", 321, 33), ("f16", 4100, 64), ("bf16", 1025, 65), ("f32", 130, 33),
     ("f16", 3000, 2),          # hundreds of keys move from one cluster to the other at once
+    ("bf16", 5000, 17),        # and from many clusters to many
     ("f16", 9000, 2100),       # more than 8192 float16 keys: whether sums may follow the moves depends on their range
     ("bf16", 8300, 8192)])     # the most centres: counts of the sort for four wavefronts only
 def test_prefill_partition_at_the_edges_of_tiles_and_chunks(dtype, N0, M0):
