@@ -724,11 +724,11 @@ __global__ __launch_bounds__(kAssignWaves * 64, 4) void kmeans_assign_kernel(Vie
 // (v.order) and the start of every cluster (v.koff).  Each of the first nw wavefronts counts a contiguous range of
 // positions, one prefix sum over (cluster, wavefront) turns the counts into places, and each wavefront hands them out in
 // order, 64 positions at a time: the lanes with equal labels find each other by one ballot per bit of the label.
-// cnt: kSortCounters ints of LDS; sm: 64.  (A bitonic sort of (label, position) in LDS took 53 us for 4096 keys and
+// cnt: kSortCounters ints of LDS; sm: 64.  Returns (to every thread) whether some cluster has no member.  (A bitonic sort of (label, position) in LDS took 53 us for 4096 keys and
 // 212 us for 16384; this takes 8 and 25 us.)
 constexpr int kSortCounters = 32768;
 static_assert(kMaxInitClusters * 4 <= kSortCounters, "at least four wavefronts hold counters");
-__device__ inline void sort_members(const View& v, int u, int N0, int* cnt, int* sm) {
+__device__ inline bool sort_members(const View& v, int u, int N0, int* cnt, int* sm) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, M0 = v.M0;
   int nw = 16;
   while (nw * M0 > kSortCounters) nw >>= 1;
@@ -757,9 +757,8 @@ __device__ inline void sort_members(const View& v, int u, int N0, int* cnt, int*
     koff[j] = run;
     for (int w = 0; w < nw; ++w) { const int n = cnt[w * M0 + j]; cnt[w * M0 + j] = run; run += n; }
   }
-  if (tid == 0) { koff[M0] = N0; v.has_empty[u] = 0; }
-  __syncthreads();
-  if (empty) v.has_empty[u] = 1;
+  if (tid == 0) koff[M0] = N0;
+  const bool any_empty = __syncthreads_or(empty);
   int bits = 0;
   while ((1 << bits) < M0) ++bits;
   for (int i0 = b; i0 < e; i0 += 64) {                 // (no barrier inside: ranges differ from wavefront to wavefront)
@@ -780,11 +779,13 @@ __device__ inline void sort_members(const View& v, int u, int N0, int* cnt, int*
     asm volatile("" ::: "memory");
   }
   __syncthreads();
+  return any_empty;
 }
 __global__ __launch_bounds__(1024) void kmeans_sort_kernel(View v, int N0) {
   __shared__ int cnt[kSortCounters];
   __shared__ int sm[64];
-  sort_members(v, blockIdx.x, N0, cnt, sm);
+  const bool any_empty = sort_members(v, blockIdx.x, N0, cnt, sm);
+  if (threadIdx.x == 0) v.has_empty[blockIdx.x] = any_empty;
 }
 
 // ---- update ---------------------------------------------------------------------------------------------
@@ -957,10 +958,13 @@ __global__ __launch_bounds__(256) void kmeans_changed_kernel(View v, const void*
   fold_norms(v, u, cn, sm);
 }
 
-// What the parallel kernels leave, one workgroup of 1024 per unit; most launches find nothing to do.
-//   units with an empty cluster: every empty cluster, in ascending id, takes the not-yet-taken point that is farthest from
-//     its own (old) centre, ties to the lowest position; the others get their sums formed anew
-//   units whose sums are not order-free, in every iteration after the first: all sums formed anew
+// What the parallel kernels leave, in workgroups of 1024; most launches find nothing to do.
+//   units with an empty cluster, one workgroup each: every empty cluster, in ascending id, takes the not-yet-taken point that is
+//     farthest from its own (old) centre, ties to the lowest position; the others get their sums formed anew
+//   units whose sums are not order-free, in every iteration after the first: all sums formed anew.  Each of the unit's
+//     gridDim.y workgroups sorts the labels for itself (all write the same order) and takes its share of the clusters
+// (one bfloat16 unit of 16384 keys x 8192 centres that is not order-free: 850 us by one workgroup, 130 by sixteen).
+constexpr int kSlowShare = 512;                          // clusters that warrant a workgroup of their own
 template <int DT>
 __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X, int N0, int which, int first, int last) {
   __shared__ int cnt[kSortCounters];
@@ -969,9 +973,11 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
   __shared__ int si[16];
   const int u = blockIdx.x, tid = threadIdx.x, c = tid & 15;
   const bool sorted = first || DT == DYNAKV_F32;         // this iteration's kmeans_sort_kernel has run
-  if (!(v.has_empty[u] && !last) && !(!sorted && !sums_order_free(v, u, N0))) return;       // workgroup-uniform
-  if (!sorted) sort_members(v, u, N0, cnt, sm);
-  const bool reseed = v.has_empty[u] && !last;
+  const bool anew = !sorted && !sums_order_free(v, u, N0);
+  if (!anew && (blockIdx.y > 0 || last || !v.has_empty[u])) return;       // workgroup-uniform
+  const bool any_empty = sorted ? true : sort_members(v, u, N0, cnt, sm);
+  const bool reseed = any_empty && !last;
+  if (reseed && blockIdx.y > 0) return;
   const int* lab = v.labels + (size_t)u * v.Ncap;
   const int* koff = v.koff + (size_t)u * (v.Mcap + 1);
   double* dist = v.dist + (size_t)u * v.Ncap;
@@ -1003,9 +1009,10 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
     __syncthreads();
   }
   CentreNorms cn{0.f, 0.f};
-  const OffsetPart off = load_offset<DT>(v, u, c);
   int* counts = km_counts(v, u, N0, which);
-  for (int j = tid >> 4; j < v.M0; j += 64) update_cluster<DT, DT == DYNAKV_F32 ? 8 : 16>(v, X, N0, u, j, c, counts, off, cn);
+  const int share = reseed ? 1 : gridDim.y, mine = reseed ? 0 : blockIdx.y;
+  for (int j = mine * 64 + (tid >> 4); j < v.M0; j += share * 64)
+    update_cluster<DT, DT == DYNAKV_F32 ? 8 : 16>(v, X, N0, u, j, c, counts, load_offset<DT>(v, u, c), cn);
   __syncthreads();
   if (reseed) {
     const int lane = tid & 63, w = tid >> 6;
@@ -1032,7 +1039,7 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
       if (tid < 16) {
         float r[8];
         load8(X, ((size_t)u * N0 + bi) * kHeadDim + c * 8, DT, r);
-        write_centre<DT>(v, u, j, c, r, off, cn);
+        write_centre<DT>(v, u, j, c, r, load_offset<DT>(v, u, c), cn);
       }
       __syncthreads();                                  // every thread has read sv / si and this round's distances
       if (tid == 0) dist[bi] = -2.0;                    // taken
@@ -1040,8 +1047,7 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
     }
   }
   if constexpr (DT != DYNAKV_F32) fold_norms(v, u, cn, sm);
-  __syncthreads();
-  if (tid == 0) v.has_empty[u] = 0;
+  if (blockIdx.y == 0 && tid == 0) v.has_empty[u] = 0;
 }
 
 // dist[i] = squared distance of point i to the (updated) centre of its own cluster.  Sixteen lanes per point, one
@@ -1200,7 +1206,7 @@ static void launch_kmeans(const View& v, const void* K, int N0, const int* init_
     }
     const bool sorted = first || DT == DYNAKV_F32;
     if (!last || (!sorted && !sums_order_free_by_type(DT, N0)))
-      kmeans_slow_kernel<DT><<<v.U, 1024, 0, st>>>(v, K, N0, which, first, last);
+      kmeans_slow_kernel<DT><<<dim3(v.U, min(16, (v.M0 + kSlowShare - 1) / kSlowShare)), 1024, 0, st>>>(v, K, N0, which, first, last);
   }
   if (DT != DYNAKV_F32 && iters > 1) kmeans_sort_kernel<<<v.U, 1024, 0, st>>>(v, N0);
 }

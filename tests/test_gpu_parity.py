@@ -721,6 +721,32 @@ def test_prefill_with_keys_that_are_not_finite(dtype, bad):
         assert not np.isfinite(c[0]).all() and np.isfinite(c[1:]).all()
 
 
+@pytest.mark.parametrize("dtype,M0,N0", [("bf16", 65, 700), ("bf16", 513, 1200), ("bf16", 1100, 2000), ("f16", 600, 9000), ("f32", 40, 300)])
+@pytest.mark.parametrize("distinct", [0, 30])
+def test_prefill_forms_all_sums_anew_and_reseeds(dtype, M0, N0, distinct):
+    """Units whose sums are not order-free (one coordinate at the end of the type's range; more than 8192 float16 keys need
+    that check), with one and with several workgroups to a unit; with few distinct keys most clusters run empty in every
+    iteration and choose one after the other, more of them than there are keys at any distance."""
+    s = WorkloadSpec("anew", dtype, 2, 2, N0, 4, M0, 64, 4, 0.05, var_alpha=1.5, size_factor=0.0, seed=M0 + distinct)
+    w = generate(s)
+    if distinct:
+        w["K0"][1] = w["K0"][1, np.random.default_rng(2).integers(0, distinct, N0)]
+    w["K0"][:, 3, 17] = 2.0 ** -24 if dtype == "f16" else 1e-30
+    w["K0"][0, 9] *= 40.0
+    w["K0"] = torch.from_numpy(w["K0"]).to(binding.TORCH_DTYPES[dtype]).float().numpy()
+    ix, o = make_pair(s, 2, kmeans_iters=3 if N0 > 5000 else 5)
+    ix.dynakv_build_index(to_dev(w["K0"], dtype), to_dev(w["V0"], dtype), torch.from_numpy(w["init_idx"]).to(DEV))
+    o.build_index(w["K0"], w["V0"], w["init_idx"])
+    st = ix.dynakv_export_state(["offsets", "members", "centroids", "error"])
+    assert not st["error"].any()
+    for u in range(2):
+        moff, mem = o.members(u)
+        np.testing.assert_array_equal(st["offsets"][u, :M0 + 1].numpy(), moff)
+        np.testing.assert_array_equal(st["members"][u, :N0].numpy(), mem)
+        # sums of the same numbers in the same order, rounded to float32 once
+        np.testing.assert_allclose(st["centroids"][u, :M0].numpy(), o.clusters(u)["centroids"], rtol=1.2e-7, atol=0)
+
+
 @pytest.mark.parametrize("dtype,M0,N0,offset", [
     ("f16", 60, 700, 2), ("f16", 150, 1000, 200), ("bf16", 129, 513, 30), ("f16", 300, 1000, 15), ("bf16", 700, 1500, 200), ("f16", 5, 400, 8000)])
 def test_prefill_where_most_keys_have_many_candidates(dtype, M0, N0, offset):
