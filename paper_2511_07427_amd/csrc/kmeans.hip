@@ -958,19 +958,40 @@ __global__ __launch_bounds__(256) void kmeans_changed_kernel(View v, const void*
   fold_norms(v, u, cn, sm);
 }
 
+// Largest (value, index) of a wavefront, lowest index among equal values, index < 0: none.  Every lane of the last row gets it
+// (ROW: every lane of a row gets its row's).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ void far_step(double& val, int& idx) {
+  const int lo = dpp_or<CTRL, ROWS>(__double2loint(val), __double2loint(val)), hi = dpp_or<CTRL, ROWS>(__double2hiint(val), __double2hiint(val));
+  const int oi = dpp_or<CTRL, ROWS>(idx, idx);
+  const double ov = __hiloint2double(hi, lo);
+  if (oi >= 0 && (idx < 0 || ov > val || (ov == val && oi < idx))) { val = ov; idx = oi; }
+}
+template <bool ROW>
+__device__ __forceinline__ void far_reduce(double& val, int& idx) {
+  far_step<kDppXor1, 0xF>(val, idx);
+  far_step<kDppXor2, 0xF>(val, idx);
+  far_step<kDppHalfMirror, 0xF>(val, idx);
+  far_step<kDppMirror, 0xF>(val, idx);
+  if constexpr (!ROW) { far_step<kDppBcast15, 0xA>(val, idx); far_step<kDppBcast31, 0xC>(val, idx); }
+}
+
 // What the parallel kernels leave, in workgroups of 1024; most launches find nothing to do.
 //   units with an empty cluster, one workgroup each: every empty cluster, in ascending id, takes the not-yet-taken point that is
 //     farthest from its own (old) centre, ties to the lowest position; the others get their sums formed anew
 //   units whose sums are not order-free, in every iteration after the first: all sums formed anew.  Each of the unit's
 //     gridDim.y workgroups sorts the labels for itself (all write the same order) and takes its share of the clusters
-// (one bfloat16 unit of 16384 keys x 8192 centres that is not order-free: 850 us by one workgroup, 130 by sixteen).
+// The points' distances stay in registers while the empty clusters choose, and their centres are written together afterwards:
+// with some 200 empty clusters in each of ten iterations (2 units x 4096 float16 keys of 300 values x 512 centres) a launch
+// took 1180 us when every choice wrote its centre and read all distances again, now 610.  One bfloat16 unit of 16384 keys x
+// 8192 centres that is not order-free: 850 us by one workgroup, 130 by sixteen.
 constexpr int kSlowShare = 512;                          // clusters that warrant a workgroup of their own
 template <int DT>
 __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X, int N0, int which, int first, int last) {
   __shared__ int cnt[kSortCounters];
   __shared__ int sm[64];
-  __shared__ double sv[16];
-  __shared__ int si[16];
+  __shared__ double sv[2][16];
+  __shared__ int si[2][16];
   const int u = blockIdx.x, tid = threadIdx.x, c = tid & 15;
   const bool sorted = first || DT == DYNAKV_F32;         // this iteration's kmeans_sort_kernel has run
   const bool anew = !sorted && !sums_order_free(v, u, N0);
@@ -1013,37 +1034,48 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
   const int share = reseed ? 1 : gridDim.y, mine = reseed ? 0 : blockIdx.y;
   for (int j = mine * 64 + (tid >> 4); j < v.M0; j += share * 64)
     update_cluster<DT, DT == DYNAKV_F32 ? 8 : 16>(v, X, N0, u, j, c, counts, load_offset<DT>(v, u, c), cn);
-  __syncthreads();
   if (reseed) {
     const int lane = tid & 63, w = tid >> 6;
-    for (int j = 0; j < v.M0; ++j) {
-      if (koff[j + 1] != koff[j]) continue;              // uniform across the block
+    int* const ids = cnt;                                // empty clusters, ascending
+    int* const pick = cnt + kMaxInitClusters;            // the points they take
+    const int R = (v.M0 + 1023) / 1024;
+    int mine_empty = 0, n;
+    for (int k = 0; k < R; ++k) {
+      const int j = tid * R + k;
+      mine_empty += j < v.M0 && koff[j + 1] == koff[j];
+    }
+    int at = block_excl_scan(mine_empty, sm, n);
+    for (int k = 0; k < R; ++k) {
+      const int j = tid * R + k;
+      if (j < v.M0 && koff[j + 1] == koff[j]) ids[at++] = j;
+    }
+    constexpr int kHeld = kMaxPrefill / 1024;
+    double d[kHeld];                                     // points tid, tid + 1024, ..
+#pragma unroll
+    for (int k = 0; k < kHeld; ++k) d[k] = tid + 1024 * k < N0 ? dist[tid + 1024 * k] : -2.0;
+    int taken = 0;
+    for (; taken < n; ++taken) {
       double bv = -1.0;
       int bi = -1;
-      for (int i = tid; i < N0; i += 1024) {
-        const double t = dist[i];
-        if (t > bv) { bv = t; bi = i; }                 // ascending i per thread: the first maximum stays
-      }
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const double ov = __shfl_xor(bv, o);
-        const int oi = __shfl_xor(bi, o);
-        if (oi >= 0 && (bi < 0 || ov > bv || (ov == bv && oi < bi))) { bv = ov; bi = oi; }
-      }
-      if (lane == 0) { sv[w] = bv; si[w] = bi; }
-      __syncthreads();
-      bv = sv[0]; bi = si[0];
-      for (int k = 1; k < 16; ++k)
-        if (si[k] >= 0 && (bi < 0 || sv[k] > bv || (sv[k] == bv && si[k] < bi))) { bv = sv[k]; bi = si[k]; }
-      if (bi < 0) break;                                // every point already taken
-      if (tid < 16) {
-        float r[8];
-        load8(X, ((size_t)u * N0 + bi) * kHeadDim + c * 8, DT, r);
-        write_centre<DT>(v, u, j, c, r, load_offset<DT>(v, u, c), cn);
-      }
-      __syncthreads();                                  // every thread has read sv / si and this round's distances
-      if (tid == 0) dist[bi] = -2.0;                    // taken
-      __syncthreads();
+      for (int k = 0; k < kHeld; ++k)
+        if (d[k] > bv) { bv = d[k]; bi = tid + 1024 * k; }          // ascending: the first maximum stays
+      far_reduce<false>(bv, bi);
+      if (lane == 63) { sv[taken & 1][w] = bv; si[taken & 1][w] = bi; }
+      lds_barrier();                                     // (two places in turn: one barrier per choice)
+      bv = sv[taken & 1][lane & 15]; bi = si[taken & 1][lane & 15];
+      far_reduce<true>(bv, bi);
+      if (bi < 0) break;                                 // every point already taken (the same in every thread)
+#pragma unroll
+      for (int k = 0; k < kHeld; ++k)
+        if (bi == tid + 1024 * k) d[k] = -2.0;
+      if (tid == 0) pick[taken] = bi;
+    }
+    __syncthreads();
+    for (int e = tid >> 4; e < taken; e += 64) {
+      float r[8];
+      load8(X, ((size_t)u * N0 + pick[e]) * kHeadDim + c * 8, DT, r);
+      write_centre<DT>(v, u, ids[e], c, r, load_offset<DT>(v, u, c), cn);
     }
   }
   if constexpr (DT != DYNAKV_F32) fold_norms(v, u, cn, sm);
