@@ -866,7 +866,7 @@ def test_timing_aid_brackets_an_even_sample_of_the_launches():
 @pytest.mark.parametrize("dtype,N0,M0,Mcap", [("f16", 1501, 3, 67), ("f32", 700, 65, 65), ("bf16", 333, 333, 9000)])
 def test_snapshot_round_trip(dtype, N0, M0, Mcap):
     """Export, import into a second index and export again: clusters of many pages (chains past the inline page table),
-    capacities that are no multiple of a table tile, more clusters than one round of the prefix sum takes."""
+    capacities that are no multiple of a table tile, far more slots than clusters."""
     s = WorkloadSpec("snap", dtype, 3, 2, N0, 4, M0, 256, 6, 0.05, var_alpha=1.5, size_factor=0.0, seed=99 + N0)
     w = generate(s)
     a, _ = make_pair(s, 3, max_clusters=Mcap, kmeans_iters=2)
@@ -878,14 +878,66 @@ def test_snapshot_round_trip(dtype, N0, M0, Mcap):
     y = b.dynakv_export_state(binding.IMPORT_FIELDS + ("error",), to_cpu=False)
     assert int(y["error"].abs().sum()) == 0
     for k in x:
-        if k == "selected":                      # past the active set the snapshot says -1, an import leaves what was there
-            continue
         assert torch.equal(x[k], y[k]), k
     K = to_dev(w["K0"], dtype)
     for u in range(3):
         m = x["members"][u, :N0].long()
         assert torch.equal(torch.sort(m).values, torch.arange(N0, device=DEV))
         assert torch.equal(x["keys"][u, :N0], K[u])
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+def test_snapshot_and_retrieval_of_many_clusters(dtype):
+    """More clusters than one round of the snapshots' prefix sums (8192) and one trip of the selection's passes over all
+    scores (16384) take: the snapshot comes out of the index as it went in, and retrievals are the oracle's."""
+    U, N, Mcap, Ncap, Ms = 2, 41003, 21003, 41010, (20001, 8193)
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    rnd = lambda *a: torch.randn(*a, generator=gen, device=DEV)  # noqa: E731
+    K, V = rnd(U, Ncap, 128).to(binding.TORCH_DTYPES[dtype]), rnd(U, Ncap, 128).to(binding.TORCH_DTYPES[dtype])
+    K[:, N:], V[:, N:] = 0, 0
+    i32 = lambda *a: torch.zeros(*a, dtype=torch.int32, device=DEV)  # noqa: E731
+    x = dict(n_clusters=torch.tensor(Ms, dtype=torch.int32, device=DEV), n_tokens=torch.full((U,), N, dtype=torch.int32, device=DEV),
+             tau=torch.tensor([1.5, 2.5], dtype=torch.float64, device=DEV), centroids=torch.zeros(U, Mcap, 128, device=DEV),
+             size=i32(U, Mcap), buffered=i32(U, Mcap), flag=i32(U, Mcap), m2=torch.zeros(U, Mcap, dtype=torch.float64, device=DEV),
+             offsets=i32(U, Mcap + 1), members=i32(U, Ncap), n_selected=i32(U), selected=torch.full((U, Mcap), -1, dtype=torch.int32, device=DEV),
+             keys=K, values=V)
+    for u, M in enumerate(Ms):
+        label = torch.cat([torch.arange(M, device=DEV), torch.randint(0, M, (N - M,), generator=gen, device=DEV)])
+        label = label[torch.randperm(N, generator=gen, device=DEV)]
+        order = torch.argsort(label, stable=True)
+        stored = torch.bincount(label, minlength=M).int()
+        flag = (torch.arange(M, device=DEV) % 977 == 5).int()
+        x["flag"][u, :M] = flag
+        x["buffered"][u, :M] = torch.where((flag > 0) & (stored > 1), torch.ones_like(stored), torch.zeros_like(stored))
+        x["size"][u, :M] = stored - x["buffered"][u, :M]
+        x["m2"][u, :M] = torch.rand(M, generator=gen, device=DEV).double()
+        x["offsets"][u, 1:M + 1] = stored.cumsum(0).int()
+        x["offsets"][u, M + 1:] = N
+        x["members"][u, :N] = order.int()
+        x["centroids"][u, :M] = torch.zeros(M, 128, device=DEV).index_add_(0, label, K[u, :N].float()) / stored[:, None]
+        x["n_selected"][u] = 3000
+        x["selected"][u, :3000] = torch.randperm(M, generator=gen, device=DEV)[:3000].int()
+    s = WorkloadSpec("many", dtype, U, 4, N, 7, 8, 2500, 8, 0.05, var_alpha=1.5, size_factor=0.0)
+    ix, o = make_pair(s, U, max_tokens=Ncap, max_clusters=Mcap)
+    ix.dynakv_import_state(x)
+    y = ix.dynakv_export_state(binding.IMPORT_FIELDS + ("error",), to_cpu=False)
+    assert not y["error"].any()
+    for k in x:
+        assert torch.equal(x[k], y[k]), k
+    tally = Tally()
+    parity.resync(ix, o, None, {0, 1}, tally)
+    out, lse = torch.empty(U, 4, 128, device=DEV), torch.empty(U, 4, device=DEV)
+    for t, budget in enumerate((1, 60, 2500, 4900)):
+        Q = K[:, 100 * t, None].float() + 0.5 * rnd(U, 4, 128)
+        Qs = Q.to(binding.TORCH_DTYPES[dtype])
+        Qn = Qs.float().cpu().numpy()
+        ix.dynakv_retrieve_attend(Qs.contiguous(), budget, out, lse)
+        oo, ol = o.retrieve_attend(Qn, budget)
+        dirty = compare_retrieval(ix, o, tally, "budget %d" % budget, Q=Qn, budget=budget)
+        keep = [u for u in range(U) if u not in dirty]
+        check_attention(out.cpu().numpy()[keep], lse.cpu().numpy()[keep], oo[keep], ol[keep], "budget %d" % budget)
+    assert not ix.dynakv_export_state(["error"])["error"].any()
+    say("many clusters", dtype, dict(tally))
 
 
 def test_snapshot_arrays_need_their_element_alignment_only():
