@@ -867,20 +867,26 @@ __global__ __launch_bounds__(1024) void select_kernel(View v, const void* Q, int
   if constexpr (!BIG) {
     int Mpad = 2;
     while (Mpad < M) Mpad <<= 1;
-    // eight of each in flight, and none past the last cluster: a table of a few dozen clusters is one load of each
-    for (int i0 = tid; i0 < Mpad; i0 += 8 * 1024) {
-      float sc8[8];
-      int sz8[8];
+    // eight of each in flight (loads past the last cluster repeat it: without a branch around each they overlap; 128 units of
+    // 7300 clusters 0.7 % of a step faster than with one); a table that one of each per thread covers is read by just that
+    if (M <= 1024) {
+      if (tid < Mpad) skey_[tid] = tid < M ? orderable(v.score[(size_t)u * v.Mcap + tid]) : 0u;
+      if (tid < M) ssz_[tid] = v.csz[(size_t)u * v.Mcap + tid];
+    } else {
+      for (int i0 = tid; i0 < Mpad; i0 += 8 * 1024) {
+        float sc8[8];
+        int sz8[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int i = i0 + k * 1024;
-        if (i < M) { sc8[k] = v.score[(size_t)u * v.Mcap + i]; sz8[k] = v.csz[(size_t)u * v.Mcap + i]; }
-      }
+        for (int k = 0; k < 8; ++k) {
+          const size_t i = (size_t)u * v.Mcap + min(i0 + k * 1024, M - 1);
+          sc8[k] = v.score[i]; sz8[k] = v.csz[i];
+        }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int i = i0 + k * 1024;
-        if (i < M) { skey_[i] = orderable(sc8[k]); ssz_[i] = sz8[k]; }
-        else if (i < Mpad) skey_[i] = 0u;
+        for (int k = 0; k < 8; ++k) {
+          const int i = i0 + k * 1024;
+          if (i < Mpad) skey_[i] = i < M ? orderable(sc8[k]) : 0u;
+          if (i < M) ssz_[i] = sz8[k];
+        }
       }
     }
     for (int i = tid; i < kSelectLds / 32; i += 1024) selbits_[i] = 0u;
