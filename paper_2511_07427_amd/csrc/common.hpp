@@ -170,10 +170,12 @@ __device__ inline void store_centroid(const View& v, int u, int j, int d, float 
 }
 
 // ---- the fixed summation order ----------------------------------------------------------------------
-// Every float64 sum over the 128 coordinates runs in one order: blocks of 8 consecutive coordinates are
-// accumulated left to right from zero (one fused multiply-add per term), and the 16 block sums are added left
-// to right.  Dependency chains stay short, and the value is the same whether one lane owns the whole sum or 16
-// lanes own one block each.
+// Float64 sums over the 128 coordinates run in one order wherever several pieces of code decide about the same value (the
+// k-means' distances, the scans of the float32 means, the workgroup path of a split, UpdateVar by a workgroup): blocks of 8
+// consecutive coordinates are accumulated left to right from zero (one fused multiply-add per term), and the 16 block sums are
+// added left to right.  Dependency chains stay short, and the value is the same whether one lane owns the whole sum or 16
+// lanes own one block each.  (The candidates of the 16-bit search copy that are re-scored in float64, UpdateVar by one
+// wavefront and the splits decided by one wavefront have orders of their own, each the same in every launch.)
 
 // One thread: block_sum(k) returns the sum of block k (k = 0..15, called in ascending k).
 template <class F>

@@ -9,9 +9,11 @@
 //
 // One iteration of a 16-bit type is two launches that matter: the assignment, which reads every key once, and the
 // update, which reads the keys of the points that changed their cluster.  256 units x 4096 float16 keys x 256 centres:
-// assignment 115 us, update 35 us, where nine launches that formed every sum anew, checked near-ties in a kernel of their
-// own and split the centres into two 16-bit terms took 320 us; the whole build 4.07 -> 2.57 ms (128 x 8192 x 512: 5.17 ->
-// 3.40 ms; 8 x 16384 x 2048 bfloat16: 3.62 -> 2.52 ms).
+// assignment 116 us, update 37 us, where nine launches that formed every sum anew, checked near-ties in a kernel of their
+// own and split the centres into two 16-bit terms took 320 us; build and export of the partition 4.12 -> 2.56 ms (128 x 8192 x
+// 512: 5.21 -> 3.17 ms; 8 x 16384 x 2048 bfloat16: 3.72 -> 2.16 ms).  How many points the float64 decisions take depends on the
+// keys; what is slower than on the mixture of these figures is given where it is handled (Offset, scan_centres,
+// kmeans_changed_kernel, kmeans_slow_kernel).
 #include "common.hpp"
 
 namespace dynakv {
@@ -373,7 +375,8 @@ __device__ __forceinline__ void load_to_lds(const void* src, void* base) {
 // Shape: 64 points per wavefront as two B operands held in registers; Z^T = R~ X^T in 32x32 tiles, so lane (p, h) ends up
 // with 16 values of point p per tile and the running best three need no cross-lane work until the end.  Four vector
 // instructions per value (number into the low bits, two medians, one maximum) against 8 NT matrix instructions per 32
-// values: with one term the two pipes are about level (measured 49 % and 31 % busy), which is why the second term of
+// values: with one term the vector pipe is the longer one (busy in 53 % of the cycles, the matrix pipe in 32 %, at 256 x 4096 x
+// 256), with two they would change places, which is why the second term of
 // float16 was worth dropping for a few per cent of the points to be re-checked.  Centres go through two LDS buffers of 16 KB, the next one filled by direct
 // global-to-LDS loads while this one is consumed, one barrier per buffer; four wavefronts share them (eight were slower: one phase
 // of latency more in step).  All workgroups of a unit have the same number modulo 8, i.e. share an L2.
@@ -976,7 +979,8 @@ __device__ __forceinline__ void far_reduce(double& val, int& idx) {
   if constexpr (!ROW) { far_step<kDppBcast15, 0xA>(val, idx); far_step<kDppBcast31, 0xC>(val, idx); }
 }
 
-// What the parallel kernels leave, in workgroups of 1024; most launches find nothing to do.
+// What the parallel kernels leave, in workgroups of 1024.  Most launches find nothing to do (4.5 us); where the first centres
+// leave some cluster empty, one or two iterations do (up to 190 us at 256 x 4096 x 256, 0.36 ms of that build in all).
 //   units with an empty cluster, one workgroup each: every empty cluster, in ascending id, takes the not-yet-taken point that is
 //     farthest from its own (old) centre, ties to the lowest position; the others get their sums formed anew
 //   units whose sums are not order-free, in every iteration after the first: all sums formed anew.  Each of the unit's

@@ -4,7 +4,7 @@
 //                   in a whole-step call the due splits follow in the same launch
 //   split_kernel  - delayed splits of flagged clusters in the active set, then the forced split
 // One workgroup per unit; each unit's record is touched by that workgroup only.  All decisions are
-// taken on float64 values summed in the fixed order of common.hpp, ties to the lowest index.
+// taken on float64 values summed in an order that does not depend on the launch, ties to the lowest index.
 #include "split.hpp"
 #include "score.hpp"
 
@@ -112,7 +112,9 @@ __global__ __launch_bounds__(256) void append_kernel(View v, const void* kin, co
 // of them an entry waits for: the table in batches of four tiles per wavefront with the next batch in flight (read wherever
 // they lie in the table's padded range, so that the first does not wait for M), the entries' rows sixteen
 // at a time through LDS, the split's look at the flagged list only where the append has left a flag.
-// 256 units, 256 clusters, 1024 entries (163 splits a unit): 11.5 -> 10.4 ms; without splits 6.6 us per entry.
+// 256 units, 256 clusters, 1024 entries (163 splits a unit): 11.5 -> 10.4 ms.  Per entry: 6.6 us in the static update mode,
+// where no cluster is ever flagged (1024 entries behind 2048 as well as 2048 behind 4096); 7.3 and 7.6 us with one and five
+// splits per unit on average, because the launch waits for the unit with most of them; 10.1 and 10.5 us with 163 and 334.
 template <int DT, bool MEAN>
 __global__ __launch_bounds__(256) void extend_kernel(View v, const void* K, const void* V, int n) {
   __shared__ AppendSmem a;
