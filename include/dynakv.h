@@ -213,7 +213,8 @@ dynakv_status_t dynakv_append(dynakv_index_t* index, const void* k_new, const vo
 dynakv_status_t dynakv_split(dynakv_index_t* index, void* stream);
 
 /* One whole decode step of Algorithm 1 (decode block): dynakv_retrieve_attend(Q), dynakv_append(k_new,
- * v_new) and dynakv_split(), in that order and with the same results bit for bit, so the three calls and
+ * v_new) and dynakv_split(), in that order and with the same results (M2 up to its last digits: the single launch
+ * takes that float64 sum in an order of its own; attention outputs up to float32 rounding), so the three calls and
  * this one can be mixed freely.  It exists because the step's two passes over the centroid table (query
  * similarity, Section 4.1; nearest cluster of the new key, Section 4.2) read the same data, and because a
  * step is a chain of short dependent phases: with 16-bit storage read through its 16-bit search copy, at most
