@@ -1,195 +1,60 @@
 // The part of an append that follows the nearest-cluster search (Algorithm 1, decode block; UpdateVar of
-// Section 4.2): shared by the stand-alone append kernel and by the retrieval kernel that finds the nearest
-// cluster during its own pass over the centroid table.
+// Section 4.2), by one wavefront with no workgroup barrier: shared by the stand-alone append kernel, the
+// retrieval kernel that finds the nearest cluster during its own pass over the centroid table, and the extension.
+// Lane l owns the coordinates 2 l and 2 l + 1.  Bound by latency: the cluster's record and centroid are one trip to memory
+// (everything else was requested when the kernel began), the rest a chain of float64 arithmetic.  (By a workgroup, with a
+// barrier and a trip to LDS or memory per step, an append took 5.6 us of a step over 128 units of 7300 clusters, now 2.3.)
 #pragma once
 #include "common.hpp"
 
 namespace dynakv {
 
-struct AppendSmem {
-  double kd[kHeadDim];       // the new key, filled (and synchronised) by the caller
-  double delta[kHeadDim], r1[kHeadDim];
-  double bs[16];             // block sums of the M2 increment
-  double m2, tau;
-  int cn, cb, ctail, cflag, nflag, free_top, bump, free_page;
-  int ok, commit, page, slot;
-  int nflag1, top1, bump1;   // the unit's flag count and allocator state as the append leaves them
+// The bits of a key's and a value's coordinates 2 lane and 2 lane + 1 (16-bit types: one word).
+struct EntryBits {
+  uint2 k, v;
 };
-
-// What one thread fetches for an append: thread d < 128 coordinate d of the centroid, threads 128..136 one field
-// each of the cluster's record or of the unit's allocator state.  All of it in one round trip to memory (two where the height
-// of the free-page stack is not known to the caller: top < 0).
-struct AppendFetch {
-  double x;
-  int i, k;
-};
-__device__ inline AppendFetch append_fetch(const View& v, int u, int j, int top = -1) {
-  const int tid = threadIdx.x;
-  const size_t cbase = (size_t)u * v.Mcap;
-  AppendFetch f{0.0, 0, 0};
-  if (tid < kHeadDim) f.x = (double)unit_R(v, u)[r_index(j, tid)];
-  switch (tid - kHeadDim) {
-    case 0: f.i = v.cn[cbase + j]; break;
-    case 1: f.i = v.cb[cbase + j]; break;
-    case 2: f.i = v.ctail[cbase + j]; break;
-    case 3: f.i = v.cflag[cbase + j]; break;
-    case 4: f.x = v.cM2[cbase + j]; break;
-    case 5: f.x = v.tau[u]; break;
-    case 6: f.i = v.nflag[u]; break;
-    case 7: f.i = v.bump[u]; break;
-    case 8: {
-      f.i = top >= 0 ? top : v.free_top[u];
-      f.k = f.i > 0 ? v.freelist[(size_t)u * v.Pcap + f.i - 1] : -1;
-      break;
-    }
-    default: break;
+template <int DT>
+__device__ __forceinline__ uint2 load_pair(const void* base, size_t row, int lane) {
+  if constexpr (DT == DYNAKV_F32) return ((const uint2*)base)[row * (kHeadDim / 2) + lane];
+  else return uint2{((const uint32_t*)base)[row * (kHeadDim / 2) + lane], 0};
+}
+template <int DT>
+__device__ __forceinline__ void store_pair(void* row, int lane, uint2 x) {
+  if constexpr (DT == DYNAKV_F32) ((uint2*)row)[lane] = x;
+  else ((uint32_t*)row)[lane] = x.x;
+}
+template <int DT>
+__device__ __forceinline__ float2 pair_value(uint2 x) {
+  if constexpr (DT == DYNAKV_F32) return float2{__uint_as_float(x.x), __uint_as_float(x.y)};
+  else return float2{bits_value(x.x & 0xFFFFu, DT), bits_value(x.x >> 16, DT)};
+}
+// The rows of tensors of a caller need not be aligned beyond their elements.
+template <int DT>
+__device__ __forceinline__ EntryBits load_entry(const void* kin, const void* vin, size_t row, int lane) {
+  EntryBits e;
+  if constexpr (DT == DYNAKV_F32) {
+    const uint32_t* k = (const uint32_t*)kin + row * kHeadDim + 2 * lane;
+    const uint32_t* x = (const uint32_t*)vin + row * kHeadDim + 2 * lane;
+    e.k = uint2{k[0], k[1]}; e.v = uint2{x[0], x[1]};
+  } else {
+    const uint16_t* k = (const uint16_t*)kin + row * kHeadDim + 2 * lane;
+    const uint16_t* x = (const uint16_t*)vin + row * kHeadDim + 2 * lane;
+    e.k = uint2{(uint32_t)k[0] | ((uint32_t)k[1] << 16), 0}; e.v = uint2{(uint32_t)x[0] | ((uint32_t)x[1] << 16), 0};
   }
-  return f;
+  return e;
+}
+// Coordinates 2 lane and 2 lane + 1 of centroid j: the float32 master and, for 16-bit storage, the search copy, whose bits are returned.
+template <int DT>
+__device__ __forceinline__ uint32_t store_centroid_pair(const View& v, int u, int j, int lane, float2 x) {
+  // (the search copy rounds the float32 value: left to itself the compiler turns float64 -> float32 -> 16 bits into one rounding)
+  asm("" : "+v"(x.x), "+v"(x.y));
+  *(float2*)(unit_R(v, u) + r_index(j, 2 * lane)) = x;
+  if constexpr (DT == DYNAKV_F32) return 0;
+  const uint32_t w = (uint32_t)round_bits16(x.x, DT) | ((uint32_t)round_bits16(x.y, DT) << 16);
+  *(uint32_t*)(unit_Rq(v, u) + rq_index(j, 2 * lane)) = w;
+  return w;
 }
 
-// Cluster j (of M) receives token N of unit u.  Called by all NT >= 256 threads of the unit's workgroup with
-// what append_fetch returned to each of them (the caller may have issued it long before).  The sum of UpdateVar
-// is formed from 16 block sums computed side by side, and one thread then takes the decisions.
-// HELD: thread d < 128 holds the bits of the key's coordinate d, thread 128 + d those of the value's (kin, vin are not read).
-template <int NT, bool HELD = false>
-__device__ inline void append_commit(const View& v, int u, int j, int M, int N, const void* kin, const void* vin,
-                                     AppendSmem& a, const AppendFetch& f, uint32_t held = 0) {
-  const int tid = threadIdx.x;
-  const size_t cbase = (size_t)u * v.Mcap;
-  const double r = f.x;
-  switch (tid - kHeadDim) {
-    case 0: a.cn = f.i; break;
-    case 1: a.cb = f.i; break;
-    case 2: a.ctail = f.i; break;
-    case 3: a.cflag = f.i; break;
-    case 4: a.m2 = f.x; break;
-    case 5: a.tau = f.x; break;
-    case 6: a.nflag = f.i; break;
-    case 7: a.bump = f.i; break;
-    case 8: a.free_top = f.i; a.free_page = f.k; break;
-    default: break;
-  }
-  lds_barrier();
-  // UpdateVar, element-wise part: delta_d = k_d - r_d, r'_d = r_d + delta_d / n'
-  const int n1 = a.cn + 1;
-  if (tid < kHeadDim) {
-    const double dl = a.kd[tid] - r;
-    a.delta[tid] = dl;
-    a.r1[tid] = r + dl / (double)n1;
-  }
-  lds_barrier();
-  if (tid < 16) {                           // block tid of sum_d delta_d * (k_d - r'_d)
-    double s = 0.0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s = fma(a.delta[tid * 8 + e], a.kd[tid * 8 + e] - a.r1[tid * 8 + e], s);
-    a.bs[tid] = s;
-  }
-  lds_barrier();
-  if (tid == 0) {
-    const int sz = a.cn + a.cb;
-    const int slot = sz % kPageTokens;
-    int page = a.ctail;
-    int ok = 1;
-    a.nflag1 = a.nflag; a.top1 = a.free_top; a.bump1 = a.bump;
-    if (slot == 0) {                      // no page yet, or the tail page is full
-      int np = -1;                        // from the free stack, else from the untouched tail of the pool
-      if (a.free_top > 0) {
-        np = a.free_page;
-        v.free_top[u] = a.free_top - 1;
-        a.top1 = a.free_top - 1;
-      } else if (a.bump < v.Pcap) {
-        np = a.bump;
-        v.bump[u] = a.bump + 1;
-        a.bump1 = a.bump + 1;
-      }
-      if (np < 0) {
-        v.err[u] |= DYNAKV_ERR_TOKENS;
-        ok = 0;
-      } else {
-        v.pnext[(size_t)u * v.Pcap + np] = -1;
-        if (sz != 0) v.pnext[(size_t)u * v.Pcap + page] = np;
-        if (sz / kPageTokens < kInlinePages) v.cpg[(cbase + j) * kInlinePages + sz / kPageTokens] = np;
-        v.ctail[cbase + j] = np;
-        page = np;
-      }
-    }
-    int commit = 0;
-    if (ok) {
-      v.last_assign[u] = j;
-      if (a.cflag) {
-        v.cb[cbase + j] = a.cb + 1;       // goes to the buffer of a flagged cluster
-        v.csz[cbase + j] = a.cn + a.cb + 1;
-      } else {
-        // UpdateVar, the running part: M2' = M2 + sum_d delta_d * (k_d - r'_d)
-        const double M2 = a.m2 + blocked16([&](int k) __attribute__((always_inline)) { return a.bs[k]; });
-        const double var1 = M2 / (double)n1;
-        bool trig = false;
-        if (n1 >= 2 && !v.static_update) {
-          if (v.var_alpha > 0.f && var1 > a.tau) trig = true;
-          if (v.size_factor > 0.f && (double)n1 * (double)M > (double)v.size_factor * (double)(N + 1)) trig = true;
-        }
-        if (!trig) {
-          v.cn[cbase + j] = n1;
-          v.csz[cbase + j] = n1 + a.cb;
-          v.cM2[cbase + j] = M2;
-          commit = 1;
-        } else {
-          v.cflag[cbase + j] = 1;
-          v.cb[cbase + j] = 1;
-          v.csz[cbase + j] = a.cn + 1;
-          v.flist[cbase + a.nflag] = j;
-          v.nflag[u] = a.nflag + 1;
-          a.nflag1 = a.nflag + 1;
-        }
-      }
-      v.N[u] = N + 1;
-      v.ppos[((size_t)u * v.Pcap + page) * kPageTokens + slot] = N;
-    }
-    a.ok = ok; a.commit = commit; a.page = page; a.slot = slot;
-  }
-  lds_barrier();
-  if (!a.ok) return;
-  if (a.commit && tid < kHeadDim) store_centroid(v, u, j, tid, (float)a.r1[tid]);
-  char* pg = page_ptr(v, u, a.page);
-  if constexpr (HELD) {
-    if (tid < 2 * kHeadDim)
-      store_bits(pg, tid < kHeadDim ? k_index(v.dtype, a.slot, tid) : v_index(v.dtype, a.slot, tid - kHeadDim), held, v.dtype);
-  } else if (tid < kHeadDim) copy_elem(pg, k_index(v.dtype, a.slot, tid), kin, (size_t)u * kHeadDim + tid, v.dtype);
-  else if (tid < 2 * kHeadDim)
-    copy_elem(pg, v_index(v.dtype, a.slot, tid - kHeadDim), vin, (size_t)u * kHeadDim + tid - kHeadDim, v.dtype);
-}
-
-// ---- the same by one wavefront ------------------------------------------------------------------------
-// Lane l fetches coordinates l and l + 64 of the centroid, lanes 0..8 one field each of the cluster's record or of
-// the unit's allocator state (the fields of AppendFetch, in the same order).
-struct AppendFetchWave {
-  double x0, x1, xf;
-  int i, k;
-};
-__device__ inline AppendFetchWave append_fetch_wave(const View& v, int u, int j) {
-  const int lane = threadIdx.x & 63;
-  const size_t cbase = (size_t)u * v.Mcap;
-  AppendFetchWave f{0.0, 0.0, 0.0, 0, 0};
-  f.x0 = (double)unit_R(v, u)[r_index(j, lane)];
-  f.x1 = (double)unit_R(v, u)[r_index(j, lane + 64)];
-  switch (lane) {
-    case 0: f.i = v.cn[cbase + j]; break;
-    case 1: f.i = v.cb[cbase + j]; break;
-    case 2: f.i = v.ctail[cbase + j]; break;
-    case 3: f.i = v.cflag[cbase + j]; break;
-    case 4: f.xf = v.cM2[cbase + j]; break;
-    case 5: f.xf = v.tau[u]; break;
-    case 6: f.i = v.nflag[u]; break;
-    case 7: f.i = v.bump[u]; break;
-    case 8: {
-      f.i = v.free_top[u];
-      f.k = f.i > 0 ? v.freelist[(size_t)u * v.Pcap + f.i - 1] : -1;
-      break;
-    }
-    default: break;
-  }
-  return f;
-}
 __device__ __forceinline__ double readlane_f64(double x, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
 }
@@ -209,87 +74,141 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
   x += dpp_f64<kDppBcast31, 0xC>(x);
   return readlane_f64(x, 63);
 }
-// append_commit by ONE wavefront, with no workgroup barrier: the other wavefronts of the workgroup are free to do
-// something else meanwhile.  a.kd holds the new key; on return the fields of `a` that the plan of the splits reads
-// (ok, cn, cb, slot, page, nflag1, top1, bump1) are in place, and every global store of the append has completed.
-__device__ inline void append_commit_wave(const View& v, int u, int j, int M, int N, const void* kin, const void* vin,
-                                          AppendSmem& a, const AppendFetchWave& f) {
-  const int lane = threadIdx.x & 63;
-  const size_t cbase = (size_t)u * v.Mcap;
-  const int cn = __builtin_amdgcn_readlane(f.i, 0), cb = __builtin_amdgcn_readlane(f.i, 1);
-  const int ctail = __builtin_amdgcn_readlane(f.i, 2), cflag = __builtin_amdgcn_readlane(f.i, 3);
-  const double m2 = readlane_f64(f.xf, 4), tau = readlane_f64(f.xf, 5);
-  const int nflag = __builtin_amdgcn_readlane(f.i, 6), bump = __builtin_amdgcn_readlane(f.i, 7);
-  const int free_top = __builtin_amdgcn_readlane(f.i, 8), free_page = __builtin_amdgcn_readlane(f.k, 8);
-  // UpdateVar: delta_d = k_d - r_d, r'_d = r_d + delta_d / n', M2' = M2 + sum_d delta_d (k_d - r'_d)
-  const int n1 = cn + 1;
-  const double k0 = a.kd[lane], k1 = a.kd[lane + 64];
-  const double d0 = k0 - f.x0, d1 = k1 - f.x1;
-  const double r0 = f.x0 + d0 / (double)n1, r1 = f.x1 + d1 / (double)n1;
-  const double M2 = m2 + wave_sum_f64(fma(d0, k0 - r0, d1 * (k1 - r1)));
-  // the decisions, by every lane alike (all operands are wavefront-uniform); lane 0 writes
-  const int sz = cn + cb, slot = sz % kPageTokens;
-  int page = ctail, ok = 1, nflag1 = nflag, top1 = free_top, bump1 = bump;
-  if (slot == 0) {                        // no page yet, or the tail page is full
-    int np = -1;                          // from the free stack, else from the untouched tail of the pool
-    if (free_top > 0) { np = free_page; top1 = free_top - 1; }
-    else if (bump < v.Pcap) { np = bump; bump1 = bump + 1; }
-    if (np < 0) ok = 0;
-    else {
-      if (lane == 0) {
-        v.free_top[u] = top1; v.bump[u] = bump1;
-        v.pnext[(size_t)u * v.Pcap + np] = -1;
-        if (sz != 0) v.pnext[(size_t)u * v.Pcap + page] = np;
-        if (sz / kPageTokens < kInlinePages) v.cpg[(cbase + j) * kInlinePages + sz / kPageTokens] = np;
-        v.ctail[cbase + j] = np;
-      }
-      page = np;
-    }
-  }
-  int commit = 0;
-  if (ok) {
-    bool trig = false;
-    if (!cflag && n1 >= 2 && !v.static_update) {
-      if (v.var_alpha > 0.f && M2 / (double)n1 > tau) trig = true;
-      if (v.size_factor > 0.f && (double)n1 * (double)M > (double)v.size_factor * (double)(N + 1)) trig = true;
-    }
-    commit = !cflag && !trig;
-    if (!cflag && trig) nflag1 = nflag + 1;
-    if (lane == 0) {
-      v.last_assign[u] = j;
-      if (cflag) {                          // goes to the buffer of a flagged cluster
-        v.cb[cbase + j] = cb + 1;
-        v.csz[cbase + j] = cn + cb + 1;
-      } else if (!trig) {
-        v.cn[cbase + j] = n1;
-        v.csz[cbase + j] = n1 + cb;
-        v.cM2[cbase + j] = M2;
-      } else {
-        v.cflag[cbase + j] = 1;
-        v.cb[cbase + j] = 1;
-        v.csz[cbase + j] = cn + 1;
-        v.flist[cbase + nflag] = j;
-        v.nflag[u] = nflag + 1;
-      }
-      v.N[u] = N + 1;
-      v.ppos[((size_t)u * v.Pcap + page) * kPageTokens + slot] = N;
-    }
-    if (commit) { store_centroid(v, u, j, lane, (float)r0); store_centroid(v, u, j, lane + 64, (float)r1); }
-    char* pg = page_ptr(v, u, page);
-    copy_elem(pg, k_index(v.dtype, slot, lane), kin, (size_t)u * kHeadDim + lane, v.dtype);
-    copy_elem(pg, k_index(v.dtype, slot, lane + 64), kin, (size_t)u * kHeadDim + lane + 64, v.dtype);
-    copy_elem(pg, v_index(v.dtype, slot, lane), vin, (size_t)u * kHeadDim + lane, v.dtype);
-    copy_elem(pg, v_index(v.dtype, slot, lane + 64), vin, (size_t)u * kHeadDim + lane + 64, v.dtype);
-  } else if (lane == 0) {
-    v.err[u] |= DYNAKV_ERR_TOKENS;
-  }
-  if (lane == 0) {
-    a.cn = cn; a.cb = cb; a.ok = ok; a.commit = commit; a.page = page; a.slot = slot;
-    a.nflag1 = nflag1; a.top1 = top1; a.bump1 = bump1;
-  }
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+// 1 / n for a count n, and x / n from it, rounded as a division rounds: the remainder of the first quotient, exact in one fused
+// multiply-add, corrects it (Markstein).  Three instructions instead of the thirty of a float64 division.
+struct CountInverse {
+  double n, r;
+};
+__device__ __forceinline__ CountInverse count_inverse(int n) {
+  CountInverse c{(double)n, 0.0};
+  c.r = __builtin_amdgcn_rcp(c.n);
+  c.r = fma(fma(-c.n, c.r, 1.0), c.r, c.r);
+  c.r = fma(fma(-c.n, c.r, 1.0), c.r, c.r);
+  return c;
+}
+__device__ __forceinline__ double over_count(double x, const CountInverse& c) {
+  const double q = x * c.r;
+  const double d = fma(fma(-c.n, q, x), c.r, q);
+  return fabs(q) < __builtin_inf() ? d : q;      // (an infinity has no remainder)
 }
 
+// The unit's counters before an append; requested as early as possible.
+struct UnitState {
+  int M, N, nflag, top, bump;
+  double tau;
+};
+__device__ __forceinline__ UnitState load_unit(const View& v, int u) {
+  return UnitState{v.M[u], v.N[u], v.nflag[u], v.free_top[u], v.bump[u], v.tau[u]};
+}
+// A cluster as an append finds it: lane l its coordinates 2 l and 2 l + 1, the rest the same in every lane.  free_page: the top
+// of the unit's stack of free pages.
+struct ClusterState {
+  float2 r;
+  int cn, cb, ctail, cflag, free_page;
+  double m2;
+};
+// One load: lanes 0 .. 6 fetch a word of the record each (see cluster_state).
+struct ClusterFetch {
+  float2 r;
+  int w;
+};
+__device__ __forceinline__ ClusterFetch fetch_cluster(const View& v, int u, int j, int top, int lane) {
+  const size_t cj = (size_t)u * v.Mcap + j;
+  ClusterFetch f;
+  const int* p = v.cn + cj;
+  p = lane == 1 ? v.cb + cj : p;
+  p = lane == 2 ? v.ctail + cj : p;
+  p = lane == 3 ? v.cflag + cj : p;
+  p = lane == 4 ? (const int*)(v.cM2 + cj) : p;
+  p = lane == 5 ? (const int*)(v.cM2 + cj) + 1 : p;
+  p = lane == 6 && top > 0 ? v.freelist + (size_t)u * v.Pcap + top - 1 : p;
+  f.w = lane < 7 ? *p : 0;
+  f.r = *(const float2*)(unit_R(v, u) + r_index(j, 2 * lane));
+  return f;
+}
+__device__ __forceinline__ ClusterState cluster_state(const ClusterFetch& f, int top) {
+  ClusterState c;
+  c.r = f.r;
+  c.cn = __builtin_amdgcn_readlane(f.w, 0); c.cb = __builtin_amdgcn_readlane(f.w, 1); c.ctail = __builtin_amdgcn_readlane(f.w, 2);
+  c.cflag = __builtin_amdgcn_readlane(f.w, 3);
+  c.m2 = __hiloint2double(__builtin_amdgcn_readlane(f.w, 5), __builtin_amdgcn_readlane(f.w, 4));
+  c.free_page = top > 0 ? __builtin_amdgcn_readlane(f.w, 6) : -1;
+  return c;
+}
+
+// What an append does to its cluster and its unit (the same in every lane).
+struct AppendResult {
+  int ok, commit, page, slot;      // carried out; the statistics were updated (else: buffered); the entry's place
+  int nflag, top, bump;            // the unit's counters afterwards
+  float2 r;                        // the centroid afterwards (lane l: coordinates 2 l, 2 l + 1)
+  uint32_t rq;                     // and its search copy's bits (16-bit types)
+  double m2;
+};
+// Cluster j receives entry s.N of unit u, by one wavefront.  Stores are left in flight.
+template <int DT>
+__device__ __forceinline__ AppendResult append_wave(const View& v, int u, int j, const UnitState& s, const ClusterState& c,
+                                                    const EntryBits& e, int lane) {
+  const size_t cj = (size_t)u * v.Mcap + j, up = (size_t)u * v.Pcap;
+  AppendResult a{1, 0, c.ctail, 0, s.nflag, s.top, s.bump, c.r, 0, c.m2};
+  // UpdateVar: delta_d = k_d - r_d, r'_d = r_d + delta_d / n', M2' = M2 + sum_d delta_d (k_d - r'_d)
+  const int n1 = c.cn + 1, sz = c.cn + c.cb;
+  const CountInverse inv = count_inverse(n1);
+  const float2 kf = pair_value<DT>(e.k);
+  const double k0 = (double)kf.x, k1 = (double)kf.y;
+  const double d0 = k0 - (double)c.r.x, d1 = k1 - (double)c.r.y;
+  const double r0 = (double)c.r.x + over_count(d0, inv), r1 = (double)c.r.y + over_count(d1, inv);
+  const double M2 = c.m2 + wave_sum_f64(fma(d0, k0 - r0, d1 * (k1 - r1)));
+  // the decisions, by every lane alike (all operands are wavefront-uniform); lane 0 writes
+  a.slot = sz % kPageTokens;
+  if (a.slot == 0) {                      // no page yet, or the tail page is full: from the free stack, else from the
+    int np = -1;                          // untouched tail of the pool
+    if (s.top > 0) { np = c.free_page; a.top = s.top - 1; }
+    else if (s.bump < v.Pcap) { np = s.bump; a.bump = s.bump + 1; }
+    if (np < 0) {
+      a.ok = 0;
+      if (lane == 0) v.err[u] |= DYNAKV_ERR_TOKENS;
+      return a;
+    }
+    if (lane == 0) {
+      v.free_top[u] = a.top; v.bump[u] = a.bump;
+      v.pnext[up + np] = -1;
+      if (sz != 0) v.pnext[up + a.page] = np;
+      if (sz / kPageTokens < kInlinePages) v.cpg[cj * kInlinePages + sz / kPageTokens] = np;
+      v.ctail[cj] = np;
+    }
+    a.page = np;
+  }
+  char* pg = page_ptr(v, u, a.page);
+  constexpr int kEs = DT == DYNAKV_F32 ? 4 : 2;
+  store_pair<DT>(pg + (size_t)k_index(DT, a.slot, 0) * kEs, lane, e.k);
+  store_pair<DT>(pg + (size_t)v_index(DT, a.slot, 0) * kEs, lane, e.v);
+  bool trig = false;
+  if (!c.cflag && n1 >= 2 && !v.static_update) {
+    if (v.var_alpha > 0.f && over_count(M2, inv) > s.tau) trig = true;
+    if (v.size_factor > 0.f && (double)n1 * (double)s.M > (double)v.size_factor * (double)(s.N + 1)) trig = true;
+  }
+  a.commit = !c.cflag && !trig;
+  if (!c.cflag && trig) a.nflag = s.nflag + 1;
+  if (a.commit) {
+    a.r = float2{(float)r0, (float)r1};
+    a.rq = store_centroid_pair<DT>(v, u, j, lane, a.r);
+    a.m2 = M2;
+  }
+  if (lane == 0) {
+    v.csz[cj] = sz + 1;
+    if (a.commit) {
+      v.cn[cj] = n1;
+      v.cM2[cj] = M2;
+    } else {                              // goes to the buffer of a flagged cluster (which this entry has flagged, if trig)
+      v.cb[cj] = c.cb + 1;
+      if (trig) { v.cflag[cj] = 1; v.flist[(size_t)u * v.Mcap + s.nflag] = j; v.nflag[u] = a.nflag; }
+    }
+    v.last_assign[u] = j;
+    v.N[u] = s.N + 1;
+    v.ppos[(up + a.page) * kPageTokens + a.slot] = s.N;
+  }
+  return a;
+}
 // Workgroup-wide arg-min over (value, index) pairs, one per thread (index < 0: none); equal values go to the
 // lowest index.  NT / 64 <= 16 wavefronts; sv / si need 16 entries.  Every thread gets the winning index.
 template <int NT>

@@ -23,83 +23,103 @@ namespace {
 //              the bound are compared in float64
 // SPLIT: the unit's due splits follow in the same launch (the rest of a decode step on the separate-kernel path).
 enum { kScanMean = 0, kPreMean = 1, kPreZ = 2 };
-template <bool ON>
+template <int DT, bool ON>
 struct SplitLds {
-  alignas(16) unsigned char raw[kSplitRaw];
+  alignas(16) unsigned char raw[kSplitRaw<DT>];
   SplitWork wk;
 };
-template <>
-struct SplitLds<false> {};
+template <int DT>
+struct SplitLds<DT, false> {};
 template <int DT, int MODE, bool SPLIT>
 __global__ __launch_bounds__(256) void append_kernel(View v, const void* kin, const void* vin) {
   static_assert(kSplitThreads == 256, "split_unit is run by this kernel's whole workgroup");
-  __shared__ AppendSmem a;
+  __shared__ double kd[kHeadDim];
   __shared__ double sv[16];
   __shared__ int si[16];
   __shared__ float s2[16];
-  __shared__ SplitLds<SPLIT> sp;
-  const int u = blockIdx.x, tid = threadIdx.x;
+  __shared__ SplitLds<DT, SPLIT> sp;
+  const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const float* R = unit_R(v, u);
   f4 row[8];
   if constexpr (MODE == kScanMean)
     if ((size_t)(tid | 63) * kHeadDim < v.Rstride) load_centroid_head(R, tid, row);     // requested before anything else
-  const int M = v.M[u], N = v.N[u];
-  if (N >= v.Ncap || M <= 0) {                          // refused (workgroup-uniform); due splits still run
-    if (tid == 0) v.err[u] |= DYNAKV_ERR_TOKENS;
-    if constexpr (SPLIT) {
-      __syncthreads();
-      split_unit<DT>(v, u, sp.raw, sp.wk, false);
+  // what the first wavefront will need for the append and for the plan of the splits
+  const UnitState us = load_unit(v, u);
+  EntryBits entry{uint2{0, 0}, uint2{0, 0}};
+  int flagged0 = 0;
+  if (tid < 64) {
+    entry = load_entry<DT>(kin, vin, u, lane);
+    if constexpr (SPLIT) flagged0 = lane < v.Mcap ? v.flist[(size_t)u * v.Mcap + lane] : 0;
+  }
+  const int M = us.M;
+  const bool room = us.N < v.Ncap && M > 0;             // otherwise refused (workgroup-uniform); due splits still run
+  int j = -1;
+  if (room) {
+    float k2 = 0.f;
+    if (tid < kHeadDim) {
+      const float kf = load_elem(kin, (size_t)u * kHeadDim + tid, DT);
+      kd[tid] = (double)kf;
+      k2 = kf * kf;
     }
-    return;
-  }
-  float k2 = 0.f;
-  if (tid < kHeadDim) {
-    const float kf = load_elem(kin, (size_t)u * kHeadDim + tid, v.dtype);
-    a.kd[tid] = (double)kf;
-    k2 = kf * kf;
-  }
-  __syncthreads();
-  int j;
-  if constexpr (MODE == kPreZ) {
-    for (int o = 32; o > 0; o >>= 1) k2 += __shfl_xor(k2, o);
-    if ((tid & 63) == 0) s2[tid >> 6] = k2;
-    __syncthreads();
-    const float kn = __builtin_sqrtf(s2[0] + s2[1]) * 1.0001f;
-    const float* zd = v.zdist + (size_t)u * v.Mcap;
-    // the matrix-core pass has left best / runner-up per 64 clusters
-    float zb = -__builtin_inff(), z2 = -__builtin_inff();
-    int jb = -1;
-    const size_t wbase = (size_t)u * v.NB * 4;
-    for (int w = tid; w * 64 < M; w += 256) merge_best2(zb, jb, z2, v.near_zb[wbase + w], v.near_zj[wbase + w], v.near_z2[wbase + w]);
-    j = nearest_resolve<256>(v, u, M, zb, jb, z2, kn, __int_as_float(v.rmax2[u]), zd, unit_Rq(v, u), a.kd, sv, si, s2);
-  } else {
-    double best = __builtin_inf();
-    int arg = -1;
-    if constexpr (MODE == kPreMean) {
-      for (int b = tid; b * 256 < M; b += 256) {          // blocks past the last cluster hold nothing of this step
-        const double d = v.near_d[(size_t)u * v.NB + b];
-        const int jj = v.near_j[(size_t)u * v.NB + b];
-        if (arg < 0 || d < best || (d == best && jj < arg)) { best = d; arg = jj; }
-      }
+    if constexpr (MODE == kPreZ) {
+      // the matrix-core pass has left best / runner-up per 64 clusters
+      float zb = -__builtin_inff(), z2 = -__builtin_inff();
+      int jb = -1;
+      const size_t wbase = (size_t)u * v.NB * 4;
+      for (int w = tid; w * 64 < M; w += 256) merge_best2(zb, jb, z2, v.near_zb[wbase + w], v.near_zj[wbase + w], v.near_z2[wbase + w]);
+      const float rmax2 = __int_as_float(v.rmax2[u]);
+      for (int o = 32; o > 0; o >>= 1) k2 += __shfl_xor(k2, o);
+      wave_best2(zb, jb, z2);
+      if (lane == 0) { const int w = tid >> 6; sv[w] = (double)zb; si[w] = jb; s2[w] = z2; s2[8 + w] = k2; }
+      lds_barrier();
+      const float kn = __builtin_sqrtf(s2[8] + s2[9]) * 1.0001f;
+      j = nearest_decide<256>(v, u, M, kn, rmax2, v.zdist + (size_t)u * v.Mcap, unit_Rq(v, u), kd, sv, si, s2);
     } else {
-      // nearest centre (squared Euclidean distance); lane = cluster, 16 contiguous bytes per lane and load
-      for (int jj = tid; jj < M; jj += 256) {
-        double dist[1];
-        if (jj != tid) load_centroid_head(R, jj, row);
-        centroid_sums<1>(R, jj, row, dist, [&](int d, float rv, double (&acc)[1]) __attribute__((always_inline)) {
-          const double t = a.kd[d] - (double)rv;
-          acc[0] = fma(t, t, acc[0]);
-        });
-        if (dist[0] < best || arg < 0) { best = dist[0]; arg = jj; }
+      __syncthreads();
+      double best = __builtin_inf();
+      int arg = -1;
+      if constexpr (MODE == kPreMean) {
+        for (int b = tid; b * 256 < M; b += 256) {          // blocks past the last cluster hold nothing of this step
+          const double d = v.near_d[(size_t)u * v.NB + b];
+          const int jj = v.near_j[(size_t)u * v.NB + b];
+          if (arg < 0 || d < best || (d == best && jj < arg)) { best = d; arg = jj; }
+        }
+      } else {
+        // nearest centre (squared Euclidean distance); lane = cluster, 16 contiguous bytes per lane and load
+        for (int jj = tid; jj < M; jj += 256) {
+          double dist[1];
+          if (jj != tid) load_centroid_head(R, jj, row);
+          centroid_sums<1>(R, jj, row, dist, [&](int d, float rv, double (&acc)[1]) __attribute__((always_inline)) {
+            const double t = kd[d] - (double)rv;
+            acc[0] = fma(t, t, acc[0]);
+          });
+          if (dist[0] < best || arg < 0) { best = dist[0]; arg = jj; }
+        }
       }
+      j = block_argmin<256>(best, arg, sv, si);
     }
-    j = block_argmin<256>(best, arg, sv, si);
   }
-  const AppendFetch f = append_fetch(v, u, j);
-  append_commit<256>(v, u, j, M, N, kin, vin, a, f);
+  // the append and the plan of the splits, by the first wavefront: what both ask of memory travels together
+  if (tid < 64) {
+    ClusterFetch cf{float2{0.f, 0.f}, 0};
+    PlanEarly pe{};
+    if (room) cf = fetch_cluster(v, u, j, us.top, lane);
+    if constexpr (SPLIT) pe = plan_fetch_early(v, u, flagged0, us, j, lane, nullptr);
+    AppendResult res{};
+    int sz0 = 0;
+    if (room) {
+      const ClusterState cs = cluster_state(cf, us.top);
+      res = append_wave<DT>(v, u, j, us, cs, entry, lane);
+      sz0 = cs.cn + cs.cb;
+    } else if (lane == 0) {
+      v.err[u] |= DYNAKV_ERR_TOKENS;
+    }
+    if constexpr (SPLIT)
+      if (plan_finish<DT>(v, sp.wk, pe, us, j, room, res, sz0, 0)) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the entry is in place
+  }
   if constexpr (SPLIT) {
-    __syncthreads();                                    // the append's record is in place for the whole workgroup
-    split_unit<DT>(v, u, sp.raw, sp.wk, false);
+    lds_barrier();
+    split_unit<DT>(v, u, sp.raw, sp.wk, true);
   }
 }
 
@@ -108,29 +128,252 @@ __global__ __launch_bounds__(256) void append_kernel(View v, const void* kin, co
 // entries in order; each entry is assigned to its nearest cluster (matrix cores + float64 where needed for the
 // 16-bit search copy, float64 scan for float32 means), appended with UpdateVar and the threshold test, and a
 // flagged cluster is split at once (the view's B_max is 0).  K, V: [U][n][128].
-// Entry t + 1 depends on what entry t did, so a unit's time is a chain of round trips to memory and what counts is how many
-// of them an entry waits for: the table in batches of four tiles per wavefront with the next batch in flight (read wherever
-// they lie in the table's padded range, so that the first does not wait for M), the entries' rows sixteen
-// at a time through LDS, the split's look at the flagged list only where the append has left a flag.
-// 256 units, 256 clusters, 1024 entries (163 splits a unit): 11.5 -> 10.4 ms.  Per entry: 6.6 us in the static update mode,
-// where no cluster is ever flagged (1024 entries behind 2048 as well as 2048 behind 4096); 7.3 and 7.6 us with one and five
-// splits per unit on average, because the launch waits for the unit with most of them; 10.1 and 10.5 us with 163 and 334.
+// Entry t + 1 depends on what entry t did, so a unit's time is a chain, and what counts is what an entry waits for.
+//
+// extend_batch_kernel (16-bit search copy): up to sixteen entries are the rows of one pass over the table (z_j = <k, r~_j> -
+// |r~_j|^2 / 2 of each entry and cluster, kept in LDS), and the records and centroids of the clusters that they are likely to join are
+// fetched together into slots of LDS.  The entries are then taken one after another by the first wavefront with no
+// trip to memory: nearest cluster from the entry's row of z (float64 where the runner-up lies within the rounding bound), UpdateVar and
+// threshold on the slot, and one matrix product of the new centroid with the entries to come, which corrects their z of that
+// cluster.  A cluster outside the slots is fetched when it is met; a flag ends the batch, its split is carried out by the whole
+// workgroup, and the next batch begins.  LDS holds z of kExtendClusters clusters for one entry, of a sixteenth of that for sixteen.
+// 256 units, 256 clusters, 1024 entries (163 splits a unit): 10.3 -> 7.3 ms.
+//
+// extend_kernel (float32 means; more clusters than that): one entry per pass over the table, the table in batches of four tiles
+// per wavefront with the next batch in flight.
+constexpr int kExtendBatch = 16, kExtendSpare = 8, kExtendZ = 10240;      // entries per batch, slots beyond them, floats of z
+constexpr int kExtendClusters = kExtendZ - 4;                             // (one entry's row, and the cluster it may add)
+static_assert(kSplitThreads == 2 * kHeadDim, "one coordinate of the key or of the value per thread");
+
+// What the extension holds of a cluster in LDS.
+struct ExtendSlot {
+  float2 r[64];
+  double m2;
+  int id, cn, cb, ctail, cflag, pad_;
+};
+
+// Best and runner-up of row[0 .. M) (padded to a multiple of four with -inf), by one wavefront; every lane gets them.
+__device__ __forceinline__ void row_best2(const float* row, int M, int lane, float& zb, int& jb, float& z2) {
+  zb = -__builtin_inff(); z2 = -__builtin_inff(); jb = -1;
+#pragma unroll 1
+  for (int j0 = 4 * lane; j0 < M; j0 += 256) {
+    const f4 z = *(const f4*)(row + j0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (j0 + e < M && (jb < 0 || z[e] > zb)) { z2 = jb < 0 ? z2 : zb; zb = z[e]; jb = j0 + e; }      // ascending: the first maximum stays
+      else z2 = fmaxf(z2, z[e]);
+    }
+  }
+  wave_best2(zb, jb, z2);
+}
+
+template <int DT>
+__global__ __launch_bounds__(256) void extend_batch_kernel(View v, const void* K, const void* V, int n) {
+  static_assert(DT != DYNAKV_F32, "needs the 16-bit search copy");
+  constexpr bool BF = DT == DYNAKV_BF16;
+  __shared__ SplitLds<DT, true> sp;
+  __shared__ __align__(16) float zs[kExtendZ];
+  __shared__ __align__(16) ExtendSlot slot[kExtendBatch + kExtendSpare];
+  __shared__ __align__(16) unsigned char rows[kExtendBatch][2][kHeadDim * 2];
+  __shared__ __align__(16) uint32_t vec[kHeadDim / 2];
+  __shared__ int s_rmax2, s_done, s_nflag;
+  const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, cl = lane & 15;
+  const uint4* tiles = (const uint4*)unit_Rq(v, u);
+  int t = 0;
+#pragma unroll 1
+  while (t < n) {
+    UnitState us = load_unit(v, u);                    // (a full barrier lies behind the last store)
+    const int M = us.M;
+    if (us.N >= v.Ncap || M <= 0) {                    // workgroup-uniform
+      if (tid == 0) v.err[u] |= DYNAKV_ERR_TOKENS;
+      t = n;
+      break;
+    }
+    if (M > kExtendClusters) break;
+    int B = kExtendBatch;
+    while (B > 1 && B * ((M + 3) & ~3) > kExtendZ) B >>= 1;
+    const int stride = (M + 3) & ~3, nb = min(min(B, n - t), v.Ncap - us.N);
+    // ---- the entries, and z of every cluster
+    uint32_t x[kExtendBatch];
+#pragma unroll
+    for (int i = 0; i < kExtendBatch; ++i)
+      x[i] = ((const uint16_t*)(tid < kHeadDim ? K : V))[((size_t)u * n + min(t + i, n - 1)) * kHeadDim + (tid & (kHeadDim - 1))];
+    const int fl = us.top - 1 - lane >= 0 ? v.freelist[(size_t)u * v.Pcap + us.top - 1 - lane] : -1;      // the top of the free stack
+#pragma unroll
+    for (int i = 0; i < kExtendBatch; ++i) ((uint16_t*)rows[i][0])[tid] = (uint16_t)x[i];
+    if (tid == 0) s_rmax2 = 0;
+    if (tid < kExtendSpare) slot[kExtendBatch + tid].id = -1;
+    lds_barrier();
+    uint4 A[4];                                        // rows = the entries (those past nb repeat others: nobody asks for them)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) A[s] = *(const uint4*)(rows[cl][0] + 64 * s + 16 * lg);
+    float kn = 0.f;                                    // |entry cl|
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const uint32_t ww[4] = {A[s].x, A[s].y, A[s].z, A[s].w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float k = bits_value((ww[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu, DT);
+        kn = fmaf(k, k, kn);
+      }
+    }
+    kn = __builtin_sqrtf(rows_sum(kn)) * 1.0001f;
+    const int ntile = (M + kTileClusters - 1) / kTileClusters;
+    float rmax2 = 0.f;
+#pragma unroll 1
+    for (int T0 = wave * 4; T0 < ntile; T0 += 16) {
+      uint4 b[4][4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) b[k][s] = tiles[((size_t)min(T0 + k, ntile - 1) * 4 + s) * 64 + lane];
+      f4 acc[4], gram[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) { acc[k] = f4{0, 0, 0, 0}; gram[k] = f4{0, 0, 0, 0}; }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          acc[k] = mfma_k32<BF>(A[s], b[k][s], acc[k]);
+          gram[k] = mfma_k32<BF>(b[k][s], b[k][s], gram[k]);
+        }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float nrm2 = gram_diagonal(gram[k], lane);
+        const int j = (T0 + k) * kTileClusters + cl;
+        if (j >= M) continue;                          // (clusters of a repeated tile lie past M as well)
+        rmax2 = fmaxf(rmax2, nrm2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (4 * lg + i < B) zs[(4 * lg + i) * stride + j] = acc[k][i] - 0.5f * nrm2;
+      }
+    }
+    if (tid < B * 4 && M + (tid & 3) < stride) zs[(tid >> 2) * stride + M + (tid & 3)] = -__builtin_inff();
+    atomicMax(&s_rmax2, __float_as_int(rmax2));        // (non-negative floats order like their bits)
+    lds_barrier();
+    // ---- the clusters that the entries would join as things stand: four entries per wavefront, fetched together
+    int pj[4];
+    ClusterFetch pf[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float zb, z2;
+      pj[i] = -1;
+      if (4 * wave + i < nb) row_best2(zs + (4 * wave + i) * stride, M, lane, zb, pj[i], z2);
+      if (pj[i] >= 0) pf[i] = fetch_cluster(v, u, pj[i], 0, lane);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      ExtendSlot& sl = slot[4 * wave + i];
+      if (pj[i] >= 0) {
+        const ClusterState c = cluster_state(pf[i], 0);
+        sl.r[lane] = c.r;
+        if (lane == 0) { sl.m2 = c.m2; sl.cn = c.cn; sl.cb = c.cb; sl.ctail = c.ctail; sl.cflag = c.cflag; }
+      }
+      if (lane == 0) sl.id = pj[i];
+    }
+    lds_barrier();
+    // ---- the entries one after another
+    if (wave == 0) {
+      const int top0 = us.top;
+      int spare = kExtendBatch, r = 0;
+      float rmax = __builtin_sqrtf(__int_as_float(s_rmax2)) * 1.0001f;
+#pragma unroll 1
+      for (; r < nb; ++r) {
+        float* const row = zs + r * stride;
+        float zb, z2;
+        int j;
+        row_best2(row, M, lane, zb, j, z2);
+        const EntryBits e{uint2{((const uint32_t*)rows[r][0])[lane], 0}, uint2{((const uint32_t*)rows[r][1])[lane], 0}};
+        const float knr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(kn), r));
+        const float eps = kAccBound * (knr * rmax + 0.5f * rmax * rmax) * 1.01f;
+        if (!(zb - z2 > 2.f * eps)) {                  // several within the bound of the best: float64, the lowest id among equals
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (this batch's centroids are in place)
+          const float2 kf = pair_value<DT>(e.k);
+          double best = __builtin_inf();
+          const int j32 = j;
+          j = -1;
+#pragma unroll 1
+          for (int j0 = 0; j0 < M; j0 += 64)
+#pragma unroll 1
+            for (unsigned long long mk = __ballot(j0 + lane < M && row[min(j0 + lane, M - 1)] >= zb - 2.f * eps); mk; mk &= mk - 1) {
+              const int c = j0 + (int)__builtin_ctzll(mk);
+              const float2 rf = pair_value<DT>(uint2{*(const uint32_t*)(unit_Rq(v, u) + rq_index(c, 2 * lane)), 0});
+              const double d0 = (double)kf.x - (double)rf.x, d1 = (double)kf.y - (double)rf.y;
+              const double d = wave_sum_f64(fma(d0, d0, d1 * d1));
+              if (d < best || j < 0) { best = d; j = c; }
+            }
+          if (j < 0) j = max(j32, 0);                  // (an entry that is not finite)
+          if (lane == 0) count(v, u, 7, 1);
+        }
+        // the cluster's slot: the first that holds it
+        const unsigned long long hit = __ballot(lane < kExtendBatch + kExtendSpare && slot[min(lane, kExtendBatch + kExtendSpare - 1)].id == j);
+        int at;
+        if (hit) at = (int)__builtin_ctzll(hit);
+        else {
+          if (spare == kExtendBatch + kExtendSpare) break;       // no slot left: the next batch begins with this entry
+          at = spare++;
+          const ClusterState c = cluster_state(fetch_cluster(v, u, j, 0, lane), 0);      // (not touched in this batch)
+          slot[at].r[lane] = c.r;
+          if (lane == 0) { slot[at].m2 = c.m2; slot[at].cn = c.cn; slot[at].cb = c.cb; slot[at].ctail = c.ctail; slot[at].cflag = c.cflag; slot[at].id = j; }
+          wave_sync();
+        }
+        ExtendSlot& sl = slot[at];
+        ClusterState c{sl.r[lane], sl.cn, sl.cb, sl.ctail, sl.cflag, -1, sl.m2};
+        c.cn = __builtin_amdgcn_readfirstlane(c.cn); c.cb = __builtin_amdgcn_readfirstlane(c.cb);
+        c.ctail = __builtin_amdgcn_readfirstlane(c.ctail); c.cflag = __builtin_amdgcn_readfirstlane(c.cflag);
+        c.free_page = us.top > 0 ? __builtin_amdgcn_readlane(fl, top0 - us.top) : -1;
+        const AppendResult a = append_wave<DT>(v, u, j, us, c, e, lane);
+        if (!a.ok) continue;
+        us.N += 1; us.nflag = a.nflag; us.top = a.top; us.bump = a.bump;
+        if (us.nflag > 0) { ++r; break; }
+        if (a.commit) {
+          sl.r[lane] = a.r;
+          vec[lane] = a.rq;
+          if (lane == 0) { sl.m2 = a.m2; sl.cn = c.cn + 1; sl.ctail = a.page; }
+          wave_sync();
+          uint4 b[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) b[s] = *(const uint4*)((const unsigned char*)vec + 64 * s + 16 * lg);
+          f4 acc = {0, 0, 0, 0}, gram = {0, 0, 0, 0};
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            acc = mfma_k32<BF>(A[s], b[s], acc);
+            gram = mfma_k32<BF>(b[s], b[s], gram);     // (the centroid in every column: |r|^2 everywhere)
+          }
+          rmax = fmaxf(rmax, __builtin_sqrtf(gram[0]) * 1.0001f);
+          if (cl < 4 && 4 * lg + cl < B) zs[(4 * lg + cl) * stride + j] = sel4(acc, cl) - 0.5f * gram[0];
+          wave_sync();
+        }
+      }
+      if (lane == 0) { s_done = r; s_nflag = us.nflag; }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what the batch has stored is in place
+    }
+    __syncthreads();
+    t += s_done;
+    if (s_nflag > 0) {                                 // workgroup-uniform
+      split_unit<DT>(v, u, sp.raw, sp.wk, false);
+      __syncthreads();
+    }
+  }
+  if (tid == 0) v.nflagged[u] = t;                     // how far this kernel came
+}
+
 template <int DT, bool MEAN>
 __global__ __launch_bounds__(256) void extend_kernel(View v, const void* K, const void* V, int n) {
-  __shared__ AppendSmem a;
+  __shared__ double kd[kHeadDim];
   __shared__ double sv[16];
   __shared__ int si[16];
   __shared__ float s2[16];
-  __shared__ int s_rmax2;
-  __shared__ SplitLds<true> sp;
+  __shared__ int s_rmax2, s_nflag;
+  __shared__ SplitLds<DT, true> sp;
   constexpr bool BF = DT == DYNAKV_BF16;
   const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  static_assert(kSplitThreads == 2 * kHeadDim, "one coordinate of the key or of the value per thread");
   // kRows entries' keys and values at a time wait in LDS: one trip to memory for all of them
   constexpr int kRows = 16, kEs = DT == DYNAKV_F32 ? 4 : 2;
   __shared__ __align__(16) unsigned char rows[kRows][2][kHeadDim * kEs];
-  for (int t = 0; t < n; ++t) {
-    const int r = t % kRows;
+  const int t0 = MEAN ? 0 : v.nflagged[u];             // where extend_batch_kernel has stopped
+  for (int t = t0; t < n; ++t) {
+    const int r = (t - t0) % kRows;
     if (r == 0) {                                       // (a full barrier lies behind the last use of the rows)
       uint32_t x[kRows];
 #pragma unroll
@@ -140,7 +383,6 @@ __global__ __launch_bounds__(256) void extend_kernel(View v, const void* K, cons
       for (int i = 0; i < kRows; ++i) store_bits(rows[i][0], tid, x[i], DT);
       lds_barrier();
     }
-    const uint32_t held = load_bits(rows[r][0], tid, DT);
     constexpr int kBatch = 4;
     const uint4* tiles = MEAN ? nullptr : (const uint4*)unit_Rq(v, u);
     const int table_tiles = (int)(v.Rstride / kTileElems);   // the table's padded end: these rows exist in every state
@@ -158,15 +400,16 @@ __global__ __launch_bounds__(256) void extend_kernel(View v, const void* K, cons
       fetch(cur, wave);
       load_score_rows<1>(A, 0, nullptr, rows[r][0], 0, lane);    // row 0 = the entry
     }
-    const int M = v.M[u], N = v.N[u], top = v.free_top[u];
-    if (N >= v.Ncap || M <= 0) {                       // workgroup-uniform
+    const UnitState us = load_unit(v, u);
+    const int M = us.M;
+    if (us.N >= v.Ncap || M <= 0) {                    // workgroup-uniform
       if (tid == 0) v.err[u] |= DYNAKV_ERR_TOKENS;
       return;
     }
     float k2 = 0.f;
     if (tid < kHeadDim) {
-      const float kf = bits_value(held, v.dtype);
-      a.kd[tid] = (double)kf;
+      const float kf = bits_value(load_bits(rows[r][0], tid, DT), DT);
+      kd[tid] = (double)kf;
       k2 = kf * kf;
     }
     if (tid == 0) s_rmax2 = 0;
@@ -181,7 +424,7 @@ __global__ __launch_bounds__(256) void extend_kernel(View v, const void* K, cons
         double dist[1];
         load_centroid_head(R, jj, row);
         centroid_sums<1>(R, jj, row, dist, [&](int d, float rv, double (&acc)[1]) __attribute__((always_inline)) {
-          const double x = a.kd[d] - (double)rv;
+          const double x = kd[d] - (double)rv;
           acc[0] = fma(x, x, acc[0]);
         });
         if (dist[0] < best || arg < 0) { best = dist[0]; arg = jj; }
@@ -224,12 +467,18 @@ __global__ __launch_bounds__(256) void extend_kernel(View v, const void* K, cons
       if (lane == 0) atomicMax(&s_rmax2, __float_as_int(rmax2));
       lds_barrier();                                    // (nearest_resolve waits for zd itself if it needs it)
       const float kn = __builtin_sqrtf(s2[0] + s2[1]) * 1.0001f;
-      j = nearest_resolve<256>(v, u, M, zb, jb, z2, kn, __int_as_float(s_rmax2), zd, unit_Rq(v, u), a.kd, sv, si, s2);
+      j = nearest_resolve<256>(v, u, M, zb, jb, z2, kn, __int_as_float(s_rmax2), zd, unit_Rq(v, u), kd, sv, si, s2);
     }
-    const AppendFetch f = append_fetch(v, u, j, top);
-    append_commit<256, true>(v, u, j, M, N, nullptr, nullptr, a, f, held);
+    if (wave == 0) {
+      const ClusterFetch cf = fetch_cluster(v, u, j, us.top, lane);
+      EntryBits e;
+      if constexpr (DT == DYNAKV_F32) { e.k = ((const uint2*)rows[r][0])[lane]; e.v = ((const uint2*)rows[r][1])[lane]; }
+      else { e.k = uint2{((const uint32_t*)rows[r][0])[lane], 0}; e.v = uint2{((const uint32_t*)rows[r][1])[lane], 0}; }
+      const AppendResult a = append_wave<DT>(v, u, j, us, cluster_state(cf, us.top), e, lane);
+      if (lane == 0) s_nflag = a.nflag;
+    }
     __syncthreads();                                    // the append's record is in place for the whole workgroup
-    if (a.nflag1 == 0) continue;                        // workgroup-uniform (and nothing above writes it before a barrier)
+    if (s_nflag == 0) continue;                         // workgroup-uniform (and nothing above writes it before a barrier)
     split_unit<DT>(v, u, sp.raw, sp.wk, false);
     __syncthreads();                                    // and the unit's counters for the next entry
   }
@@ -399,7 +648,7 @@ __global__ __launch_bounds__(256) void local_recluster_kernel(View v, int iters)
 // ------------------------------------------------------------------------------------------- split
 template <int DT>
 __global__ __launch_bounds__(kSplitThreads) void split_kernel(View v) {
-  __shared__ __align__(16) unsigned char raw[kSplitRaw];
+  __shared__ __align__(16) unsigned char raw[kSplitRaw<DT>];
   __shared__ SplitWork wk;
   split_unit<DT>(v, blockIdx.x, raw, wk, false);
 }
@@ -447,10 +696,16 @@ hipError_t launch_extend(const View& v, const void* K, const void* V, int n, hip
   if (v.dtype == DYNAKV_F32) extend_kernel<DYNAKV_F32, true><<<v.U, 256, 0, st>>>(v, K, V, n);
   else if (v.dtype == DYNAKV_F16) {
     if (v.search_mean) extend_kernel<DYNAKV_F16, true><<<v.U, 256, 0, st>>>(v, K, V, n);
-    else extend_kernel<DYNAKV_F16, false><<<v.U, 256, 0, st>>>(v, K, V, n);
+    else {
+      extend_batch_kernel<DYNAKV_F16><<<v.U, 256, 0, st>>>(v, K, V, n);
+      if (v.Mcap > kExtendClusters) extend_kernel<DYNAKV_F16, false><<<v.U, 256, 0, st>>>(v, K, V, n);
+    }
   } else {
     if (v.search_mean) extend_kernel<DYNAKV_BF16, true><<<v.U, 256, 0, st>>>(v, K, V, n);
-    else extend_kernel<DYNAKV_BF16, false><<<v.U, 256, 0, st>>>(v, K, V, n);
+    else {
+      extend_batch_kernel<DYNAKV_BF16><<<v.U, 256, 0, st>>>(v, K, V, n);
+      if (v.Mcap > kExtendClusters) extend_kernel<DYNAKV_BF16, false><<<v.U, 256, 0, st>>>(v, K, V, n);
+    }
   }
   return hipGetLastError();
 }

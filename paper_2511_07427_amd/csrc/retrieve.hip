@@ -1279,7 +1279,7 @@ constexpr int kFusedList = 2048;       // gather-list entries it keeps in LDS (l
 // With SPLIT (only with APPEND) the unit's due splits are part of the same launch: a whole decode step is then
 // one kernel.  The splits are planned right after the append; while the pages are streamed, the first wavefronts,
 // one per due split (up to kWaveSplits), decide their split instead of streaming, which only reads the index;
-// these splits are written while the attention output is merged, and whatever is left (recycling the parents'
+// these splits are written by all wavefronts after the merge of the attention output, and whatever is left (recycling the parents'
 // pages, further splits, the workgroup-wide path for large clusters) is carried out by the first kSplitThreads
 // threads, once the others have left.
 template <int DT, int NW, int GP, bool APPEND, bool SPLIT>
@@ -1298,10 +1298,11 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   // the split's LDS follows everything the streaming uses: its wavefront contexts are filled meanwhile
   constexpr int kPreSplits = kWaveSplits;              // splits decided while the pages are streamed
   constexpr size_t kRawOff = SPLIT ? (kPhases + 15) / 16 * 16 : 0;
-  static_assert(!SPLIT || kRawOff + kSplitRaw + 16 * 1024 <= 160 * 1024, "LDS of one compute unit");
-  __shared__ __align__(16) unsigned char smem[SPLIT ? kRawOff + kSplitRaw : kPhases];
+  static_assert(!SPLIT || kRawOff + kSplitRaw<DT> + 16 * 1024 <= 160 * 1024, "LDS of one compute unit");
+  __shared__ __align__(16) unsigned char smem[SPLIT ? kRawOff + kSplitRaw<DT> : kPhases];
   __shared__ SplitWork wk;
-  __shared__ AppendSmem ap;
+  __shared__ double kd[kHeadDim];                     // the new key
+  __shared__ UnitState s_unit;                        // the unit before the append (kept in LDS until the selection is done)
   __shared__ double am_v[16];
   __shared__ int am_i[16];
   __shared__ float am_2[16];
@@ -1337,16 +1338,14 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
     }
   };
   fetch(cur, wave);                                   // requested before anything is waited for
-  // the flagged list and the free-page stack as they are before this step's append: the plan of the splits
-  // starts from them
-  int flagged0 = 0, nflag0 = 0, top0 = 0;            // kept in LDS (wk) until the selection is done
+  // the unit's counters and its flagged list as they are before this step's append: the append and the plan of the splits
+  // start from them
+  int flagged0 = 0;
   if constexpr (SPLIT)
-    if (wave == 0) {
-      if (lane < v.Mcap) flagged0 = v.flist[(size_t)u * v.Mcap + lane];
-      nflag0 = v.nflag[u];
-      top0 = v.free_top[u];
-    }
-  const int M = v.M[u];
+    if (wave == 0 && lane < v.Mcap) flagged0 = v.flist[(size_t)u * v.Mcap + lane];
+  UnitState us{v.M[u], 0, 0, 0, 0, 0.0};
+  if constexpr (APPEND) us = load_unit(v, u);
+  const int M = us.M;
   // stored sizes, requested for every cluster slot of the unit so that the requests do not wait for M
   int szr[kFusedClusters / NT];
 #pragma unroll
@@ -1356,9 +1355,8 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   }
   ScoreRows<1> A;
   load_score_rows<1>(A, G, Q, APPEND ? kin : nullptr, u, lane);
-  const int N = APPEND ? v.N[u] : 0;
-  const bool room = APPEND && N < v.Ncap && M > 0;     // otherwise the append is refused, as by the append kernel
-  if (APPEND && tid < kHeadDim) ap.kd[tid] = (double)load_elem(kin, (size_t)u * kHeadDim + tid, v.dtype);
+  const bool room = APPEND && us.N < v.Ncap && M > 0;     // otherwise the append is refused, as by the append kernel
+  if (APPEND && tid < kHeadDim) kd[tid] = (double)load_elem(kin, (size_t)u * kHeadDim + tid, v.dtype);
   int Mpad = 2;
   while (Mpad < M) Mpad <<= 1;
   for (int i = M + tid; i < Mpad; i += NT) skey[i] = 0u;
@@ -1370,10 +1368,9 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   for (int k = 0; k < kFusedClusters / NT; ++k)
     if (tid + k * NT < M) ssz[tid + k * NT] = szr[k];
   if constexpr (SPLIT)
-    if (wave == 0) {
-      wk.flagged0[lane] = flagged0;
-      if (lane == 0) { wk.nflag0 = nflag0; wk.top0 = top0; }
-    }
+    if (wave == 0) wk.flagged0[lane] = flagged0;
+  if constexpr (APPEND)
+    if (tid == 0) s_unit = us;
   const RowNorms rn = row_norms<BF, 1>(A, G, v.group_reduce, lane);
   lds_barrier();
   float zb = -__builtin_inff(), z2 = -__builtin_inff(), rmax2 = 0.f;
@@ -1427,10 +1424,14 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   const float unit_rmax2 = __int_as_float(rmu);
   // the append's nearest cluster: its record is requested here and used after the selection
   int ja = -1;
-  AppendFetchWave apf{0.0, 0.0, 0.0, 0, 0};
+  ClusterFetch apf{float2{0.f, 0.f}, 0};
+  EntryBits entry{uint2{0, 0}, uint2{0, 0}};
   if constexpr (APPEND) {
-    ja = nearest_decide<NT>(v, u, M, rn.kn, unit_rmax2, v.zdist + (size_t)u * v.Mcap, Rq, ap.kd, am_v, am_i, am_2);
-    if (room && wave == 0) apf = append_fetch_wave(v, u, ja);       // the first wavefront will carry out the append
+    ja = nearest_decide<NT>(v, u, M, rn.kn, unit_rmax2, v.zdist + (size_t)u * v.Mcap, Rq, kd, am_v, am_i, am_2);
+    if (room && wave == 0) {                          // the first wavefront will carry out the append
+      apf = fetch_cluster(v, u, ja, us.top, lane);
+      entry = load_entry<DT>(kin, vin, u, lane);
+    }
   }
 
   // ---- selection
@@ -1465,17 +1466,25 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   bool decides = false;                                // this wavefront decides a split instead of streaming
   if constexpr (APPEND) {
     if (wave == 0) {
+      us = s_unit;
       PlanEarly pe{};
       if constexpr (SPLIT) {
-        flagged0 = wk.flagged0[lane]; nflag0 = wk.nflag0; top0 = wk.top0;
-        pe = plan_fetch_early(v, u, flagged0, nflag0, top0, room ? ja : -1, lane, selbits);
+        flagged0 = wk.flagged0[lane];
+        pe = plan_fetch_early(v, u, flagged0, us, room ? ja : -1, lane, selbits);
       }
-      if (room) append_commit_wave(v, u, ja, M, N, kin, vin, ap, apf);
-      else if (lane == 0) v.err[u] |= DYNAKV_ERR_TOKENS;
+      AppendResult res{};
+      int sz0 = 0;
+      if (room) {
+        const ClusterState cs = cluster_state(apf, us.top);
+        res = append_wave<DT>(v, u, ja, us, cs, entry, lane);
+        sz0 = cs.cn + cs.cb;
+      } else if (lane == 0) {
+        v.err[u] |= DYNAKV_ERR_TOKENS;
+      }
       if constexpr (SPLIT) {
-        wave_sync();
-        plan_finish<DT>(v, wk, pe, nflag0, top0, M, ja, room ? &ap : nullptr, kPreSplits);
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");     // plan and appended entry before the flag
+        if (plan_finish<DT>(v, wk, pe, us, ja, room, res, sz0, kPreSplits))
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // the appended entry before the flag
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (lane == 0) __hip_atomic_store(&wk.ready, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         decides = wk.npre > 0;
       }
@@ -1546,23 +1555,24 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
       for (int i = 0; i < 4; ++i) o[F::out_col(c, 4 * lg + i)] = st.acc[c][i];
     if (lg == 0) { o[kHeadDim] = st.m; o[kHeadDim + 1] = l; }
   }
-  // the splits decided meanwhile get their ids and pages in plan order (one thread) ...
+  // the splits decided meanwhile get their ids and pages in plan order (first wavefront) ...
   if constexpr (SPLIT)
-    if (tid == 0 && nprep > 0) split_assign(v, u, (WaveCtx*)(smem + kRawOff), wk.pl, nprep);
+    if (wave == 0 && nprep > 0) split_assign(v, u, (WaveCtx*)(smem + kRawOff), wk.pl, nprep);
   lds_barrier();
-  if (SPLIT && wave < nprep) {
-    // ... and are written by the wavefronts that decided them, while the others merge the attention output
-    wave_split_commit<DT>(v, u, ((WaveCtx*)(smem + kRawOff))[ctx_of(wave)], pre_v, true);
-  } else {
-    for (int t = tid - nprep * 64; t < G * kHeadDim; t += NT - nprep * 64) {
-      const int gg = t / kHeadDim, dc = t % kHeadDim;
-      const float* b = sm_o + gg * hs;
-      float Mx, L, O;
-      merge_partials(b + kHeadDim, b + kHeadDim + 1, b + dc, NW, ws, Mx, L, O);
-      out[((size_t)u * G + gg) * kHeadDim + dc] = L > 0.f ? O / L : 0.f;
-      if (lse && dc == 0) lse[(size_t)u * G + gg] = L > 0.f ? (Mx + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
-    }
+  // ... and are written by everybody, before and after the merge of the attention output: first the values that the wavefronts
+  // which decided them hold in registers
+  if constexpr (SPLIT)
+    if (wave < nprep) wave_split_commit_ahead<DT>(v, u, ((WaveCtx*)(smem + kRawOff))[ctx_of(wave)], 0, 1, pre_v);
+  for (int t = tid; t < G * kHeadDim; t += NT) {
+    const int gg = t / kHeadDim, dc = t % kHeadDim;
+    const float* b = sm_o + gg * hs;
+    float Mx, L, O;
+    merge_partials(b + kHeadDim, b + kHeadDim + 1, b + dc, NW, ws, Mx, L, O);
+    out[((size_t)u * G + gg) * kHeadDim + dc] = L > 0.f ? O / L : 0.f;
+    if (lse && dc == 0) lse[(size_t)u * G + gg] = L > 0.f ? (Mx + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
   }
+  if constexpr (SPLIT)
+    for (int k = 0; k < nprep; ++k) wave_split_commit<DT>(v, u, ((WaveCtx*)(smem + kRawOff))[ctx_of(k)], 1, wave, NW);
   if constexpr (SPLIT) {
     __syncthreads();                                 // every use of smem lies behind
     if (tid >= kSplitThreads) return;                // barriers from here on count the remaining wavefronts only

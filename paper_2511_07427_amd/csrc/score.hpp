@@ -236,7 +236,7 @@ __device__ inline int nearest_decide(const View& v, int u, int M, float kn, floa
       if (arg < 0 || dj < best) { best = dj; arg = j; }
     }
   if (threadIdx.x == 0) count(v, u, 7, 1);
-  return block_argmin<NT>(best, arg, sv, si);
+  return max(block_argmin<NT>(best, arg, sv, si), 0);      // (a key that is not finite is near nothing)
 }
 template <int NT>
 __device__ inline int nearest_resolve(const View& v, int u, int M, float zb, int jb, float z2, float kn, float rmax2,
