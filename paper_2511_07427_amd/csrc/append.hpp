@@ -209,17 +209,33 @@ __device__ __forceinline__ AppendResult append_wave(const View& v, int u, int j,
   }
   return a;
 }
-// Workgroup-wide arg-min over (value, index) pairs, one per thread (index < 0: none); equal values go to the
-// lowest index.  NT / 64 <= 16 wavefronts; sv / si need 16 entries.  Every thread gets the winning index.
+// Arg-min over (value, index) pairs, one per lane (index < 0: none); equal values go to the lowest index.  Every lane gets it.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double min_step(double x) {             // a lane that the step does not reach sees its own value
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(x), __double2loint(x), CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(x), __double2hiint(x), CTRL, ROWS, 0xF, false);
+  return fmin(x, __hiloint2double(hi, lo));
+}
+__device__ __forceinline__ void wave_argmin(double& val, int& idx) {
+  double m = idx >= 0 ? val : __builtin_inf();
+  m = min_step<kDppXor1, 0xF>(m);
+  m = min_step<kDppXor2, 0xF>(m);
+  m = min_step<kDppHalfMirror, 0xF>(m);
+  m = min_step<kDppMirror, 0xF>(m);
+  m = min_step<kDppBcast15, 0xA>(m);
+  m = min_step<kDppBcast31, 0xC>(m);
+  m = readlane_f64(m, 63);
+  unsigned long long who = __ballot(idx >= 0 && val == m);
+  if (who == 0) who = __ballot(idx >= 0);                          // (nothing but numbers that are none)
+  const bool mine = (who >> (threadIdx.x & 63)) & 1ull;
+  idx = who ? wave_min(mine ? idx : 0x7FFFFFFE) : -1;
+  val = m;
+}
+// The same over a workgroup of NT threads.  NT / 64 <= 16 wavefronts; sv / si need 16 entries.  Every thread gets the winning index.
 template <int NT>
 __device__ inline int block_argmin(double val, int idx, double* sv, int* si) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const double ov = __shfl_xor(val, o);
-    const int oi = __shfl_xor(idx, o);
-    if (oi >= 0 && (idx < 0 || ov < val || (ov == val && oi < idx))) { val = ov; idx = oi; }
-  }
+  wave_argmin(val, idx);
   lds_barrier();
   if (lane == 0) { sv[w] = val; si[w] = idx; }
   lds_barrier();

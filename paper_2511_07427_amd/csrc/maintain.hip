@@ -135,14 +135,17 @@ __global__ __launch_bounds__(256) void append_kernel(View v, const void* kin, co
 // fetched together into slots of LDS.  The entries are then taken one after another by the first wavefront with no
 // trip to memory: nearest cluster from the entry's row of z (float64 where the runner-up lies within the rounding bound), UpdateVar and
 // threshold on the slot, and one matrix product of the new centroid with the entries to come, which corrects their z of that
-// cluster.  A cluster outside the slots is fetched when it is met; a flag ends the batch, its split is carried out by the whole
-// workgroup, and the next batch begins.  LDS holds z of kExtendClusters clusters for one entry, of a sixteenth of that for sixteen.
-// 256 units, 256 clusters, 1024 entries (163 splits a unit): 10.3 -> 7.3 ms.
+// cluster.  A cluster outside the slots is fetched when it is met; a flag calls the whole workgroup for the split, after which the
+// z of the two clusters that it leaves are put right in the same way.  LDS holds z of kExtendClusters clusters for one entry, of a
+// sixteenth of that for sixteen.
+// 256 units, 256 clusters, 1024 entries (163 splits a unit): 10.3 -> 4.8 ms, of which an entry takes 2.1 us where nothing is
+// flagged (6.6).
 //
 // extend_kernel (float32 means; more clusters than that): one entry per pass over the table, the table in batches of four tiles
 // per wavefront with the next batch in flight.
 constexpr int kExtendBatch = 16, kExtendSpare = 8, kExtendZ = 10240;      // entries per batch, slots beyond them, floats of z
-constexpr int kExtendClusters = kExtendZ - 4;                             // (one entry's row, and the cluster it may add)
+constexpr int kExtendRoom = kExtendBatch;                                 // clusters that a batch may add
+constexpr int kExtendClusters = kExtendZ - kExtendRoom - 4;
 static_assert(kSplitThreads == 2 * kHeadDim, "one coordinate of the key or of the value per thread");
 
 // What the extension holds of a cluster in LDS.
@@ -158,11 +161,11 @@ __device__ __forceinline__ void row_best2(const float* row, int M, int lane, flo
 #pragma unroll 1
   for (int j0 = 4 * lane; j0 < M; j0 += 256) {
     const f4 z = *(const f4*)(row + j0);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (j0 + e < M && (jb < 0 || z[e] > zb)) { z2 = jb < 0 ? z2 : zb; zb = z[e]; jb = j0 + e; }      // ascending: the first maximum stays
-      else z2 = fmaxf(z2, z[e]);
-    }
+    const float hi01 = fmaxf(z[0], z[1]), lo01 = fminf(z[0], z[1]), hi23 = fmaxf(z[2], z[3]), lo23 = fminf(z[2], z[3]);
+    const float hi = fmaxf(hi01, hi23), next = fmaxf(fminf(hi01, hi23), hi01 >= hi23 ? lo01 : lo23);
+    const int at = j0 + (hi == z[0] ? 0 : hi == z[1] ? 1 : hi == z[2] ? 2 : 3);
+    z2 = fmaxf(fminf(zb, hi), fmaxf(z2, next));
+    if (jb < 0 || hi > zb) { zb = hi; jb = min(at, M - 1); }
   }
   wave_best2(zb, jb, z2);
 }
@@ -175,8 +178,8 @@ __global__ __launch_bounds__(256) void extend_batch_kernel(View v, const void* K
   __shared__ __align__(16) float zs[kExtendZ];
   __shared__ __align__(16) ExtendSlot slot[kExtendBatch + kExtendSpare];
   __shared__ __align__(16) unsigned char rows[kExtendBatch][2][kHeadDim * 2];
-  __shared__ __align__(16) uint32_t vec[kHeadDim / 2];
-  __shared__ int s_rmax2, s_done, s_nflag;
+  __shared__ __align__(16) uint32_t vec[2][kHeadDim / 2];
+  __shared__ int s_rmax2, s_done, s_nflag, s_j, s_at, s_planned;
   const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, cl = lane & 15;
   const uint4* tiles = (const uint4*)unit_Rq(v, u);
   int t = 0;
@@ -191,14 +194,15 @@ __global__ __launch_bounds__(256) void extend_batch_kernel(View v, const void* K
     }
     if (M > kExtendClusters) break;
     int B = kExtendBatch;
-    while (B > 1 && B * ((M + 3) & ~3) > kExtendZ) B >>= 1;
-    const int stride = (M + 3) & ~3, nb = min(min(B, n - t), v.Ncap - us.N);
+    const int stride = (M + kExtendRoom + 3) & ~3;
+    while (B > 1 && B * stride > kExtendZ) B >>= 1;
+    const int nb = min(min(B, n - t), v.Ncap - us.N);
     // ---- the entries, and z of every cluster
     uint32_t x[kExtendBatch];
 #pragma unroll
     for (int i = 0; i < kExtendBatch; ++i)
       x[i] = ((const uint16_t*)(tid < kHeadDim ? K : V))[((size_t)u * n + min(t + i, n - 1)) * kHeadDim + (tid & (kHeadDim - 1))];
-    const int fl = us.top - 1 - lane >= 0 ? v.freelist[(size_t)u * v.Pcap + us.top - 1 - lane] : -1;      // the top of the free stack
+    int fl = us.top - 1 - lane >= 0 ? v.freelist[(size_t)u * v.Pcap + us.top - 1 - lane] : -1;      // the top of the free stack
 #pragma unroll
     for (int i = 0; i < kExtendBatch; ++i) ((uint16_t*)rows[i][0])[tid] = (uint16_t)x[i];
     if (tid == 0) s_rmax2 = 0;
@@ -248,7 +252,10 @@ __global__ __launch_bounds__(256) void extend_batch_kernel(View v, const void* K
           if (4 * lg + i < B) zs[(4 * lg + i) * stride + j] = acc[k][i] - 0.5f * nrm2;
       }
     }
-    if (tid < B * 4 && M + (tid & 3) < stride) zs[(tid >> 2) * stride + M + (tid & 3)] = -__builtin_inff();
+    for (int i = tid; i < B * (kExtendRoom + 4); i += 256) {
+      const int j = M + i % (kExtendRoom + 4);
+      if (j < stride) zs[i / (kExtendRoom + 4) * stride + j] = -__builtin_inff();
+    }
     atomicMax(&s_rmax2, __float_as_int(rmax2));        // (non-negative floats order like their bits)
     lds_barrier();
     // ---- the clusters that the entries would join as things stand: four entries per wavefront, fetched together
@@ -273,87 +280,135 @@ __global__ __launch_bounds__(256) void extend_batch_kernel(View v, const void* K
     }
     lds_barrier();
     // ---- the entries one after another
-    if (wave == 0) {
-      const int top0 = us.top;
-      int spare = kExtendBatch, r = 0;
-      float rmax = __builtin_sqrtf(__int_as_float(s_rmax2)) * 1.0001f;
-#pragma unroll 1
-      for (; r < nb; ++r) {
-        float* const row = zs + r * stride;
-        float zb, z2;
-        int j;
-        row_best2(row, M, lane, zb, j, z2);
-        const EntryBits e{uint2{((const uint32_t*)rows[r][0])[lane], 0}, uint2{((const uint32_t*)rows[r][1])[lane], 0}};
-        const float knr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(kn), r));
-        const float eps = kAccBound * (knr * rmax + 0.5f * rmax * rmax) * 1.01f;
-        if (!(zb - z2 > 2.f * eps)) {                  // several within the bound of the best: float64, the lowest id among equals
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (this batch's centroids are in place)
-          const float2 kf = pair_value<DT>(e.k);
-          double best = __builtin_inf();
-          const int j32 = j;
-          j = -1;
-#pragma unroll 1
-          for (int j0 = 0; j0 < M; j0 += 64)
-#pragma unroll 1
-            for (unsigned long long mk = __ballot(j0 + lane < M && row[min(j0 + lane, M - 1)] >= zb - 2.f * eps); mk; mk &= mk - 1) {
-              const int c = j0 + (int)__builtin_ctzll(mk);
-              const float2 rf = pair_value<DT>(uint2{*(const uint32_t*)(unit_Rq(v, u) + rq_index(c, 2 * lane)), 0});
-              const double d0 = (double)kf.x - (double)rf.x, d1 = (double)kf.y - (double)rf.y;
-              const double d = wave_sum_f64(fma(d0, d0, d1 * d1));
-              if (d < best || j < 0) { best = d; j = c; }
-            }
-          if (j < 0) j = max(j32, 0);                  // (an entry that is not finite)
-          if (lane == 0) count(v, u, 7, 1);
-        }
-        // the cluster's slot: the first that holds it
-        const unsigned long long hit = __ballot(lane < kExtendBatch + kExtendSpare && slot[min(lane, kExtendBatch + kExtendSpare - 1)].id == j);
-        int at;
-        if (hit) at = (int)__builtin_ctzll(hit);
-        else {
-          if (spare == kExtendBatch + kExtendSpare) break;       // no slot left: the next batch begins with this entry
-          at = spare++;
-          const ClusterState c = cluster_state(fetch_cluster(v, u, j, 0, lane), 0);      // (not touched in this batch)
-          slot[at].r[lane] = c.r;
-          if (lane == 0) { slot[at].m2 = c.m2; slot[at].cn = c.cn; slot[at].cb = c.cb; slot[at].ctail = c.ctail; slot[at].cflag = c.cflag; slot[at].id = j; }
-          wave_sync();
-        }
-        ExtendSlot& sl = slot[at];
-        ClusterState c{sl.r[lane], sl.cn, sl.cb, sl.ctail, sl.cflag, -1, sl.m2};
-        c.cn = __builtin_amdgcn_readfirstlane(c.cn); c.cb = __builtin_amdgcn_readfirstlane(c.cb);
-        c.ctail = __builtin_amdgcn_readfirstlane(c.ctail); c.cflag = __builtin_amdgcn_readfirstlane(c.cflag);
-        c.free_page = us.top > 0 ? __builtin_amdgcn_readlane(fl, top0 - us.top) : -1;
-        const AppendResult a = append_wave<DT>(v, u, j, us, c, e, lane);
-        if (!a.ok) continue;
-        us.N += 1; us.nflag = a.nflag; us.top = a.top; us.bump = a.bump;
-        if (us.nflag > 0) { ++r; break; }
-        if (a.commit) {
-          sl.r[lane] = a.r;
-          vec[lane] = a.rq;
-          if (lane == 0) { sl.m2 = a.m2; sl.cn = c.cn + 1; sl.ctail = a.page; }
-          wave_sync();
+    int r = 0, spare = kExtendBatch, Mz = M;             // entries done, slots in use, clusters in z (first wavefront)
+    float rmax = __builtin_sqrtf(__int_as_float(s_rmax2)) * 1.0001f;
+    while (true) {
+      if (wave == 0) {
+        const int top0 = us.top;
+        // z of the clusters whose search copies are in vec: columns of even number the first, of odd number the second
+        auto correct = [&](int ja, int jb) __attribute__((always_inline)) {
           uint4 b[4];
 #pragma unroll
-          for (int s = 0; s < 4; ++s) b[s] = *(const uint4*)((const unsigned char*)vec + 64 * s + 16 * lg);
+          for (int s = 0; s < 4; ++s) b[s] = *(const uint4*)((const unsigned char*)vec[lane & 1] + 64 * s + 16 * lg);
           f4 acc = {0, 0, 0, 0}, gram = {0, 0, 0, 0};
 #pragma unroll
           for (int s = 0; s < 4; ++s) {
             acc = mfma_k32<BF>(A[s], b[s], acc);
-            gram = mfma_k32<BF>(b[s], b[s], gram);     // (the centroid in every column: |r|^2 everywhere)
+            gram = mfma_k32<BF>(b[s], b[s], gram);       // row and column of the same parity: |r|^2
           }
-          rmax = fmaxf(rmax, __builtin_sqrtf(gram[0]) * 1.0001f);
-          if (cl < 4 && 4 * lg + cl < B) zs[(4 * lg + cl) * stride + j] = sel4(acc, cl) - 0.5f * gram[0];
+          const float nrm2 = (cl & 1) ? gram[1] : gram[0];
+          const int j = (cl & 1) ? jb : ja, e = 4 * lg + (cl >> 1);
+          if (cl < 8 && e < B && j >= 0) zs[e * stride + j] = sel4(acc, cl >> 1) - 0.5f * nrm2;
+          // (lanes 0 and 1 hold the two norms: the bound must be the same in every lane)
+          const float na = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(nrm2), 0));
+          const float nb2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(nrm2), 1));
+          rmax = fmaxf(rmax, __builtin_sqrtf(fmaxf(na, nb2)) * 1.0001f);
           wave_sync();
+        };
+        if (r > 0) {                                     // back from a split: what it has left of cluster s_j and the one it may have added
+          const int j = s_j, jn = us.M > Mz ? Mz : -1;
+          const ClusterFetch fa = fetch_cluster(v, u, j, 0, lane), fb = fetch_cluster(v, u, max(jn, 0), 0, lane);
+          vec[0][lane] = *(const uint32_t*)(unit_Rq(v, u) + rq_index(j, 2 * lane));
+          vec[1][lane] = *(const uint32_t*)(unit_Rq(v, u) + rq_index(jn >= 0 ? jn : j, 2 * lane));
+          const ClusterState ca = cluster_state(fa, 0), cb = cluster_state(fb, 0);
+          ExtendSlot& sa = slot[s_at];
+          sa.r[lane] = ca.r;
+          if (lane == 0) { sa.m2 = ca.m2; sa.cn = ca.cn; sa.cb = ca.cb; sa.ctail = ca.ctail; sa.cflag = ca.cflag; }
+          if (jn >= 0 && spare < kExtendBatch + kExtendSpare) {
+            ExtendSlot& sb = slot[spare++];
+            sb.r[lane] = cb.r;
+            if (lane == 0) { sb.m2 = cb.m2; sb.cn = cb.cn; sb.cb = cb.cb; sb.ctail = cb.ctail; sb.cflag = cb.cflag; sb.id = jn; }
+          }
+          wave_sync();
+          correct(j, jn);
+          Mz = us.M;
         }
+        bool planned = false;
+        int j = -1, at = 0;
+#pragma unroll 1
+        for (; r < nb; ++r) {
+          float* const row = zs + r * stride;
+          float zb, z2;
+          row_best2(row, Mz, lane, zb, j, z2);
+          const EntryBits e{uint2{((const uint32_t*)rows[r][0])[lane], 0}, uint2{((const uint32_t*)rows[r][1])[lane], 0}};
+          const float knr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(kn), r));
+          const float eps = kAccBound * (knr * rmax + 0.5f * rmax * rmax) * 1.01f;
+          if (!(zb - z2 > 2.f * eps)) {                  // several within the bound of the best: float64, the lowest id among equals
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (this batch's centroids are in place)
+            const float2 kf = pair_value<DT>(e.k);
+            double best = __builtin_inf();
+            const int j32 = j;
+            j = -1;
+#pragma unroll 1
+            for (int j0 = 0; j0 < Mz; j0 += 64)
+#pragma unroll 1
+              for (unsigned long long mk = __ballot(j0 + lane < Mz && row[min(j0 + lane, Mz - 1)] >= zb - 2.f * eps); mk; mk &= mk - 1) {
+                const int c = j0 + (int)__builtin_ctzll(mk);
+                const float2 rf = pair_value<DT>(uint2{*(const uint32_t*)(unit_Rq(v, u) + rq_index(c, 2 * lane)), 0});
+                const double d0 = (double)kf.x - (double)rf.x, d1 = (double)kf.y - (double)rf.y;
+                const double d = wave_sum_f64(fma(d0, d0, d1 * d1));
+                if (d < best || j < 0) { best = d; j = c; }
+              }
+            if (j < 0) j = max(j32, 0);                  // (an entry that is not finite)
+            if (lane == 0) count(v, u, 7, 1);
+          }
+          // the cluster's slot: the first that holds it
+          const unsigned long long hit = __ballot(lane < kExtendBatch + kExtendSpare && slot[min(lane, kExtendBatch + kExtendSpare - 1)].id == j);
+          if (hit) at = (int)__builtin_ctzll(hit);
+          else {
+            if (spare == kExtendBatch + kExtendSpare) break;       // no slot left: the next batch begins with this entry
+            at = spare++;
+            const ClusterState c = cluster_state(fetch_cluster(v, u, j, 0, lane), 0);      // (not touched in this batch)
+            slot[at].r[lane] = c.r;
+            if (lane == 0) { slot[at].m2 = c.m2; slot[at].cn = c.cn; slot[at].cb = c.cb; slot[at].ctail = c.ctail; slot[at].cflag = c.cflag; slot[at].id = j; }
+            wave_sync();
+          }
+          ExtendSlot& sl = slot[at];
+          ClusterState c{sl.r[lane], sl.cn, sl.cb, sl.ctail, sl.cflag, -1, sl.m2};
+          c.cn = __builtin_amdgcn_readfirstlane(c.cn); c.cb = __builtin_amdgcn_readfirstlane(c.cb);
+          c.ctail = __builtin_amdgcn_readfirstlane(c.ctail); c.cflag = __builtin_amdgcn_readfirstlane(c.cflag);
+          c.free_page = us.top > 0 ? __builtin_amdgcn_readlane(fl, top0 - us.top) : -1;
+          const AppendResult a = append_wave<DT>(v, u, j, us, c, e, lane);
+          if (!a.ok) continue;
+          if (a.nflag > 0) {                             // its split follows at once
+            if (us.nflag == 0) {                         // (the plan, where this flag is the only one)
+              PlanEarly pe{-1, 0, 0, 0, __shfl(fl, min(lane + top0 - us.top, 63)), int4{-1, -1, -1, -1}, int4{-1, -1, -1, -1}};
+              if (lane == 0) {
+                const int4* pg = (const int4*)&v.cpg[((size_t)u * v.Mcap + j) * kInlinePages];
+                pe.id = j; pe.cn = c.cn; pe.pg = pg[0]; pe.pg2 = pg[1];
+              }
+              plan_finish<DT>(v, sp.wk, pe, us, j, true, a, c.cn + c.cb, 0);
+              planned = true;
+            }
+            us.nflag = a.nflag;
+            ++r;
+            break;
+          }
+          us.N += 1; us.top = a.top; us.bump = a.bump;
+          if (a.commit) {
+            sl.r[lane] = a.r;
+            vec[0][lane] = a.rq; vec[1][lane] = a.rq;
+            if (lane == 0) { sl.m2 = a.m2; sl.cn = c.cn + 1; sl.ctail = a.page; }
+            wave_sync();
+            correct(j, -1);
+          }
+        }
+        if (lane == 0) { s_done = r; s_nflag = us.nflag; s_j = j; s_at = at; s_planned = planned; }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what was stored is in place
       }
-      if (lane == 0) { s_done = r; s_nflag = us.nflag; }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // what the batch has stored is in place
-    }
-    __syncthreads();
-    t += s_done;
-    if (s_nflag > 0) {                                 // workgroup-uniform
-      split_unit<DT>(v, u, sp.raw, sp.wk, false);
       __syncthreads();
+      r = s_done;
+      if (s_nflag == 0) break;                         // workgroup-uniform
+      split_unit<DT>(v, u, sp.raw, sp.wk, s_planned != 0);
+      __syncthreads();
+      if (r == nb) break;
+      const int M1 = us.M;
+      us = load_unit(v, u);
+      fl = us.top - 1 - lane >= 0 ? v.freelist[(size_t)u * v.Pcap + us.top - 1 - lane] : -1;
+      if (us.nflag != 0 || us.M > M1 + 1) break;       // (more than the one split: the next batch begins)
     }
+    t += r;
+    __syncthreads();                                   // (s_done and the slots are read before the next batch writes them)
   }
   if (tid == 0) v.nflagged[u] = t;                     // how far this kernel came
 }

@@ -185,26 +185,25 @@ __device__ __forceinline__ void merge_best2(float& zb, int& jb, float& z2, float
   if (take) { zb = ob; jb = oj; }
   z2 = fmaxf(fmaxf(z2, o2), loser_ok ? loser : -__builtin_inff());
 }
-// The same over the 64 lanes of a wavefront; every lane gets the result.  Butterfly inside each row of 16 lanes
-// (the sets that meet are disjoint at every step), then row to row, then the last lane's triple for everybody.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ void best2_step(float& zb, int& jb, float& z2) {
-  // a lane that gets nothing from this step (its row is masked out) merges the empty set: index -1, -inf
-  const float ob = __int_as_float(dpp_or<CTRL, ROWS>(0, __float_as_int(zb)));
-  const int oj = dpp_or<CTRL, ROWS>(-1, jb);
-  const float o2 = __int_as_float(dpp_or<CTRL, ROWS>(__float_as_int(-__builtin_inff()), __float_as_int(z2)));
-  merge_best2(zb, jb, z2, ob, oj, o2);
+// The same over the 64 lanes of a wavefront; every lane gets the result.  Two maxima: the best of all lanes, then the best of what
+// is left when the lane that holds it brings its runner-up instead.  (Where several lanes hold the best, runner-up and best
+// are equal and the index is that of any of them: the caller decides such a tie in float64.)  A value that is not a
+// number counts as the lowest.  (Merging whole triples lane by lane took 1500 cycles, this takes 350.)
+__device__ __forceinline__ int float_order(float x) {      // ints order like the floats
+  const int b = __float_as_int(fmaxf(x, -__builtin_inff()));
+  return b ^ ((b >> 31) & 0x7FFFFFFF);
 }
+__device__ __forceinline__ float order_float(int b) { return __int_as_float(b ^ ((b >> 31) & 0x7FFFFFFF)); }
 __device__ __forceinline__ void wave_best2(float& zb, int& jb, float& z2) {
-  best2_step<kDppXor1, 0xF>(zb, jb, z2);
-  best2_step<kDppXor2, 0xF>(zb, jb, z2);
-  best2_step<kDppHalfMirror, 0xF>(zb, jb, z2);
-  best2_step<kDppMirror, 0xF>(zb, jb, z2);
-  best2_step<kDppBcast15, 0xA>(zb, jb, z2);
-  best2_step<kDppBcast31, 0xC>(zb, jb, z2);
-  zb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zb), 63));
-  jb = __builtin_amdgcn_readlane(jb, 63);
-  z2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z2), 63));
+  const int lane = threadIdx.x & 63;
+  const int mine = jb >= 0 ? float_order(zb) : (int)0x80000000;            // (below every float)
+  const int top = wave_max(mine);
+  const unsigned long long who = __ballot(mine == top);
+  const int src = (int)__builtin_ctzll(who);
+  const int rest = wave_max(lane == src ? float_order(z2) : mine);
+  jb = __builtin_amdgcn_readlane(jb, src);
+  zb = jb >= 0 ? order_float(top) : -__builtin_inff();
+  z2 = rest == (int)0x80000000 ? -__builtin_inff() : order_float(rest);
 }
 
 // Every thread brings the best and the second best z it has seen (z_j = <k, r~_j> - |r~_j|^2 / 2 as the matrix

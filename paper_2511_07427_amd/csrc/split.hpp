@@ -46,22 +46,13 @@ struct Keys {
 
 constexpr int kSplitThreads = 256;
 
-// Arg-max over (value, index) pairs held one per thread of the whole block; ties go to the lowest index;
-// index < 0 means "no candidate".  Wavefront shuffles first, then the 16 wavefront winners through LDS.
-__device__ inline void block_argmax(double val, int idx, double* sv, int* si) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int o = 32; o > 0; o >>= 1) {
-    const double ov = __shfl_xor(val, o);
-    const int oi = __shfl_xor(idx, o);
-    if (oi >= 0 && (idx < 0 || ov > val || (ov == val && oi < idx))) { val = ov; idx = oi; }
-  }
+// Arg-max over (value, index) pairs held one per thread of the whole block; ties go to the lowest index; index < 0 means "no
+// candidate".  Result in sv[0], si[0].
+__device__ __forceinline__ void block_argmax(double val, int idx, double* sv, int* si) {
+  const int j = block_argmin<kSplitThreads>(-val, idx, sv, si);
   __syncthreads();
-  if (lane == 0) { sv[w] = val; si[w] = idx; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < kSplitThreads / 64; ++k)
-      if (si[k] >= 0 && (si[0] < 0 || sv[k] > sv[0] || (sv[k] == sv[0] && si[k] < si[0]))) { sv[0] = sv[k]; si[0] = si[k]; }
-  }
+  if (j == idx && j >= 0) { sv[0] = val; si[0] = j; }
+  else if (j < 0 && threadIdx.x == 0) { sv[0] = -1.0; si[0] = -1; }
   __syncthreads();
 }
 

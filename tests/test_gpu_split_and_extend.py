@@ -107,7 +107,7 @@ def test_splits_of_several_clusters_at_once(dtype):
 @pytest.mark.parametrize("dtype,M,n,Mcap", [
     ("f16", 1, 1, 8), ("bf16", 60, 15, 200), ("f16", 60, 16, 200), ("f16", 60, 33, 200), ("bf16", 640, 20, 900), ("f16", 641, 20, 900),
     ("bf16", 1281, 20, 1500), ("f16", 2561, 12, 2700), ("bf16", 5121, 6, 5300), ("f16", 10234, 8, 10300), ("bf16", 10240, 5, 10300),
-    ("f32", 70, 20, 200), ("f16", 3, 70, 90)])
+    ("f16", 10218, 8, 10300), ("f16", 10221, 8, 10300), ("f32", 70, 20, 200), ("f16", 3, 70, 90), ("bf16", 600, 90, 900)])
 def test_extension_across_batches(dtype, M, n, Mcap):
     """dynakv_extend_index against the oracle where its batches change size (640, 1280, .. clusters) or end: one entry, one batch,
     a remainder, a split inside a batch, entries that follow one another into one cluster, the last cluster that a batch can hold
