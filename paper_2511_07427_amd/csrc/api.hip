@@ -1,5 +1,6 @@
 // Host side of the C ABI declared in include/dynakv.h: argument checks, the carving of the caller's
 // workspace into the arrays of `View`, and the kernel launches of every call.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -72,7 +73,8 @@ void plan_attention(const dynakv_config_t& c, int* S, int* NW) {
   if (s > 8) s = 8;
   // where the single-kernel retrieval can run (see retrieve_is_fused) it beats split-KV at every unit count:
   // measured 16.5k against 15.5k steps/s with 8 units, 15.1k against 13.1k with 24 (configuration 2's shape)
-  if (c.dtype != DYNAKV_F32 && c.search_copy == DYNAKV_SEARCH_STORAGE && c.max_clusters <= kFusedClusters && c.group_size <= 8 &&
+  if ((c.dtype == DYNAKV_F32 ? c.max_clusters <= kFusedClusters32
+                             : c.search_copy == DYNAKV_SEARCH_STORAGE && c.max_clusters <= kFusedClusters) && c.group_size <= 8 &&
       c.update_mode != DYNAKV_UPDATE_TOKENS && c.update_mode != DYNAKV_UPDATE_LOCAL)
     s = 1;
   int nw = pow2_floor(4096 / (c.n_units * s) > 0 ? 4096 / (c.n_units * s) : 1);
@@ -119,7 +121,7 @@ size_t carve(const dynakv_config_t& c, char* base, View* out) {
   v.search_mean = c.dtype == DYNAKV_F32 || c.search_copy == DYNAKV_SEARCH_MEAN;
   v.M = (int*)take(U * 4); v.N = (int*)take(U * 4); v.err = (int*)take(U * 4); v.tau = (double*)take(U * 8);
   v.nflag = (int*)take(U * 4); v.n_sel = (int*)take(U * 4); v.t_sel = (int*)take(U * 4); v.n_list = (int*)take(U * 4);
-  v.ticket = (int*)take(U * 4); v.bump = (int*)take(U * 4); v.free_top = (int*)take(U * 4);
+  v.ticket = (int*)take(3 * U * 4); v.bump = (int*)take(U * 4); v.free_top = (int*)take(U * 4);
   v.NB = (v.Mcap + 255) / 256;
   v.near_d = (double*)take(U * v.NB * 8); v.near_j = (int*)take(U * v.NB * 4);
   v.zdist = (float*)take(v.search_mean ? 0 : UM * 4); v.rmax2 = (int*)take(U * 4); v.lcount = (int*)take(U * 4);
@@ -136,7 +138,7 @@ size_t carve(const dynakv_config_t& c, char* base, View* out) {
   v.pages = take(UP * (size_t)kPageElems * elem_size(c.dtype));
   v.ppos = (int*)take(UP * kPageTokens * 4); v.pnext = (int*)take(UP * 4); v.freelist = (int*)take(UP * 4);
   v.plist = (int*)take(U * v.Lcap * 4); v.plist_off = (int*)take(U * v.Lcap * 4);
-  v.part = (float*)take(U * v.S * v.G * (kHeadDim + 2) * 4);
+  v.part = (float*)take(U * std::max(v.S, retrieve_is_fused(v) ? fused_splits_max(v.U) : 1) * v.G * (kHeadDim + 2) * 4);
   v.labels = (int*)take(UN * 4); v.order = (int*)take(UN * 4); v.dist = (double*)take(UN * 8);
   v.koff = (int*)take(U * (v.Mcap + 1) * 4);
   const size_t mpad = km_pad(v.M0);
@@ -270,7 +272,8 @@ dynakv_status_t dynakv_retrieve_attend_static(dynakv_index_t* ix, const void* Q,
                                               float* lse, void* stream) {
   if (!ix || !Q || !out || token_budget < 0) return DYNAKV_EINVAL;
   const View& v = ix->view;
-  const size_t part_bytes = ((size_t)v.U * v.S * v.G * (kHeadDim + 2) * sizeof(float) + 255) & ~(size_t)255;
+  const bool fused = retrieve_is_fused(v);           // (its workgroups count their arrivals in the workspace, from launch to launch)
+  const size_t part_bytes = ((size_t)v.U * (fused ? fused_splits_max(v.U) : v.S) * v.G * (kHeadDim + 2) * sizeof(float) + 255) & ~(size_t)255;
   const size_t ticket_bytes = (size_t)v.U * sizeof(int);
   if (part_bytes + ticket_bytes > kStaticScratchBytes) return DYNAKV_ECAPACITY;
   if (!ix->built) return DYNAKV_ESTATE;
@@ -278,7 +281,7 @@ dynakv_status_t dynakv_retrieve_attend_static(dynakv_index_t* ix, const void* Q,
   if (scratch_of_current_device(&base) != hipSuccess) return DYNAKV_EHIP;
   View vs = v;                       // the kernels take the scratch as they take the workspace's: through the view
   vs.part = (float*)base;
-  vs.ticket = (int*)(base + part_bytes);   // reset by the selection of this very call before any workgroup takes one
+  if (!fused) vs.ticket = (int*)(base + part_bytes);   // reset by the selection of this very call before any workgroup takes one
   bool appended;
   return retrieve_impl(ix, vs, Q, token_budget, out, lse, nullptr, nullptr, false, (hipStream_t)stream, &appended);
 }

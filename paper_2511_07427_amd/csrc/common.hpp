@@ -18,6 +18,8 @@ constexpr int kSelectLds = 16384;               // clusters whose scores and siz
                                                 // it reads them from memory in every pass
 constexpr int kMaxPrefill = 16384;              // k-means checks one unit's initial positions in an LDS bitmap
 constexpr int kFusedClusters = 4096;            // clusters per unit the single-kernel retrieval can hold in LDS
+constexpr int kFusedClusters32 = 2048;          // the same for float32 storage
+constexpr int kFusedSplits = 8;                 // workgroups of the single kernel that can share a unit
 constexpr int kMaxSplitMembers = 4096;          // largest cluster the split kernel handles
 constexpr int kMaxKvSplits = 64;
 constexpr int kCounters = 8;
@@ -48,7 +50,8 @@ struct View {
   int* n_sel;        // [U] clusters selected by the last retrieval
   int* t_sel;        // [U] entries gathered by the last retrieval
   int* n_list;       // [U] entries in the gather list
-  int* ticket;       // [U] arrival counter of the split-KV workgroups
+  int* ticket;       // [3][U] arrival counters of the workgroups that share a unit: of the separate kernels' attention; of the
+                     // single kernel, after the selection and after the attention (these only grow, by 8 in every launch)
   int NB;            // blocks of 256 clusters per unit (ceil(Mcap / 256))
   double* near_d;    // [U][NB] float32 means only: nearest cluster of the step's new key among clusters 256b .. 256b+255,
   int* near_j;       //         left by the score kernel of a whole decode step for the append that follows it
@@ -457,6 +460,8 @@ hipError_t launch_build_index(const View& v, const void* K, const void* V, int n
 hipError_t launch_score_select(const View& v, const void* Q, int budget, const void* kin, hipStream_t st);
 hipError_t launch_near(const View& v, const void* kin, hipStream_t st);
 bool retrieve_is_fused(const View& v);
+// Most workgroups per unit that the single-kernel retrieval takes for U units (1, 2, 4 or 8).
+inline int fused_splits_max(int U) { return U <= 32 ? 8 : U <= 64 ? 4 : U <= 128 ? 2 : 1; }
 hipError_t launch_retrieve_fused(const View& v, const void* Q, int budget, float* out, float* lse, const void* kin,
                                  const void* vin, bool split, hipStream_t st);
 hipError_t launch_gather_attend(const View& v, const void* Q, float* out, float* lse, hipStream_t st);

@@ -8,6 +8,7 @@
 //                    several workgroups per unit and merged by the last one to arrive.
 //   retrieve_fused - all of the above for one unit in one workgroup and, in a whole decode step, the append
 //                    (Section 4.2) and the due splits as well: the step is one launch.
+#include <algorithm>
 #include <type_traits>
 
 #include "split.hpp"
@@ -186,6 +187,7 @@ struct SelectLds {
   int* list;
   int list_cap;
   const int* ids;          // select_phase with MAPPED: the cluster behind each position of skey and sw (otherwise unused)
+  bool tally;              // this workgroup counts the unit's retrieval (one of those that share the unit does)
   unsigned* selbits;       // [ceil(M / 32)] zeroed by the caller, or null: bit j is set for every selected cluster j, so that
                            // threads of the same workgroup can read the active set without a trip through memory
 };
@@ -289,6 +291,35 @@ __device__ inline void block_excl_scan3(int& a, int& b, int& c, int* sm, int& ta
   a = ba + xa - a; b = bb + xb - b; c = bc + xc - c;
 }
 
+// List entries of one cluster holding `take` entries in the pages pa, pb and, past the inline table, along its chain.
+__device__ __forceinline__ void emit_cluster(const View& v, int u, int take, int4 pa, int4 pb, int quads, int tok, int* plist, int* poff,
+                                             const SelectLds& s) {
+  const int npages = (take + kPageTokens - 1) / kPageTokens;
+  const int pgs[kInlinePages] = {pa.x, pa.y, pa.z, pa.w, pb.x, pb.y, pb.z, pb.w};
+  int page = -1;
+#pragma unroll
+  for (int k = 0; k < kInlinePages; ++k)
+    if (k < npages) {
+      page = pgs[k];
+      if (page >= 0)
+        emit_page(page, min(kPageTokens, take - k * kPageTokens), quads + 4 * k, tok + k * kPageTokens, plist, poff, s.list, s.list_cap);
+    }
+  for (int kk = kInlinePages; kk < npages && page >= 0; ++kk) {
+    page = v.pnext[(size_t)u * v.Pcap + page];
+    if (page >= 0)
+      emit_page(page, min(kPageTokens, take - kk * kPageTokens), quads + 4 * kk, tok + kk * kPageTokens, plist, poff, s.list, s.list_cap);
+  }
+}
+// What a selection leaves besides the list: c clusters, t entries, q list entries, of M clusters scored (one thread).
+__device__ __forceinline__ void leave_selection(const View& v, int u, const SelectLds& s, int c, int t, int q, int M) {
+  v.n_sel[u] = c; v.t_sel[u] = t; v.n_list[u] = q; v.ticket[u] = 0;
+  if (s.tally) {
+    count(v, u, 4, t);
+    count(v, u, 5, 1);
+    count(v, u, 6, M);
+  }
+}
+
 // Records the active set held in s.selbits and writes its gather list, in ascending cluster id: thread t takes the
 // R = ceil(M / NT) <= MAXR (8 or 16) clusters t R .. t R + R - 1 (sizes in s.sw), one block-wide prefix sum places
 // every cluster's entries.  No cluster is ranked: the order in which selected clusters are attended does not matter
@@ -345,32 +376,65 @@ __device__ inline int emit_by_id(const View& v, int u, int M, const SelectLds& s
       if (base + e >= R) break;                          // workgroup-uniform
       if (!((bits >> (base + e)) & 1u)) continue;
       v.sel_ids[cb + cnt] = j0 + base + e;
-      const int take = w[base + e], npages = (take + kPageTokens - 1) / kPageTokens;
-      const int pgs[kInlinePages] = {pa[e].x, pa[e].y, pa[e].z, pa[e].w, pb[e].x, pb[e].y, pb[e].z, pb[e].w};
-      int page = -1;
-#pragma unroll
-      for (int k = 0; k < kInlinePages; ++k)
-        if (k < npages) {
-          page = pgs[k];
-          if (page >= 0)
-            emit_page(page, min(kPageTokens, take - k * kPageTokens), quads + 4 * k, tok + k * kPageTokens, plist, poff,
-                      s.list, s.list_cap);
-        }
-      for (int kk = kInlinePages; kk < npages && page >= 0; ++kk) {    // pages past the inline table: walk the chain
-        page = v.pnext[(size_t)u * v.Pcap + page];
-        if (page >= 0)
-          emit_page(page, min(kPageTokens, take - kk * kPageTokens), quads + 4 * kk, tok + kk * kPageTokens, plist, poff,
-                    s.list, s.list_cap);
-      }
+      const int take = w[base + e];
+      emit_cluster(v, u, take, pa[e], pb[e], quads, tok, plist, poff, s);
       tok += take; quads += (take + 3) >> 2; ++cnt;
     }
   }
-  if (tid == 0) {
-    v.n_sel[u] = t_cnt; v.t_sel[u] = t_tok; v.n_list[u] = t_quads; v.ticket[u] = 0;
-    count(v, u, 4, t_tok);
-    count(v, u, 5, 1);
-    count(v, u, 6, M);
+  if (tid == 0) leave_selection(v, u, s, t_cnt, t_tok, t_quads, M);
+  return t_quads;
+}
+
+// The same for any number of clusters whose sizes are not in LDS: thread t takes a run of the bitmap's words and walks its set bits
+// eight at a time, once for the sizes and once more, when its place in the list is known, for the page tables.  (8 units of
+// 50 000 clusters, 1600 selected: ranking them by score, with bins of up to a few hundred keys, took 8 to 45 us of the selection, this
+// takes 5.)
+template <int NT>
+__device__ inline int emit_by_bits(const View& v, int u, int M, const SelectLds& s, int take_all) {
+  const int tid = threadIdx.x;
+  const size_t cb = (size_t)u * v.Mcap;
+  const int words = (M + 31) >> 5, K = (words + NT - 1) / NT, w0 = min(words, tid * K), w1 = min(words, w0 + K);
+  int tok = 0, quads = 0, cnt = 0, t_tok, t_quads, t_cnt;
+  int* plist = v.plist + (size_t)u * v.Lcap;
+  int* poff = v.plist_off + (size_t)u * v.Lcap;
+#pragma unroll 1
+  for (int pass = 0; pass < 2; ++pass) {
+    int wi = w0;
+    unsigned bits = w0 < w1 ? s.selbits[w0] : 0u;
+    while (true) {
+      int id[8], w[8];
+      int4 pa[8], pb[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        while (bits == 0 && wi + 1 < w1) bits = s.selbits[++wi];
+        id[e] = bits ? wi * 32 + (int)__builtin_ctz(bits) : -1;
+        bits &= bits - 1;
+      }
+      if (id[0] < 0) break;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        w[e] = id[e] >= 0 ? v.csz[cb + id[e]] : 0;
+        pa[e] = int4{-1, -1, -1, -1}; pb[e] = int4{-1, -1, -1, -1};
+        if (pass && id[e] >= 0) {
+          const int4* row = (const int4*)&v.cpg[(cb + id[e]) * kInlinePages];
+          pa[e] = row[0]; pb[e] = row[1];
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (id[e] < 0) continue;
+        const int take = take_all >= 0 ? take_all : w[e];
+        if (pass) {
+          v.sel_ids[cb + cnt] = id[e];
+          emit_cluster(v, u, take, pa[e], pb[e], quads, tok, plist, poff, s);
+        }
+        tok += take; quads += (take + 3) >> 2; ++cnt;
+      }
+      if (id[7] < 0) break;
+    }
+    if (pass == 0) block_excl_scan3<true>(tok, quads, cnt, s.sm, t_tok, t_quads, t_cnt);
   }
+  if (tid == 0) leave_selection(v, u, s, t_cnt, t_tok, t_quads, M);
   return t_quads;
 }
 
@@ -391,10 +455,12 @@ __device__ inline int emit_by_id(const View& v, int u, int M, const SelectLds& s
 // they fit.  The selected SET is therefore that of exact arithmetic.  Bands of more than kBandMax clusters
 // (degenerate inputs: many equal scores) are resolved on the float32 scores alone.
 // MAPPED: skey and sw hold only M contenders of the unit's clusters, in any order, s.ids says which; they include
-// every cluster that could be selected and at least one that cannot (see contenders).  Returns -1, with nothing but active-set
+// every cluster that could be selected and at least one that cannot (see contenders).  The list follows the cluster ids (emit_by_bits;
+// s.selbits has a bit for every cluster of the unit).  Returns -1, with nothing but active-set
 // flags written, if the cut falls among equal scores that only their ids can order (nothing keeps the contenders in
-// that order); the caller then takes the unmapped way.
-template <int NT, int CMAX = kCountMax, int MAXR = 8, bool MAPPED = false>
+// that order) or more than CMAX clusters are selected; the caller then takes the unmapped way.
+// BY_ID: keys, sizes and the active set's bitmap are in LDS and M <= MAXR * NT.
+template <int NT, bool BY_ID, int CMAX = kCountMax, int MAXR = 8, bool MAPPED = false>
 __device__ inline int select_phase(const View& v, int u, int M, int budget, const SelectLds& s, const SelectExact& ex,
                                    bool first_ready = false) {
   const int tid = threadIdx.x, lane = tid & 63;
@@ -406,7 +472,8 @@ __device__ inline int select_phase(const View& v, int u, int M, int budget, cons
   auto key_at = [&](int j) __attribute__((always_inline)) { return DYNAKV_KEY(j); };
   auto id_of = [&](int j) __attribute__((always_inline)) { return MAPPED ? s.ids[j] : j; };
   // keys, sizes and the active set's bitmap in LDS: nothing is ranked, the list follows the cluster ids (emit_by_id)
-  const bool id_order = !MAPPED && s.skey && s.sw && s.selbits && M <= MAXR * NT;
+  constexpr bool id_order = BY_ID;
+  static_assert(!BY_ID || !MAPPED, "contenders are in no particular order");
   if (!first_ready) {
     for (int i = tid; i < 1024; i += NT) s.hist[i] = 0;
     if (tid < 8) s.misc[tid] = tid == 4 ? 0x7fffffff : 0;
@@ -505,7 +572,7 @@ __device__ inline int select_phase(const View& v, int u, int M, int budget, cons
         if (lane == 0) {
           bmask[0] = (int)(unsigned)mask; bmask[1] = (int)(unsigned)(mask >> 32);
           s.misc[5] = above - s.misc[5] + tsb;            // entries selected in all
-          count(v, u, 7, 1);
+          if (s.tally) count(v, u, 7, 1);
         }
       }
       lds_barrier();
@@ -526,7 +593,7 @@ __device__ inline int select_phase(const View& v, int u, int M, int budget, cons
         if (id_order) s.misc[2] = 1;                        // (something is selected)
         else {
           const int pos = atomicAdd(&s.misc[2], 1);
-          if (pos < CMAX) { ck[pos] = ((unsigned long long)k << kIdBits) | (unsigned)(kIdMask - j); cw[pos] = DYNAKV_WEIGHT(p); }
+          if (!MAPPED && pos < CMAX) { ck[pos] = ((unsigned long long)k << kIdBits) | (unsigned)(kIdMask - j); cw[pos] = DYNAKV_WEIGHT(p); }
         }
       }
     } else if (cross && !refined && k == kstar) {
@@ -540,7 +607,7 @@ __device__ inline int select_phase(const View& v, int u, int M, int budget, cons
         if (id_order) s.misc[2] = 1;                        // (something is selected)
         else {
           const int pos = atomicAdd(&s.misc[2], 1);
-          if (pos < CMAX) { ck[pos] = ((unsigned long long)k << kIdBits) | (unsigned)(kIdMask - j); cw[pos] = DYNAKV_WEIGHT(p); }
+          if (!MAPPED && pos < CMAX) { ck[pos] = ((unsigned long long)k << kIdBits) | (unsigned)(kIdMask - j); cw[pos] = DYNAKV_WEIGHT(p); }
         }
       }
     }
@@ -590,7 +657,7 @@ __device__ inline int select_phase(const View& v, int u, int M, int budget, cons
   } else if (cross && !refined && tid == 0) {
     v.in_req[cb + xid] = 0;
   }
-  if (id_order) {
+  if constexpr (BY_ID) {
     const bool truncated = cross && s.misc[2] == 0 && budget > 0;    // the best cluster alone is over budget: its first entries
     if (truncated) {
       __syncthreads();                                 // (another thread may have cleared the same active-set flag)
@@ -601,7 +668,19 @@ __device__ inline int select_phase(const View& v, int u, int M, int budget, cons
       lds_barrier();
     }
     return emit_by_id<NT, MAXR>(v, u, M, s, truncated ? budget : -1);
-  }
+  } else if constexpr (MAPPED) {
+    if (s.misc[2] > CMAX) return -1;                   // workgroup-uniform
+    const bool truncated = cross && s.misc[2] == 0 && budget > 0;    // the best cluster alone is over budget: its first entries
+    if (truncated) {
+      __syncthreads();                                 // (another thread may have cleared the same active-set flag)
+      if (tid == 0) {
+        v.in_req[cb + xid] = 1;
+        atomicOr(&s.selbits[xid >> 5], 1u << (xid & 31));
+      }
+      lds_barrier();
+    }
+    return emit_by_bits<NT>(v, u, v.M[u], s, truncated ? budget : -1);
+  } else {
   int cut = s.misc[2], tsel = !cross ? total : refined ? s.misc[5] : above + tie_w;
   if (cut > CMAX) {
     __syncthreads();
@@ -745,15 +824,11 @@ __device__ inline int select_phase(const View& v, int u, int M, int budget, cons
   if (quads) atomicAdd(&s.misc[6], quads);
   lds_barrier();
   const int nlist = s.misc[6];
-  if (tid == 0) {
-    v.n_sel[u] = cut; v.t_sel[u] = tsel; v.n_list[u] = nlist; v.ticket[u] = 0;
-    count(v, u, 4, tsel);
-    count(v, u, 5, 1);
-    count(v, u, 6, MAPPED ? v.M[u] : M);
+  if (tid == 0) leave_selection(v, u, s, cut, tsel, nlist, M);
+  return nlist;
   }
 #undef DYNAKV_WEIGHT
 #undef DYNAKV_KEY
-  return nlist;
 }
 
 // Bound on |float32 score - exact score| of a unit: float32 accumulation of 128 exact products, scaled.
@@ -911,17 +986,20 @@ __global__ __launch_bounds__(1024) void select_kernel(View v, const void* Q, int
     for (int g = 0; g < v.G; ++g) qb = v.group_reduce == DYNAKV_GROUP_MAX ? fmaxf(qb, qn[g]) : qb + qn[g];
     ex.eps = score_eps(v, qb, __int_as_float(v.rmax2[u]));
   }
-  const SelectLds s{BIG ? nullptr : skey_, BIG ? nullptr : ssz_, region, hist, srt, sm, misc, nullptr, 0, nullptr, BIG ? nullptr : selbits_};
+  const SelectLds s{BIG ? nullptr : skey_, BIG ? nullptr : ssz_, region, hist, srt, sm, misc, nullptr, 0, nullptr, true, BIG ? nullptr : selbits_};
   if constexpr (BIG) {
+    unsigned* const bits = (unsigned*)region;          // (the candidates of the unmapped way come later)
+    static_assert(sizeof(region) >= kMaxClusters / 8, "one bit per cluster");
+    for (int i = tid; i < (M + 31) >> 5; i += 1024) bits[i] = 0u;
     const int n = contenders<1024>(v, u, M, budget, ex.eps, lkey, lid, lsz, srt, sm, found);
     if (n >= 0) {
-      const SelectLds sc{lkey, lsz, region, hist, srt, sm, misc, nullptr, 0, lid, nullptr};
-      if (select_phase<1024, CMAX, 8, true>(v, u, n, budget, sc, ex) >= 0) return;
+      const SelectLds sc{lkey, lsz, region, hist, srt, sm, misc, nullptr, 0, lid, true, bits};
+      if (select_phase<1024, false, CMAX, 8, true>(v, u, n, budget, sc, ex) >= 0) return;
       __builtin_amdgcn_s_waitcnt(0);                   // the active-set flags written so far stay behind those to come
     }
     __syncthreads();
   }
-  select_phase<1024, CMAX, BIG ? 8 : kSelectLds / 1024>(v, u, M, budget, s, ex);
+  select_phase<1024, !BIG, CMAX, BIG ? 8 : kSelectLds / 1024>(v, u, M, budget, s, ex);
 }
 
 // ------------------------------------------------------------------------------------------- attention
@@ -1266,7 +1344,7 @@ __global__ __launch_bounds__(NW * 64) void gather_attend_kernel(View v, const vo
   }
 }
 
-// Whole retrieval of one unit in one workgroup (16-bit storage, at most kFusedClusters clusters and 8 query heads
+// Whole retrieval of one unit in one workgroup (at most kFusedClusters clusters, kFusedClusters32 of float32, and 8 query heads
 // per unit; at every unit count, because the step is bound by dependent round trips rather than by the number of
 // busy compute units): scores -> LDS, budget cut in LDS, gather list in LDS, then the same page loop and merge
 // as gather_attend_kernel.  Saves two launches and every trip through the workspace between the phases.
@@ -1282,23 +1360,32 @@ constexpr int kFusedList = 2048;       // gather-list entries it keeps in LDS (l
 // these splits are written by all wavefronts after the merge of the attention output, and whatever is left (recycling the parents'
 // pages, further splits, the workgroup-wide path for large clusters) is carried out by the first kSplitThreads
 // threads, once the others have left.
+// S > 1 workgroups share a unit: all of them take the scores and the cut (the same in each, and none waits for another), each
+// streams its share of the gather list, and the last to have written its partial result merges them.  The append, the splits
+// and everything they write belong to whichever workgroup is the last to have made its selection (the first counter): by then
+// nobody reads what they change, and the pages that are still being streamed are neither written nor handed out again in this
+// launch, unless a further round of splits wants pages that the first has freed: that waits for the others' partial results.
+// float32 storage (GP query heads at most): scores and distances are float64 sums on the vector units, one cluster per thread.
 template <int DT, int NW, int GP, bool APPEND, bool SPLIT>
 __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const void* Q, int budget, float* out,
-                                                                float* lse, const void* kin, const void* vin) {
+                                                                float* lse, const void* kin, const void* vin, int S) {
   using F = Frag<DT>;
+  constexpr bool MEAN = DT == DYNAKV_F32;
+  constexpr int kClusters = MEAN ? kFusedClusters32 : kFusedClusters;
   constexpr int NT = NW * 64;
   constexpr int ES = DT == DYNAKV_F32 ? 4 : 2;
   constexpr int kMergeBytes = 64 * (kHeadDim + 2) * 4;          // NW * G <= 64 head rows
-  constexpr int kKeys = kFusedClusters * 4, kSizes = kFusedClusters * 4, kList = kFusedList * 4;
-  static_assert(kSelRegion >= 2 * kFusedClusters && kKeys + kSizes + kSelRegion + kList >= kMergeBytes, "LDS plan");
-  static_assert(NW * F::kVTile <= kKeys + kSizes + kSelRegion, "the V tiles take the space of the selection's tables");
-  // scores, sizes, candidates, gather list; after the page loop the front doubles as the merge buffer
-  constexpr size_t kPhases = kKeys + kSizes + kSelRegion + kList;
+  constexpr int kKeys = kClusters * 4, kSizes = kClusters * 4, kList = kFusedList * 4, kTables = kKeys + kSizes + kSelRegion;
+  // scores, sizes, candidates (while scoring float32: the queries), later the V tiles, in front of the gather list; after the page
+  // loop all of it is the merge buffer
+  constexpr int kFront = kTables > NW * F::kVTile ? kTables : NW * F::kVTile;
+  static_assert(kSelRegion >= kHeadDim * GP * 8 && kFront + kList >= kMergeBytes && kClusters <= 8 * NT, "LDS plan");
+  constexpr size_t kPhases = kFront + kList;
   static_assert(!SPLIT || (APPEND && NW * 64 >= kSplitThreads), "splits follow an append");
   // the split's LDS follows everything the streaming uses: its wavefront contexts are filled meanwhile
-  constexpr int kPreSplits = kWaveSplits;              // splits decided while the pages are streamed
+  constexpr int kPreSplits = kWaveSplits < NW / 2 ? kWaveSplits : NW / 2;   // splits decided while the others stream the pages
   constexpr size_t kRawOff = SPLIT ? (kPhases + 15) / 16 * 16 : 0;
-  static_assert(!SPLIT || kRawOff + kSplitRaw<DT> + 16 * 1024 <= 160 * 1024, "LDS of one compute unit");
+  static_assert(!SPLIT || kRawOff + kSplitRaw<DT> + 8 * 1024 <= 160 * 1024, "LDS of one compute unit");
   __shared__ __align__(16) unsigned char smem[SPLIT ? kRawOff + kSplitRaw<DT> : kPhases];
   __shared__ SplitWork wk;
   __shared__ double kd[kHeadDim];                     // the new key
@@ -1308,16 +1395,19 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   __shared__ float am_2[16];
   __shared__ int am_r[16];
   __shared__ int s_tile;                              // next tile of the page stream
-  __shared__ unsigned selbits[kFusedClusters / 32];    // the active set: for the gather list and the plan of the splits
+  __shared__ int s_last;                              // this workgroup is the last of its unit to have arrived
+  __shared__ unsigned selbits[kClusters / 32];    // the active set: for the gather list and the plan of the splits
   __shared__ __align__(16) int sm[64];
   __shared__ int misc[8];
   uint32_t* skey = (uint32_t*)smem;
   int* ssz = (int*)(smem + kKeys);
-  int* list = (int*)(smem + kKeys + kSizes + kSelRegion);
+  int* list = (int*)(smem + kFront);
   int* hist = list;                                   // the histograms are dead before the list is written
   static_assert(kList >= 1024 * 4, "histograms must fit the list");
   float* sm_o = (float*)smem;
-  const int u = blockIdx.x, tid = threadIdx.x;
+  // workgroup b: unit b % U of those that begin with it, the workgroups of a unit on one L2
+  const int U8 = S == 1 ? v.U : (v.U + 7) / 8 * 8, share = blockIdx.x / U8, u = blockIdx.x - share * U8, tid = threadIdx.x;
+  if (u >= v.U) return;
   const int lane = tid & 63, wave = tid >> 6;
   const int G = v.G;
 
@@ -1325,11 +1415,12 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   // w + NW, ...; kBatch of them are consumed while the loads of the next kBatch are in flight (16 KB per wavefront).
   constexpr bool BF = DT == DYNAKV_BF16;
   constexpr int kBatch = 4;
-  const uint16_t* Rq = unit_Rq(v, u);
+  const uint16_t* Rq = MEAN ? nullptr : unit_Rq(v, u);
   const uint4* tiles = (const uint4*)Rq;
   const int table_tiles = (int)(v.Rstride / kTileElems);   // the table's padded end: these rows exist in every state
-  uint4 cur[kBatch][4], nxt[kBatch][4];
-  auto fetch = [&](uint4 (&dst)[kBatch][4], int t0) __attribute__((always_inline)) {
+  uint4 cur[MEAN ? 1 : kBatch][4], nxt[MEAN ? 1 : kBatch][4];
+  f4 row[8];
+  auto fetch = [&](auto& dst, int t0) __attribute__((always_inline)) {
 #pragma unroll
     for (int b = 0; b < kBatch; ++b) {
       const int T = t0 + b * NW;
@@ -1337,7 +1428,8 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
       for (int s2 = 0; s2 < 4; ++s2) dst[b][s2] = T < table_tiles ? tiles[((size_t)T * 4 + s2) * 64 + lane] : uint4{0, 0, 0, 0};
     }
   };
-  fetch(cur, wave);                                   // requested before anything is waited for
+  if constexpr (!MEAN) fetch(cur, wave);              // requested before anything is waited for
+  else if ((size_t)(tid | 63) * kHeadDim < v.Rstride) load_centroid_head(unit_R(v, u), tid, row);
   // the unit's counters and its flagged list as they are before this step's append: the append and the plan of the splits
   // start from them
   int flagged0 = 0;
@@ -1347,14 +1439,20 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   if constexpr (APPEND) us = load_unit(v, u);
   const int M = us.M;
   // stored sizes, requested for every cluster slot of the unit so that the requests do not wait for M
-  int szr[kFusedClusters / NT];
+  int szr[kClusters / NT];
 #pragma unroll
-  for (int k = 0; k < kFusedClusters / NT; ++k) {
+  for (int k = 0; k < kClusters / NT; ++k) {
     const int j = tid + k * NT;
     szr[k] = j < v.Mcap ? v.csz[(size_t)u * v.Mcap + j] : 0;
   }
   ScoreRows<1> A;
-  load_score_rows<1>(A, G, Q, APPEND ? kin : nullptr, u, lane);
+  double (*qs)[GP] = (double (*)[GP])(smem + kKeys + kSizes);
+  if constexpr (!MEAN) load_score_rows<1>(A, G, Q, APPEND ? kin : nullptr, u, lane);
+  else
+    for (int t = tid; t < GP * kHeadDim; t += NT) {
+      const int g = t / kHeadDim, d = t % kHeadDim;
+      qs[d][g] = g < G ? (double)load_elem(Q, ((size_t)u * G + g) * kHeadDim + d, DT) : 0.0;
+    }
   const bool room = APPEND && us.N < v.Ncap && M > 0;     // otherwise the append is refused, as by the append kernel
   if (APPEND && tid < kHeadDim) kd[tid] = (double)load_elem(kin, (size_t)u * kHeadDim + tid, v.dtype);
   int Mpad = 2;
@@ -1363,16 +1461,54 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   for (int i = tid; i < 1024; i += NT) hist[i] = 0;
   if (tid < 8) misc[tid] = tid == 4 ? 0x7fffffff : 0;
   if (tid == 0) { s_tile = 0; if constexpr (SPLIT) wk.ready = 0; }
-  if (tid < kFusedClusters / 32) selbits[tid] = 0u;
+  if (tid < kClusters / 32) selbits[tid] = 0u;
 #pragma unroll
-  for (int k = 0; k < kFusedClusters / NT; ++k)
+  for (int k = 0; k < kClusters / NT; ++k)
     if (tid + k * NT < M) ssz[tid + k * NT] = szr[k];
   if constexpr (SPLIT)
     if (wave == 0) wk.flagged0[lane] = flagged0;
   if constexpr (APPEND)
     if (tid == 0) s_unit = us;
-  const RowNorms rn = row_norms<BF, 1>(A, G, v.group_reduce, lane);
+  RowNorms rn{0.f, 0.f};
+  if constexpr (!MEAN) rn = row_norms<BF, 1>(A, G, v.group_reduce, lane);
   lds_barrier();
+  int ja = -1;                                        // the append's nearest cluster
+  float unit_rmax2 = 0.f;
+  if constexpr (MEAN) {
+    // one cluster per thread: GP inner products and (APPEND) the distance to the new key, in float64
+    constexpr int NA = GP + (APPEND ? 1 : 0);
+    const float* R = unit_R(v, u);
+    double best = __builtin_inf();
+    for (int j = tid; (j & ~63) < M; j += NT) {
+      if (j != tid) load_centroid_head(R, j, row);
+      double acc[NA];
+      centroid_sums<NA>(R, j, row, acc, [&](int d, float rv, double (&a)[NA]) __attribute__((always_inline)) {
+        const double rd = (double)rv;
+#pragma unroll
+        for (int g = 0; g < GP; ++g) a[g] = fma(qs[d][g], rd, a[g]);
+        if constexpr (APPEND) {
+          const double t = kd[d] - rd;
+          a[GP] = fma(t, t, a[GP]);
+        }
+      });
+      if (j < M) {
+        double red = acc[0];
+#pragma unroll
+        for (int g = 1; g < GP; ++g)
+          if (g < G) red = v.group_reduce == DYNAKV_GROUP_MAX ? fmax(red, acc[g]) : red + acc[g];
+        const float sc = (float)(red * v.scale_d);
+        v.score[(size_t)u * v.Mcap + j] = sc;
+        const uint32_t key = orderable(sc);
+        skey[j] = key;
+        const int w = ssz[j];                          // first pass of the selection's radix search
+        if (w) atomicAdd(&hist[key >> 24], w);
+        if constexpr (APPEND)
+          if (ja < 0 || acc[NA - 1] < best) { best = acc[NA - 1]; ja = j; }      // ascending j per thread: the first minimum stays
+      }
+    }
+    if constexpr (APPEND) ja = block_argmin<NT>(best, ja, am_v, am_i);
+    lds_barrier();                                    // scores and first histogram are in place
+  } else {
   float zb = -__builtin_inff(), z2 = -__builtin_inff(), rmax2 = 0.f;
   int jb = -1;
   const int nctile = (M + kTileClusters - 1) / kTileClusters;
@@ -1421,13 +1557,14 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   int rmu = am_r[0];
 #pragma unroll
   for (int k = 1; k < NW; ++k) rmu = max(rmu, am_r[k]);
-  const float unit_rmax2 = __int_as_float(rmu);
-  // the append's nearest cluster: its record is requested here and used after the selection
-  int ja = -1;
+  unit_rmax2 = __int_as_float(rmu);
+  if constexpr (APPEND)
+    ja = nearest_decide<NT>(v, u, M, rn.kn, unit_rmax2, v.zdist + (size_t)u * v.Mcap, Rq, kd, am_v, am_i, am_2);
+  }
+  // the append's record is requested here and used after the selection
   ClusterFetch apf{float2{0.f, 0.f}, 0};
   EntryBits entry{uint2{0, 0}, uint2{0, 0}};
   if constexpr (APPEND) {
-    ja = nearest_decide<NT>(v, u, M, rn.kn, unit_rmax2, v.zdist + (size_t)u * v.Mcap, Rq, kd, am_v, am_i, am_2);
     if (room && wave == 0) {                          // the first wavefront will carry out the append
       apf = fetch_cluster(v, u, ja, us.top, lane);
       entry = load_entry<DT>(kin, vin, u, lane);
@@ -1435,9 +1572,9 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   }
 
   // ---- selection
-  const SelectLds sel{skey, ssz, smem + kKeys + kSizes, hist, ssz, sm, misc, list, kFusedList, nullptr, selbits};
-  const SelectExact ex{score_eps(v, rn.qbound, unit_rmax2), Q};
-  const int nlist = select_phase<NT>(v, u, M, budget, sel, ex, true);
+  const SelectLds sel{skey, ssz, smem + kKeys + kSizes, hist, ssz, sm, misc, list, kFusedList, nullptr, share == 0, selbits};
+  const SelectExact ex{MEAN ? 0.f : score_eps(v, rn.qbound, unit_rmax2), Q};
+  const int nlist = select_phase<NT, true>(v, u, M, budget, sel, ex, true);
   // a full barrier only where other threads read back what the selection wrote to memory: a list too long for LDS
   // (page loop); the plan of the splits takes the active set from the bitmap in LDS
   if (nlist > kFusedList) __syncthreads();
@@ -1464,26 +1601,36 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   char* vtile = (char*)smem + wave * F::kVTile;            // scores, sizes and candidates are dead
   uint4 pre_v[kVAhead] = {};
   bool decides = false;                                // this wavefront decides a split instead of streaming
+  const unsigned arrival = kFusedSplits / S;              // every launch adds kFusedSplits to a counter, whatever S is
   if constexpr (APPEND) {
     if (wave == 0) {
       us = s_unit;
+      unsigned n = kFusedSplits - arrival;               // (a barrier lies behind every read of what the append changes)
+      if (S > 1 && lane == 0)
+        n = __hip_atomic_fetch_add((unsigned*)&v.ticket[v.U + u], arrival, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
       PlanEarly pe{};
       if constexpr (SPLIT) {
         flagged0 = wk.flagged0[lane];
         pe = plan_fetch_early(v, u, flagged0, us, room ? ja : -1, lane, selbits);
       }
-      AppendResult res{};
-      int sz0 = 0;
-      if (room) {
-        const ClusterState cs = cluster_state(apf, us.top);
-        res = append_wave<DT>(v, u, ja, us, cs, entry, lane);
-        sz0 = cs.cn + cs.cb;
-      } else if (lane == 0) {
-        v.err[u] |= DYNAKV_ERR_TOKENS;
+      const bool owner = ((unsigned)__builtin_amdgcn_readfirstlane((int)n) & (kFusedSplits - 1)) == kFusedSplits - arrival;
+      if (owner) {
+        AppendResult res{};
+        int sz0 = 0;
+        if (room) {
+          const ClusterState cs = cluster_state(apf, us.top);
+          res = append_wave<DT>(v, u, ja, us, cs, entry, lane);
+          sz0 = cs.cn + cs.cb;
+        } else if (lane == 0) {
+          v.err[u] |= DYNAKV_ERR_TOKENS;
+        }
+        if constexpr (SPLIT)
+          if (plan_finish<DT>(v, wk, pe, us, ja, room, res, sz0, kPreSplits))
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // the appended entry before the flag
+      } else if (SPLIT && lane == 0) {
+        wk.npre = 0; wk.nf0 = 0;
       }
       if constexpr (SPLIT) {
-        if (plan_finish<DT>(v, wk, pe, us, ja, room, res, sz0, kPreSplits))
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // the appended entry before the flag
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (lane == 0) __hip_atomic_store(&wk.ready, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         decides = wk.npre > 0;
@@ -1496,7 +1643,7 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   auto grab = [&]() __attribute__((always_inline)) {
     int t = 0;
     if (lane == 0) t = atomicAdd(&s_tile, 1);
-    return __builtin_amdgcn_readfirstlane(t);
+    return __builtin_amdgcn_readfirstlane(t) * S + share;
   };
   // a wavefront that may be asked to decide a split looks at the plan between two tiles
   auto called_away = [&]() __attribute__((always_inline)) {
@@ -1563,17 +1710,55 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   // which decided them hold in registers
   if constexpr (SPLIT)
     if (wave < nprep) wave_split_commit_ahead<DT>(v, u, ((WaveCtx*)(smem + kRawOff))[ctx_of(wave)], 0, 1, pre_v);
+  float* const part = v.part + ((size_t)u * S + share) * ws;
   for (int t = tid; t < G * kHeadDim; t += NT) {
     const int gg = t / kHeadDim, dc = t % kHeadDim;
     const float* b = sm_o + gg * hs;
     float Mx, L, O;
     merge_partials(b + kHeadDim, b + kHeadDim + 1, b + dc, NW, ws, Mx, L, O);
-    out[((size_t)u * G + gg) * kHeadDim + dc] = L > 0.f ? O / L : 0.f;
-    if (lse && dc == 0) lse[(size_t)u * G + gg] = L > 0.f ? (Mx + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
+    if (S == 1) {
+      out[((size_t)u * G + gg) * kHeadDim + dc] = L > 0.f ? O / L : 0.f;
+      if (lse && dc == 0) lse[(size_t)u * G + gg] = L > 0.f ? (Mx + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
+    } else {
+      st_device(&part[gg * hs + dc], O);
+      if (dc == 0) { st_device(&part[gg * hs + kHeadDim], Mx); st_device(&part[gg * hs + kHeadDim + 1], L); }
+    }
   }
   if constexpr (SPLIT)
     for (int k = 0; k < nprep; ++k) wave_split_commit<DT>(v, u, ((WaveCtx*)(smem + kRawOff))[ctx_of(k)], 1, wave, NW);
+  unsigned arrived = 0;
+  if (S > 1) {
+    // every thread waits for its own stores, the barrier collects the workgroup, one thread takes the second counter; the last
+    // of the unit to do so sees all partial results
+    __builtin_amdgcn_s_waitcnt(0);
+    lds_barrier();
+    if (tid == 0) {
+      arrived = __hip_atomic_fetch_add((unsigned*)&v.ticket[2 * v.U + u], arrival, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+      s_last = (arrived & (kFusedSplits - 1)) == kFusedSplits - arrival;
+    }
+    lds_barrier();
+    if (s_last) {
+      const float* all = v.part + (size_t)u * S * ws;
+      for (int t = tid; t < G * kHeadDim; t += NT) {
+        const int gg = t / kHeadDim, dc = t % kHeadDim;
+        const float* b = all + gg * hs;
+        float Mx, L, O;
+        merge_partials<true>(b + kHeadDim, b + kHeadDim + 1, b + dc, S, ws, Mx, L, O);
+        out[((size_t)u * G + gg) * kHeadDim + dc] = L > 0.f ? O / L : 0.f;
+        if (lse && dc == 0) lse[(size_t)u * G + gg] = L > 0.f ? (Mx + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
+      }
+    }
+  }
   if constexpr (SPLIT) {
+    if (wk.nf0 == 0) return;                         // workgroup-uniform: nothing is flagged, or another workgroup has the splits
+    if (S > 1 && (nprep == 0 || nprep < wk.pl.n_cand) && (wk.pl.n_cand > 0 || !wk.pl.fast)) {
+      // more splits than were decided ahead: they may take pages that this launch frees, which the unit's other workgroups may
+      // still be streaming.  All of those are running (this one was the last to select) and wait for nobody.
+      if (tid == 0)
+        while (__hip_atomic_load((unsigned*)&v.ticket[2 * v.U + u], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) -
+                   (arrived & ~(unsigned)(kFusedSplits - 1)) < (unsigned)kFusedSplits)
+          __builtin_amdgcn_s_sleep(8);
+    }
     __syncthreads();                                 // every use of smem lies behind
     if (tid >= kSplitThreads) return;                // barriers from here on count the remaining wavefronts only
     split_unit<DT>(v, u, smem + kRawOff, wk, true);
@@ -1598,30 +1783,40 @@ void launch_ga_dt(const View& v, const void* Q, float* out, float* lse, hipStrea
 }  // namespace
 
 bool retrieve_is_fused(const View& v) {
-  return v.fuse && v.S == 1 && !v.search_mean && !v.token_level && v.Mcap <= kFusedClusters && v.G <= 8;
+  const bool fits = v.dtype == DYNAKV_F32 ? v.Mcap <= kFusedClusters32 : !v.search_mean && v.Mcap <= kFusedClusters;
+  return v.fuse && v.S == 1 && !v.token_level && fits && v.G <= 8;
 }
 
-template <int DT, bool APPEND, bool SPLIT>
-static void launch_fused(const View& v, const void* Q, int budget, float* out, float* lse, const void* kin,
-                         const void* vin, hipStream_t st) {
-  // eight wavefronts: 256 registers per lane leave room for float64 scoring and a second tile in flight
-  if (v.G <= 4) retrieve_fused_kernel<DT, 8, 4, APPEND, SPLIT><<<v.U, 512, 0, st>>>(v, Q, budget, out, lse, kin, vin);
-  else retrieve_fused_kernel<DT, 8, 8, APPEND, SPLIT><<<v.U, 512, 0, st>>>(v, Q, budget, out, lse, kin, vin);
+template <int DT, int GP>
+static void launch_fused(const View& v, const void* Q, int budget, float* out, float* lse, const void* kin, const void* vin, bool split,
+                         int S, hipStream_t st) {
+  // 16-bit types: eight wavefronts, 256 registers per lane leave room for float64 scoring and a second tile in flight
+  constexpr int NW = DT == DYNAKV_F32 ? 4 : 8;
+  const int grid = S == 1 ? v.U : S * ((v.U + 7) / 8 * 8);
+  if (kin && split) retrieve_fused_kernel<DT, NW, GP, true, true><<<grid, 64 * NW, 0, st>>>(v, Q, budget, out, lse, kin, vin, S);
+  else if (kin) retrieve_fused_kernel<DT, NW, GP, true, false><<<grid, 64 * NW, 0, st>>>(v, Q, budget, out, lse, kin, vin, S);
+  else retrieve_fused_kernel<DT, NW, GP, false, false><<<grid, 64 * NW, 0, st>>>(v, Q, budget, out, lse, kin, vin, S);
 }
 
 // kin == nullptr: retrieval only; otherwise retrieval followed by the append of (kin, vin) and, with `split`,
 // by the splits that are due.
 hipError_t launch_retrieve_fused(const View& v, const void* Q, int budget, float* out, float* lse, const void* kin,
                                  const void* vin, bool split, hipStream_t st) {
-  if (v.dtype == DYNAKV_F16) {
-    if (kin && split) launch_fused<DYNAKV_F16, true, true>(v, Q, budget, out, lse, kin, vin, st);
-    else if (kin) launch_fused<DYNAKV_F16, true, false>(v, Q, budget, out, lse, kin, vin, st);
-    else launch_fused<DYNAKV_F16, false, false>(v, Q, budget, out, lse, kin, vin, st);
-  } else {
-    if (kin && split) launch_fused<DYNAKV_BF16, true, true>(v, Q, budget, out, lse, kin, vin, st);
-    else if (kin) launch_fused<DYNAKV_BF16, true, false>(v, Q, budget, out, lse, kin, vin, st);
-    else launch_fused<DYNAKV_BF16, false, false>(v, Q, budget, out, lse, kin, vin, st);
-  }
+  // Several workgroups share a unit where the units leave compute units idle and the pages to be streamed are worth it: one workgroup
+  // streams about 35 KB per us (8 units, budget 4000: 78 us a retrieval, 41 with eight), and sharing costs 2 us for the partial results,
+  // in a step also the wait for the last selection (112 units, 1 MB each: retrieval 45.8 -> 38.6 us, but a step 54.1 -> 56.3, because the
+  // slowest unit's split, which begins later, ends it; 128 units, 2 MB each: step 108.9 -> 97.7; 48 units, 512 KB each: retrieval
+  // 38.0 -> 33.3, step 45.8 -> 50.4; 2 units, 1 MB each: step 46.2 -> 34.8; 1 float32 unit, 1 MB: step 55.5 -> 37.2, 256 KB: 29.2 either way).
+  const size_t bytes = (size_t)std::min(budget, v.Ncap) * 2 * kHeadDim * elem_size(v.dtype);
+  const size_t worth = (v.U <= 16 ? 256 : kin ? 768 : v.U <= 64 ? 256 : 512) * 1024;
+  const int most = fused_splits_max(v.U);
+  int S = 1;
+  while (S < most && bytes >= worth * 2 * S) S *= 2;
+  if (v.dtype == DYNAKV_F32) {
+    if (v.G <= 4) launch_fused<DYNAKV_F32, 4>(v, Q, budget, out, lse, kin, vin, split, S, st);
+    else launch_fused<DYNAKV_F32, 8>(v, Q, budget, out, lse, kin, vin, split, S, st);
+  } else if (v.dtype == DYNAKV_F16) launch_fused<DYNAKV_F16, 8>(v, Q, budget, out, lse, kin, vin, split, S, st);
+  else launch_fused<DYNAKV_BF16, 8>(v, Q, budget, out, lse, kin, vin, split, S, st);
   return hipGetLastError();
 }
 

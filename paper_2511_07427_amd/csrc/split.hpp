@@ -387,7 +387,7 @@ __device__ __forceinline__ void split_cluster(const View& v, int u, int j, int p
 // Most clusters that get split hold a few dozen entries at most.  Up to four flagged clusters of a unit (64 entries of a
 // 16-bit type, 32 of float32 each; two if one has up to twice that) are split side by side, one wavefront each, with no
 // workgroup barrier inside the 2-means.  A cluster that is split alone has all four wavefronts and the staging rows of all
-// contexts (256 entries of a 16-bit type, 192 of float32): staging, sums over the members, statistics and copies are dealt
+// contexts (256 entries of a 16-bit type, 160 of float32): staging, sums over the members, statistics and copies are dealt
 // to them, the 2-means itself stays with the first.  (One wavefront alone: 47 us of a launch of 256 units for 64
 // entries each, 90 for 128; beyond, the workgroup path below took 514 us for 200.)
 // Same 2-means as split_cluster_impl (seeds, side test with its float64 re-check, rounds, stable partition, exact
@@ -400,7 +400,7 @@ static_assert(32 * kStageRow32 * 4 <= kWaveStage, "float32 rows must fit");
 template <int DT>
 constexpr int kSmallRows = DT == DYNAKV_F32 ? 32 : 64;           // one context's rows; two contexts': a wide plan
 template <int DT>
-constexpr int kLoneRows = DT == DYNAKV_F32 ? 192 : 256;          // members of the largest cluster that is split alone
+constexpr int kLoneRows = DT == DYNAKV_F32 ? 160 : 256;          // members of the largest cluster that is split alone
 constexpr int kWaveRows = 256;
 constexpr int kWavePages = kWaveRows / kPageTokens;
 template <int DT>
@@ -414,10 +414,10 @@ constexpr int kVAhead = 4;
 
 struct WaveCtx {
   double cA[kHeadDim], cB[kHeadDim];             // cB: partial sums before and after the 2-means, nrm / R / side during it
-  alignas(16) float rA[kHeadDim], rB[kHeadDim];
-  float d32[kWaveRows];                          // the members' squared distances in a seed search, then Rall
+  alignas(16) float rA[kHeadDim], rB[kHeadDim];  // the children's means in the end, Rall during the rounds
+  float d32[kWaveRows];                          // the members' squared distances in a seed search
   double m2[2];
-  unsigned char perm[kWaveRows], inv[kWaveRows];     // inv[member] = its place in perm
+  alignas(4) unsigned char perm[kWaveRows], inv[kWaveRows];     // inv[member] = its place in perm
   int chain[kWavePages], newpg[kWavePages + 2];
   int pos[kWaveRows];                            // sequence positions of the members
   int j, m, ok, nS, idM;
@@ -425,10 +425,11 @@ struct WaveCtx {
   // 16-bit types: the members' squared norms until the seeds are found; then sums of inner products with side A and with all members
   __device__ float* nrm() { return (float*)cB; }
   __device__ float* R() { return (float*)cB; }
-  __device__ float* Rall() { return d32; }
+  __device__ float* Rall() { return rA; }
+  __device__ unsigned short* moved() { return (unsigned short*)perm; }   // members that change side in a round
   __device__ unsigned char* side() { return (unsigned char*)cB; }    // float32: the sides of a round
 };
-static_assert(sizeof(double) * kHeadDim >= sizeof(float) * kWaveRows, "the norms take the place of WaveCtx::cB");
+static_assert(sizeof(double) * kHeadDim >= sizeof(float) * kWaveRows && 2 * kHeadDim >= kWaveRows, "norms and sums take the places of WaveCtx::cB, rA and rB");
 static_assert(sizeof(WaveCtx) % 16 == 0, "the staging rows behind the contexts are 16-byte aligned");
 // The contexts lie at the front of the split's LDS, the staging rows of all of them behind: context x of a plan
 // of small clusters has rows 64x .. 64x + 63, context x = 2, 3 of a wide plan rows 128(x - 2) .. 128(x - 2) + 127, a
@@ -955,7 +956,11 @@ __device__ __forceinline__ bool find_seeds(WaveCtx& c, const unsigned char* stag
       uint4 op[4];
       wave_terms<DT>(c, (float)w0 * scale, (float)w1 * scale, lane, op);
 #pragma unroll 1
-      for (int g = 0; g < m; g += 64) c.d32[g + lane] = fmaxf(c.nrm()[g + lane] - 2.f * inv * wave_dots<DT, kDotVector>(stage, g, m, lane, op) + na, 0.f);
+      for (int g = 0; g < m; g += 64) {
+        const float dot = inv * wave_dots<DT, kDotVector>(stage, g, m, lane, op);
+        if (pass == 0) c.Rall()[g + lane] = dot * (float)m;
+        c.d32[g + lane] = fmaxf(c.nrm()[g + lane] - 2.f * dot + na, 0.f);
+      }
       wave_sync();
     }
     double dub = -1.0;
@@ -964,9 +969,10 @@ __device__ __forceinline__ bool find_seeds(WaveCtx& c, const unsigned char* stag
 #pragma unroll 1
     while (true) {
       if (direct) {
-        c.rA[2 * lane] = (float)w0; c.rA[2 * lane + 1] = (float)w1;
+        float* const r = (float*)c.cA;                 // (the terms are dead)
+        r[2 * lane] = (float)w0; r[2 * lane + 1] = (float)w1;
         wave_sync();
-        wave_distances<DT>(ks, c.rA, c.d32, m, lane);
+        wave_distances<DT>(ks, r, c.d32, m, lane);
       }
       far = wave_farthest<DT>(stage, c.d32, m, lane, 1.53e-5f * reach * reach + 1e-30f,
                               !direct ? -1.f : pass == 0 ? 2.4e-7f * mn : 0.f, direct ? kWaveRows : 12, w0, w1, dub);
@@ -1000,8 +1006,8 @@ template <int DT>
 __device__ inline void wave_two_means(WaveCtx& c, const unsigned char* stage, int m, double tot0, double tot1) {
   const int lane = threadIdx.x & 63;
   const MemberSet all = first_members(m, lane);
-  double sa0 = tot0, sa1 = tot1;                 // sum of side A
-  MemberSet A = all;
+  double sa0 = tot0, sa1 = tot1;                 // sum of side A (16-bit types: as the first round left it, first_A)
+  MemberSet A = all, first_A = all;
   bool can = m >= 2;
   int quick = -1;
   if constexpr (DT != DYNAKV_F32)
@@ -1012,7 +1018,8 @@ __device__ inline void wave_two_means(WaveCtx& c, const unsigned char* stage, in
       if (quick == 0) can = false;
     }
   if (can && quick < 0) {
-    const double mu0 = tot0 / (double)m, mu1 = tot1 / (double)m, mn2 = wave_sum_f64(mu0 * mu0 + mu1 * mu1);
+    const CountInverse im = count_inverse(m);
+    const double mu0 = over_count(tot0, im), mu1 = over_count(tot1, im), mn2 = wave_sum_f64(mu0 * mu0 + mu1 * mu1);
     float x2 = 0.f, spread = 0.f;
     if constexpr (DT != DYNAKV_F32) {                              // |member|^2, and the largest of them
       int nmax = 0;
@@ -1102,10 +1109,10 @@ __device__ inline void wave_two_means(WaveCtx& c, const unsigned char* stage, in
             unsure = lane == (g >> 6) ? un : unsure;
           }
           if (__ballot(unsure != 0)) {                             // float64 centres for those
-            double w0, w1;
-            wave_set_sums<DT>(stage, A, 0ull, m, lane, sa0, sa1);
+            double w0, w1, d0, d1;
+            wave_set_sums<DT>(stage, A ^ first_A, first_A & ~A, m, lane, d0, d1);
             const double na = 1.0 / (double)nA, nb = 1.0 / (double)(m - nA);
-            ca0 = sa0 * na; ca1 = sa1 * na; cb0 = (tot0 - sa0) * nb; cb1 = (tot1 - sa1) * nb;
+            ca0 = (sa0 + d0) * na; ca1 = (sa1 + d1) * na; cb0 = (tot0 - (sa0 + d0)) * nb; cb1 = (tot1 - (sa1 + d1)) * nb;
             w0 = cb0 - ca0; w1 = cb1 - ca1;
             const double tt = wave_sum_f64(0.5 * ((cb0 * cb0 - ca0 * ca0) + (cb1 * cb1 - ca1 * ca1)));
 #pragma unroll 1
@@ -1131,28 +1138,25 @@ __device__ inline void wave_two_means(WaveCtx& c, const unsigned char* stage, in
           const double ia = 1.0 / (double)nA, ib = 1.0 / (double)(m - nA);     // (centres of a round: one rounding more is harmless)
           ca0 = sa0 * ia; ca1 = sa1 * ia;
           cb0 = (tot0 - sa0) * ib; cb1 = (tot1 - sa1) * ib;
-        } else if (first) {                                        // R of all members and of the smaller side, as vectors
+        } else if (first) {                                        // R of the smaller side, as one vector (Rall: from the seeds' search)
           const bool isA = 2 * nA <= m;
           double d0, d1;
           wave_set_sums<DT>(stage, isA ? nw : leaves, 0ull, m, lane, d0, d1);
+          first_A = nw;
+          sa0 = isA ? d0 : tot0 - d0; sa1 = isA ? d1 : tot1 - d1;
+          float inv;
+          const float scale = wave_scale<DT>((float)d0, (float)d1, inv);
+          uint4 op[4];
+          wave_terms<DT>(c, (float)d0 * scale, (float)d1 * scale, lane, op);
 #pragma unroll 1
-          for (int k = 0; k < 2; ++k) {
-            const float v0 = (float)(k ? d0 : tot0), v1 = (float)(k ? d1 : tot1);
-            float inv;
-            const float scale = wave_scale<DT>(v0, v1, inv);
-            uint4 op[4];
-            wave_terms<DT>(c, v0 * scale, v1 * scale, lane, op);
-#pragma unroll 1
-            for (int g = 0; g < m; g += 64) {
-              const float r = wave_dots<DT, kDotVector>(stage, g, m, lane, op) * inv;
-              if (k == 0) c.Rall()[g + lane] = r;
-              else c.R()[g + lane] = isA ? r : c.Rall()[g + lane] - r;
-            }
+          for (int g = 0; g < m; g += 64) {
+            const float r = wave_dots<DT, kDotVector>(stage, g, m, lane, op) * inv;
+            c.R()[g + lane] = isA ? r : c.Rall()[g + lane] - r;
           }
           err_r = 1.1f * unit * (float)(isA ? nA : 2 * m - nA);
         } else {
           // the members that moved, sixteen at a time as rows (those that leave side A with their signs changed)
-          unsigned short* const list = (unsigned short*)c.rA;
+          unsigned short* const list = c.moved();
           int n = 0;
 #pragma unroll 1
           for (int g = 0; g < m; g += 64) {
@@ -1204,16 +1208,18 @@ __device__ inline void wave_two_means(WaveCtx& c, const unsigned char* stage, in
   double sS0 = tot0, sS1 = tot1;
   if (can) {
     if constexpr (DT == DYNAKV_F32) { sS0 = a_first ? sa0 : tot0 - sa0; sS1 = a_first ? sa1 : tot1 - sa1; }
-    else {                                                   // exact sum of the smaller child
-      const bool small_S = 2 * nS <= m;
-      wave_set_sums<DT>(stage, small_S ? S : all & ~S, 0ull, m, lane, sa0, sa1);
-      sS0 = small_S ? sa0 : tot0 - sa0; sS1 = small_S ? sa1 : tot1 - sa1;
+    else {                                                   // from the first round's, by the members that have moved since
+      const bool fewer = quick == 1 && 2 * nS > m;           // (none: from all members, by the smaller side)
+      const MemberSet base = quick == 1 ? (fewer ? all : 0ull) : a_first ? first_A : all & ~first_A;
+      double b0 = fewer ? tot0 : 0.0, b1 = fewer ? tot1 : 0.0, d0, d1;
+      if (quick != 1) { b0 = a_first ? sa0 : tot0 - sa0; b1 = a_first ? sa1 : tot1 - sa1; }
+      wave_set_sums<DT>(stage, S ^ base, base & ~S, m, lane, d0, d1);
+      sS0 = b0 + d0; sS1 = b1 + d1;
     }
   }
-  c.rA[2 * lane] = (float)(sS0 / (double)nS); c.rA[2 * lane + 1] = (float)(sS1 / (double)nS);
-  if (can) {
-    c.rB[2 * lane] = (float)((tot0 - sS0) / (double)nM); c.rB[2 * lane + 1] = (float)((tot1 - sS1) / (double)nM);
-  }
+  const CountInverse iS = count_inverse(nS), iM = count_inverse(max(nM, 1));
+  c.rA[2 * lane] = (float)over_count(sS0, iS); c.rA[2 * lane + 1] = (float)over_count(sS1, iS);
+  if (can) { c.rB[2 * lane] = (float)over_count(tot0 - sS0, iM); c.rB[2 * lane + 1] = (float)over_count(tot1 - sS1, iM); }
 }
 
 // Decides one split, by one wavefront (W = 1; w = 0) or by the W wavefronts of the workgroup together (wavefront w of them):

@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256) void export_clusters_kernel(View v, dynakv_sta
 // One thread: unit u's scalars as they are before its first retrieval, with nothing flagged or selected and no page recycled.
 __device__ inline void reset_unit(const View& v, int u, int M, int N, double tau, int pages) {
   v.M[u] = M; v.N[u] = N; v.tau[u] = tau; v.err[u] = 0; v.nflag[u] = 0; v.n_sel[u] = 0; v.t_sel[u] = 0; v.n_list[u] = 0;
-  v.ticket[u] = 0; v.bump[u] = pages; v.free_top[u] = 0; v.last_assign[u] = -1; v.lcount[u] = 0; v.rmax2[u] = 0;
+  v.ticket[u] = 0; v.ticket[v.U + u] = 0; v.ticket[2 * v.U + u] = 0; v.bump[u] = pages; v.free_top[u] = 0; v.last_assign[u] = -1; v.lcount[u] = 0; v.rmax2[u] = 0;
   for (int k = 0; k < kCounters; ++k) v.counters[(size_t)u * kCounters + k] = 0;
 }
 

@@ -130,3 +130,69 @@ def test_extension_across_batches(dtype, M, n, Mcap):
     assert not dirty and not out["error"].any()
     if n >= 20:
         assert int(out["n_clusters"].min()) > M
+
+
+@pytest.mark.parametrize("dtype,units,G", [("f16", 3, 4), ("bf16", 40, 7), ("f32", 2, 5)])
+def test_units_shared_by_several_workgroups(dtype, units, G):
+    """Budgets at which the single kernel takes one, two, four and eight workgroups per unit, in retrievals and whole steps in turn
+    (its arrival counters go on from launch to launch), with more than four splits due in one step, whose later rounds want the
+    pages that the first has freed."""
+    sizes = [[9, 12, 30, 4, 8, 20, 3, 60, 100] + [1 + (j * 5 + u) % 23 for j in range(180)] for u in range(units)]
+    flagged = [9] * units
+    ix, o, tally, gen = pair(dtype, sizes, flagged, 400, extra=64, tau=9.0)
+    o_units = list(range(units))
+    N = min(sum(s) for s in sizes)
+    keys = ix.dynakv_export_state(["keys"], to_cpu=False)["keys"].float()
+    dt = binding.TORCH_DTYPES[dtype]
+    out, lse = torch.empty(units, G, D, device=DEV), torch.empty(units, G, device=DEV)
+    s = WorkloadSpec("share", dtype, units, G, N, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=0, seed=5)
+    ix, o = make_pair(s, units, max_tokens=max(sum(x) for x in sizes) + 64, max_clusters=400)
+    ix.dynakv_import_state(snapshot(dtype, sizes, flagged, 400, max(sum(x) for x in sizes) + 64, torch.Generator(device=DEV).manual_seed(3), 0.0, 9.0))
+    tally = Tally()
+    parity.resync(ix, o, None, set(o_units), tally)
+    for t, budget in enumerate((1 << 20, 1030, 300, 2060, 1 << 20, 520, 40)):
+        Q = (keys[:, 11 * t + 3, None] + 0.5 * torch.randn(units, G, D, generator=gen, device=DEV)).to(dt).contiguous()
+        k = (keys[:, 7 * t + 1] + 0.2 * torch.randn(units, D, generator=gen, device=DEV)).to(dt).contiguous()
+        v = torch.randn(units, D, generator=gen, device=DEV).to(dt)
+        Qn = Q.float().cpu().numpy()
+        if t % 3 == 1:
+            ix.dynakv_retrieve_attend(Q, budget, out, lse)
+            oo, ol = o.retrieve_attend(Qn, budget)
+        else:
+            ix.dynakv_decode_step(Q, budget, out, lse, k, v)
+            oo, ol = o.retrieve_attend(Qn, budget)
+            o.append(k.float().cpu().numpy(), v.float().cpu().numpy())
+            o.split()
+        parity.check_attention(out.cpu().numpy(), lse.cpu().numpy(), oo, ol, "budget %d" % budget)
+        if t % 3 == 1:
+            assert not parity.compare_retrieval(ix, o, tally, "budget %d" % budget, Q=Qn, budget=budget)
+        else:
+            assert not compare_state(ix, o, tally, "budget %d" % budget)
+    print("shared units", dtype, units, dict(tally), flush=True)
+
+
+def test_extension_decides_ties_between_coinciding_clusters():
+    """Every entry lies near two clusters of the same entries, and the splits that follow one another raise the norms that the
+    error bounds are made of: the lowest id wins each tie, in every lane."""
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    sizes, n = [[4, 4, 3, 3, 2, 2, 5, 5]] * 2, 48
+    s = WorkloadSpec("ties", "f16", 2, 2, 28, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=0, seed=9)
+    ix, o = make_pair(s, 2, max_tokens=28 + n, max_clusters=120)
+    st = snapshot("f16", sizes, [0, 0], 120, 28 + n, gen, 0.0, 6.0)
+    for u in range(2):                                  # clusters 2k + 1 are copies of clusters 2k
+        off, mem = st["offsets"][u], st["members"][u].long()
+        for j in range(0, 8, 2):
+            a, b = mem[off[j]:off[j + 1]], mem[off[j + 1]:off[j + 2]]
+            st["keys"][u, b] = st["keys"][u, a]
+            st["centroids"][u, j + 1] = st["centroids"][u, j]
+            st["m2"][u, j + 1] = st["m2"][u, j]
+    ix.dynakv_import_state(st)
+    tally = Tally()
+    parity.resync(ix, o, None, {0, 1}, tally)
+    grow = 1.0 + 0.04 * torch.arange(n, device=DEV)[None, :, None]
+    K = (st["keys"][:, torch.arange(n, device=DEV) % 28].float() * grow + 0.1 * torch.randn(2, n, D, generator=gen, device=DEV)).half()
+    V = torch.randn(2, n, D, generator=gen, device=DEV).half()
+    ix.dynakv_extend_index(K.contiguous(), V)
+    o.extend(K.float().cpu().numpy(), V.float().cpu().numpy())
+    assert not compare_state(ix, o, tally, "ties", assign=False)
+    assert int(ix.dynakv_export_state(["n_clusters"])["n_clusters"].min()) > 12
