@@ -14,6 +14,8 @@
 // 512: 5.21 -> 3.17 ms; 8 x 16384 x 2048 bfloat16: 3.72 -> 2.16 ms).  How many points the float64 decisions take depends on the
 // keys; what is slower than on the mixture of these figures is given where it is handled (Offset, scan_centres,
 // kmeans_changed_kernel, kmeans_slow_kernel).
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace dynakv {
@@ -787,8 +789,20 @@ __device__ inline bool sort_members(const View& v, int u, int N0, int* cnt, int*
 __global__ __launch_bounds__(1024) void kmeans_sort_kernel(View v, int N0) {
   __shared__ int cnt[kSortCounters];
   __shared__ int sm[64];
-  const bool any_empty = sort_members(v, blockIdx.x, N0, cnt, sm);
-  if (threadIdx.x == 0) v.has_empty[blockIdx.x] = any_empty;
+  const int u = blockIdx.x, tid = threadIdx.x;
+  const bool any_empty = sort_members(v, u, N0, cnt, sm);
+  if (tid == 0) v.has_empty[u] = any_empty;
+  // the first page of every cluster, for the layout
+  const int* koff = v.koff + (size_t)u * (v.Mcap + 1);
+  const int R = (v.M0 + 1023) / 1024;
+  auto pages = [&](int j) { return j < v.M0 ? (koff[j + 1] - koff[j] + kPageTokens - 1) / kPageTokens : 0; };
+  int n = 0, total;
+  for (int k = 0; k < R; ++k) n += pages(tid * R + k);
+  int base = block_excl_scan(n, sm, total);
+  for (int k = 0; k < R && tid * R + k < v.M0; ++k) {
+    v.pg_off[(size_t)u * v.Mcap + tid * R + k] = base;
+    base += pages(tid * R + k);
+  }
 }
 
 // ---- update ---------------------------------------------------------------------------------------------
@@ -850,11 +864,43 @@ __global__ __launch_bounds__(256) void kmeans_update_kernel(View v, const void* 
   if constexpr (DT != DYNAKV_F32) fold_norms(v, u, cn, sm);
 }
 
+// dist[i] = squared distance of point i to the centre of its own cluster for the points first, first + step, .. (sixteen lanes
+// each, eight points in flight).
+template <int DT>
+__device__ __forceinline__ void own_distances(const View& v, const void* X, int N0, int u, int first, int step) {
+  const int c = threadIdx.x & 15;
+  const int* lab = v.labels + (size_t)u * v.Ncap;
+  double* dist = v.dist + (size_t)u * v.Ncap;
+  const float* R = unit_R(v, u);
+  constexpr int kPts = DT == DYNAKV_F32 ? 4 : 8;
+  for (int i0 = first; i0 < N0; i0 += step * kPts) {
+    float x[kPts][8];
+    f4 ra[kPts], rb[kPts];
+#pragma unroll
+    for (int k = 0; k < kPts; ++k) {
+      const int i = min(i0 + step * k, N0 - 1), j = lab[i];
+      load8(X, ((size_t)u * N0 + i) * kHeadDim + c * 8, DT, x[k]);
+      if constexpr (DT == DYNAKV_F32) { ra[k] = *(const f4*)(R + r_index(j, c * 8)); rb[k] = *(const f4*)(R + r_index(j, c * 8 + 4)); }
+      else { const f4* r = (const f4*)(km_rows(v, u) + (size_t)j * kHeadDim + c * 8); ra[k] = r[0]; rb[k] = r[1]; }
+    }
+#pragma unroll
+    for (int k = 0; k < kPts; ++k) {
+      double acc = 0.0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const double t = (double)x[k][e] - (double)(e < 4 ? ra[k][e] : rb[k][e - 4]);
+        acc = fma(t, t, acc);
+      }
+      acc = row_blocked16(acc);
+      if (c == 15 && i0 + step * k < N0) dist[i0 + step * k] = acc;
+    }
+  }
+}
+
 // The sums follow the points that changed their cluster (16-bit types whose sums are order-free).  A workgroup takes 16
 // clusters: it reads the unit's list of changes once, counts every cluster's members (counts are kept twice, the old ones
 // are still being read by other workgroups) and queues the changes of its own clusters in LDS; sixteen lanes per cluster then
-// add and subtract the rows.  If some cluster of the unit has run empty, nothing is touched and kmeans_slow_kernel takes
-// the unit.  Bound by the dependent round trips list - rows - sums; the list is short after the first iterations.
+// add and subtract the rows.  If some cluster of the unit has run empty, the centres are left to kmeans_slow_kernel.  Bound by the dependent round trips list - rows - sums; the list is short after the first iterations.
 // A cluster with more changes than its queue holds (hundreds of keys per cluster, or one cluster that most keys share) has its
 // sixteen lanes go through the list again, 64 entries at a time.  (One entry at a time: 64 units x 16384 float16 keys x 64
 // centres build in 4.5 ms, 8 x 16384 bfloat16 x 128 in 2.4; now 3.1 and 1.7.)
@@ -891,13 +937,17 @@ __global__ __launch_bounds__(256) void kmeans_changed_kernel(View v, const void*
     }
   }
   __syncthreads();
+  bool centres = true;
   if (!last) {
     for (int i = tid; i < v.M0; i += 256)
       if (was[i] + delta[i] == 0) any_empty = 1;
     __syncthreads();
     if (any_empty) {                                    // the same in every workgroup of the unit
+      // the sums follow as ever, but the old centres stay until kmeans_slow_kernel has chosen points for the empty
+      // clusters: by their distances to those centres, of which each workgroup takes a share
+      centres = false;
       if (blockIdx.x == 0 && tid == 0) v.has_empty[u] = 1;
-      return;
+      own_distances<DT>(v, X, N0, u, blockIdx.x * 16 + (tid >> 4), gridDim.x * 16);
     }
   }
   const int k = tid >> 4, j = j0 + k;
@@ -950,7 +1000,7 @@ __global__ __launch_bounds__(256) void kmeans_changed_kernel(View v, const void*
       }
 #pragma unroll
       for (int d = 0; d < 8; d += 2) *(double2*)(S + d) = double2{s[d], s[d + 1]};
-      if (m > 0) {
+      if (m > 0 && centres) {
         float r[8];
 #pragma unroll
         for (int d = 0; d < 8; ++d) r[d] = (float)(s[d] / (double)m);
@@ -958,7 +1008,7 @@ __global__ __launch_bounds__(256) void kmeans_changed_kernel(View v, const void*
       }
     }
   }
-  fold_norms(v, u, cn, sm);
+  if (centres) fold_norms(v, u, cn, sm);                // (workgroup-uniform)
 }
 
 // Largest (value, index) of a wavefront, lowest index among equal values, index < 0: none.  Every lane of the last row gets it
@@ -980,16 +1030,24 @@ __device__ __forceinline__ void far_reduce(double& val, int& idx) {
 }
 
 // What the parallel kernels leave, in workgroups of 1024.  Most launches find nothing to do (4.5 us); where the first centres
-// leave some cluster empty, one or two iterations do (up to 190 us at 256 x 4096 x 256, 0.36 ms of that build in all).
+// leave some cluster empty, one or two iterations do.
 //   units with an empty cluster, one workgroup each: every empty cluster, in ascending id, takes the not-yet-taken point that is
-//     farthest from its own (old) centre, ties to the lowest position; the others get their sums formed anew
+//     farthest from its own (old) centre, ties to the lowest position; the others get their centres from their sums, which the
+//     changes have followed (256 units x 4096 x 256: 46 us; 160 us while this workgroup took all distances and sums itself)
 //   units whose sums are not order-free, in every iteration after the first: all sums formed anew.  Each of the unit's
 //     gridDim.y workgroups sorts the labels for itself (all write the same order) and takes its share of the clusters
 // The points' distances stay in registers while the empty clusters choose, and their centres are written together afterwards:
 // with some 200 empty clusters in each of ten iterations (2 units x 4096 float16 keys of 300 values x 512 centres) a launch
-// took 1180 us when every choice wrote its centre and read all distances again, now 610.  One bfloat16 unit of 16384 keys x
-// 8192 centres that is not order-free: 850 us by one workgroup, 130 by sixteen.
-constexpr int kSlowShare = 512;                          // clusters that warrant a workgroup of their own
+// took 1180 us when every choice wrote its centre and read all distances again, now 610.
+// A workgroup has room for 64 clusters at a time; where few units leave the chip idle, each gets as many workgroups as that
+// (8 units x 16384 bfloat16 keys x 2048 centres, not order-free: 4 workgroups a unit 100 us, 32 52 us).
+// (One workgroup per compute unit at most, for launches that find nothing to do; one per unit where no sums are formed anew.)
+constexpr int kSlowShare = 64, kSlowMost = 256;          // clusters per workgroup, workgroups of a launch
+inline int slow_workgroups(const View& v, int N0) {
+  if (v.dtype == DYNAKV_F32 || sums_order_free_by_type(v.dtype, N0)) return 1;
+  const int few = std::min(16, (v.M0 + 511) / 512);      // (many units: one for every 512 clusters)
+  return std::max(few, std::min(std::min(32, (v.M0 + kSlowShare - 1) / kSlowShare), kSlowMost / v.U));
+}
 template <int DT>
 __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X, int N0, int which, int first, int last) {
   __shared__ int cnt[kSortCounters];
@@ -1000,42 +1058,34 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
   const bool sorted = first || DT == DYNAKV_F32;         // this iteration's kmeans_sort_kernel has run
   const bool anew = !sorted && !sums_order_free(v, u, N0);
   if (!anew && (blockIdx.y > 0 || last || !v.has_empty[u])) return;       // workgroup-uniform
-  const bool any_empty = sorted ? true : sort_members(v, u, N0, cnt, sm);
+  const bool any_empty = sorted || !anew ? true : sort_members(v, u, N0, cnt, sm);
   const bool reseed = any_empty && !last;
   if (reseed && blockIdx.y > 0) return;
-  const int* lab = v.labels + (size_t)u * v.Ncap;
   const int* koff = v.koff + (size_t)u * (v.Mcap + 1);
-  double* dist = v.dist + (size_t)u * v.Ncap;
-  if (reseed) {                                         // distances to the centres of this assignment, before the update
-    const float* R = unit_R(v, u);
-    constexpr int kPts = DT == DYNAKV_F32 ? 4 : 8;       // points in flight per 16 lanes
-    for (int i0 = tid >> 4; i0 < N0; i0 += 64 * kPts) {
-      float x[kPts][8];
-      f4 ra[kPts], rb[kPts];
-#pragma unroll
-      for (int k = 0; k < kPts; ++k) {
-        const int i = min(i0 + 64 * k, N0 - 1), j = lab[i];
-        load8(X, ((size_t)u * N0 + i) * kHeadDim + c * 8, DT, x[k]);
-        if constexpr (DT == DYNAKV_F32) { ra[k] = *(const f4*)(R + r_index(j, c * 8)); rb[k] = *(const f4*)(R + r_index(j, c * 8 + 4)); }
-        else { const f4* r = (const f4*)(km_rows(v, u) + (size_t)j * kHeadDim + c * 8); ra[k] = r[0]; rb[k] = r[1]; }
-      }
-#pragma unroll
-      for (int k = 0; k < kPts; ++k) {
-        double acc = 0.0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const double t = (double)x[k][e] - (double)(e < 4 ? ra[k][e] : rb[k][e - 4]);
-          acc = fma(t, t, acc);
-        }
-        acc = row_blocked16(acc);
-        if (c == 15 && i0 + 64 * k < N0) dist[i0 + 64 * k] = acc;
-      }
-    }
+  const double* dist = v.dist + (size_t)u * v.Ncap;
+  const bool follows = !sorted && !anew;                 // kmeans_changed_kernel has taken sums, counts and distances
+  if (reseed && !follows) {                             // distances to the centres of this assignment, before the update
+    own_distances<DT>(v, X, N0, u, tid >> 4, 64);
     __syncthreads();
   }
   CentreNorms cn{0.f, 0.f};
   int* counts = km_counts(v, u, N0, which);
   const int share = reseed ? 1 : gridDim.y, mine = reseed ? 0 : blockIdx.y;
+  if (follows) {
+    const OffsetPart off = load_offset<DT>(v, u, c);
+    for (int j = tid >> 4; j < v.M0; j += 64) {
+      const int m = counts[j];
+      if (m == 0) continue;
+      const double* S = km_sums(v, u) + (size_t)j * kHeadDim + c * 8;
+      float r[8];
+#pragma unroll
+      for (int d = 0; d < 8; d += 2) {
+        const double2 w = *(const double2*)(S + d);
+        r[d] = (float)(w.x / (double)m); r[d + 1] = (float)(w.y / (double)m);
+      }
+      write_centre<DT>(v, u, j, c, r, off, cn);
+    }
+  } else
   for (int j = mine * 64 + (tid >> 4); j < v.M0; j += share * 64)
     update_cluster<DT, DT == DYNAKV_F32 ? 8 : 16>(v, X, N0, u, j, c, counts, load_offset<DT>(v, u, c), cn);
   if (reseed) {
@@ -1043,16 +1093,12 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
     int* const ids = cnt;                                // empty clusters, ascending
     int* const pick = cnt + kMaxInitClusters;            // the points they take
     const int R = (v.M0 + 1023) / 1024;
+    auto empty = [&](int j) { return j < v.M0 && (follows ? counts[j] == 0 : koff[j + 1] == koff[j]); };
     int mine_empty = 0, n;
-    for (int k = 0; k < R; ++k) {
-      const int j = tid * R + k;
-      mine_empty += j < v.M0 && koff[j + 1] == koff[j];
-    }
+    for (int k = 0; k < R; ++k) mine_empty += empty(tid * R + k);
     int at = block_excl_scan(mine_empty, sm, n);
-    for (int k = 0; k < R; ++k) {
-      const int j = tid * R + k;
-      if (j < v.M0 && koff[j + 1] == koff[j]) ids[at++] = j;
-    }
+    for (int k = 0; k < R; ++k)
+      if (empty(tid * R + k)) ids[at++] = tid * R + k;
     constexpr int kHeld = kMaxPrefill / 1024;
     double d[kHeld];                                     // points tid, tid + 1024, ..
 #pragma unroll
@@ -1086,86 +1132,81 @@ __global__ __launch_bounds__(1024) void kmeans_slow_kernel(View v, const void* X
   if (blockIdx.y == 0 && tid == 0) v.has_empty[u] = 0;
 }
 
-// dist[i] = squared distance of point i to the (updated) centre of its own cluster.  Sixteen lanes per point, one
-// block of 8 coordinates each; the 16 block sums are then added left to right by one thread per point.  Points
-// are taken in the sorted order (by cluster), so the 16 points of a workgroup mostly share one centre and its
-// lines of the lane-interleaved table are fetched once.
-__global__ __launch_bounds__(256) void point_dist_kernel(View v, const void* X, int N0) {
-  __shared__ double bs[16][17];
-  const int u = blockIdx.y, p = threadIdx.x >> 4, k = threadIdx.x & 15;
-  const int i = v.order[(size_t)u * v.Ncap + min((int)blockIdx.x * 16 + p, N0 - 1)];
-  const int j = v.labels[(size_t)u * v.Ncap + i];
-  const float* R = unit_R(v, u);
+// 16 consecutive entries of the sorted order per workgroup, 16 lanes per entry, 8 coordinates per lane: keys and values move
+// as whole 16-byte chunks of their token's rows, and dist[q] = squared distance of entry q of that order to the (updated)
+// centre of its own cluster, taken while its key is at hand.  Entries lie in cluster order, so the 16 of a workgroup mostly share one
+// centre and its lines of the lane-interleaved table are fetched once.  Bound by memory: 256 units x 4096 float16 entries 0.54 GB
+// read and as much written (221 us; a distance pass of its own read the keys once more: 317 us together).
+template <int DT>
+__global__ __launch_bounds__(256) void layout_copy_kernel(View v, const void* K, const void* V, int N0) {
+  const int u = blockIdx.y, q = blockIdx.x * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15;
+  const int pos = v.order[(size_t)u * v.Ncap + min(q, N0 - 1)];
+  const int j = v.labels[(size_t)u * v.Ncap + pos];
+  const size_t src = ((size_t)u * N0 + pos) * kHeadDim + c * 8;
   float x[8];
-  load8(X, ((size_t)u * N0 + i) * kHeadDim + k * 8, v.dtype, x);
-  const f4 ra = *(const f4*)(R + r_index(j, k * 8)), rb = *(const f4*)(R + r_index(j, k * 8 + 4));
+  uint4 kb[DT == DYNAKV_F32 ? 2 : 1], vb[DT == DYNAKV_F32 ? 2 : 1];
+  constexpr int kEs = DT == DYNAKV_F32 ? 4 : 2;
+#pragma unroll
+  for (int h = 0; h < kEs / 2; ++h) {
+    kb[h] = ((const uint4*)((const char*)K + src * kEs))[h];
+    vb[h] = ((const uint4*)((const char*)V + src * kEs))[h];
+  }
+  const float* R = unit_R(v, u);
+  const f4 ra = *(const f4*)(R + r_index(j, c * 8)), rb = *(const f4*)(R + r_index(j, c * 8 + 4));
+  const int rank = q - v.koff[(size_t)u * (v.Mcap + 1) + j];
+  const int page = v.pg_off[(size_t)u * v.Mcap + j] + rank / kPageTokens, slot = rank % kPageTokens;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const uint4 w = kb[e / (16 / kEs)];
+    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+    if constexpr (DT == DYNAKV_F32) x[e] = __uint_as_float(ww[e & 3]);
+    else x[e] = bits_value((ww[e >> 1] >> ((e & 1) * 16)) & 0xFFFFu, DT);
+  }
   double acc = 0.0;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const double t = (double)x[e] - (double)(e < 4 ? ra[e] : rb[e - 4]);
     acc = fma(t, t, acc);
   }
-  bs[p][k] = acc;
-  __syncthreads();
-  // (thread 16 t holds the index of point t of the workgroup)
-  if ((threadIdx.x & 15) == 0 && blockIdx.x * 16 + p < N0)
-    v.dist[(size_t)u * v.Ncap + i] = blocked16([&](int kk) __attribute__((always_inline)) { return bs[p][kk]; });
+  acc = row_blocked16(acc);
+  if (q >= N0) return;
+  char* pg = page_ptr(v, u, page);
+#pragma unroll
+  for (int h = 0; h < kEs / 2; ++h) {
+    ((uint4*)(pg + (size_t)k_index(DT, slot, c * 8) * kEs))[h] = kb[h];
+    ((uint4*)(pg + (size_t)v_index(DT, slot, c * 8) * kEs))[h] = vb[h];
+  }
+  if (c == 0) v.ppos[((size_t)u * v.Pcap + page) * kPageTokens + slot] = pos;
+  if (c == 15) v.dist[(size_t)u * v.Ncap + q] = acc;
 }
 
-// One workgroup per unit: per-cluster n, M2 (members in order), page chains, tau, counters.
+// One workgroup per unit, last kernel of a build: per-cluster n, M2 (members in order), page chains, tau, counters, the search
+// copy.  Consecutive threads take consecutive clusters throughout, so that every array is written in whole lines.
 __global__ __launch_bounds__(1024) void finalize_kernel(View v, int N0) {
-  __shared__ int sm[64];
   __shared__ double jsum[16];                   // per-wavefront sums of M2, for the objective that gives tau
-  static_assert(kMaxInitClusters <= 8 * 1024, "eight consecutive clusters per thread cover every initial cluster");
   const int u = blockIdx.x, tid = threadIdx.x;
   const int* koff = v.koff + (size_t)u * (v.Mcap + 1);
-  const int* order = v.order + (size_t)u * v.Ncap;
   const double* dist = v.dist + (size_t)u * v.Ncap;
   const size_t cb = (size_t)u * v.Mcap;
-  // pages per cluster, 8 consecutive clusters per thread
-  int np[8], tot = 0;
-  for (int k = 0; k < 8; ++k) {
-    const int j = tid * 8 + k;
-    np[k] = j < v.M0 ? (koff[j + 1] - koff[j] + kPageTokens - 1) / kPageTokens : 0;
-    tot += np[k];
-  }
-  int total;
-  int base = block_excl_scan(tot, sm, total);
-  for (int k = 0; k < 8; ++k) {
-    const int j = tid * 8 + k;
-    if (j >= v.Mcap) break;
-    if (j < v.M0) {
-      v.cn[cb + j] = koff[j + 1] - koff[j];
-      v.csz[cb + j] = koff[j + 1] - koff[j];
-      v.pg_off[cb + j] = base;
-      for (int p = 0; p < kInlinePages; ++p) v.cpg[(cb + j) * kInlinePages + p] = p < np[k] ? base + p : -1;
-      v.ctail[cb + j] = np[k] ? base + np[k] - 1 : -1;
-      for (int p = 0; p < np[k]; ++p) v.pnext[(size_t)u * v.Pcap + base + p] = p + 1 < np[k] ? base + p + 1 : -1;
-      base += np[k];
-    } else {
-      v.cn[cb + j] = 0; v.csz[cb + j] = 0; v.cM2[cb + j] = 0.0; v.ctail[cb + j] = -1;
-      for (int p = 0; p < kInlinePages; ++p) v.cpg[(cb + j) * kInlinePages + p] = -1;
-    }
-    v.cb[cb + j] = 0; v.cflag[cb + j] = 0; v.in_req[cb + j] = 0; v.score[cb + j] = 0.f;
-  }
-  for (int j = 8 * 1024 + tid; j < v.Mcap; j += 1024) {          // slots that no thread's run of eight reaches
-    v.cn[cb + j] = 0; v.csz[cb + j] = 0; v.cM2[cb + j] = 0.0; v.ctail[cb + j] = -1;
-    for (int p = 0; p < kInlinePages; ++p) v.cpg[(cb + j) * kInlinePages + p] = -1;
-    v.cb[cb + j] = 0; v.cflag[cb + j] = 0; v.in_req[cb + j] = 0; v.score[cb + j] = 0.f;
-  }
-  // M2 of cluster j = sum of its members' distances in storage order: one thread per cluster, eight members
-  // requested at a time, added one by one
+  // M2 of cluster j = sum of its members' distances in storage order: one thread per cluster, eight members requested at a
+  // time, added one by one
   double jmine = 0.0;
-  for (int j = tid; j < v.M0; j += 1024) {
-    const int b = koff[j], e = koff[j + 1];
+  for (int j = tid; j < v.Mcap; j += 1024) {
+    const bool in = j < v.M0;
+    const int b = in ? koff[j] : 0, e = in ? koff[j + 1] : 0, np = (e - b + kPageTokens - 1) / kPageTokens;
+    const int base = in ? v.pg_off[cb + j] : 0;
+    v.cn[cb + j] = e - b; v.csz[cb + j] = e - b; v.ctail[cb + j] = np ? base + np - 1 : -1;
+    v.cb[cb + j] = 0; v.cflag[cb + j] = 0; v.in_req[cb + j] = 0; v.score[cb + j] = 0.f;
+    int4* pg = (int4*)&v.cpg[(cb + j) * kInlinePages];
+    auto page = [&](int p) { return p < np ? base + p : -1; };
+    pg[0] = int4{page(0), page(1), page(2), page(3)};
+    pg[1] = int4{page(4), page(5), page(6), page(7)};
+    for (int p = 0; p < np; ++p) v.pnext[(size_t)u * v.Pcap + base + p] = p + 1 < np ? base + p + 1 : -1;
     double m2 = 0.0;
     for (int q0 = b; q0 < e; q0 += 8) {
-      int o[8];
       double x[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) o[k] = order[min(q0 + k, e - 1)];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) x[k] = dist[o[k]];
+      for (int k = 0; k < 8; ++k) x[k] = dist[min(q0 + k, e - 1)];
 #pragma unroll
       for (int k = 0; k < 8; ++k)
         if (q0 + k < e) m2 += x[k];
@@ -1175,46 +1216,33 @@ __global__ __launch_bounds__(1024) void finalize_kernel(View v, int N0) {
   }
   for (int o = 32; o > 0; o >>= 1) jmine += __shfl_xor(jmine, o);
   if ((tid & 63) == 0) jsum[tid >> 6] = jmine;
-  if (v.dtype != DYNAKV_F32) {               // search copy of the final centroids
+  if (v.dtype != DYNAKV_F32) {               // search copy of the final centroids, eight coordinates (16 bytes) at a time
     const float* R = unit_R(v, u);
     uint16_t* Rq = unit_Rq(v, u);
-    for (int t = tid; t < v.M0 * kHeadDim; t += 1024)
-      Rq[rq_index(t >> 7, t & 127)] = round_bits16(R[r_index(t >> 7, t & 127)], v.dtype);
+    for (int t = tid; t < ((v.M0 + 15) & ~15) * (kHeadDim / 8); t += 1024) {      // lane order of the copy's tiles: 16 clusters, then the next chunk
+      const int tile = t / (16 * 16), r = t % (16 * 16), j = tile * 16 + (r & 15), d = (r >> 4) * 8;
+      if (j >= v.M0) continue;
+      const f4 a = *(const f4*)(R + r_index(j, d)), b = *(const f4*)(R + r_index(j, d + 4));
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float lo = e < 2 ? a[2 * e] : b[2 * e - 4], hi = e < 2 ? a[2 * e + 1] : b[2 * e - 3];
+        w[e] = (uint32_t)round_bits16(lo, v.dtype) | ((uint32_t)round_bits16(hi, v.dtype) << 16);
+      }
+      *(uint4*)(Rq + rq_index(j, d)) = uint4{w[0], w[1], w[2], w[3]};
+    }
   }
   __syncthreads();
   if (tid == 0) {
     double J = 0.0;
     for (int w = 0; w < 16; ++w) J += jsum[w];
+    const int last = v.M0 - 1, total = v.pg_off[cb + last] + (koff[v.M0] - koff[last] + kPageTokens - 1) / kPageTokens;
     v.tau[u] = (double)v.var_alpha * (J / (double)N0);
     v.M[u] = v.M0; v.N[u] = N0; v.nflag[u] = 0; v.n_sel[u] = 0; v.t_sel[u] = 0; v.n_list[u] = 0;
-    v.ticket[u] = 0; v.ticket[v.U + u] = 0; v.ticket[2 * v.U + u] = 0; v.bump[u] = total; v.free_top[u] = 0; v.last_assign[u] = -1; v.lcount[u] = 0; v.rmax2[u] = 0;
+    v.ticket[u] = 0; v.ticket[v.U + u] = 0; v.ticket[2 * v.U + u] = 0; v.bump[u] = total;
+    v.free_top[u] = 0; v.last_assign[u] = -1; v.lcount[u] = 0; v.rmax2[u] = 0;
     for (int k = 0; k < kCounters; ++k) v.counters[(size_t)u * kCounters + k] = 0;
   }
-}
-
-// 16 consecutive entries of the sorted order per workgroup, 16 threads per entry, 8 coordinates per thread:
-// keys and values move as whole 16-byte chunks of their token's rows.
-__global__ __launch_bounds__(256) void layout_copy_kernel(View v, const void* K, const void* V, int N0) {
-  const int u = blockIdx.y, q = blockIdx.x * 16 + (threadIdx.x >> 4), c = threadIdx.x & 15;
-  if (q >= N0) return;
-  const int pos = v.order[(size_t)u * v.Ncap + q];
-  const int j = v.labels[(size_t)u * v.Ncap + pos];
-  const int rank = q - v.koff[(size_t)u * (v.Mcap + 1) + j];
-  const int page = v.pg_off[(size_t)u * v.Mcap + j] + rank / kPageTokens, slot = rank % kPageTokens;
-  char* pg = page_ptr(v, u, page);
-  const size_t src = ((size_t)u * N0 + pos) * kHeadDim + c * 8;
-  if (v.dtype == DYNAKV_F32) {
-    const f4* ks = (const f4*)((const float*)K + src);
-    const f4* vs = (const f4*)((const float*)V + src);
-    *(f4*)((float*)pg + k_index32(slot, c * 8)) = ks[0];
-    *(f4*)((float*)pg + k_index32(slot, c * 8 + 4)) = ks[1];
-    *(f4*)((float*)pg + v_index32(slot, c * 8)) = vs[0];
-    *(f4*)((float*)pg + v_index32(slot, c * 8 + 4)) = vs[1];
-  } else {
-    *(uint4*)((uint16_t*)pg + k_index16(slot, c * 8)) = *(const uint4*)((const uint16_t*)K + src);
-    *(uint4*)((uint16_t*)pg + v_index16(slot, c * 8)) = *(const uint4*)((const uint16_t*)V + src);
-  }
-  if (c == 0) v.ppos[((size_t)u * v.Pcap + page) * kPageTokens + slot] = pos;
 }
 
 }  // namespace
@@ -1242,7 +1270,7 @@ static void launch_kmeans(const View& v, const void* K, int N0, const int* init_
     }
     const bool sorted = first || DT == DYNAKV_F32;
     if (!last || (!sorted && !sums_order_free_by_type(DT, N0)))
-      kmeans_slow_kernel<DT><<<dim3(v.U, min(16, (v.M0 + kSlowShare - 1) / kSlowShare)), 1024, 0, st>>>(v, K, N0, which, first, last);
+      kmeans_slow_kernel<DT><<<dim3(v.U, slow_workgroups(v, N0)), 1024, 0, st>>>(v, K, N0, which, first, last);
   }
   if (DT != DYNAKV_F32 && iters > 1) kmeans_sort_kernel<<<v.U, 1024, 0, st>>>(v, N0);
 }
@@ -1253,9 +1281,11 @@ hipError_t launch_build_index(const View& v, const void* K, const void* V, int N
   if (v.dtype == DYNAKV_F32) launch_kmeans<DYNAKV_F32>(v, K, N0, init_idx, iters, st);
   else if (v.dtype == DYNAKV_F16) launch_kmeans<DYNAKV_F16>(v, K, N0, init_idx, iters, st);
   else launch_kmeans<DYNAKV_BF16>(v, K, N0, init_idx, iters, st);
-  point_dist_kernel<<<dim3((N0 + 15) / 16, v.U), 256, 0, st>>>(v, K, N0);
+  const dim3 grid((N0 + 15) / 16, v.U);
+  if (v.dtype == DYNAKV_F32) layout_copy_kernel<DYNAKV_F32><<<grid, 256, 0, st>>>(v, K, V, N0);
+  else if (v.dtype == DYNAKV_F16) layout_copy_kernel<DYNAKV_F16><<<grid, 256, 0, st>>>(v, K, V, N0);
+  else layout_copy_kernel<DYNAKV_BF16><<<grid, 256, 0, st>>>(v, K, V, N0);
   finalize_kernel<<<v.U, 1024, 0, st>>>(v, N0);
-  layout_copy_kernel<<<dim3((N0 + 15) / 16, v.U), 256, 0, st>>>(v, K, V, N0);
   return hipGetLastError();
 }
 

@@ -88,6 +88,12 @@ __global__ __launch_bounds__(256) void export_clusters_kernel(View v, dynakv_sta
   }
   if (o.centroids) {
     const float* R = unit_R(v, u);
+    if (j0 >= M) {                                       // nothing but unused slots: whole lines of zeros
+      float* z = o.centroids + (cbase + j0) * kHeadDim;
+      const int n = min(kStateTile, v.Mcap - j0) * (kHeadDim / 4);
+#pragma unroll 8
+      for (int t = tid; t < n; t += 256) *(f4u*)(z + 4 * t) = f4{0, 0, 0, 0};
+    } else
     for_each_table_piece([&](int c, int d) __attribute__((always_inline)) {
       const int j = j0 + c;
       if (j < v.Mcap) *(f4u*)(o.centroids + (cbase + j) * kHeadDim + d) = j < M ? *(const f4*)(R + r_index(j, d)) : f4{0, 0, 0, 0};
