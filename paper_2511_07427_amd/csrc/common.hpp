@@ -322,6 +322,18 @@ __device__ inline float page_key(const View& v, int u, int page, int slot, int d
   return load_elem(page_ptr(v, u, page), k_index(v.dtype, slot, d), v.dtype);
 }
 
+// Asks for every cache line of a kernel's first BYTES of arguments at once: read where they are needed, each line of a large
+// argument is a round trip to memory of its own.  For a kernel of one round of workgroups; where many rounds follow each other,
+// and in the short kernels of the prompt's clustering, it changed nothing (within 0.5 % of theirs).
+template <size_t BYTES>
+__device__ __forceinline__ void request_arguments() {
+  const auto* p = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
+  int x = 0;
+#pragma unroll
+  for (size_t b = 0; b < BYTES; b += 64) x |= p[b / 4];
+  asm volatile("" ::"s"(x));
+}
+
 // ---- wavefront scans and reductions on DPP ----------------------------------------------------------
 // Cross-lane moves inside a row of 16 lanes (row shifts, quad permutes, mirrors) and from one row to the next (row
 // broadcasts) are operand modifiers of ordinary vector instructions: a 64-lane scan or reduction built from them

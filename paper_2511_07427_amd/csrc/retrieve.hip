@@ -1171,14 +1171,11 @@ struct Frag16 {
 template <> struct Frag<DYNAKV_F16> : Frag16<false> {};
 template <> struct Frag<DYNAKV_BF16> : Frag16<true> {};
 
-// Merges `n` partial results (running max in the log2 domain, denominator, one accumulator) that sit
-// `stride` floats apart.  DEVICE: the partial results were written by other workgroups (see st_device).
-template <bool DEVICE = false>
+// Merges `n` partial results (running max in the log2 domain, denominator, one accumulator) that sit `stride` floats apart and
+// were written by other workgroups (see st_device).
 __device__ inline void merge_partials(const float* mx, const float* den, const float* acc, int n, int stride,
                                       float& M, float& L, float& O) {
-  auto ld = [](const float* p) {
-    return DEVICE ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
-  };
+  auto ld = [](const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
   M = -__builtin_inff();
   for (int w = 0; w < n; ++w) M = fmaxf(M, ld(mx + (size_t)w * stride));
   L = 0.f; O = 0.f;
@@ -1188,6 +1185,25 @@ __device__ inline void merge_partials(const float* mx, const float* den, const f
     const float sc = __builtin_amdgcn_exp2f(mw - M);
     L += sc * ld(den + (size_t)w * stride);
     O += sc * ld(acc + (size_t)w * stride);
+  }
+}
+// The same for the N wavefronts of a workgroup, in LDS: everything is requested at once.  (Eight wavefronts, 4 heads: the loop above
+// took 6000 cycles of a step with the stores before it, having a branch and three trips to LDS per partial result; this takes 5200.)
+template <int N>
+__device__ __forceinline__ void merge_wavefronts(const float* mx, const float* den, const float* acc, int stride, float& M, float& L, float& O) {
+  float m[N], d[N], a[N];
+#pragma unroll
+  for (int w = 0; w < N; ++w) { m[w] = mx[w * stride]; d[w] = den[w * stride]; a[w] = acc[w * stride]; }
+  M = m[0];
+#pragma unroll
+  for (int w = 1; w < N; ++w) M = fmaxf(M, m[w]);
+  L = 0.f; O = 0.f;
+#pragma unroll
+  for (int w = 0; w < N; ++w) {
+    const bool none = m[w] == -__builtin_inff();       // nothing to attend to, whatever its sums hold
+    const float sc = __builtin_amdgcn_exp2f(m[w] - M);
+    L += none ? 0.f : sc * d[w];
+    O += none ? 0.f : sc * a[w];
   }
 }
 // Store that other workgroups of the device can read back (with the matching load above) once it has completed,
@@ -1314,7 +1330,7 @@ __global__ __launch_bounds__(NW * 64) void gather_attend_kernel(View v, const vo
     const int gg = t / kHeadDim, dc = t % kHeadDim;
     const float* b = sm_o + gg * hs;
     float M, L, O;
-    merge_partials(b + kHeadDim, b + kHeadDim + 1, b + dc, NW, ws, M, L, O);
+    merge_wavefronts<NW>(b + kHeadDim, b + kHeadDim + 1, b + dc, ws, M, L, O);
     if (S == 1) {
       out[((size_t)u * G + gg) * kHeadDim + dc] = L > 0.f ? O / L : 0.f;
       if (lse && dc == 0) lse[(size_t)u * G + gg] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
@@ -1338,7 +1354,7 @@ __global__ __launch_bounds__(NW * 64) void gather_attend_kernel(View v, const vo
     const int gg = t / kHeadDim, dc = t % kHeadDim;
     const float* b = all + gg * hs;
     float M, L, O;
-    merge_partials<true>(b + kHeadDim, b + kHeadDim + 1, b + dc, S, ws, M, L, O);
+    merge_partials(b + kHeadDim, b + kHeadDim + 1, b + dc, S, ws, M, L, O);
     out[((size_t)u * G + gg) * kHeadDim + dc] = L > 0.f ? O / L : 0.f;
     if (lse && dc == 0) lse[(size_t)u * G + gg] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
   }
@@ -1369,6 +1385,7 @@ constexpr int kFusedList = 2048;       // gather-list entries it keeps in LDS (l
 template <int DT, int NW, int GP, bool APPEND, bool SPLIT>
 __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const void* Q, int budget, float* out,
                                                                 float* lse, const void* kin, const void* vin, int S) {
+  request_arguments<sizeof(View)>();
   using F = Frag<DT>;
   constexpr bool MEAN = DT == DYNAKV_F32;
   constexpr int kClusters = MEAN ? kFusedClusters32 : kFusedClusters;
@@ -1420,16 +1437,27 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   const int table_tiles = (int)(v.Rstride / kTileElems);   // the table's padded end: these rows exist in every state
   uint4 cur[MEAN ? 1 : kBatch][4], nxt[MEAN ? 1 : kBatch][4];
   f4 row[8];
-  auto fetch = [&](auto& dst, int t0) __attribute__((always_inline)) {
+  // tiles t0, t0 + NW, .. of the batch, of those from `from` on and before `to` (wavefront-uniform)
+  auto fetch = [&](auto& dst, int t0, int from, int to) __attribute__((always_inline)) {
 #pragma unroll
     for (int b = 0; b < kBatch; ++b) {
       const int T = t0 + b * NW;
+      if (T < from || T >= to) continue;
 #pragma unroll
-      for (int s2 = 0; s2 < 4; ++s2) dst[b][s2] = T < table_tiles ? tiles[((size_t)T * 4 + s2) * 64 + lane] : uint4{0, 0, 0, 0};
+      for (int s2 = 0; s2 < 4; ++s2) dst[b][s2] = tiles[((size_t)T * 4 + s2) * 64 + lane];
     }
   };
-  if constexpr (!MEAN) fetch(cur, wave);              // requested before anything is waited for
+  // the first M0 clusters exist in every state but an empty unit's (whose table is there as well): their tiles are requested before
+  // anything is waited for, the others once M is known.  (All of the first batch at once, of which a session's beginning uses half,
+  // kept the small loads behind it waiting.  256 units of 256 clusters: 16 500 cycles until the first score, 13 200 this way, 10 900
+  // with the arguments asked for in one go, the LDS cleared while these loads run and the rows' norms without LDS.)
+  const int early = MEAN ? 0 : min((v.M0 + kTileClusters - 1) / kTileClusters, table_tiles);
+  if constexpr (!MEAN) fetch(cur, wave, 0, early);
   else if ((size_t)(tid | 63) * kHeadDim < v.Rstride) load_centroid_head(unit_R(v, u), tid, row);
+  for (int i = tid; i < 1024; i += NT) hist[i] = 0;
+  if (tid < 8) misc[tid] = tid == 4 ? 0x7fffffff : 0;
+  if (tid == 0) { s_tile = 0; if constexpr (SPLIT) wk.ready = 0; }
+  if (tid < kClusters / 32) selbits[tid] = 0u;
   // the unit's counters and its flagged list as they are before this step's append: the append and the plan of the splits
   // start from them
   int flagged0 = 0;
@@ -1447,7 +1475,11 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   }
   ScoreRows<1> A;
   double (*qs)[GP] = (double (*)[GP])(smem + kKeys + kSizes);
-  if constexpr (!MEAN) load_score_rows<1>(A, G, Q, APPEND ? kin : nullptr, u, lane);
+  const int nctile = (M + kTileClusters - 1) / kTileClusters;
+  if constexpr (!MEAN) {
+    load_score_rows<1>(A, G, Q, APPEND ? kin : nullptr, u, lane);
+    fetch(cur, wave, early, nctile);
+  }
   else
     for (int t = tid; t < GP * kHeadDim; t += NT) {
       const int g = t / kHeadDim, d = t % kHeadDim;
@@ -1458,10 +1490,6 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   int Mpad = 2;
   while (Mpad < M) Mpad <<= 1;
   for (int i = M + tid; i < Mpad; i += NT) skey[i] = 0u;
-  for (int i = tid; i < 1024; i += NT) hist[i] = 0;
-  if (tid < 8) misc[tid] = tid == 4 ? 0x7fffffff : 0;
-  if (tid == 0) { s_tile = 0; if constexpr (SPLIT) wk.ready = 0; }
-  if (tid < kClusters / 32) selbits[tid] = 0u;
 #pragma unroll
   for (int k = 0; k < kClusters / NT; ++k)
     if (tid + k * NT < M) ssz[tid + k * NT] = szr[k];
@@ -1511,10 +1539,9 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   } else {
   float zb = -__builtin_inff(), z2 = -__builtin_inff(), rmax2 = 0.f;
   int jb = -1;
-  const int nctile = (M + kTileClusters - 1) / kTileClusters;
   for (int t0 = wave; t0 < nctile; t0 += kBatch * NW) {
     const bool more = t0 + kBatch * NW < nctile;
-    if (more) fetch(nxt, t0 + kBatch * NW);
+    if (more) fetch(nxt, t0 + kBatch * NW, 0, nctile);
 #pragma unroll
     for (int b = 0; b < kBatch; ++b) {
       const int T = t0 + b * NW;
@@ -1640,9 +1667,15 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
 #define DYNAKV_TILE(T) make_tile<ES>(pages, 4 * (T) + selK < nlist ? src[4 * (T) + selK] : -1, \
                                      4 * (T) + lg < nlist ? src[4 * (T) + lg] : -1, lane)
   // next tile of the unit (wavefront-uniform); tiles past the end mean there is nothing left
+  // A retrieval alone keeps every wavefront at it: tiles in turn, so that equal calls add up in the same order.
+  int own_tile = wave;
   auto grab = [&]() __attribute__((always_inline)) {
-    int t = 0;
-    if (lane == 0) t = atomicAdd(&s_tile, 1);
+    int t = own_tile;
+    own_tile += NW;
+    if constexpr (APPEND) {
+      t = 0;
+      if (lane == 0) t = atomicAdd(&s_tile, 1);
+    }
     return __builtin_amdgcn_readfirstlane(t) * S + share;
   };
   // a wavefront that may be asked to decide a split looks at the plan between two tiles
@@ -1715,7 +1748,7 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
     const int gg = t / kHeadDim, dc = t % kHeadDim;
     const float* b = sm_o + gg * hs;
     float Mx, L, O;
-    merge_partials(b + kHeadDim, b + kHeadDim + 1, b + dc, NW, ws, Mx, L, O);
+    merge_wavefronts<NW>(b + kHeadDim, b + kHeadDim + 1, b + dc, ws, Mx, L, O);
     if (S == 1) {
       out[((size_t)u * G + gg) * kHeadDim + dc] = L > 0.f ? O / L : 0.f;
       if (lse && dc == 0) lse[(size_t)u * G + gg] = L > 0.f ? (Mx + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
@@ -1743,7 +1776,7 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
         const int gg = t / kHeadDim, dc = t % kHeadDim;
         const float* b = all + gg * hs;
         float Mx, L, O;
-        merge_partials<true>(b + kHeadDim, b + kHeadDim + 1, b + dc, S, ws, Mx, L, O);
+        merge_partials(b + kHeadDim, b + kHeadDim + 1, b + dc, S, ws, Mx, L, O);
         out[((size_t)u * G + gg) * kHeadDim + dc] = L > 0.f ? O / L : 0.f;
         if (lse && dc == 0) lse[(size_t)u * G + gg] = L > 0.f ? (Mx + __builtin_amdgcn_logf(L)) * kLn2 : -__builtin_inff();
       }

@@ -47,6 +47,14 @@ __device__ inline void load_score_rows(ScoreRows<NBLK>& A, int G, const void* Q,
   }
 }
 
+// Sum over the lanes l, l + 16, l + 32, l + 48 of a wavefront; all four get it.
+__device__ __forceinline__ float rows_sum(float x) {
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+
 // Norms of the rows, for the error bounds: qbound = max_g |q_g| (group max) or sum_g |q_g| (group sum), kn = |new key|.
 struct RowNorms {
   float qbound, kn;
@@ -67,17 +75,21 @@ __device__ inline RowNorms row_norms(const ScoreRows<NBLK>& A, int G, int group_
         s2 = fmaf(x, x, s2);
       }
     }
-    s2 += __shfl_xor(s2, 16);
-    s2 += __shfl_xor(s2, 32);
+    s2 = rows_sum(s2);
     const int r = (lane & 15) + 16 * blk;
     const float nr = __builtin_sqrtf(s2) * 1.0001f;
     float q = r < G ? nr : 0.f, k = r == G ? nr : 0.f;
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-      const float oq = __shfl_xor(q, o);
-      q = group_reduce == DYNAKV_GROUP_MAX ? fmaxf(q, oq) : q + oq;
-      k = fmaxf(k, __shfl_xor(k, o));
-    }
+    const bool mx = group_reduce == DYNAKV_GROUP_MAX;
+    auto step = [&](auto ctrl) __attribute__((always_inline)) {
+      constexpr int C = decltype(ctrl)::value;
+      const float oq = __int_as_float(dpp_or_zero<C>(__float_as_int(q)));
+      q = mx ? fmaxf(q, oq) : q + oq;
+      k = fmaxf(k, __int_as_float(dpp_or_zero<C>(__float_as_int(k))));
+    };
+    step(std::integral_constant<int, kDppXor1>{});
+    step(std::integral_constant<int, kDppXor2>{});
+    step(std::integral_constant<int, kDppHalfMirror>{});
+    step(std::integral_constant<int, kDppMirror>{});
     n.qbound = group_reduce == DYNAKV_GROUP_MAX ? fmaxf(n.qbound, q) : n.qbound + q;
     n.kn = fmaxf(n.kn, k);
   }

@@ -769,13 +769,6 @@ __device__ __forceinline__ void wave_terms(WaveCtx& c, float w0, float w1, int l
   }
   wave_sync();
 }
-// Sum over the lanes l, l + 16, l + 32, l + 48 of a wavefront; all four get it.
-__device__ __forceinline__ float rows_sum(float x) {
-  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = __uint_as_float(h[0]) + __uint_as_float(h[1]);
-  const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(q[0]) + __uint_as_float(q[1]);
-}
 __device__ __forceinline__ float wave_sum_f32(float x) {
   x += __int_as_float(dpp_or_zero<kDppXor1>(__float_as_int(x)));
   x += __int_as_float(dpp_or_zero<kDppXor2>(__float_as_int(x)));
