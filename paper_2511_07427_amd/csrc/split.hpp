@@ -1266,17 +1266,24 @@ __device__ __forceinline__ void wave_split_decide(const View& v, int u, WaveCtx&
   if (w == 0) wave_two_means<DT>(c, stage, m, tot0, tot1);
   split_sync(W);
   // M2 of the children about their means (differences in float32, off by 2^-24 of themselves; sums of 32 squares in
-  // float32, the rest in float64)
+  // float32, the rest in float64; all of it in float64 for clusters that only four wavefronts together take, as the workgroup
+  // path has it)
   const WaveKeys<DT> ks{stage};
   const int grp = lane >> 2, kb = lane & 3, nS = c.nS;
   double acc[2] = {0.0, 0.0};
 #pragma unroll 1
   for (int base = 16 * w; base < m; base += 16 * W) {
     const int q = base + grp;
-    float fr[32];
-    load_quarter(q < nS ? c.rA : c.rB, kb, fr);
-    const float d = quad_sqdist32(ks, c.perm[min(q, m - 1)], kb, fr);
-    const double dv = kb == 0 && q < m ? (double)d : 0.0;
+    double d;
+    if (m > 2 * kSmallRows<DT>) {
+      double none;
+      quad_sqdist<WaveKeys<DT>, float>(ks, c.perm[min(q, m - 1)], kb, q < nS ? c.rA : c.rB, nullptr, d, none);
+    } else {
+      float fr[32];
+      load_quarter(q < nS ? c.rA : c.rB, kb, fr);
+      d = (double)quad_sqdist32(ks, c.perm[min(q, m - 1)], kb, fr);
+    }
+    const double dv = kb == 0 && q < m ? d : 0.0;
     acc[0] += q < nS ? dv : 0.0;
     acc[1] += q < nS ? 0.0 : dv;
   }
