@@ -31,8 +31,9 @@
  *               the nearest cluster among all candidates within the error bound of the best, and
  *               the budget cut among all clusters whose score lies within the bound of the cut.
  *               The selected set therefore is the one of exact arithmetic; the order in which the
- *               selected clusters are attended is the library's own (ascending id; descending
- *               float32 score where max_clusters > 16384).  Ties go to the lowest index.
+ *               selected clusters are attended is the library's own (a snapshot lists them by
+ *               ascending id; by descending float32 score where max_clusters > 16384).  Ties go to
+ *               the lowest index.
  *               Attention uses matrix cores with float32 accumulation.
  */
 #ifndef DYNAKV_H
@@ -217,10 +218,10 @@ dynakv_status_t dynakv_split(dynakv_index_t* index, void* stream);
  * takes that float64 sum in an order of its own; attention outputs up to float32 rounding), so the three calls and
  * this one can be mixed freely.  It exists because the step's two passes over the centroid table (query
  * similarity, Section 4.1; nearest cluster of the new key, Section 4.2) read the same data, and because a
- * step is a chain of short dependent phases: with 16-bit storage read through its 16-bit search copy, at most
- * 4096 clusters and at most 8 query heads per unit the whole step is ONE kernel launch that reads the table
+ * step is a chain of short dependent phases: with 16-bit storage read through its 16-bit search copy and at most
+ * 4096 clusters, or float32 storage and at most 2048, and at most 8 query heads per unit the whole step is ONE kernel launch that reads the table
  * once, commits the append before it streams the selected pages, and prepares the due splits while it streams
- * them.  Otherwise (float32 storage or search copy, more clusters, more query heads) it is four launches
+ * them.  Otherwise (16-bit storage read through its means, more clusters, more query heads) it is four launches
  * instead of the six of the three calls: the score kernel also evaluates the new key's distances, and the
  * splits run in the append's launch.  Arguments as in the three calls. */
 dynakv_status_t dynakv_decode_step(dynakv_index_t* index, const void* Q, int32_t token_budget, float* out,
@@ -242,10 +243,10 @@ typedef struct {
   int32_t* members;      /* [U][max_tokens]     token positions in storage order                 */
   float* scores;         /* [U][max_clusters]   scores of the last retrieval                     */
   int32_t* n_selected;   /* [U]                 clusters selected by the last retrieval          */
-  int32_t* selected;     /* [U][max_clusters]   their ids in the order they are attended: ascending id
-                                                (descending score where max_clusters > 16384)     */
+  int32_t* selected;     /* [U][max_clusters]   their ids, ascending (by descending score where
+                                                max_clusters > 16384)                             */
   int32_t* n_gathered;   /* [U]                 entries attended by the last retrieval           */
-  int32_t* gathered;     /* [U][max_tokens]     their token positions in gather order            */
+  int32_t* gathered;     /* [U][max_tokens]     their token positions, in that order of clusters */
   int32_t* last_assign;  /* [U]                 cluster chosen by the last append                */
   int64_t* counters;     /* [U][8]              splits, failed splits, forced splits, pages in use,
                                                 entries gathered, retrievals, clusters scored,

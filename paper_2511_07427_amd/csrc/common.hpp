@@ -79,10 +79,11 @@ struct View {
   int* cpg;          // [.][8] first pages of the cluster (-1: none); later pages follow pnext
   int* ctail;        // last page
   float* score;      // last scores
-  int* sel_ids;      // the active set in the order it is attended: ascending id, or (selection with its keys in memory) descending score
+  int* sel_ids;      // the active set in the order it is attended: ascending id, or (keys left in memory) descending score
   unsigned char* in_req;  // membership in the last active set
   int* tok_off;      // scratch: exclusive prefix of sizes in score order
-  int* pg_off;       // scratch: exclusive prefix of gather-list entry counts in score order
+  int* pg_off;       // scratch: first page of every cluster (build, import); where more than kSelectLds clusters are possible, the
+                     // exclusive prefix of the selected clusters' sizes in the order of the last retrieval's list
   // pages [U][Pcap]
   char* pages;       // [U][Pcap][kPageElems * elem size]
   int* ppos;         // [U][Pcap][16] token position of every slot
@@ -177,11 +178,11 @@ __device__ inline void store_centroid(const View& v, int u, int j, int d, float 
 
 // ---- the fixed summation order ----------------------------------------------------------------------
 // Float64 sums over the 128 coordinates run in one order wherever several pieces of code decide about the same value (the
-// k-means' distances, the scans of the float32 means, the workgroup path of a split, UpdateVar by a workgroup): blocks of 8
+// k-means' distances, the scans of the float32 means, the workgroup path of a split): blocks of 8
 // consecutive coordinates are accumulated left to right from zero (one fused multiply-add per term), and the 16 block sums are
 // added left to right.  Dependency chains stay short, and the value is the same whether one lane owns the whole sum or 16
-// lanes own one block each.  (The candidates of the 16-bit search copy that are re-scored in float64, UpdateVar by one
-// wavefront and the splits decided by one wavefront have orders of their own, each the same in every launch.)
+// lanes own one block each.  (The candidates of the 16-bit search copy that are re-scored in float64, UpdateVar and
+// the splits decided by one wavefront have orders of their own, each the same in every launch.)
 
 // One thread: block_sum(k) returns the sum of block k (k = 0..15, called in ascending k).
 template <class F>
@@ -320,6 +321,12 @@ __device__ inline char* page_ptr(const View& v, int u, int page) {
 // Key coordinate d of the token in `slot` of `page`, as float.
 __device__ inline float page_key(const View& v, int u, int page, int slot, int d) {
   return load_elem(page_ptr(v, u, page), k_index(v.dtype, slot, d), v.dtype);
+}
+
+// Integers that order like the floats.
+__device__ inline uint32_t orderable(float f) {
+  const uint32_t b = __float_as_uint(f);
+  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
 // Asks for every cache line of a kernel's first BYTES of arguments at once: read where they are needed, each line of a large

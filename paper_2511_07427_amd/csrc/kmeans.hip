@@ -11,7 +11,8 @@
 // update, which reads the keys of the points that changed their cluster.  256 units x 4096 float16 keys x 256 centres:
 // assignment 116 us, update 37 us, where nine launches that formed every sum anew, checked near-ties in a kernel of their
 // own and split the centres into two 16-bit terms took 320 us; build and export of the partition 4.12 -> 2.56 ms (128 x 8192 x
-// 512: 5.21 -> 3.17 ms; 8 x 16384 x 2048 bfloat16: 3.72 -> 2.16 ms).  How many points the float64 decisions take depends on the
+// 512: 5.21 -> 3.17 ms; 8 x 16384 x 2048 bfloat16: 3.72 -> 2.16 ms); with the distances in the layout pass, records in whole
+// lines and reseeding spread over the chip 2.25, 2.94 and 2.08 ms.  How many points the float64 decisions take depends on the
 // keys; what is slower than on the mixture of these figures is given where it is handled (Offset, scan_centres,
 // kmeans_changed_kernel, kmeans_slow_kernel).
 #include <algorithm>

@@ -3,6 +3,7 @@
 //                   whole-step call left), UpdateVar, threshold test, AddEntry + UpdateStats or buffer + flag;
 //                   in a whole-step call the due splits follow in the same launch
 //   split_kernel  - delayed splits of flagged clusters in the active set, then the forced split
+//   extend_batch_kernel, extend_kernel - a further chunk of the prompt, entry by entry, with every split done at once
 // One workgroup per unit; each unit's record is touched by that workgroup only.  All decisions are
 // taken on float64 values summed in an order that does not depend on the launch, ties to the lowest index.
 #include "split.hpp"

@@ -6,7 +6,7 @@
 //   gather_attend  - streams the selected clusters' pages once; QK^T and PV on matrix cores with an
 //                    online (running-max) softmax, so any gather order is overflow-safe; split over
 //                    several workgroups per unit and merged by the last one to arrive.
-//   retrieve_fused - all of the above for one unit in one workgroup and, in a whole decode step, the append
+//   retrieve_fused - all of the above for one unit in one workgroup (or several that share its pages) and, in a whole decode step, the append
 //                    (Section 4.2) and the due splits as well: the step is one launch.
 #include <algorithm>
 #include <type_traits>
@@ -151,11 +151,6 @@ __global__ __launch_bounds__(256) void score_mfma_kernel(View v, const void* Q, 
 }
 
 // ------------------------------------------------------------------------------------------- selection
-__device__ inline uint32_t orderable(float f) {
-  const uint32_t b = __float_as_uint(f);
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-
 constexpr int kIdBits = 18, kIdMask = (1 << kIdBits) - 1;   // a candidate's key: score above, kIdMask - id below
 static_assert(kMaxClusters <= kIdMask + 1, "cluster ids must fit the candidate keys");
 constexpr int kCountMax = 1024;     // selected clusters ordered by counting; larger selections take the full sort
@@ -388,7 +383,7 @@ __device__ inline int emit_by_id(const View& v, int u, int M, const SelectLds& s
 // The same for any number of clusters whose sizes are not in LDS: thread t takes a run of the bitmap's words and walks its set bits
 // eight at a time, once for the sizes and once more, when its place in the list is known, for the page tables.  (8 units of
 // 50 000 clusters, 1600 selected: ranking them by score, with bins of up to a few hundred keys, took 8 to 45 us of the selection, this
-// takes 5.)
+// takes 5.)  A snapshot lists these units' selection by score as it always has: where each cluster's entries begin is left for it.
 template <int NT>
 __device__ inline int emit_by_bits(const View& v, int u, int M, const SelectLds& s, int take_all) {
   const int tid = threadIdx.x;
@@ -425,7 +420,7 @@ __device__ inline int emit_by_bits(const View& v, int u, int M, const SelectLds&
         if (id[e] < 0) continue;
         const int take = take_all >= 0 ? take_all : w[e];
         if (pass) {
-          v.sel_ids[cb + cnt] = id[e];
+          v.sel_ids[cb + cnt] = id[e]; v.pg_off[cb + cnt] = tok;
           emit_cluster(v, u, take, pa[e], pb[e], quads, tok, plist, poff, s);
         }
         tok += take; quads += (take + 3) >> 2; ++cnt;
@@ -442,7 +437,7 @@ __device__ inline int emit_by_bits(const View& v, int u, int M, const SelectLds&
 // is found by a radix search over the 32-bit orderable scores (four passes of size-weighted 256-bin histograms);
 // everything above it is selected, equal scores are taken by ascending id while they fit.  With keys, sizes and
 // the active set's bitmap in LDS (s.skey, s.sw, s.selbits; at most MAXR clusters per thread) the gather list then
-// follows the cluster ids (emit_by_id).  Otherwise (more clusters than LDS holds) each selected cluster finds its
+// follows the cluster ids (emit_by_id).  Otherwise (more clusters than LDS holds, and not MAPPED) each selected cluster finds its
 // rank and its gather offsets by counting the selected clusters that precede it: the list is in score order, and at
 // most CMAX clusters can be selected (more: the retrieval is cut short and DYNAKV_ERR_SELECT is set).
 // first_ready: the caller has zeroed s.hist and set s.misc (entry 4 = 0x7fffffff, the others 0), has added every
@@ -788,6 +783,7 @@ __device__ inline int select_phase(const View& v, int u, int M, int budget, cons
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int r = tid * PER + k;
+    if (r < cut) v.pg_off[cb + r] = (int)(pre & 0xFFFFFFu);
     if (r < cut)      // id, first gather offset, first list entry
       ck[r] = ((unsigned long long)by_id[r] << 46) | ((pre & 0xFFFFFFu) << 22) | ((pre >> 32) & 0x3FFFFFu);   // 18 + 24 + 22 bits
     pre += loc[k];
@@ -920,7 +916,8 @@ __device__ inline int contenders(const View& v, int u, int M, int budget, float 
 }
 
 // One workgroup per unit.  BIG: more than kSelectLds clusters per unit: scores and sizes stay in the workspace (they
-// are a few hundred KB per unit), LDS holds the contenders and a larger candidate list instead.
+// are a few hundred KB per unit), LDS holds the contenders and a bitmap of the active set, or the keys stay in memory and LDS holds
+// a larger candidate list (see MAPPED).
 constexpr int kCountBig = 4096;
 template <bool BIG>
 __global__ __launch_bounds__(1024) void select_kernel(View v, const void* Q, int budget) {

@@ -69,11 +69,33 @@ __device__ __forceinline__ void for_each_table_piece(F&& f) {
   for (int k = wave; k < 32; k += 4) f((k >> 1) * 4 + (lane & 3), ((k & 1) * 16 + (lane >> 2)) * 4);
 }
 
+// Where more than kSelectLds clusters are possible, a retrieval lists the selected clusters by id or by score, whichever it can do
+// sooner, and a snapshot lists them by descending score (lowest id among equals).  The number of selected clusters that come before
+// the i-th of the list there, and how many entries they have.
+__device__ inline int selected_before(const View& v, int u, int i, int n, int& entries) {
+  const size_t cb = (size_t)u * v.Mcap;
+  const int id = v.sel_ids[cb + i];
+  const uint32_t key = orderable(v.score[cb + id]);
+  int before = 0;
+  entries = 0;
+#pragma unroll 4
+  for (int k = 0; k < n; ++k) {
+    const int o = v.sel_ids[cb + k];
+    const uint32_t ok = orderable(v.score[cb + o]);
+    if (ok > key || (ok == key && o < id)) {
+      ++before;
+      entries += (k + 1 < n ? v.pg_off[cb + k + 1] : v.t_sel[u]) - v.pg_off[cb + k];
+    }
+  }
+  return before;
+}
+
 // Clusters 64 blockIdx.x .. + 63 of unit blockIdx.y: records, centroids, and the members (keys and values too) page by page,
 // sixteen lanes per cluster.
 __global__ __launch_bounds__(256) void export_clusters_kernel(View v, dynakv_state_t o) {
   const int u = blockIdx.y, tid = threadIdx.x, M = v.M[u], j0 = blockIdx.x * kStateTile;
   const size_t cbase = (size_t)u * v.Mcap;
+  const bool by_score = v.Mcap > kSelectLds && v.n_list[u] > 0;      // (an imported selection has no list and stays as it came)
   if (tid < kStateTile && j0 + tid < v.Mcap) {
     const int j = j0 + tid;
     const size_t cj = cbase + j;
@@ -83,7 +105,12 @@ __global__ __launch_bounds__(256) void export_clusters_kernel(View v, dynakv_sta
     if (o.flag) o.flag[cj] = in ? v.cflag[cj] : 0;
     if (o.m2) o.m2[cj] = in ? v.cM2[cj] : 0.0;
     if (o.scores) o.scores[cj] = in ? v.score[cj] : 0.f;
-    if (o.selected) o.selected[cj] = j < v.n_sel[u] ? v.sel_ids[cj] : -1;
+    if (o.selected) {
+      const int n = v.n_sel[u];
+      int to = j, entries;
+      if (by_score && j < n) to = selected_before(v, u, j, n, entries);
+      o.selected[cbase + to] = j < n ? v.sel_ids[cj] : -1;
+    }
     if (o.first_page) o.first_page[cj] = in && v.csz[cj] > 0 ? v.cpg[cj * kInlinePages] : -1;
   }
   if (o.centroids) {
@@ -102,10 +129,21 @@ __global__ __launch_bounds__(256) void export_clusters_kernel(View v, dynakv_sta
   if (o.gathered) {
     const int nl = v.n_list[u];
     for (int w = blockIdx.x * 256 + tid; w < nl; w += gridDim.x * 256) {
-      const int e = v.plist[(size_t)u * v.Lcap + w], t0 = v.plist_off[(size_t)u * v.Lcap + w];
+      const int e = v.plist[(size_t)u * v.Lcap + w];
+      int t0 = v.plist_off[(size_t)u * v.Lcap + w];
+      if (by_score) {                                    // the cluster that this entry belongs to, and its place by score
+        int lo = 0, hi = v.n_sel[u] - 1, entries;
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (v.pg_off[cbase + mid] <= t0) lo = mid; else hi = mid - 1;
+        }
+        const int from = v.pg_off[cbase + lo];
+        selected_before(v, u, lo, v.n_sel[u], entries);
+        t0 += entries - from;
+      }
       const int page = e >> 4, first = ((e >> 2) & 3) * 4, nv = (e & 3) + 1;
       for (int sl = 0; sl < nv; ++sl)
-        o.gathered[(size_t)u * v.Ncap + t0 + sl] = v.ppos[((size_t)u * v.Pcap + page) * kPageTokens + first + sl];
+        if ((unsigned)(t0 + sl) < (unsigned)v.Ncap) o.gathered[(size_t)u * v.Ncap + t0 + sl] = v.ppos[((size_t)u * v.Pcap + page) * kPageTokens + first + sl];
     }
   }
   if (!(o.members || o.keys || o.values)) return;

@@ -196,3 +196,31 @@ def test_extension_decides_ties_between_coinciding_clusters():
     o.extend(K.float().cpu().numpy(), V.float().cpu().numpy())
     assert not compare_state(ix, o, tally, "ties", assign=False)
     assert int(ix.dynakv_export_state(["n_clusters"])["n_clusters"].min()) > 12
+
+
+@pytest.mark.parametrize("clusters,copies", [(700, 0), (700, 2), (20, 20), (17000, 0)])
+def test_snapshot_lists_a_long_selection_by_score(clusters, copies):
+    """Where more than 16384 clusters are possible a snapshot lists the last selection by descending score, the lowest id first
+    among equals, and the entries in that order, whichever order the retrieval has attended them in (copies of a cluster have
+    equal scores: a cut among them is left to the selection on the scores in memory)."""
+    gen = torch.Generator(device=DEV).manual_seed(clusters + copies)
+    sizes = [[1 + (7 * j) % 3 if clusters < 5000 else 1 for j in range(clusters)]] * 2
+    N = sum(sizes[0])
+    s = WorkloadSpec("listing", "f16", 2, 2, N, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, seed=9)
+    ix, o = make_pair(s, 2, max_tokens=N, max_clusters=17100)
+    st = snapshot("f16", sizes, [0, 0], 17100, N, gen, 0.0, 6.0)
+    for j in range(1, copies):
+        st["centroids"][:, j] = st["centroids"][:, 0]
+    ix.dynakv_import_state(st)
+    out, lse = torch.empty(2, 2, D, device=DEV), torch.empty(2, 2, device=DEV)
+    Q = (st["centroids"][:, :1] + 0.5 * torch.randn(2, 2, D, generator=gen, device=DEV)).half().contiguous()
+    for budget in (1, 2, 30, 333, min(N // 2, 4000)):
+        ix.dynakv_retrieve_attend(Q, budget, out, lse)
+        e = ix.dynakv_export_state(["n_selected", "selected", "n_gathered", "gathered", "scores", "offsets", "members", "error"])
+        assert not e["error"].any()
+        for u in range(2):
+            ids, score = e["selected"][u, :e["n_selected"][u]].long(), e["scores"][u]
+            assert ids.tolist() == sorted(ids.tolist(), key=lambda j: (-float(score[j]), j)), budget
+            off, mem = e["offsets"][u].tolist(), e["members"][u]
+            want = torch.cat([mem[off[j]:off[j + 1]] for j in ids.tolist()])[:budget]
+            assert int(e["n_gathered"][u]) == len(want) and torch.equal(e["gathered"][u, :len(want)], want), budget
