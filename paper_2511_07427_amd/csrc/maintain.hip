@@ -137,7 +137,7 @@ __global__ __launch_bounds__(256) void append_kernel(View v, const void* kin, co
 // trip to memory: nearest cluster from the entry's row of z (float64 where the runner-up lies within the rounding bound), UpdateVar and
 // threshold on the slot, and one matrix product of the new centroid with the entries to come, which corrects their z of that
 // cluster.  A cluster outside the slots is fetched when it is met; a flag calls the whole workgroup for the split, after which the
-// z of the two clusters that it leaves are put right in the same way.  LDS holds z of kExtendClusters clusters for one entry, of a
+// z of the two clusters that it leaves are put right in the same way (a split of any other cluster ends the batch).  LDS holds z of kExtendClusters clusters for one entry, of a
 // sixteenth of that for sixteen.
 // 256 units, 256 clusters, 1024 entries (163 splits a unit): 10.3 -> 4.8 ms, of which an entry takes 2.1 us where nothing is
 // flagged (6.6).
@@ -399,14 +399,17 @@ __global__ __launch_bounds__(256) void extend_batch_kernel(View v, const void* K
       }
       __syncthreads();
       r = s_done;
+      const bool own = s_planned != 0;                 // the entry's own flag is the unit's only one
       if (s_nflag == 0) break;                         // workgroup-uniform
-      split_unit<DT>(v, u, sp.raw, sp.wk, s_planned != 0);
+      split_unit<DT>(v, u, sp.raw, sp.wk, own);
       __syncthreads();
       if (r == nb) break;
       const int M1 = us.M;
       us = load_unit(v, u);
       fl = us.top - 1 - lane >= 0 ? v.freelist[(size_t)u * v.Pcap + us.top - 1 - lane] : -1;
-      if (us.nflag != 0 || us.M > M1 + 1) break;       // (more than the one split: the next batch begins)
+      // clusters that were flagged before the call are split along with the first entry: z and slots of the batch still hold their
+      // parents, and the next batch begins
+      if (!own || us.nflag != 0 || us.M > M1 + 1) break;
     }
     t += r;
     __syncthreads();                                   // (s_done and the slots are read before the next batch writes them)

@@ -10,9 +10,9 @@ import torch
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 
 import parity  # noqa: E402
-from parity import DEV, Tally, compare_state, make_pair  # noqa: E402
+from parity import DEV, Tally, compare_build, compare_state, make_pair, to_dev  # noqa: E402
 from paper_2511_07427_amd import binding  # noqa: E402
-from paper_2511_07427_amd.workload import WorkloadSpec  # noqa: E402
+from paper_2511_07427_amd.workload import CONFIGS, WorkloadSpec, generate  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 D = 128
@@ -130,6 +130,70 @@ def test_extension_across_batches(dtype, M, n, Mcap):
     assert not dirty and not out["error"].any()
     if n >= 20:
         assert int(out["n_clusters"].min()) > M
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_extension_of_an_index_that_holds_flagged_clusters(dtype):
+    """Flagged clusters from before the call (a snapshot's; none, one, two and one that cannot be split) are split along with the
+    first entry, which goes elsewhere; the entries that follow in the same batch go to them."""
+    n = 40
+    sizes = [[40, 30, 9, 12, 6, 20, 3, 11]] * 5
+    flagged = [1, 2, 1, 0, 2]
+    gen = torch.Generator(device=DEV).manual_seed(17)
+    cap = sum(sizes[0]) + n
+    s = WorkloadSpec("flagged", dtype, 5, 2, cap, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=16, seed=17)
+    ix, o = make_pair(s, 5, max_tokens=cap, max_clusters=100)
+    st = snapshot(dtype, sizes, flagged, 100, cap, gen, 0.0, 9.0)
+    off, mem = st["offsets"], st["members"].long()
+    st["keys"][2, mem[2, :40]] = st["keys"][2, mem[2, :1]]           # unit 2: all entries equal, statistics that are not theirs
+    ix.dynakv_import_state(st)
+    tally = Tally()
+    parity.resync(ix, o, None, set(range(5)), tally)
+    K = torch.empty(5, n, D, device=DEV)
+    for u in range(5):
+        for t in range(n):
+            j = (4, 0, 0, 1, 0, 2, 1, 0)[t % 8]
+            at = int(off[u, j]) + (5 * t) % sizes[u][j]
+            K[u, t] = st["keys"][u, mem[u, at]].float() + 0.15 * torch.randn(D, generator=gen, device=DEV)
+    K = K.to(binding.TORCH_DTYPES[dtype])
+    V = torch.randn(5, n, D, generator=gen, device=DEV).to(K.dtype)
+    ix.dynakv_extend_index(K.contiguous(), V)
+    o.extend(K.float().cpu().numpy(), V.float().cpu().numpy())
+    assert not compare_state(ix, o, tally, "extension", assign=False)
+    e = ix.dynakv_export_state(["n_clusters", "flag", "error", "keys", "values"])
+    print("flagged before the extension", dtype, e["n_clusters"].tolist(), dict(tally), flush=True)
+    assert not e["flag"].any() and not e["error"].any()
+    N = sum(sizes[0])
+    assert torch.equal(e["keys"][:, N:], K.cpu()) and torch.equal(e["values"][:, N:], V.cpu())
+    Q = (K[:, :2].float() + 0.1 * torch.randn(5, 2, D, generator=gen, device=DEV)).to(K.dtype).contiguous()
+    out, lse = torch.empty(5, 2, D, device=DEV), torch.empty(5, 2, device=DEV)
+    for budget in (50, 1000):
+        ix.dynakv_retrieve_attend(Q, budget, out, lse)
+        oo, ol = o.retrieve_attend(Q.float().cpu().numpy(), budget)
+        assert not parity.compare_retrieval(ix, o, tally, "after it", Q=Q.float().cpu().numpy(), budget=budget)
+        parity.check_attention(out.cpu().numpy(), lse.cpu().numpy(), oo, ol, "after it")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_extension_after_decode_steps_that_leave_flags(dtype):
+    """A chunk after decode steps whose delayed splits are still due."""
+    s = CONFIGS["llama3_8b"].scaled(dtype=dtype, prefill=1024, n_clusters_init=48, budget=120, var_alpha=1.1, drift_std=0.1, buffer_max=40)
+    U, steps, n = 4, 96, 64
+    w = generate(s, units=range(U), steps=steps + n)
+    ix, o = make_pair(s, U, max_tokens=1024 + steps + n, kmeans_iters=4)
+    ix.dynakv_build_index(to_dev(w["K0"], dtype), to_dev(w["V0"], dtype), torch.from_numpy(w["init_idx"]).to(DEV))
+    o.build_index(w["K0"], w["V0"], w["init_idx"])
+    sp = parity.Stepper(ix, o, s, w)
+    compare_build(ix, o, sp.tally, 1024)
+    for t in range(steps):
+        sp.step(t, True, attention=False, full=t == steps - 1)
+    left = ix.dynakv_export_state(["flag"])["flag"].sum(1).tolist()
+    K1, V1 = (np.ascontiguousarray(w[k][steps:].transpose(1, 0, 2)) for k in ("Knew", "Vnew"))
+    ix.dynakv_extend_index(to_dev(K1, dtype), to_dev(V1, dtype))
+    o.extend(K1, V1)
+    assert not compare_state(ix, o, sp.tally, "extension", assign=False)
+    e = ix.dynakv_export_state(["flag", "error"])
+    print("extension after steps", dtype, left, dict(sp.tally), flush=True)
+    assert min(left) >= 1 and not e["flag"].any() and not e["error"].any()
 
 
 @pytest.mark.parametrize("dtype,units,G", [("f16", 3, 4), ("bf16", 40, 7), ("f32", 2, 5)])
