@@ -338,7 +338,6 @@ __global__ __launch_bounds__(256) void extend_batch_kernel(View v, const void* K
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // (this batch's centroids are in place)
             const float2 kf = pair_value<DT>(e.k);
             double best = __builtin_inf();
-            const int j32 = j;
             j = -1;
 #pragma unroll 1
             for (int j0 = 0; j0 < Mz; j0 += 64)
@@ -350,7 +349,7 @@ __global__ __launch_bounds__(256) void extend_batch_kernel(View v, const void* K
                 const double d = wave_sum_f64(fma(d0, d0, d1 * d1));
                 if (d < best || j < 0) { best = d; j = c; }
               }
-            if (j < 0) j = max(j32, 0);                  // (an entry that is not finite)
+            j = max(j, 0);                               // (an entry that is not finite is near nothing: as dynakv_append has it)
             if (lane == 0) count(v, u, 7, 1);
           }
           // the cluster's slot: the first that holds it

@@ -174,6 +174,33 @@ def test_extension_of_an_index_that_holds_flagged_clusters(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_extension_takes_entries_that_are_not_finite_as_an_append_does(dtype, bad):
+    """Such an entry is at no finite distance from any cluster: it goes to the lowest id, in a chunk as in an append."""
+    sizes, n = [[6, 5, 7, 4, 6, 5, 3, 4]] * 2, 12
+    cap = sum(sizes[0]) + n
+    gen = torch.Generator(device=DEV).manual_seed(31)
+    st = snapshot(dtype, sizes, [0, 0], 40, cap, gen, 0.0, 9.0)
+    K = (st["keys"][:, :n].float() + 0.1 * torch.randn(2, n, D, generator=gen, device=DEV)).to(binding.TORCH_DTYPES[dtype])
+    K[:, 3, 17] = bad
+    V = torch.randn(2, n, D, generator=gen, device=DEV).to(K.dtype)
+    s = WorkloadSpec("bad", dtype, 2, 2, cap, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=0, seed=31)
+    a, b = (make_pair(s, 2, max_tokens=cap, max_clusters=40)[0] for _ in range(2))
+    for ix in (a, b):
+        ix.dynakv_import_state(st)
+    a.dynakv_extend_index(K.contiguous(), V)
+    for t in range(n):
+        b.dynakv_append(K[:, t].contiguous(), V[:, t].contiguous())
+        b.dynakv_split()
+    ea, eb = (ix.dynakv_export_state(["n_clusters", "size", "offsets", "members", "error"]) for ix in (a, b))
+    for k in ea:
+        assert torch.equal(ea[k], eb[k]), k
+    for u in range(2):
+        off, mem = ea["offsets"][u], ea["members"][u]
+        assert sum(sizes[0]) + 3 in mem[off[0]:off[1]].tolist()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_extension_after_decode_steps_that_leave_flags(dtype):
     """A chunk after decode steps whose delayed splits are still due."""
     s = CONFIGS["llama3_8b"].scaled(dtype=dtype, prefill=1024, n_clusters_init=48, budget=120, var_alpha=1.1, drift_std=0.1, buffer_max=40)
