@@ -1104,8 +1104,9 @@ __device__ inline void wave_two_means(WaveCtx& c, const unsigned char* stage, in
           if (__ballot(unsure != 0)) {                             // float64 centres for those
             double w0, w1, d0, d1;
             wave_set_sums<DT>(stage, A ^ first_A, first_A & ~A, m, lane, d0, d1);
-            const double na = 1.0 / (double)nA, nb = 1.0 / (double)(m - nA);
-            ca0 = (sa0 + d0) * na; ca1 = (sa1 + d1) * na; cb0 = (tot0 - (sa0 + d0)) * nb; cb1 = (tot1 - (sa1 + d1)) * nb;
+            const CountInverse na = count_inverse(nA), nb = count_inverse(m - nA);       // (rounded as a division: exact ties stay)
+            ca0 = over_count(sa0 + d0, na); ca1 = over_count(sa1 + d1, na);
+            cb0 = over_count(tot0 - (sa0 + d0), nb); cb1 = over_count(tot1 - (sa1 + d1), nb);
             w0 = cb0 - ca0; w1 = cb1 - ca1;
             const double tt = wave_sum_f64(0.5 * ((cb0 * cb0 - ca0 * ca0) + (cb1 * cb1 - ca1 * ca1)));
 #pragma unroll 1
@@ -1128,9 +1129,9 @@ __device__ inline void wave_two_means(WaveCtx& c, const unsigned char* stage, in
           double d0, d1;
           wave_set_sums<DT>(stage, anew ? nw : moved, anew ? 0ull : leaves, m, lane, d0, d1);
           sa0 = anew ? d0 : sa0 + d0; sa1 = anew ? d1 : sa1 + d1;
-          const double ia = 1.0 / (double)nA, ib = 1.0 / (double)(m - nA);     // (centres of a round: one rounding more is harmless)
-          ca0 = sa0 * ia; ca1 = sa1 * ia;
-          cb0 = (tot0 - sa0) * ib; cb1 = (tot1 - sa1) * ib;
+          const CountInverse ia = count_inverse(nA), ib = count_inverse(m - nA);
+          ca0 = over_count(sa0, ia); ca1 = over_count(sa1, ia);
+          cb0 = over_count(tot0 - sa0, ib); cb1 = over_count(tot1 - sa1, ib);
         } else if (first) {                                        // R of the smaller side, as one vector (Rall: from the seeds' search)
           const bool isA = 2 * nA <= m;
           double d0, d1;

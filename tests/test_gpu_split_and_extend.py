@@ -88,6 +88,39 @@ def test_splits_at_the_edges_of_every_path(dtype, offset):
     assert int(ix.dynakv_export_state(["n_clusters"])["n_clusters"].sum()) >= 5 * len(sizes) - 2
 
 
+# (value, members) of clusters whose 2-means ends on an exact tie: centres p and q with a member at (p + q) / 2, where sum * (1 / n)
+# is not sum / n
+TIED = [((0, 3), (1, 150), (4, 1), (5, 5), (7, 89), (9, 5)), ((2, 6), (3, 96), (5, 3), (6, 12), (7, 111), (11, 3)),
+        ((1, 25), (2, 75), (7, 5), (10, 6), (12, 89), (15, 4)), ((6, 20), (7, 125), (11, 5), (14, 12), (15, 40), (19, 3)),
+        ((2, 6), (3, 114), (5, 3), (6, 12), (7, 9), (11, 3)), ((3, 8), (5, 93), (9, 4), (10, 2), (13, 12), (16, 2))]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_a_member_halfway_between_the_centres_goes_to_the_first(dtype):
+    """Centres of a round are rounded as a division rounds them: all values here are small whole numbers, every comparison is
+    exact, and the tie goes to side A whatever path the cluster takes."""
+    units = [(t, sign) for t in TIED for sign in (1, -1)]
+    sizes = [[sum(n for _, n in t), 3] for t, _ in units]
+    cap = max(sum(x) for x in sizes)
+    gen = torch.Generator(device=DEV).manual_seed(41)
+    st = snapshot(dtype, sizes, [1] * len(units), 8, cap, gen)
+    for u, (t, sign) in enumerate(units):
+        x = sign * torch.cat([torch.full((n,), float(v), device=DEV) for v, n in t])
+        x = x[torch.randperm(len(x), generator=gen, device=DEV)]
+        keys = torch.zeros(len(x), D, device=DEV)
+        keys[:, 5] = x
+        st["keys"][u, st["members"][u, :len(x)].long()] = keys.to(st["keys"].dtype)
+    s = WorkloadSpec("tied", dtype, len(units), 2, cap, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=0, seed=41)
+    ix, o = make_pair(s, len(units), max_tokens=cap, max_clusters=8)
+    ix.dynakv_import_state(st)
+    tally = Tally()
+    parity.resync(ix, o, None, set(range(len(units))), tally)
+    ix.dynakv_split()
+    o.split()
+    assert not compare_state(ix, o, tally, "tied", assign=False)
+    assert ix.dynakv_export_state(["n_clusters"])["n_clusters"].tolist() == [3] * len(units)
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 def test_splits_of_several_clusters_at_once(dtype):
     """Plans that mix sizes: four small ones side by side, wide ones two at a time, one that takes the whole workgroup before,
