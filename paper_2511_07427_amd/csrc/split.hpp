@@ -1219,9 +1219,10 @@ __device__ inline void wave_two_means(WaveCtx& c, const unsigned char* stage, in
 // Decides one split, by one wavefront (W = 1; w = 0) or by the W wavefronts of the workgroup together (wavefront w of them):
 // stages the keys (c.chain lists their pages), 2-means, stable partition, exact statistics of the children (of the unsplit
 // cluster if the 2-means finds nothing to split).  Sets c.ok, c.nS, c.perm, c.inv, c.pos, the float32 means c.rA / c.rB and
-// the M2 about them, c.m2.  part: 128 W float64 of LDS.
+// the M2 about them, c.m2.  part: 128 W float64 of LDS.  f64: SplitPlan::f64.
 template <int DT>
-__device__ __forceinline__ void wave_split_decide(const View& v, int u, WaveCtx& c, int w, int W, double* part, uint4 (&vahead)[kVAhead]) {
+__device__ __forceinline__ void wave_split_decide(const View& v, int u, WaveCtx& c, int w, int W, bool f64, double* part,
+                                                  uint4 (&vahead)[kVAhead]) {
   const int lane = threadIdx.x & 63;
   constexpr int kEs = DT == DYNAKV_F32 ? 4 : 2;
   constexpr int kChunks = kKeyChunks<DT>;
@@ -1267,8 +1268,8 @@ __device__ __forceinline__ void wave_split_decide(const View& v, int u, WaveCtx&
   if (w == 0) wave_two_means<DT>(c, stage, m, tot0, tot1);
   split_sync(W);
   // M2 of the children about their means (differences in float32, off by 2^-24 of themselves; sums of 32 squares in
-  // float32, the rest in float64; all of it in float64 for clusters that only four wavefronts together take, as the workgroup
-  // path has it)
+  // float32, the rest in float64; all of it in float64 in a plan with a cluster that only four wavefronts together take, as the
+  // workgroup path has it)
   const WaveKeys<DT> ks{stage};
   const int grp = lane >> 2, kb = lane & 3, nS = c.nS;
   double acc[2] = {0.0, 0.0};
@@ -1276,7 +1277,7 @@ __device__ __forceinline__ void wave_split_decide(const View& v, int u, WaveCtx&
   for (int base = 16 * w; base < m; base += 16 * W) {
     const int q = base + grp;
     double d;
-    if (m > 2 * kSmallRows<DT>) {
+    if (f64) {                                            // the same in every wavefront
       double none;
       quad_sqdist<WaveKeys<DT>, float>(ks, c.perm[min(q, m - 1)], kb, q < nS ? c.rA : c.rB, nullptr, d, none);
     } else {
@@ -1392,6 +1393,7 @@ struct SplitPlan {
   alignas(16) int pg[64][kInlinePages]; // their first pages
   int cand[64];                          // positions in the list, in the order of the splits
   int n_cand, forced, fast;
+  int f64;                               // a cluster is larger than two contexts' rows: the statistics of all are float64 sums of float64 squares
   int M, top, bump;                      // the unit's counters while the plan is carried out
   int fl[kFreeAhead], fl_base;           // top of the free-page stack, read ahead: fl[k] = entry fl_base - 1 - k
 };
@@ -1474,6 +1476,7 @@ __device__ inline void plan_splits(const View& v, SplitPlan& pl, const PlanEntry
   const int pages = wave_sum(isc ? (e.m + kPageTokens - 1) / kPageTokens + 1 : 0);
   if (lane == 0) {
     pl.n_cand = nc; pl.forced = forced;
+    pl.f64 = largest > 2 * kSmallRows<DT>;
     pl.fast = largest <= kLoneRows<DT> && pl.M + nc <= v.Mcap && pages <= pl.top + (v.Pcap - pl.bump);
   }
 }
@@ -1594,7 +1597,7 @@ __device__ inline void split_predecide(const View& v, int u, unsigned char* raw,
   // on the same SIMD (the tiles that one does not take meanwhile go to the other wavefronts)
   __builtin_amdgcn_s_setprio(3);
   wave_take(v, u, wk.pl, wk.pl.cand[k], (WaveCtx*)raw, ctx_of(k), wk.wide != 0, false, threadIdx.x & 63);
-  wave_split_decide<DT>(v, u, c, 0, 1, c.cB, pre_v);
+  wave_split_decide<DT>(v, u, c, 0, 1, wk.pl.f64 != 0, c.cB, pre_v);
   __builtin_amdgcn_s_setprio(0);
 }
 
@@ -1702,7 +1705,7 @@ __device__ __forceinline__ void split_unit(const View& v, int u, unsigned char* 
         WaveCtx& c = wc[ctx_of(k)];
         if (mine && w == 0) wave_take(v, u, pl, pl.cand[base + k], wc, ctx_of(k), wide, W > 1, lane);
         if (W > 1) lds_barrier();
-        if (mine) wave_split_decide<DT>(v, u, c, w, W, W > 1 ? (double*)raw : c.cB, vahead);
+        if (mine) wave_split_decide<DT>(v, u, c, w, W, pl.f64 != 0, W > 1 ? (double*)raw : c.cB, vahead);
         lds_barrier();
         if (wave == 0) split_assign(v, u, wc, pl, n);            // ids and pages, in the order of the splits
         lds_barrier();

@@ -88,6 +88,19 @@ def test_splits_at_the_edges_of_every_path(dtype, offset):
     assert int(ix.dynakv_export_state(["n_clusters"])["n_clusters"].sum()) >= 5 * len(sizes) - 2
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("sizes,flagged", [((10, 200, 12, 8, 60, 31), 6), ((150, 9), 2), ((2, 2, 3, 130), 4), ((20, 300, 40), 3)])
+def test_statistics_beside_a_large_cluster_are_float64_sums(dtype, sizes, flagged):
+    """A plan with a cluster above 128 entries (64 of float32) takes the squares of all its children in float64: M2 is off by the
+    roundings of two float64 sums of m * 128 squares in different orders, not by those of float32 squares (up to 2^-18)."""
+    ix, o, tally, _ = pair(dtype, [list(sizes)] * 3, [flagged] * 3, 40, offset=3.0)
+    ix.dynakv_split()
+    o.split()
+    assert not compare_state(ix, o, tally, "beside a large one", assign=False)
+    print("beside a large cluster", dtype, sizes, dict(tally), flush=True)
+    assert tally["m2_rel"] <= 2 * 128 * max(sizes) * 2.0 ** -53
+
+
 # (value, members) of clusters whose 2-means ends on an exact tie: centres p and q with a member at (p + q) / 2, where sum * (1 / n)
 # is not sum / n
 TIED = [((0, 3), (1, 150), (4, 1), (5, 5), (7, 89), (9, 5)), ((2, 6), (3, 96), (5, 3), (6, 12), (7, 111), (11, 3)),
