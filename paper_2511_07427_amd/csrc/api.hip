@@ -111,6 +111,7 @@ size_t carve(const dynakv_config_t& c, char* base, View* out) {
   v.var_alpha = c.var_alpha; v.size_factor = c.size_factor;
   v.scale_d = c.softmax_scale > 0.f ? (double)c.softmax_scale : 1.0 / std::sqrt((double)c.head_dim);
   v.scale_f = (float)v.scale_d;
+  v.share = (c.launch & 255) || v.U > 128 ? 1 : v.U <= 32 ? 8 : v.U <= 64 ? 4 : 2;      // (a number that the caller has given is kept)
   size_t off = 0;
   auto take = [&](size_t bytes) {
     char* p = base ? base + off : nullptr;
@@ -138,7 +139,7 @@ size_t carve(const dynakv_config_t& c, char* base, View* out) {
   v.pages = take(UP * (size_t)kPageElems * elem_size(c.dtype));
   v.ppos = (int*)take(UP * kPageTokens * 4); v.pnext = (int*)take(UP * 4); v.freelist = (int*)take(UP * 4);
   v.plist = (int*)take(U * v.Lcap * 4); v.plist_off = (int*)take(U * v.Lcap * 4);
-  v.part = (float*)take(U * std::max(v.S, retrieve_is_fused(v) ? fused_splits_max(v.U) : 1) * v.G * (kHeadDim + 2) * 4);
+  v.part = (float*)take(U * std::max(v.S, retrieve_is_fused(v) ? v.share : 1) * v.G * (kHeadDim + 2) * 4);
   v.labels = (int*)take(UN * 4); v.order = (int*)take(UN * 4); v.dist = (double*)take(UN * 8);
   v.koff = (int*)take(U * (v.Mcap + 1) * 4);
   const size_t mpad = km_pad(v.M0);
@@ -273,7 +274,7 @@ dynakv_status_t dynakv_retrieve_attend_static(dynakv_index_t* ix, const void* Q,
   if (!ix || !Q || !out || token_budget < 0) return DYNAKV_EINVAL;
   const View& v = ix->view;
   const bool fused = retrieve_is_fused(v);           // (its workgroups count their arrivals in the workspace, from launch to launch)
-  const size_t part_bytes = ((size_t)v.U * (fused ? fused_splits_max(v.U) : v.S) * v.G * (kHeadDim + 2) * sizeof(float) + 255) & ~(size_t)255;
+  const size_t part_bytes = ((size_t)v.U * (fused ? v.share : v.S) * v.G * (kHeadDim + 2) * sizeof(float) + 255) & ~(size_t)255;
   const size_t ticket_bytes = (size_t)v.U * sizeof(int);
   if (part_bytes + ticket_bytes > kStaticScratchBytes) return DYNAKV_ECAPACITY;
   if (!ix->built) return DYNAKV_ESTATE;

@@ -38,6 +38,7 @@ struct View {
   int static_update; // static-update baseline: nothing is ever flagged
   int token_level;   // every appended entry becomes a cluster of its own (baseline without clustering; local update)
   int local_W, local_k;  // local update: entries per local clustering and clusters it forms (0: not this mode)
+  int share;         // most workgroups of the single-kernel retrieval that may share a unit: 1, 2, 4 or 8
   size_t Rstride;    // floats of centroid table per unit
   float var_alpha, size_factor, scale_f;
   double scale_d;
@@ -93,7 +94,7 @@ struct View {
   int* plist;        // page * 16 + group * 4 + (valid tokens - 1)
   int* plist_off;    // gather offset of the entry's first token
   // split-KV partial results
-  float* part;       // [U][S][G][130]: 128 accumulators, running max (log2 domain), denominator
+  float* part;       // [U][S, or share where the single kernel runs][G][130]: 128 accumulators, running max (log2 domain), denominator
   // k-means / split scratch [U][Ncap]
   int* labels;
   int* order;        // positions sorted by (label, position)
@@ -479,8 +480,6 @@ hipError_t launch_build_index(const View& v, const void* K, const void* V, int n
 hipError_t launch_score_select(const View& v, const void* Q, int budget, const void* kin, hipStream_t st);
 hipError_t launch_near(const View& v, const void* kin, hipStream_t st);
 bool retrieve_is_fused(const View& v);
-// Most workgroups per unit that the single-kernel retrieval takes for U units (1, 2, 4 or 8).
-inline int fused_splits_max(int U) { return U <= 32 ? 8 : U <= 64 ? 4 : U <= 128 ? 2 : 1; }
 hipError_t launch_retrieve_fused(const View& v, const void* Q, int budget, float* out, float* lse, const void* kin,
                                  const void* vin, bool split, hipStream_t st);
 hipError_t launch_gather_attend(const View& v, const void* Q, float* out, float* lse, hipStream_t st);

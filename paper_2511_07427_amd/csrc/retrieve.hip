@@ -1839,9 +1839,8 @@ hipError_t launch_retrieve_fused(const View& v, const void* Q, int budget, float
   // 38.0 -> 33.3, step 45.8 -> 50.4; 2 units, 1 MB each: step 46.2 -> 34.8; 1 float32 unit, 1 MB: step 55.5 -> 37.2, 256 KB: 29.2 either way).
   const size_t bytes = (size_t)std::min(budget, v.Ncap) * 2 * kHeadDim * elem_size(v.dtype);
   const size_t worth = (v.U <= 16 ? 256 : kin ? 768 : v.U <= 64 ? 256 : 512) * 1024;
-  const int most = fused_splits_max(v.U);
   int S = 1;
-  while (S < most && bytes >= worth * 2 * S) S *= 2;
+  while (S < v.share && bytes >= worth * 2 * S) S *= 2;
   if (v.dtype == DYNAKV_F32) {
     if (v.G <= 4) launch_fused<DYNAKV_F32, 4>(v, Q, budget, out, lse, kin, vin, split, S, st);
     else launch_fused<DYNAKV_F32, 8>(v, Q, budget, out, lse, kin, vin, split, S, st);

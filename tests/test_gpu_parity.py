@@ -103,22 +103,25 @@ def test_whole_step_call_matches_the_three_calls(name, units, steps, launch):
     assert r["splits"] > 0 or name == "batched16"
 
 
-def test_long_run_through_the_whole_step_call_with_several_splits_per_step():
+@pytest.mark.parametrize("launch", [launch_shape(1), 0])
+def test_long_run_through_the_whole_step_call_with_several_splits_per_step(launch):
     # the steady state of the benchmark configuration in its launch shape (one workgroup per unit, the whole
-    # step in one kernel): small clusters, several due splits of one unit in one step (decided by separate
-    # wavefronts while the pages are streamed, the fourth after the attention)
+    # step in one kernel) and in the one that the library takes for so few units (two workgroups per unit): small
+    # clusters, several due splits of one unit in one step (decided by separate wavefronts while the pages are
+    # streamed)
     s = CONFIGS["llama3_8b"]
     r = run_trajectory(s, [16, 17, 18, 19, 20, 21, 22, 23], 2560, check_every=32, full_every=640, step_call="one",
-                       launch=launch_shape(1))
-    say("long:", {k: r[k] for k in ("worst_rel", "ties", "splits", "forced", "clusters", "most_splits_in_a_step")})
+                       launch=launch)
+    say("long:", launch, {k: r[k] for k in ("worst_rel", "ties", "splits", "forced", "clusters", "most_splits_in_a_step")})
     assert r["splits"] > 2000 and r["most_splits_in_a_step"] >= 3
 
 
-def test_long_run_through_the_whole_step_call_group_of_7():
-    # the same for the kernel variant that holds up to 8 query heads per KV head (bf16, G = 7)
+@pytest.mark.parametrize("launch", [launch_shape(1), 0])
+def test_long_run_through_the_whole_step_call_group_of_7(launch):
+    # the same for the kernel variant that holds up to 8 query heads per KV head (bf16, G = 7; four workgroups per unit)
     s = CONFIGS["qwen25_7b"]
-    r = run_trajectory(s, [30, 31, 32, 33], 2048, check_every=32, full_every=512, step_call="one", launch=launch_shape(1))
-    say("long, G = 7:", {k: r[k] for k in ("worst_rel", "ties", "splits", "forced", "clusters", "most_splits_in_a_step")})
+    r = run_trajectory(s, [30, 31, 32, 33], 2048, check_every=32, full_every=512, step_call="one", launch=launch)
+    say("long, G = 7:", launch, {k: r[k] for k in ("worst_rel", "ties", "splits", "forced", "clusters", "most_splits_in_a_step")})
     assert r["splits"] > 500 and r["most_splits_in_a_step"] >= 2
 
 

@@ -12,6 +12,7 @@ sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import parity  # noqa: E402
 from parity import DEV, Tally, compare_build, compare_state, make_pair, to_dev  # noqa: E402
 from paper_2511_07427_amd import binding  # noqa: E402
+from paper_2511_07427_amd.binding import launch_shape  # noqa: E402
 from paper_2511_07427_amd.workload import CONFIGS, WorkloadSpec, generate  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -306,6 +307,30 @@ def test_units_shared_by_several_workgroups(dtype, units, G):
         else:
             assert not compare_state(ix, o, tally, "budget %d" % budget)
     print("shared units", dtype, units, dict(tally), flush=True)
+
+
+@pytest.mark.parametrize("dtype,G", [("f16", 4), ("bf16", 7), ("f32", 5)])
+def test_a_given_number_of_workgroups_per_unit_is_kept(dtype, G):
+    """launch_shape(1) is one workgroup per unit in the single kernel too: retrievals of 8 units add up in the order, and give the
+    bits, of the same units among 136, which never share; left to the library, the 8 units are shared and the order is another."""
+    few = 8
+    sizes = [[1 + (j * 5 + u % few) % 23 for j in range(200)] for u in range(136)]
+    cap = max(sum(x) for x in sizes)
+    gen = torch.Generator(device=DEV).manual_seed(51)
+    st = snapshot(dtype, sizes[:few], [0] * few, 300, cap, gen, 0.0, 9.0)
+    Q = (st["keys"][:, 7:8].float() + 0.5 * torch.randn(few, G, D, generator=gen, device=DEV)).to(st["keys"].dtype)
+    outs, room = {}, {}
+    for name, U, launch in (("one", few, launch_shape(1)), ("many", 136, 0), ("free", few, 0)):
+        s = WorkloadSpec("kept", dtype, U, G, cap, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=0, seed=51)
+        ix = make_pair(s, U, max_tokens=cap, max_clusters=300, launch=launch, oracle_units=1)[0]
+        reps = U // few
+        ix.dynakv_import_state({k: x.repeat(reps, *[1] * (x.dim() - 1)).contiguous() for k, x in st.items()})
+        out, lse = torch.empty(U, G, D, device=DEV), torch.empty(U, G, device=DEV)
+        ix.dynakv_retrieve_attend(Q.repeat(reps, 1, 1).contiguous(), 2200, out, lse)
+        outs[name], room[name] = (out[:few].cpu(), lse[:few].cpu()), ix.workspace.numel()
+    assert all(torch.equal(a, b) for a, b in zip(outs["one"], outs["many"]))
+    assert not torch.equal(outs["one"][0], outs["free"][0])
+    assert torch.allclose(outs["one"][0], outs["free"][0], rtol=1e-4, atol=1e-5) and room["one"] < room["free"]
 
 
 def test_extension_decides_ties_between_coinciding_clusters():
