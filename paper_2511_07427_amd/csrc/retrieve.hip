@@ -1583,7 +1583,7 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   for (int k = 1; k < NW; ++k) rmu = max(rmu, am_r[k]);
   unit_rmax2 = __int_as_float(rmu);
   if constexpr (APPEND)
-    ja = nearest_decide<NT>(v, u, M, rn.kn, unit_rmax2, v.zdist + (size_t)u * v.Mcap, Rq, kd, am_v, am_i, am_2);
+    ja = nearest_decide<NT>(v, u, M, rn.kn, unit_rmax2, v.zdist + (size_t)u * v.Mcap, Rq, kd, am_v, am_i, am_2, share == 0);
   }
   // the append's record is requested here and used after the selection
   ClusterFetch apf{float2{0.f, 0.f}, 0};

@@ -223,12 +223,13 @@ __device__ __forceinline__ void wave_best2(float& zb, int& jb, float& z2) {
 // exact arithmetic finds nearest (lowest id among equals): if the runner-up lies beyond the error bound of the
 // best, the best is it; otherwise every cluster within the bound (read back from zd[0..M), which the caller has
 // made visible to the workgroup) is evaluated in float64.  kd: the key in float64 (LDS); kn, rmax2: |k| and the
-// largest |r~_j|^2.  sv / si / s2: 16 entries of LDS each.
+// largest |r~_j|^2.  sv / si / s2: 16 entries of LDS each.  tally: this workgroup counts a decision that is retaken (of those that
+// share a unit, and so take the same decision, one does).
 // Second half of nearest_resolve: every wavefront's (best, its cluster, runner-up) is in sv / si / s2 [0 .. NT / 64)
 // and a barrier lies behind that.
 template <int NT>
 __device__ inline int nearest_decide(const View& v, int u, int M, float kn, float rmax2, const float* zd, const uint16_t* Rq,
-                                     const double* kd, double* sv, int* si, float* s2) {
+                                     const double* kd, double* sv, int* si, float* s2, bool tally = true) {
   float zb = (float)sv[0], z2 = s2[0];
   int jb = si[0];
 #pragma unroll
@@ -246,7 +247,7 @@ __device__ inline int nearest_decide(const View& v, int u, int M, float kn, floa
       const double dj = exact_sqdist16(Rq, j, kd, v.dtype);
       if (arg < 0 || dj < best) { best = dj; arg = j; }
     }
-  if (threadIdx.x == 0) count(v, u, 7, 1);
+  if (tally && threadIdx.x == 0) count(v, u, 7, 1);
   return max(block_argmin<NT>(best, arg, sv, si), 0);      // (a key that is not finite is near nothing)
 }
 template <int NT>

@@ -12,7 +12,7 @@ sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import parity  # noqa: E402
 from parity import DEV, Tally, compare_build, compare_state, make_pair, to_dev  # noqa: E402
 from paper_2511_07427_amd import binding  # noqa: E402
-from paper_2511_07427_amd.binding import launch_shape  # noqa: E402
+from paper_2511_07427_amd.binding import LAUNCH_SEPARATE, launch_shape  # noqa: E402
 from paper_2511_07427_amd.workload import CONFIGS, WorkloadSpec, generate  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -331,6 +331,32 @@ def test_a_given_number_of_workgroups_per_unit_is_kept(dtype, G):
     assert all(torch.equal(a, b) for a, b in zip(outs["one"], outs["many"]))
     assert not torch.equal(outs["one"][0], outs["free"][0])
     assert torch.allclose(outs["one"][0], outs["free"][0], rtol=1e-4, atol=1e-5) and room["one"] < room["free"]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_decisions_retaken_are_counted_once_per_unit(dtype):
+    """Counter 7 of the exported state where every new entry lies as far from one cluster as from its copy: the same number of
+    decisions with one workgroup per unit, several, and separate kernels."""
+    sizes = [[1 + (j * 5) % 23 for j in range(200)]] * 3
+    cap = sum(sizes[0]) + 8
+    gen = torch.Generator(device=DEV).manual_seed(61)
+    st = snapshot(dtype, sizes, [0] * 3, 300, cap, gen, 0.0, 1e9)
+    off, mem = st["offsets"], st["members"].long()
+    st["centroids"][:, 1:200:2] = st["centroids"][:, 0:200:2]
+    counts = {}
+    for launch in (launch_shape(1), 0, LAUNCH_SEPARATE):
+        s = WorkloadSpec("counted", dtype, 3, 2, cap, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=0, seed=61)
+        ix = make_pair(s, 3, max_tokens=cap, max_clusters=300, launch=launch)[0]
+        ix.dynakv_import_state(st)
+        out, lse = torch.empty(3, 2, D, device=DEV), torch.empty(3, 2, device=DEV)
+        for t in range(8):
+            k = torch.stack([st["keys"][u, mem[u, int(off[u, 20 * t + 4])]] for u in range(3)]).contiguous()
+            Q = (k[:, None].float() + 0.5 * torch.randn(3, 2, D, generator=torch.Generator(device=DEV).manual_seed(t), device=DEV)).to(k.dtype)
+            ix.dynakv_decode_step(Q.contiguous(), 2200, out, lse, k, k)
+        counts[launch] = ix.dynakv_export_state(["counters"])["counters"][:, 4:].tolist()
+    print("retaken", dtype, counts, flush=True)
+    assert counts[0] == counts[launch_shape(1)] == counts[LAUNCH_SEPARATE]
+    assert all(c[3] >= 8 for c in counts[0])
 
 
 def test_extension_decides_ties_between_coinciding_clusters():
