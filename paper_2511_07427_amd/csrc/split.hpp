@@ -683,8 +683,8 @@ __device__ __forceinline__ void wave_distances(const WaveKeys<DT>& ks, const flo
 }
 // The member farthest from the centre (c0, c1: its coordinates 2 lane and 2 lane + 1), the lowest index among equals, from
 // the squared distances d32[0 .. m), each within eps + rel * sqrt(largest) + 3.1e-5 * largest * (rel >= 0) of the true one: the
-// members within twice that of the largest are compared in float64 if there are several (at most `most`; more: -1 with
-// `top` unchanged).  dub: an upper bound of the largest squared distance (the exact value after a comparison).
+// members within twice that of the largest are compared in float64 if there are several (at most `most`; more, or matrix-core distances
+// (rel < 0) beyond float32: -1).  dub: an upper bound of the largest squared distance (the exact value after a comparison).
 template <int DT>
 __device__ __forceinline__ int wave_farthest(const unsigned char* stage, const float* d32, int m, int lane, float eps, float rel, int most,
                                              double c0, double c1, double& dub) {
@@ -693,7 +693,8 @@ __device__ __forceinline__ int wave_farthest(const unsigned char* stage, const f
   for (int i = lane; i < m; i += 64) fm = fmaxf(fm, d32[i]);
   const float top = __int_as_float(wave_max(__float_as_int(fm)));       // (ordered like their bits; a NaN is passed over)
   if (rel >= 0.f) eps = rel * sqrtf(top) + 3.1e-5f * top;
-  const float thr = top - 2.f * eps;
+  const bool bound = eps < __builtin_inff();            // otherwise the squares leave float32: every member is compared
+  const float thr = bound ? top - 2.f * eps : -__builtin_inff();
   int n = 0, best = -1;
 #pragma unroll 1
   for (int g = 0; g < m; g += 64) {
@@ -701,11 +702,11 @@ __device__ __forceinline__ int wave_farthest(const unsigned char* stage, const f
     if (mk && best < 0) best = g + (int)__builtin_ctzll(mk);
     n += __popcll(mk);
   }
-  if (n == 1) {
+  if (n == 1 && bound) {
     dub = (double)(top + eps);
     return best;
   }
-  if (n == 0 || n > most || !(eps < 1e30f)) { dub = -1.0; return -1; }
+  if (n == 0 || n > most || (!bound && rel < 0.f)) { dub = -1.0; return -1; }
   best = -1;
   double bv = -1.0;
 #pragma unroll 1
@@ -1097,7 +1098,8 @@ __device__ inline void wave_two_means(WaveCtx& c, const unsigned char* stage, in
 #pragma unroll 1
           for (int g = 0; g < m; g += 64) {
             const float ra = c.R()[g + lane], s = (c.Rall()[g + lane] - ra) * ib - ra * ia;
-            const MemberSet side = __ballot(g + lane < m && s <= t), un = __ballot(g + lane < m && !(fabsf(s - t) > eps));
+            const float gap = fabsf(s - t);              // (not finite: a sum has left float32, which no bound covers)
+            const MemberSet side = __ballot(g + lane < m && s <= t), un = __ballot(g + lane < m && !(gap > eps && gap < __builtin_inff()));
             nw = lane == (g >> 6) ? side : nw;
             unsure = lane == (g >> 6) ? un : unsure;
           }

@@ -102,6 +102,34 @@ def test_statistics_beside_a_large_cluster_are_float64_sums(dtype, sizes, flagge
     assert tally["m2_rel"] <= 2 * 128 * max(sizes) * 2.0 ** -53
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("scale,sizes", [(1e17, (6, 10, 14)), (1e17, (40, 26, 100)), (1e18, (20, 60, 8)), (1e19, (200, 40, 12)), (1e19, (140, 6, 20)),
+                                         (1e19, (300, 20, 40))])
+def test_splits_where_squared_distances_leave_float32(dtype, scale, sizes):
+    """Keys so far apart that their squared distances reach 1e36 to 1e40, every one of them there twice (so that several members are
+    farthest): such a cluster is split like any other."""
+    sizes = list(sizes)
+    cap = sum(sizes)
+    gen = torch.Generator(device=DEV).manual_seed(71)
+    st = snapshot(dtype, [sizes] * 2, [3] * 2, 16, cap, gen)
+    off, mem = st["offsets"], st["members"].long()
+    for u in range(2):
+        for j, m in enumerate(sizes):
+            a = mem[u, int(off[u, j]):int(off[u, j + 1])]
+            x = (scale * (st["keys"][u, a[:m // 2]].float() - st["centroids"][u, j])).to(st["keys"].dtype)
+            st["keys"][u, a] = torch.cat([x, x.flip(0)])
+            st["centroids"][u, j] = st["keys"][u, a].double().mean(0).float()
+    s = WorkloadSpec("far", dtype, 2, 2, cap, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=0, seed=71)
+    ix, o = make_pair(s, 2, max_tokens=cap, max_clusters=16)
+    ix.dynakv_import_state(st)
+    tally = Tally()
+    parity.resync(ix, o, None, {0, 1}, tally)
+    ix.dynakv_split()
+    o.split()
+    assert not compare_state(ix, o, tally, "far apart", assign=False)
+    assert ix.dynakv_export_state(["n_clusters"])["n_clusters"].tolist() == [6, 6]
+
+
 # (value, members) of clusters whose 2-means ends on an exact tie: centres p and q with a member at (p + q) / 2, where sum * (1 / n)
 # is not sum / n
 TIED = [((0, 3), (1, 150), (4, 1), (5, 5), (7, 89), (9, 5)), ((2, 6), (3, 96), (5, 3), (6, 12), (7, 111), (11, 3)),
