@@ -827,7 +827,9 @@ __device__ __forceinline__ float wave_dots(const unsigned char* stage, int first
 // from sums of inner products,  <x, c_A> = sum_{j in A} <x, x_j> / n_A,  |c_A|^2 = sum_{i in A} <x_i, c_A> / n_A, a handful of
 // vector instructions a round.  Every inner product is off by 2^-17 x2 at most (x2 >= every |member|^2), and so is a mean of
 // them; B's are what A's leave of the totals, so theirs is off by m / n_B times that: eps below is the sum of what enters a
-// comparison, rounded up.  Returns 1 (split: side holds A), 0 (one side ran empty) or -1: a decision fell within eps; wave_two_means takes it.
+// comparison, rounded up.  A seed's distance takes in 4 such units (|x|^2, twice a product or mean, |centre|^2); the float32 sums behind
+// it (five additions for a mean, doubled, eleven for the mean's norm, the roundings of 1 / m, products and differences) come to less
+// than 40 * 2^-24 x2, 0.32 of a unit: 4.5.  Returns 1 (split: side holds A), 0 (one side ran empty) or -1: a decision fell within eps; wave_two_means takes it.
 template <int DT>
 __device__ __forceinline__ int gram_two_means(const unsigned char* stage, int m, int lane, unsigned& side) {
   constexpr bool BF = DT == DYNAKV_BF16;
@@ -857,10 +859,10 @@ __device__ __forceinline__ int gram_two_means(const unsigned char* stage, int m,
     return __popc(cand) == 1 && top > 2.f * eps ? (int)__builtin_ctz(cand) : -1;
   };
   const float Rall = with(all), im = 1.f / (float)m;
-  const int a = farthest(nrm - 2.f * Rall * im + wave_sum_f32(lane < m ? Rall : 0.f) * im * im, 4.f * unit);
+  const int a = farthest(nrm - 2.f * Rall * im + wave_sum_f32(lane < m ? Rall : 0.f) * im * im, 4.5f * unit);
   if (a < 0) return -1;
   const float na = __shfl(nrm, a), Ga = with(1u << a);
-  const int bb = farthest(nrm - 2.f * Ga + na, 4.f * unit);
+  const int bb = farthest(nrm - 2.f * Ga + na, 4.5f * unit);
   if (bb < 0) return -1;
   float s = with(1u << bb) - Ga, t = 0.5f * (__shfl(nrm, bb) - na), eps = 4.f * unit;
   unsigned A = all;

@@ -130,6 +130,20 @@ def test_splits_where_squared_distances_leave_float32(dtype, scale, sizes):
     assert ix.dynakv_export_state(["n_clusters"])["n_clusters"].tolist() == [6, 6]
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("offset", [8.0, 100.0])
+def test_small_clusters_about_a_large_offset(dtype, offset):
+    """Clusters of up to 16 entries whose spread is of the order of what float32 inner products can tell apart: whatever they
+    cannot decide goes to float64."""
+    sizes = [[3 + (u + j) % 14 for j in range(7)] for u in range(64)]
+    ix, o, tally, _ = pair(dtype, sizes, [7] * 64, 24, offset=offset)
+    ix.dynakv_split()
+    o.split()
+    dirty = compare_state(ix, o, tally, "offset", assign=False)
+    print("small clusters", dtype, offset, dict(tally), flush=True)
+    assert len(dirty) <= tally.get("tie_split", 0) <= 4
+
+
 # (value, members) of clusters whose 2-means ends on an exact tie: centres p and q with a member at (p + q) / 2, where sum * (1 / n)
 # is not sum / n
 TIED = [((0, 3), (1, 150), (4, 1), (5, 5), (7, 89), (9, 5)), ((2, 6), (3, 96), (5, 3), (6, 12), (7, 111), (11, 3)),
