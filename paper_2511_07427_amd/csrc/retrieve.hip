@@ -1657,19 +1657,25 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
       if constexpr (SPLIT) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (lane == 0) __hip_atomic_store(&wk.ready, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        decides = wk.npre > 0;
+        decides = !MEAN && wk.npre > 0;
       }
     }
   }
 #define DYNAKV_TILE(T) make_tile<ES>(pages, 4 * (T) + selK < nlist ? src[4 * (T) + selK] : -1, \
                                      4 * (T) + lg < nlist ? src[4 * (T) + lg] : -1, lane)
   // next tile of the unit (wavefront-uniform); tiles past the end mean there is nothing left
-  // A retrieval alone keeps every wavefront at it: tiles in turn, so that equal calls add up in the same order.
-  int own_tile = wave;
+  // A retrieval alone keeps every wavefront at it: tiles in turn, so that equal calls add up in the same order.  So do float32 steps, whose
+  // tiles the first wavefront leaves to the others whether it has a split to decide or not (and in every workgroup of a unit: which of
+  // them has the append differs from run to run); the second decides its split when it has streamed its share.  (Against tiles through
+  // the counter: 256 units, 500 clusters, budget 1024 121 -> 104 us; 1 unit, budget 256 29.6 -> 31.0; all four wavefronts in turn, the split after the
+  // stream: 100 and 30, but 16 units 42.4 -> 45.0, budget 1024 51.9 -> 58.2.)
+  constexpr bool kTurns = !APPEND || MEAN;
+  constexpr int kFirst = APPEND && MEAN ? 1 : 0, kStreams = NW - kFirst;
+  int own_tile = wave >= kFirst ? wave - kFirst : 1 << 24;
   auto grab = [&]() __attribute__((always_inline)) {
     int t = own_tile;
-    own_tile += NW;
-    if constexpr (APPEND) {
+    own_tile += kStreams;
+    if constexpr (!kTurns) {
       t = 0;
       if (lane == 0) t = atomicAdd(&s_tile, 1);
     }
@@ -1678,7 +1684,7 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   // a wavefront that may be asked to decide a split looks at the plan between two tiles
   auto called_away = [&]() __attribute__((always_inline)) {
     if constexpr (SPLIT) {
-      if (wave > 0 && wave < kPreSplits && !decides &&
+      if (!kTurns && wave > 0 && wave < kPreSplits && !decides &&
           __hip_atomic_load(&wk.ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != 0 && wave < wk.npre)
         decides = true;
     }
@@ -1709,6 +1715,7 @@ __global__ __launch_bounds__(NW * 64) void retrieve_fused_kernel(View v, const v
   if constexpr (SPLIT) {
     // wavefronts 1 .. kPreSplits - 1 whose tiles ran out before the plan was there wait for it (it is a few
     // microseconds away at most: the first wavefront does nothing else first)
+    if (kTurns) decides = wave == 0 && wk.npre > 0;
     if (wave > 0 && wave < kPreSplits && !decides) {
       int spins = 0;
       while (__hip_atomic_load(&wk.ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0 && ++spins < (1 << 20))

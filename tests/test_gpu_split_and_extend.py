@@ -400,6 +400,31 @@ def test_decisions_retaken_are_counted_once_per_unit(dtype):
     assert counts[0] == counts[launch_shape(1)] == counts[LAUNCH_SEPARATE]
     assert all(c[3] >= 8 for c in counts[0])
 
+@pytest.mark.parametrize("units,budget", [(1, 256), (1, 2100), (5, 600), (40, 700), (130, 300)])
+def test_float32_steps_repeat_bit_for_bit(units, budget):
+    """Whole steps of float32 storage add up in the same order every time, however many workgroups share a unit, whichever of them has the
+    append, and with splits due or not."""
+    sizes = [[9, 12, 30, 4, 8, 20, 3, 60, 40] + [1 + (j * 5 + u) % 23 for j in range(180)] for u in range(units)]
+    flagged = [u % 7 for u in range(units)]
+    cap = max(sum(x) for x in sizes) + 8
+    gen = torch.Generator(device=DEV).manual_seed(81)
+    st = snapshot("f32", sizes, flagged, 400, cap, gen, 0.0, 9.0)
+    Q = [(st["keys"][:, 7 * t + 3, None] + 0.5 * torch.randn(units, 4, D, generator=gen, device=DEV)).contiguous() for t in range(8)]
+    k = [(st["keys"][:, 5 * t + 1] + 0.2 * torch.randn(units, D, generator=gen, device=DEV)).contiguous() for t in range(8)]
+    s = WorkloadSpec("repeat", "f32", units, 4, cap, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=0, seed=81)
+    ix = make_pair(s, units, max_tokens=cap, max_clusters=400, oracle_units=1)[0]
+    first = None
+    for _ in range(6):
+        ix.dynakv_import_state(st)
+        out, lse = torch.empty(8, units, 4, D, device=DEV), torch.empty(8, units, 4, device=DEV)
+        for t in range(8):
+            ix.dynakv_decode_step(Q[t], budget, out[t], lse[t], k[t], k[t])
+        e = ix.dynakv_export_state(["n_clusters", "members", "offsets", "centroids", "m2", "error"])
+        got = (out.cpu(), lse.cpu(), *e.values())
+        assert not e["error"].any()
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(first, got))
+
 
 def test_extension_decides_ties_between_coinciding_clusters():
     """Every entry lies near two clusters of the same entries, and the splits that follow one another raise the norms that the
