@@ -219,7 +219,7 @@ dynakv_status_t dynakv_split(dynakv_index_t* index, void* stream);
  * this one can be mixed freely.  It exists because the step's two passes over the centroid table (query
  * similarity, Section 4.1; nearest cluster of the new key, Section 4.2) read the same data, and because a
  * step is a chain of short dependent phases: with 16-bit storage read through its 16-bit search copy and at most
- * 4096 clusters, or float32 storage and at most 2048, and at most 8 query heads per unit the whole step is ONE kernel launch that reads the table
+ * 4096 clusters, or float32 storage and at most 512, and at most 8 query heads per unit the whole step is ONE kernel launch that reads the table
  * once, commits the append before it streams the selected pages, and prepares the due splits while it streams
  * them.  Otherwise (16-bit storage read through its means, more clusters, more query heads) it is four launches
  * instead of the six of the three calls: the score kernel also evaluates the new key's distances, and the

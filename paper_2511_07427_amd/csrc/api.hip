@@ -59,12 +59,10 @@ int pow2_floor(int x) {
 }
 
 // Shape of the gather + attention launch: S workgroups per unit of NW wavefronts each (the workgroup merge
-// needs NW * G * 130 floats of LDS).  With S = 1 the single-kernel retrieval runs where it can.  Where it cannot
-// (float32, more than kFusedClusters clusters or more than 8 query heads per unit) the separate kernels use one
-// workgroup per unit from 32 units on: the step is bound by dependent round trips to memory rather than by the
-// number of busy compute units, and every further workgroup per unit adds partial results, a ticket and a merge
-// (measured on the 8-unit configuration: 4 workgroups per unit beat 1, 2, 8, 16 and 32; with 112 and 128 units
-// 1 beats 2 and 3).  The configuration's `launch` field overrides both numbers.
+// needs NW * G * 130 floats of LDS).  With S = 1 the single-kernel retrieval runs where it can (and shares units by a rule of its
+// own).  Where it cannot (more than kFusedClusters clusters, kFusedClusters32 of float32, 16-bit storage searched through its float32
+// means, more than 8 query heads per unit, modes in which every entry is a cluster) the separate kernels share a unit among several
+// workgroups while there are few units.  The configuration's `launch` field overrides both numbers.
 void plan_attention(const dynakv_config_t& c, int* S, int* NW) {
   // split-KV (separate kernels): measured at 16384 + tokens per unit, budget 4096, with 1..128 units: 8 workgroups
   // per unit up to 32 units, then 256 / units (e.g. 16 units: 10.8k steps/s with 8, 9.5k with 2; 64 units: 7.6k with 4,
@@ -72,8 +70,9 @@ void plan_attention(const dynakv_config_t& c, int* S, int* NW) {
   int s = (256 + c.n_units - 1) / c.n_units;
   if (s > 8) s = 8;
   // where the single-kernel retrieval can run (see retrieve_is_fused) it beats split-KV at every unit count:
-  // measured 16.5k against 15.5k steps/s with 8 units, 15.1k against 13.1k with 24 (configuration 2's shape)
-  if ((c.dtype == DYNAKV_F32 ? c.max_clusters <= kFusedClusters32
+  // measured 16.5k against 15.5k steps/s with 8 units, 15.1k against 13.1k with 24 (256 clusters, budget 1024).  (float32
+  // that is to run the separate kernels all the same keeps its split-KV: 900 clusters, budget 2048, 1 unit 54 us, 104 without.)
+  if ((c.dtype == DYNAKV_F32 ? c.max_clusters <= kFusedClusters32 && !(c.launch & DYNAKV_LAUNCH_SEPARATE)
                              : c.search_copy == DYNAKV_SEARCH_STORAGE && c.max_clusters <= kFusedClusters) && c.group_size <= 8 &&
       c.update_mode != DYNAKV_UPDATE_TOKENS && c.update_mode != DYNAKV_UPDATE_LOCAL)
     s = 1;

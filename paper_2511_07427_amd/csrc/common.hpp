@@ -18,7 +18,9 @@ constexpr int kSelectLds = 16384;               // clusters whose scores and siz
                                                 // it reads them from memory in every pass
 constexpr int kMaxPrefill = 16384;              // k-means checks one unit's initial positions in an LDS bitmap
 constexpr int kFusedClusters = 4096;            // clusters per unit the single-kernel retrieval can hold in LDS
-constexpr int kFusedClusters32 = 2048;          // the same for float32 storage
+constexpr int kFusedClusters32 = 512;           // the same for float32 storage, whose float64 scores one workgroup of four
+                                                // wavefronts takes: with 4 units, budget 256, a retrieval of 500 clusters is as fast as by the
+                                                // separate kernels (40 us against 42), of 700 slower (45 / 42), of 1900 much (65 / 45)
 constexpr int kFusedSplits = 8;                 // workgroups of the single kernel that can share a unit
 constexpr int kMaxSplitMembers = 4096;          // largest cluster the split kernel handles
 constexpr int kMaxKvSplits = 64;

@@ -1843,10 +1843,13 @@ hipError_t launch_retrieve_fused(const View& v, const void* Q, int budget, float
   // streams about 35 KB per us (8 units, budget 4000: 78 us a retrieval, 41 with eight), and sharing costs 2 us for the partial results,
   // in a step also the wait for the last selection (112 units, 1 MB each: retrieval 45.8 -> 38.6 us, but a step 54.1 -> 56.3, because the
   // slowest unit's split, which begins later, ends it; 128 units, 2 MB each: step 108.9 -> 97.7; 48 units, 512 KB each: retrieval
-  // 38.0 -> 33.3, step 45.8 -> 50.4; 2 units, 1 MB each: step 46.2 -> 34.8; 1 float32 unit, 1 MB: step 55.5 -> 37.2, 256 KB: 29.2 either way).
+  // 38.0 -> 33.3, step 45.8 -> 50.4; 2 units, 1 MB each: step 46.2 -> 34.8).  float32 has four wavefronts per workgroup, three of which stream in a
+  // step, and 300 clusters at most in these figures: 64 units, 1 MB each: step 86 -> 63, 112 units, 0.5 MB each: retrieval 51.6 -> 47.4; up to 8
+  // units from 256 KB on (1 unit: step 38.7 -> 36.8; 16 units: 41.8 -> 44.4, so not there).
   const size_t bytes = (size_t)std::min(budget, v.Ncap) * 2 * kHeadDim * elem_size(v.dtype);
-  const size_t worth = (v.U <= 16 ? 256 : kin ? 768 : v.U <= 64 ? 256 : 512) * 1024;
-  int S = 1;
+  const bool f32 = v.dtype == DYNAKV_F32;
+  const size_t worth = (v.U <= 16 || f32 ? 256 : kin ? 768 : v.U <= 64 ? 256 : 512) * 1024;
+  int S = f32 && v.U <= 8 && v.share > 1 && bytes >= worth ? 2 : 1;
   while (S < v.share && bytes >= worth * 2 * S) S *= 2;
   if (v.dtype == DYNAKV_F32) {
     if (v.G <= 4) launch_fused<DYNAKV_F32, 4>(v, Q, budget, out, lse, kin, vin, split, S, st);
