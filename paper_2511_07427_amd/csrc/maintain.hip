@@ -137,16 +137,19 @@ __global__ __launch_bounds__(256) void append_kernel(View v, const void* kin, co
 // trip to memory: nearest cluster from the entry's row of z (float64 where the runner-up lies within the rounding bound), UpdateVar and
 // threshold on the slot, and one matrix product of the new centroid with the entries to come, which corrects their z of that
 // cluster.  A cluster outside the slots is fetched when it is met; a flag calls the whole workgroup for the split, after which the
-// z of the two clusters that it leaves are put right in the same way (a split of any other cluster ends the batch).  LDS holds z of kExtendClusters clusters for one entry, of a
-// sixteenth of that for sixteen.
+// z of the two clusters that it leaves are put right in the same way (a split of any other cluster ends the batch).  LDS holds z
+// of kExtendClusters clusters for two entries, of an eighth of that for sixteen.
 // 256 units, 256 clusters, 1024 entries (163 splits a unit): 10.3 -> 4.8 ms, of which an entry takes 2.1 us where nothing is
 // flagged (6.6).
 //
-// extend_kernel (float32 means; more clusters than that): one entry per pass over the table, the table in batches of four tiles
-// per wavefront with the next batch in flight.
+// extend_kernel (float32 means; more clusters than that; one or two entries): one entry per pass over the table, the table in batches of four
+// tiles per wavefront with the next batch in flight.  It is the faster one where a pass serves a single entry: 8 units of 8000 clusters, 64
+// entries 2.93 ms against 3.67, of 5000 clusters, two entries a pass, 1.70 in batches against 2.2; a lone entry to one unit of 2000 clusters
+// 65 us against 74 with the import before it, two of them 77 against 82, three 91 against 86.
 constexpr int kExtendBatch = 16, kExtendSpare = 8, kExtendZ = 10240;      // entries per batch, slots beyond them, floats of z
 constexpr int kExtendRoom = kExtendBatch;                                 // clusters that a batch may add
-constexpr int kExtendClusters = kExtendZ - kExtendRoom - 4;
+constexpr int kExtendLeast = 3;                                           // entries that warrant a batch
+constexpr int kExtendClusters = kExtendZ / 2 - kExtendRoom - 4;
 static_assert(kSplitThreads == 2 * kHeadDim, "one coordinate of the key or of the value per thread");
 
 // What the extension holds of a cluster in LDS.
@@ -417,7 +420,7 @@ __global__ __launch_bounds__(256) void extend_batch_kernel(View v, const void* K
 }
 
 template <int DT, bool MEAN>
-__global__ __launch_bounds__(256) void extend_kernel(View v, const void* K, const void* V, int n) {
+__global__ __launch_bounds__(256) void extend_kernel(View v, const void* K, const void* V, int n, int resumes) {
   __shared__ double kd[kHeadDim];
   __shared__ double sv[16];
   __shared__ int si[16];
@@ -429,7 +432,7 @@ __global__ __launch_bounds__(256) void extend_kernel(View v, const void* K, cons
   // kRows entries' keys and values at a time wait in LDS: one trip to memory for all of them
   constexpr int kRows = 16, kEs = DT == DYNAKV_F32 ? 4 : 2;
   __shared__ __align__(16) unsigned char rows[kRows][2][kHeadDim * kEs];
-  const int t0 = MEAN ? 0 : v.nflagged[u];             // where extend_batch_kernel has stopped
+  const int t0 = resumes ? v.nflagged[u] : 0;             // where extend_batch_kernel has stopped
   for (int t = t0; t < n; ++t) {
     const int r = (t - t0) % kRows;
     if (r == 0) {                                       // (a full barrier lies behind the last use of the rows)
@@ -751,18 +754,19 @@ hipError_t launch_local_recluster(const View& v, int iters, hipStream_t st) {
   return hipGetLastError();
 }
 hipError_t launch_extend(const View& v, const void* K, const void* V, int n, hipStream_t st) {
-  if (v.dtype == DYNAKV_F32) extend_kernel<DYNAKV_F32, true><<<v.U, 256, 0, st>>>(v, K, V, n);
+  const bool batch = n >= kExtendLeast;
+  if (v.dtype == DYNAKV_F32) extend_kernel<DYNAKV_F32, true><<<v.U, 256, 0, st>>>(v, K, V, n, false);
   else if (v.dtype == DYNAKV_F16) {
-    if (v.search_mean) extend_kernel<DYNAKV_F16, true><<<v.U, 256, 0, st>>>(v, K, V, n);
+    if (v.search_mean) extend_kernel<DYNAKV_F16, true><<<v.U, 256, 0, st>>>(v, K, V, n, false);
     else {
-      extend_batch_kernel<DYNAKV_F16><<<v.U, 256, 0, st>>>(v, K, V, n);
-      if (v.Mcap > kExtendClusters) extend_kernel<DYNAKV_F16, false><<<v.U, 256, 0, st>>>(v, K, V, n);
+      if (batch) extend_batch_kernel<DYNAKV_F16><<<v.U, 256, 0, st>>>(v, K, V, n);
+      if (!batch || v.Mcap > kExtendClusters) extend_kernel<DYNAKV_F16, false><<<v.U, 256, 0, st>>>(v, K, V, n, batch);
     }
   } else {
-    if (v.search_mean) extend_kernel<DYNAKV_BF16, true><<<v.U, 256, 0, st>>>(v, K, V, n);
+    if (v.search_mean) extend_kernel<DYNAKV_BF16, true><<<v.U, 256, 0, st>>>(v, K, V, n, false);
     else {
-      extend_batch_kernel<DYNAKV_BF16><<<v.U, 256, 0, st>>>(v, K, V, n);
-      if (v.Mcap > kExtendClusters) extend_kernel<DYNAKV_BF16, false><<<v.U, 256, 0, st>>>(v, K, V, n);
+      if (batch) extend_batch_kernel<DYNAKV_BF16><<<v.U, 256, 0, st>>>(v, K, V, n);
+      if (!batch || v.Mcap > kExtendClusters) extend_kernel<DYNAKV_BF16, false><<<v.U, 256, 0, st>>>(v, K, V, n, batch);
     }
   }
   return hipGetLastError();

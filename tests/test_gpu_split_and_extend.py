@@ -196,9 +196,10 @@ def test_splits_of_several_clusters_at_once(dtype):
 @pytest.mark.parametrize("dtype,M,n,Mcap", [
     ("f16", 1, 1, 8), ("bf16", 60, 15, 200), ("f16", 60, 16, 200), ("f16", 60, 33, 200), ("bf16", 640, 20, 900), ("f16", 641, 20, 900),
     ("bf16", 1281, 20, 1500), ("f16", 2561, 12, 2700), ("bf16", 5121, 6, 5300), ("f16", 10234, 8, 10300), ("bf16", 10240, 5, 10300),
-    ("f16", 10218, 8, 10300), ("f16", 10221, 8, 10300), ("f32", 70, 20, 200), ("f16", 3, 70, 90), ("bf16", 600, 90, 900)])
+    ("f16", 10218, 8, 10300), ("f16", 10221, 8, 10300), ("f16", 5096, 12, 5300), ("bf16", 5100, 9, 5300), ("f16", 5101, 9, 5300),
+    ("bf16", 70, 2, 200), ("f16", 70, 3, 200), ("f32", 70, 20, 200), ("f16", 3, 70, 90), ("bf16", 600, 90, 900)])
 def test_extension_across_batches(dtype, M, n, Mcap):
-    """dynakv_extend_index against the oracle where its batches change size (640, 1280, .. clusters) or end: one entry, one batch,
+    """dynakv_extend_index against the oracle where its batches change size (620, 1260, .. clusters) or end: one entry, two, three, one batch,
     a remainder, a split inside a batch, entries that follow one another into one cluster, the last cluster that a batch can hold
     and the first that it cannot."""
     U = 2
