@@ -787,13 +787,14 @@ __device__ inline bool sort_members(const View& v, int u, int N0, int* cnt, int*
   __syncthreads();
   return any_empty;
 }
-__global__ __launch_bounds__(1024) void kmeans_sort_kernel(View v, int N0) {
+__global__ __launch_bounds__(1024) void kmeans_sort_kernel(View v, int N0, int last) {
   __shared__ int cnt[kSortCounters];
   __shared__ int sm[64];
   const int u = blockIdx.x, tid = threadIdx.x;
   const bool any_empty = sort_members(v, u, N0, cnt, sm);
   if (tid == 0) v.has_empty[u] = any_empty;
-  // the first page of every cluster, for the layout
+  if (!last) return;
+  // the labels are final: the first page of every cluster, for the layout
   const int* koff = v.koff + (size_t)u * (v.Mcap + 1);
   const int R = (v.M0 + 1023) / 1024;
   auto pages = [&](int j) { return j < v.M0 ? (koff[j + 1] - koff[j] + kPageTokens - 1) / kPageTokens : 0; };
@@ -1264,7 +1265,7 @@ static void launch_kmeans(const View& v, const void* K, int N0, const int* init_
       kmeans_assign_kernel<DT><<<gx * ((v.U + 7) / 8 * 8), 64 * kAssignWaves, 0, st>>>(v, K, N0, gx, first, slot, code_bits);
     }
     if (first || DT == DYNAKV_F32) {
-      kmeans_sort_kernel<<<v.U, 1024, 0, st>>>(v, N0);
+      kmeans_sort_kernel<<<v.U, 1024, 0, st>>>(v, N0, last);
       kmeans_update_kernel<DT><<<gcl, 256, 0, st>>>(v, K, N0, which, last);
     } else if constexpr (DT != DYNAKV_F32) {
       kmeans_changed_kernel<DT><<<gcl, 256, v.M0 * sizeof(int), st>>>(v, K, N0, slot, which, last);
@@ -1273,7 +1274,7 @@ static void launch_kmeans(const View& v, const void* K, int N0, const int* init_
     if (!last || (!sorted && !sums_order_free_by_type(DT, N0)))
       kmeans_slow_kernel<DT><<<dim3(v.U, slow_workgroups(v, N0)), 1024, 0, st>>>(v, K, N0, which, first, last);
   }
-  if (DT != DYNAKV_F32 && iters > 1) kmeans_sort_kernel<<<v.U, 1024, 0, st>>>(v, N0);
+  if (DT != DYNAKV_F32 && iters > 1) kmeans_sort_kernel<<<v.U, 1024, 0, st>>>(v, N0, 1);
 }
 
 hipError_t launch_build_index(const View& v, const void* K, const void* V, int N0, const int* init_idx, int iters,
