@@ -16,6 +16,7 @@ constexpr int kMaxClusters = 131072;            // per unit (the selection packs
 constexpr int kMaxInitClusters = 8192;          // clusters built at prefill
 constexpr int kSelectLds = 16384;               // clusters whose scores and sizes the selection keeps in LDS; beyond,
                                                 // it reads them from memory in every pass
+constexpr int kCountBig = 4096;                 // selected clusters where more than kSelectLds are possible (more: the retrieval is cut short)
 constexpr int kMaxPrefill = 16384;              // k-means checks one unit's initial positions in an LDS bitmap
 constexpr int kFusedClusters = 4096;            // clusters per unit the single-kernel retrieval can hold in LDS
 constexpr int kFusedClusters32 = 512;           // the same for float32 storage, whose float64 scores one workgroup of four
@@ -84,9 +85,9 @@ struct View {
   float* score;      // last scores
   int* sel_ids;      // the active set in the order it is attended: ascending id, or (keys left in memory) descending score
   unsigned char* in_req;  // membership in the last active set
-  int* tok_off;      // scratch: exclusive prefix of sizes in score order
-  int* pg_off;       // scratch: first page of every cluster (build, import); where more than kSelectLds clusters are possible, the
-                     // exclusive prefix of the selected clusters' sizes in the order of the last retrieval's list
+  int* tok_off;      // scratch of exports and placements; where more than kSelectLds clusters are possible, two more arrays of
+                     // that size: see list_offsets()
+  int* pg_off;       // scratch: first page of every cluster (build, import, placement)
   // pages [U][Pcap]
   char* pages;       // [U][Pcap][kPageElems * elem size]
   int* ppos;         // [U][Pcap][16] token position of every slot
@@ -120,6 +121,11 @@ static_assert(sizeof(View) <= 568, "View: see above");
 __host__ __device__ inline int km_pad(int M0) { return (M0 + 63) & ~63; }
 
 __host__ __device__ inline int elem_size(int dtype) { return dtype == DYNAKV_F32 ? 4 : 2; }
+
+// Where more than kSelectLds clusters are possible: the place in the gather list at which the entries of each selected cluster begin, in
+// the order of the last retrieval's list (which outlives a refused import), and, while a snapshot is taken, by score.
+__device__ inline int* list_offsets(const View& v, int u) { return v.tok_off + ((size_t)v.U + u) * v.Mcap; }
+__device__ inline int* score_offsets(const View& v, int u) { return v.tok_off + ((size_t)2 * v.U + u) * v.Mcap; }
 
 // ---- page layout -----------------------------------------------------------------------------
 // A page stores 16 tokens: a K region and a V region, each [16 slots][128], one row per token, so that the

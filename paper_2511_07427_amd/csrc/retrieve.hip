@@ -420,7 +420,7 @@ __device__ inline int emit_by_bits(const View& v, int u, int M, const SelectLds&
         if (id[e] < 0) continue;
         const int take = take_all >= 0 ? take_all : w[e];
         if (pass) {
-          v.sel_ids[cb + cnt] = id[e]; v.pg_off[cb + cnt] = tok;
+          v.sel_ids[cb + cnt] = id[e]; list_offsets(v, u)[cnt] = tok;
           emit_cluster(v, u, take, pa[e], pb[e], quads, tok, plist, poff, s);
         }
         tok += take; quads += (take + 3) >> 2; ++cnt;
@@ -783,7 +783,7 @@ __device__ inline int select_phase(const View& v, int u, int M, int budget, cons
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int r = tid * PER + k;
-    if (r < cut) v.pg_off[cb + r] = (int)(pre & 0xFFFFFFu);
+    if (r < cut) list_offsets(v, u)[r] = (int)(pre & 0xFFFFFFu);
     if (r < cut)      // id, first gather offset, first list entry
       ck[r] = ((unsigned long long)by_id[r] << 46) | ((pre & 0xFFFFFFu) << 22) | ((pre >> 32) & 0x3FFFFFu);   // 18 + 24 + 22 bits
     pre += loc[k];
@@ -918,7 +918,6 @@ __device__ inline int contenders(const View& v, int u, int M, int budget, float 
 // One workgroup per unit.  BIG: more than kSelectLds clusters per unit: scores and sizes stay in the workspace (they
 // are a few hundred KB per unit), LDS holds the contenders and a bitmap of the active set, or the keys stay in memory and LDS holds
 // a larger candidate list (see MAPPED).
-constexpr int kCountBig = 4096;
 template <bool BIG>
 __global__ __launch_bounds__(1024) void select_kernel(View v, const void* Q, int budget) {
   constexpr int CMAX = BIG ? kCountBig : kCountMax;

@@ -480,3 +480,30 @@ def test_snapshot_lists_a_long_selection_by_score(clusters, copies):
             off, mem = e["offsets"][u].tolist(), e["members"][u]
             want = torch.cat([mem[off[j]:off[j + 1]] for j in ids.tolist()])[:budget]
             assert int(e["n_gathered"][u]) == len(want) and torch.equal(e["gathered"][u, :len(want)], want), budget
+
+
+def test_a_refused_import_leaves_the_listing_as_it_was():
+    """A unit that an import refuses keeps its state, the list of its last retrieval among it."""
+    gen = torch.Generator(device=DEV).manual_seed(91)
+    sizes = [[1 + (7 * j + u) % 5 for j in range(500)] for u in range(2)]
+    N = max(sum(x) for x in sizes)
+    s = WorkloadSpec("kept", "f16", 2, 2, N, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, seed=91)
+    ix = make_pair(s, 2, max_tokens=N, max_clusters=17100)[0]
+    st = snapshot("f16", sizes, [0, 0], 17100, N, gen, 0.0, 6.0)
+    ix.dynakv_import_state(st)
+    out, lse = torch.empty(2, 2, D, device=DEV), torch.empty(2, 2, device=DEV)
+    Q = (st["centroids"][:, :1] + 0.5 * torch.randn(2, 2, D, generator=gen, device=DEV)).half().contiguous()
+    ix.dynakv_retrieve_attend(Q, 700, out, lse)
+    fields = ["n_selected", "selected", "n_gathered", "gathered", "size", "members", "centroids"]
+    before = ix.dynakv_export_state(fields)
+    bad = {k: x.clone() for k, x in st.items()}
+    bad["size"][:, 499] += 1                             # the last cluster says one entry more than it has
+    ix.dynakv_import_state(bad)
+    after = ix.dynakv_export_state(fields + ["error"])
+    assert after["error"].tolist() == [binding.ERR_IMPORT] * 2 and int(before["n_gathered"].min()) > 600
+    for u in range(2):
+        g = int(before["n_gathered"][u])
+        assert torch.equal(before["gathered"][u, :g], after["gathered"][u, :g])
+    for k in fields:
+        if k != "gathered":
+            assert torch.equal(before[k], after[k]), k
