@@ -433,6 +433,22 @@ __device__ inline int emit_by_bits(const View& v, int u, int M, const SelectLds&
   return t_quads;
 }
 
+// Leaves the first `most` bits that are set in the bitmap of M clusters (thread t holds the words that it will walk in emit_by_bits).
+template <int NT>
+__device__ inline void keep_first(unsigned* bits, int M, int most, int* sm) {
+  const int tid = threadIdx.x, words = (M + 31) >> 5, K = (words + NT - 1) / NT, w0 = min(words, tid * K), w1 = min(words, w0 + K);
+  int n = 0, total;
+  for (int w = w0; w < w1; ++w) n += __popc(bits[w]);
+  int left = most - block_excl_scan<true>(n, sm, total);
+  for (int w = w0; w < w1; ++w) {
+    unsigned b = bits[w];
+    while (__popc(b) > max(left, 0)) b &= ~(0x80000000u >> __clz((int)b));        // the highest goes first
+    bits[w] = b;
+    left -= __popc(b);
+  }
+  lds_barrier();
+}
+
 // No cluster outside the active set is ever ordered.  The score at which the running size first exceeds the budget
 // is found by a radix search over the 32-bit orderable scores (four passes of size-weighted 256-bin histograms);
 // everything above it is selected, equal scores are taken by ascending id while they fit.  With keys, sizes and
@@ -453,7 +469,7 @@ __device__ inline int emit_by_bits(const View& v, int u, int M, const SelectLds&
 // every cluster that could be selected and at least one that cannot (see contenders).  The list follows the cluster ids (emit_by_bits;
 // s.selbits has a bit for every cluster of the unit).  Returns -1, with nothing but active-set
 // flags written, if the cut falls among equal scores that only their ids can order (nothing keeps the contenders in
-// that order) or more than CMAX clusters are selected; the caller then takes the unmapped way.
+// that order); the caller then takes the unmapped way.
 // BY_ID: keys, sizes and the active set's bitmap are in LDS and M <= MAXR * NT.
 template <int NT, bool BY_ID, int CMAX = kCountMax, int MAXR = 8, bool MAPPED = false>
 __device__ inline int select_phase(const View& v, int u, int M, int budget, const SelectLds& s, const SelectExact& ex,
@@ -664,7 +680,10 @@ __device__ inline int select_phase(const View& v, int u, int M, int budget, cons
     }
     return emit_by_id<NT, MAXR>(v, u, M, s, truncated ? budget : -1);
   } else if constexpr (MAPPED) {
-    if (s.misc[2] > CMAX) return -1;                   // workgroup-uniform
+    if (s.misc[2] > CMAX) {                            // workgroup-uniform: cut short to the first CMAX, and the unit's error word says so
+      if (tid == 0) atomicOr(&v.err[u], DYNAKV_ERR_SELECT);
+      keep_first<NT>(s.selbits, v.M[u], CMAX, s.sm);
+    }
     const bool truncated = cross && s.misc[2] == 0 && budget > 0;    // the best cluster alone is over budget: its first entries
     if (truncated) {
       __syncthreads();                                 // (another thread may have cleared the same active-set flag)

@@ -507,3 +507,27 @@ def test_a_refused_import_leaves_the_listing_as_it_was():
     for k in fields:
         if k != "gathered":
             assert torch.equal(before[k], after[k]), k
+
+
+@pytest.mark.parametrize("budget", [4096, 4097, 6000, 9000])
+def test_a_selection_of_more_than_4096_clusters_is_cut_short(budget):
+    """Where more than 16384 clusters are possible at most 4096 can be selected: clusters of one entry each, all of them within the budget by score,
+    and the error word where there would have been more."""
+    gen = torch.Generator(device=DEV).manual_seed(budget)
+    M = 17000
+    s = WorkloadSpec("cut", "f16", 2, 2, M, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, seed=9)
+    ix = make_pair(s, 2, max_tokens=M, max_clusters=17100, oracle_units=1)[0]
+    st = snapshot("f16", [[1] * M] * 2, [0, 0], 17100, M, gen, 0.0, 6.0)
+    ix.dynakv_import_state(st)
+    out, lse = torch.empty(2, 2, D, device=DEV), torch.empty(2, 2, device=DEV)
+    Q = (st["centroids"][:, :1] + 0.5 * torch.randn(2, 2, D, generator=gen, device=DEV)).half().contiguous()
+    ix.dynakv_retrieve_attend(Q, budget, out, lse)
+    e = ix.dynakv_export_state(["n_selected", "selected", "n_gathered", "gathered", "scores", "offsets", "members", "error"])
+    assert e["error"].tolist() == [binding.ERR_SELECT if budget > 4096 else 0] * 2 and bool(torch.isfinite(out).all())
+    for u in range(2):
+        ids, score = e["selected"][u, :4096].long(), e["scores"][u, :M]
+        assert e["n_selected"][u] == 4096 and e["n_gathered"][u] == 4096 and len(set(ids.tolist())) == 4096
+        assert ids.tolist() == sorted(ids.tolist(), key=lambda j: (-float(score[j]), j))
+        assert bool((score[ids] >= score.sort(descending=True).values[budget - 1] - 1e-4).all())
+        mem, off = e["members"][u], e["offsets"][u].long()
+        assert torch.equal(e["gathered"][u, :4096], mem[off[ids]])
