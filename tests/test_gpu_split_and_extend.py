@@ -70,13 +70,13 @@ def pair(dtype, sizes, flagged, max_clusters, extra=0, offset=0.0, seed=3, tau=1
     return ix, o, tally, gen
 
 
-SIZES = [2, 3, 5, 15, 16, 17, 32, 33, 63, 64, 65, 96, 97, 128, 129, 191, 192, 193, 255, 256, 257, 300]
+SIZES = [2, 3, 5, 15, 16, 17, 32, 33, 63, 64, 65, 96, 97, 128, 129, 160, 161, 192, 255, 256, 257, 300]
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 @pytest.mark.parametrize("offset", [0.0, 30.0])
 def test_splits_at_the_edges_of_every_path(dtype, offset):
-    """One flagged cluster per unit of every size at which another path begins (16, 32, 64, 128, 192 and 256 entries), also with
+    """One flagged cluster per unit of every size at which another path begins (16, 32, 64, 128, 160 and 256 entries), also with
     keys about an offset that the float32 filters of the 2-means cannot see past."""
     sizes = [[m, 7, 1, 12] for m in SIZES]
     ix, o, tally, _ = pair(dtype, sizes, [1] * len(sizes), 16, offset=offset)
@@ -313,43 +313,60 @@ def test_extension_after_decode_steps_that_leave_flags(dtype):
     assert min(left) >= 1 and not e["flag"].any() and not e["error"].any()
 
 
-@pytest.mark.parametrize("dtype,units,G", [("f16", 3, 4), ("bf16", 40, 7), ("f32", 2, 5)])
-def test_units_shared_by_several_workgroups(dtype, units, G):
+def workgroups_per_unit(dtype, units, budget, capacity, step):
+    """What the single kernel takes (launch_retrieve_fused)."""
+    f32, most = dtype == "f32", 8 if units <= 32 else 4 if units <= 64 else 2 if units <= 128 else 1
+    kib = min(budget, capacity) * (1 if f32 else 0.5)
+    worth = 256 if units <= 16 or f32 else 768 if step else 256 if units <= 64 else 512
+    n = 2 if f32 and units <= 8 and kib >= worth else 1
+    while n < most and kib >= 2 * worth * n:
+        n *= 2
+    return n
+
+
+@pytest.mark.parametrize("dtype,units,G,budgets,retrievals,steps", [
+    ("f16", 3, 4, (300, 1030, 2060, 4200, 1 << 20), [1, 2, 4, 8, 8], [1, 2, 4, 8, 8]),
+    ("bf16", 40, 7, (300, 1030, 2060, 3100, 1 << 20), [1, 2, 4, 4, 4], [1, 1, 1, 2, 4]),
+    ("bf16", 100, 3, (300, 2060, 3100), [1, 2, 2], [1, 1, 2]),
+    ("f32", 2, 5, (200, 300, 1030, 2060, 1 << 20), [1, 2, 4, 8, 8], [1, 2, 4, 8, 8]),
+    ("f32", 20, 4, (300, 600, 1030, 2060), [1, 2, 4, 8], [1, 2, 4, 8])])
+@pytest.mark.parametrize("buffer_max", [0, 6])
+def test_units_shared_by_several_workgroups(dtype, units, G, budgets, retrievals, steps, buffer_max):
     """Budgets at which the single kernel takes one, two, four and eight workgroups per unit, in retrievals and whole steps in turn
     (its arrival counters go on from launch to launch), with more than four splits due in one step, whose later rounds want the
-    pages that the first has freed."""
-    sizes = [[9, 12, 30, 4, 8, 20, 3, 60, 100] + [1 + (j * 5 + u) % 23 for j in range(180)] for u in range(units)]
+    pages that the first has freed, and (buffer_max > 0) a forced split after the delayed ones."""
+    sizes = [[9, 12, 30, 4, 8, 20, 3, 60, 100] + [1 + (j * 5 + u) % 47 for j in range(262)] for u in range(units)]
     flagged = [9] * units
-    ix, o, tally, gen = pair(dtype, sizes, flagged, 400, extra=64, tau=9.0)
-    o_units = list(range(units))
-    N = min(sum(s) for s in sizes)
-    keys = ix.dynakv_export_state(["keys"], to_cpu=False)["keys"].float()
-    dt = binding.TORCH_DTYPES[dtype]
-    out, lse = torch.empty(units, G, D, device=DEV), torch.empty(units, G, device=DEV)
-    s = WorkloadSpec("share", dtype, units, G, N, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=0, seed=5)
-    ix, o = make_pair(s, units, max_tokens=max(sum(x) for x in sizes) + 64, max_clusters=400)
-    ix.dynakv_import_state(snapshot(dtype, sizes, flagged, 400, max(sum(x) for x in sizes) + 64, torch.Generator(device=DEV).manual_seed(3), 0.0, 9.0))
+    cap = max(sum(x) for x in sizes) + 2 * len(budgets)
+    for want, step in ((retrievals, False), (steps, True)):
+        assert [workgroups_per_unit(dtype, units, b, cap, step) for b in budgets] == want
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    s = WorkloadSpec("share", dtype, units, G, cap, 1, 1, 64, 6, 0.05, var_alpha=1.5, size_factor=0.0, buffer_max=buffer_max, seed=5)
+    ix, o = make_pair(s, units, max_tokens=cap, max_clusters=400)
+    st = snapshot(dtype, sizes, flagged, 400, cap, gen, 0.0, 9.0)
+    ix.dynakv_import_state(st)
     tally = Tally()
-    parity.resync(ix, o, None, set(o_units), tally)
-    for t, budget in enumerate((1 << 20, 1030, 300, 2060, 1 << 20, 520, 40)):
+    parity.resync(ix, o, None, set(range(units)), tally)
+    keys, dt = st["keys"].float(), st["keys"].dtype
+    out, lse = torch.empty(units, G, D, device=DEV), torch.empty(units, G, device=DEV)
+    for t, budget in enumerate(b for b in budgets for _ in range(3)):
         Q = (keys[:, 11 * t + 3, None] + 0.5 * torch.randn(units, G, D, generator=gen, device=DEV)).to(dt).contiguous()
         k = (keys[:, 7 * t + 1] + 0.2 * torch.randn(units, D, generator=gen, device=DEV)).to(dt).contiguous()
         v = torch.randn(units, D, generator=gen, device=DEV).to(dt)
-        Qn = Q.float().cpu().numpy()
+        Qn, what = Q.float().cpu().numpy(), "call %d, budget %d" % (t, budget)
+        oo, ol = o.retrieve_attend(Qn, budget)
         if t % 3 == 1:
             ix.dynakv_retrieve_attend(Q, budget, out, lse)
-            oo, ol = o.retrieve_attend(Qn, budget)
+            assert not parity.compare_retrieval(ix, o, tally, what, Q=Qn, budget=budget)
         else:
             ix.dynakv_decode_step(Q, budget, out, lse, k, v)
-            oo, ol = o.retrieve_attend(Qn, budget)
             o.append(k.float().cpu().numpy(), v.float().cpu().numpy())
             o.split()
-        parity.check_attention(out.cpu().numpy(), lse.cpu().numpy(), oo, ol, "budget %d" % budget)
-        if t % 3 == 1:
-            assert not parity.compare_retrieval(ix, o, tally, "budget %d" % budget, Q=Qn, budget=budget)
-        else:
-            assert not compare_state(ix, o, tally, "budget %d" % budget)
-    print("shared units", dtype, units, dict(tally), flush=True)
+            assert not compare_state(ix, o, tally, what)
+        parity.check_attention(out.cpu().numpy(), lse.cpu().numpy(), oo, ol, what)
+    forced = int(ix.dynakv_export_state(["counters"])["counters"][:, 2].sum())
+    print("shared units", dtype, units, buffer_max, forced, dict(tally), flush=True)
+    assert (forced > 0) == (buffer_max > 0)
 
 
 @pytest.mark.parametrize("dtype,G", [("f16", 4), ("bf16", 7), ("f32", 5)])

@@ -61,6 +61,19 @@ def test_static_scratch_retrieval_matches_the_workspace_one_on_two_calls_in_a_ro
     assert _both(ix1, Q1[6], 64) > 0               # and back to the first index with a small budget
 
 
+@pytest.mark.parametrize("launch", [0, launch_shape(1)])
+def test_static_scratch_retrieval_in_the_single_kernel(launch):
+    # the single kernel, one workgroup per unit and (0: budgets from 1024 entries on) two and four that leave their partial results
+    # in the array; their arrival counters go on in the workspace, through calls of either kind
+    big = CONFIGS["llama3_8b"].scaled(prefill=4096, n_clusters_init=96, budget=700)
+    f32 = CONFIGS["tiny"].scaled(prefill=1024, n_clusters_init=24, budget=150)
+    ix1, Q1 = _index(big, [0, 1, 2], 24, launch)
+    ix2, Q2 = _index(f32, [0], 8, launch)
+    for budget, least in ((700, 300), (1100, 900), (2200, 1900), (64, 1), (4000, 3700)):
+        assert _both(ix1, Q1[5], budget) >= least
+        assert _both(ix2, Q2[3], budget) >= min(least, 900)
+
+
 def test_static_scratch_retrieval_rejects_what_does_not_fit():
     spec = CONFIGS["tiny"]
     c = binding.Config(2048, 16, "f16", 2, 4, 64, 1, 16, 0, 0.0, 0.0, 0.0, launch=launch_shape(8, 4, LAUNCH_SEPARATE))
