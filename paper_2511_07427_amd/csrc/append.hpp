@@ -14,11 +14,6 @@ struct EntryBits {
   uint2 k, v;
 };
 template <int DT>
-__device__ __forceinline__ uint2 load_pair(const void* base, size_t row, int lane) {
-  if constexpr (DT == DYNAKV_F32) return ((const uint2*)base)[row * (kHeadDim / 2) + lane];
-  else return uint2{((const uint32_t*)base)[row * (kHeadDim / 2) + lane], 0};
-}
-template <int DT>
 __device__ __forceinline__ void store_pair(void* row, int lane, uint2 x) {
   if constexpr (DT == DYNAKV_F32) ((uint2*)row)[lane] = x;
   else ((uint32_t*)row)[lane] = x.x;

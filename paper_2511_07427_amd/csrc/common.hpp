@@ -193,14 +193,6 @@ __device__ inline void store_centroid(const View& v, int u, int j, int d, float 
 // lanes own one block each.  (The candidates of the 16-bit search copy that are re-scored in float64, UpdateVar and
 // the splits decided by one wavefront have orders of their own, each the same in every launch.)
 
-// One thread: block_sum(k) returns the sum of block k (k = 0..15, called in ascending k).
-template <class F>
-__device__ __forceinline__ double blocked16(F&& block_sum) {
-  double total = 0.0;
-#pragma unroll 4
-  for (int k = 0; k < 16; ++k) total += block_sum(k);
-  return total;
-}
 // Four consecutive lanes (one DPP quad), lane q holding the sums of blocks 4q..4q+3 in bs[]: every lane of
 // the quad gets the total ((s0 + s1) + s2) + ... + s15, added strictly left to right.
 __device__ inline double blocked16_quad(const double (&bs)[4]) {
@@ -451,33 +443,6 @@ __device__ __forceinline__ void count(const View& v, int u, int k, long long n) 
 }
 __device__ inline int cluster_page(const View& v, int u, size_t cj, int k, int prev) {
   return k < kInlinePages ? v.cpg[cj * kInlinePages + k] : v.pnext[(size_t)u * v.Pcap + prev];
-}
-
-// Block-wide arg-min / arg-max over (value, index) pairs held one per thread of a 256-thread block; ties go
-// to the lowest index; index < 0 means "no candidate".  Result in sv[0], si[0].
-template <bool MAX>
-__device__ inline void block_arg_reduce(double val, int idx, double* sv, int* si) {
-  const int tid = threadIdx.x;
-  sv[tid] = val; si[tid] = idx;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (tid < o) {
-      const double ov = sv[tid + o];
-      const int oi = si[tid + o];
-      if (oi >= 0) {
-        const bool better = si[tid] < 0 || (MAX ? ov > sv[tid] : ov < sv[tid]) || (ov == sv[tid] && oi < si[tid]);
-        if (better) { sv[tid] = ov; si[tid] = oi; }
-      }
-    }
-    __syncthreads();
-  }
-}
-
-__device__ inline int pages_available(const View& v, int u) { return v.free_top[u] + (v.Pcap - v.bump[u]); }
-__device__ inline void free_page(const View& v, int u, int page) {
-  const int top = v.free_top[u];
-  v.freelist[(size_t)u * v.Pcap + top] = page;
-  v.free_top[u] = top + 1;
 }
 
 // ---- launchers (one per source file) ------------------------------------------------------------

@@ -153,11 +153,9 @@ __global__ __launch_bounds__(256) void score_mfma_kernel(View v, const void* Q, 
 // ------------------------------------------------------------------------------------------- selection
 constexpr int kIdBits = 18, kIdMask = (1 << kIdBits) - 1;   // a candidate's key: score above, kIdMask - id below
 static_assert(kMaxClusters <= kIdMask + 1, "cluster ids must fit the candidate keys");
-constexpr int kCountMax = 1024;     // selected clusters ordered by counting; larger selections take the full sort
-constexpr int kSelRegion = kCountMax * 12;   // bytes of candidate keys (8) and sizes (4)
+constexpr int kCountMax = 1024;
+constexpr int kSelRegion = kCountMax * 12;   // LDS that the single kernel sets aside beside keys and sizes
 
-// LDS of the selection.  `region` holds the candidates of the fast path (or the ids of the full sort) and
-// needs max(kSelRegion, 2 * Mpad) bytes; `list` receives the first `list_cap` gather-list entries.
 // What the selection needs to retake the budget cut in float64 (16-bit search copy only): eps = bound on the error
 // of a float32 score (0: scores are exact, nothing is retaken), Q = the queries.
 struct SelectExact {
@@ -170,6 +168,8 @@ __device__ inline float unorderable(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
 
+// LDS of the selection.  Where it ranks what it selects (keys left in memory: neither BY_ID nor MAPPED, see select_phase) `region` holds
+// the CMAX candidates' keys (8 bytes) and sizes (4); `list` receives the first `list_cap` gather-list entries.
 struct SelectLds {
   uint32_t* skey;          // [Mpad] orderable scores, padded with 0 up to the next power of two; null: the scores are
                            // read from the workspace in every pass (more clusters than LDS holds)
@@ -204,8 +204,8 @@ __device__ __forceinline__ void emit_page(int page, int nv, int w, int t0, int* 
 // Selection for one unit, run by a whole workgroup of NT threads (NT >= 256).  Clusters are ordered by
 // (score desc, id asc); the active set is the longest prefix of that order whose stored sizes fit the budget
 // (or the best cluster alone, cut to the budget, if even that one does not fit).  Records the active set and
-// writes the gather list: in ascending cluster id where keys, sizes and the set's bitmap are in LDS (emit_by_id;
-// no selected cluster is ranked), in score order otherwise.  Returns the number of gather-list entries.
+// writes the gather list: in ascending cluster id where the set's bitmap is in LDS (emit_by_id, emit_by_bits; no selected
+// cluster is ranked), in score order otherwise.  Returns the number of gather-list entries.
 //
 // Puts the positions 0 .. cut-1 of the candidate keys ck into 256 bins by the leading bits in which the keys'
 // scores differ (counting sort, bins in descending order) and returns the shift that yields a key's bin:
