@@ -23,13 +23,17 @@
  *               operation leaves the unit's state unchanged (a split that has no room leaves its
  *               cluster flagged); dynakv_export_state, which waits for the stream, reports the
  *               words and returns DYNAKV_ECAPACITY if any is set.
- *   numerics  - the statistics (mean, M2, threshold test) and the 2-means of a split are float64
- *               computations on the stored values.  With 16-bit storage, cluster scores and the
- *               distances of a new entry are first computed on the matrix cores (products of two
- *               16-bit values are exact, the 128 of them are accumulated in float32); every
- *               decision that the float32 rounding could change is then retaken on float64 values:
- *               the nearest cluster among all candidates within the error bound of the best, and
- *               the budget cut among all clusters whose score lies within the bound of the cut.
+ *   numerics  - the statistics (mean, M2, threshold test) are float64 sums of the stored values; only
+ *               where every cluster that is split in a step holds at most 128 entries of a 16-bit type
+ *               (64 of float32) are the squares that the children's M2 starts from taken in float32
+ *               (M2 off by less than 2^-18 of itself).  With 16-bit storage, cluster scores, the
+ *               distances of a new entry and the inner products of the 2-means of a split are first
+ *               computed on the matrix cores (products of two 16-bit values are exact, the 128 of them
+ *               are accumulated in float32); the 2-means of float32 storage begins in float32 too.
+ *               Every decision that the float32 rounding could change is then retaken on float64
+ *               values: the nearest cluster among all candidates within the error bound of the best,
+ *               the budget cut among all clusters whose score lies within the bound of the cut, the
+ *               seeds and sides of a 2-means.
  *               The selected set therefore is the one of exact arithmetic; the order in which the
  *               selected clusters are attended is the library's own (a snapshot lists them by
  *               ascending id; by descending float32 score where max_clusters > 16384).  Ties go to
@@ -89,7 +93,8 @@ typedef enum {
 
 /* Launch shape (dynakv_config_t.launch).  0 lets the library choose.  Otherwise the low byte is the number of
  * workgroups that share one unit's gather + attention (split-KV), the next byte their wavefronts (4, 8 or 16),
- * either 0 = chosen by the library, plus the flags below.  Results do not depend on the shape beyond float32
+ * either 0 = chosen by the library (in the single kernel as well, which a given number of 1 keeps at one workgroup per
+ * unit), plus the flags below.  Results do not depend on the shape beyond float32
  * rounding of the attention output. */
 #define DYNAKV_LAUNCH(kv_splits, att_waves) (((kv_splits) & 255) | (((att_waves) & 255) << 8))
 #define DYNAKV_LAUNCH_SEPARATE (1 << 16)     /* scores, selection, gather + attention, append, split as separate kernels */
@@ -146,7 +151,7 @@ dynakv_status_t dynakv_build_index(dynakv_index_t* index, const void* K, const v
  * split at once (as with buffer_max = 0), whatever the configured buffer.  The active set is not consulted.
  *   K, V      device, [U][n_tokens][head_dim] in cfg.dtype, contiguous; read only
  *   n_tokens  >= 1; tokens beyond max_tokens are refused with DYNAKV_ERR_TOKENS
- * One kernel: each unit's workgroup walks its chunk in order. */
+ * One or two kernels: each unit's workgroup walks its chunk in order. */
 dynakv_status_t dynakv_extend_index(dynakv_index_t* index, const void* K, const void* V, int32_t n_tokens, void* stream);
 
 /* Correlation-aware placement (Section 5.1, inter-cluster correlation, Eq. 8), kept here as a page-placement hint:
@@ -185,10 +190,13 @@ dynakv_status_t dynakv_retrieve_attend(dynakv_index_t* index, const void* Q, int
 /* dynakv_retrieve_attend for callers that cannot allocate device memory or hand over a workspace region for
  * scratch (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * kernels and results, but the scratch of the split-KV gather + attention (every workgroup's partial sums,
- * maxima and accumulators, and the arrival tickets of each unit) lives in a device array inside the library
+ * maxima and accumulators and, with separate kernels, the arrival tickets of each unit, which the single kernel
+ * keeps in the workspace from call to call) lives in a device array inside the library
  * of DYNAKV_STATIC_SCRATCH_BYTES, which every GPU the library runs on holds until the process ends.  The call
- * allocates nothing.  It needs n_units * kv_splits * group_size * 130 * 4 + n_units * 4 bytes; a configuration
- * that needs more returns DYNAKV_ECAPACITY and enqueues nothing.  All calls on one GPU share the array: calls
+ * allocates nothing.  It needs n_units * S * group_size * 130 * 4 + n_units * 4 bytes, S = the workgroups that may share
+ * a unit: the number given in cfg.launch, else 8 up to 32 units, 4 up to 64, 2 up to 128 and 1 beyond in the single
+ * kernel, min(8, ceil(256 / n_units)) in separate kernels (1 with 16-bit storage that could run the single one); a
+ * configuration that needs more returns DYNAKV_ECAPACITY and enqueues nothing.  All calls on one GPU share the array: calls
  * that overlap on one GPU (two streams, two indexes) race; what must start at zero is cleared by the call itself.
  * Arguments as dynakv_retrieve_attend. */
 #define DYNAKV_STATIC_SCRATCH_BYTES (8u << 20)
@@ -214,13 +222,14 @@ dynakv_status_t dynakv_append(dynakv_index_t* index, const void* k_new, const vo
 dynakv_status_t dynakv_split(dynakv_index_t* index, void* stream);
 
 /* One whole decode step of Algorithm 1 (decode block): dynakv_retrieve_attend(Q), dynakv_append(k_new,
- * v_new) and dynakv_split(), in that order and with the same results (M2 up to its last digits: the single launch
- * takes that float64 sum in an order of its own; attention outputs up to float32 rounding), so the three calls and
+ * v_new) and dynakv_split(), in that order and with the same results (M2 of a split's children up to its last digits: one
+ * wavefront or four together add them up; attention outputs up to float32 rounding, with float32 storage the same bits from
+ * run to run), so the three calls and
  * this one can be mixed freely.  It exists because the step's two passes over the centroid table (query
  * similarity, Section 4.1; nearest cluster of the new key, Section 4.2) read the same data, and because a
- * step is a chain of short dependent phases: with 16-bit storage read through its 16-bit search copy and at most
- * 4096 clusters, or float32 storage and at most 512, and at most 8 query heads per unit the whole step is ONE kernel launch that reads the table
- * once, commits the append before it streams the selected pages, and prepares the due splits while it streams
+ * step is a chain of short dependent phases: with 16-bit storage read through its 16-bit search copy and
+ * max_clusters <= 4096, or float32 storage and max_clusters <= 512, and at most 8 query heads per unit the whole step
+ * is ONE kernel launch that reads the table once, commits the append before it streams the selected pages, and prepares the due splits while it streams
  * them.  Otherwise (16-bit storage read through its means, more clusters, more query heads) it is four launches
  * instead of the six of the three calls: the score kernel also evaluates the new key's distances, and the
  * splits run in the append's launch.  Arguments as in the three calls. */

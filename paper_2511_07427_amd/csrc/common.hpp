@@ -191,7 +191,7 @@ __device__ inline void store_centroid(const View& v, int u, int j, int d, float 
 // consecutive coordinates are accumulated left to right from zero (one fused multiply-add per term), and the 16 block sums are
 // added left to right.  Dependency chains stay short, and the value is the same whether one lane owns the whole sum or 16
 // lanes own one block each.  (The candidates of the 16-bit search copy that are re-scored in float64, UpdateVar and
-// the splits decided by one wavefront have orders of their own, each the same in every launch.)
+// the splits decided by wavefronts have orders of their own; a split's depends on whether one or four of them work on it.)
 
 // Four consecutive lanes (one DPP quad), lane q holding the sums of blocks 4q..4q+3 in bs[]: every lane of
 // the quad gets the total ((s0 + s1) + s2) + ... + s15, added strictly left to right.

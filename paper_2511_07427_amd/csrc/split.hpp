@@ -390,6 +390,7 @@ __device__ __forceinline__ void split_cluster(const View& v, int u, int j, int p
 // contexts (256 entries of a 16-bit type, 160 of float32): staging, sums over the members, statistics and copies are dealt
 // to them, the 2-means itself stays with the first.  (One wavefront alone: 47 us of a launch of 256 units for 64
 // entries each, 90 for 128; beyond, the workgroup path below took 514 us for 200.)
+// Two entries split into one each without a 2-means: 18 -> 12 us of a launch, 15 before their matrix products, which always ended in a tie.
 // Same 2-means as split_cluster_impl (seeds, side test with its float64 re-check, rounds, stable partition, exact
 // statistics); sums over members are float64 sums, of 16-bit values in no particular order.
 // What depends on the order of the splits (new cluster ids, page allocation) is done by one thread between the
@@ -1006,8 +1007,17 @@ __device__ inline void wave_two_means(WaveCtx& c, const unsigned char* stage, in
   MemberSet A = all, first_A = all;
   bool can = m >= 2;
   int quick = -1;
+  if (m == 2) {                                            // each is its own centre, whichever is taken first, unless they are equal
+    float a0, a1, b0, b1;
+    wpair<DT>(stage, 0, lane, a0, a1);
+    wpair<DT>(stage, 1, lane, b0, b1);
+    const double d0 = (double)a0 - (double)b0, d1 = (double)a1 - (double)b1, apart = wave_sum_f64(fma(d0, d0, d1 * d1));
+    quick = apart > 0.0 && apart < __builtin_inf();
+    can = quick == 1;
+    if (can) { A = lane == 0 ? 1ull : 0ull; sa0 = (double)a0; sa1 = (double)a1; }
+  }
   if constexpr (DT != DYNAKV_F32)
-    if (m >= 2 && m <= 16) {
+    if (m > 2 && m <= 16) {
       unsigned side = 0;
       quick = gram_two_means<DT>(stage, m, lane, side);
       if (quick == 1) A = lane == 0 ? (MemberSet)side : 0ull;
@@ -1701,8 +1711,8 @@ __device__ __forceinline__ void split_unit(const View& v, int u, unsigned char* 
       for (int base = npre, n; base < nc; base += n) {
         bool wide;
         n = split_run<DT>(pl, base, nc, wide);
-        // one split, and not a small one: by all wavefronts together
-        const int W = n == 1 && pl.m[pl.cand[base]] > kSmallRows<DT> / 2 ? kWaveSplits : 1;
+        // one split, and not a small one: by all wavefronts together (24 float16 entries: 27 us by one, 25 by four)
+        const int W = n == 1 && pl.m[pl.cand[base]] > 16 ? kWaveSplits : 1;
         const int w = W == 1 ? 0 : wave, k = W == 1 ? wave : 0;                           // this wavefront's place and candidate
         const bool mine = k < n;
         uint4 vahead[kVAhead];
