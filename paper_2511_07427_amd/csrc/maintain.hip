@@ -5,7 +5,7 @@
 //   split_kernel  - delayed splits of flagged clusters in the active set, then the forced split
 //   extend_batch_kernel, extend_kernel - a further chunk of the prompt, entry by entry, with every split done at once
 // One workgroup per unit; each unit's record is touched by that workgroup only.  All decisions are
-// taken on float64 values summed in an order that does not depend on the launch, ties to the lowest index.
+// taken on float64 values, or on float32 ones where their rounding could not change them; ties to the lowest index.
 #include "split.hpp"
 #include "score.hpp"
 
