@@ -26,10 +26,10 @@ MFMA_PEAK_TFLOPS = 2500.0      # dense fp16/bf16, published
 # 256 MiB written).  Keyed by (config, steps, warmup, units); "rev" is kernel_revision() of the sources the
 # counters were taken with: another revision of the kernels, or other arguments, report null.
 PMC_TRAFFIC = {
-    ("llama3_8b", 8192, 64, 0): {"rev": "3d9c5ab94add", "kernel": "retrieve_fused_kernel", "fetch_kib": 105039.7,
-                                 "fetch_scale": 524288.0 / 262169.06, "write_kib": 4658.5, "write_scale": 262144.0 / 262144.0},
-    ("llama3_8b", 20, 5, 0): {"rev": "3d9c5ab94add", "kernel": "retrieve_fused_kernel", "fetch_kib": 77063.9,
-                              "fetch_scale": 524288.0 / 262173.94, "write_kib": 2379.8, "write_scale": 262144.0 / 262144.0},
+    ("llama3_8b", 8192, 64, 0): {"rev": "0a451c149fb0", "kernel": "retrieve_fused_kernel", "fetch_kib": 105049.4,
+                                 "fetch_scale": 524288.0 / 262169.31, "write_kib": 4659.5, "write_scale": 262144.0 / 262144.0},
+    ("llama3_8b", 20, 5, 0): {"rev": "0a451c149fb0", "kernel": "retrieve_fused_kernel", "fetch_kib": 77068.4,
+                              "fetch_scale": 524288.0 / 262169.56, "write_kib": 2379.4, "write_scale": 262144.0 / 262144.0},
 }
 
 
